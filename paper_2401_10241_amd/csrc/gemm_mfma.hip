@@ -41,6 +41,12 @@
 
 namespace zb {
 
+// gemm_mfma_edge.hip: other tiles for sizes that the 256-column tiles do not take or do not fill the chip with
+double split_cost(int M, int N, int slices, bool rides);
+void choose_edge(int M, int N, int K, size_t workspace_floats, bool rides, int* tile, int* slices, double* us);
+hipError_t launch_gemm_edge(const GemmArgs& g, long lda, long ldb, int tile, int slices, hipStream_t s);
+hipError_t launch_wgrad_multi_edge(const WgradMultiArgs& w, hipStream_t s, bool* taken);
+
 namespace {
 
 constexpr int KS = 32;   // k per pipeline step
@@ -526,6 +532,32 @@ __global__ __launch_bounds__(512, (BM == 128 && BS == 3) ? 4 : 2) void gemm_wgra
     }
 }
 
+// The K slices' planes are in the workspace: add them and apply the epilogue.
+template <int MODE>
+void finish_split_k(const GemmArgs& g, int slices, size_t plane, hipStream_t s, hipError_t* err) {
+  // The last step owns whole rows: a LayerNorm on those rows rides along instead of running as a kernel of
+  // its own on the stored result.
+  const bool ln_shape = g.ln_done && g.N <= 8192;
+  if (MODE == EPI_BIAS_RESID && g.ln_mode == 1 && ln_shape) {
+    *err = launch_splitk_layernorm_fwd<bf16_t>(g.workspace, slices, plane, g.bias, (const bf16_t*)g.aux,
+                                               (bf16_t*)g.out0, g.ln_gamma, g.ln_beta, (bf16_t*)g.ln_out, g.ln_stats,
+                                               g.M, g.N, g.ln_eps, s);
+    *g.ln_done = *err == hipSuccess;
+    return;
+  }
+  if (MODE == EPI_STORE && g.ln_mode == 2 && ln_shape) {
+    *err = launch_splitk_layernorm_bwd<bf16_t>(g.workspace, slices, plane, (bf16_t*)g.out0, (const bf16_t*)g.ln_x, g.ln_stats,
+                                               g.ln_gamma, (const bf16_t*)g.ln_resid, (bf16_t*)g.ln_out, g.ln_dgamma,
+                                               g.ln_dbeta, g.ln_partials, g.M, g.N, s);
+    *g.ln_done = *err == hipSuccess;
+    return;
+  }
+  const size_t threads = plane / 4;
+  gemm_splitk_fixup_kernel<MODE><<<(unsigned)((threads + 255) / 256), 256, 0, s>>>(g.workspace, slices, plane, g.N,
+                                                                                 make_epi(g));
+  *err = hipGetLastError();
+}
+
 // Few tiles and a long K (the N = hidden GEMMs of a 1024-token microbatch): cut K into slices so that
 // every CU gets a workgroup.  Returns false if the shape is not one for split-K.
 template <int MODE>
@@ -542,27 +574,7 @@ bool try_split_k(const GemmArgs& g, long lda, long ldb, hipStream_t s, hipError_
   p.outf = g.workspace;
   *err = run_cfg<256, 4, EPI_PARTIAL, 3>(p, lda, ldb, s, slices);
   if (*err != hipSuccess) return true;
-  // The last step owns whole rows: a LayerNorm on those rows rides along instead of running as a kernel of
-  // its own on the stored result.
-  const bool ln_shape = g.ln_done && g.N <= 8192;
-  if (MODE == EPI_BIAS_RESID && g.ln_mode == 1 && ln_shape) {
-    *err = launch_splitk_layernorm_fwd<bf16_t>(g.workspace, slices, plane, g.bias, (const bf16_t*)g.aux,
-                                               (bf16_t*)g.out0, g.ln_gamma, g.ln_beta, (bf16_t*)g.ln_out, g.ln_stats,
-                                               g.M, g.N, g.ln_eps, s);
-    *g.ln_done = *err == hipSuccess;
-    return true;
-  }
-  if (MODE == EPI_STORE && g.ln_mode == 2 && ln_shape) {
-    *err = launch_splitk_layernorm_bwd<bf16_t>(g.workspace, slices, plane, (bf16_t*)g.out0, (const bf16_t*)g.ln_x, g.ln_stats,
-                                               g.ln_gamma, (const bf16_t*)g.ln_resid, (bf16_t*)g.ln_out, g.ln_dgamma,
-                                               g.ln_dbeta, g.ln_partials, g.M, g.N, s);
-    *g.ln_done = *err == hipSuccess;
-    return true;
-  }
-  const size_t threads = plane / 4;
-  gemm_splitk_fixup_kernel<MODE><<<(unsigned)((threads + 255) / 256), 256, 0, s>>>(g.workspace, slices, plane, g.N,
-                                                                                 make_epi(g));
-  *err = hipGetLastError();
+  finish_split_k<MODE>(g, slices, plane, s, err);
   return true;
 }
 
@@ -607,10 +619,52 @@ bool try_tail_split(const GemmArgs& g, long lda, long ldb, hipStream_t s, hipErr
   return true;
 }
 
+// Microseconds the 256-column tiles below are expected to take where they do not fill the chip even once (at most
+// 128 tiles of 256 x 256): a step of 32 k takes 0.66 us with few 256-row tiles and 0.90 with one per CU (128-row
+// tiles: 0.40 and 0.70); same measurements as edge_cost's.  A larger product is theirs without asking.
+double big_tile_us(const GemmArgs& g, bool rides) {
+  if ((long)g.M * g.N > 128L * 256 * BN) return 0;
+  const int steps = g.K / KS;
+  if (g.M % 256 == 0 && g.K >= 2048 && g.workspace) {  // try_split_k's tiles
+    const long tiles = (long)(g.M / 256) * (g.N / BN);
+    const int slices = (int)(256 / tiles) < 4 ? (int)(256 / tiles) : 4;
+    if ((size_t)slices * g.M * g.N <= g.workspace_floats)
+      return 3.0 + (double)(steps / slices) * (0.66 + 0.24 * tiles * slices / 256) + split_cost(g.M, g.N, slices, rides);
+  }
+  const long t128 = (long)(g.M / 128) * (g.N / BN);  // at most 256: one round
+  return 3.0 + steps * (0.40 + 0.30 * t128 / 256);
+}
+
+// The other tiles (gemm_mfma_edge.hip)
+template <int MODE>
+hipError_t run_edge_shape(const GemmArgs& g, long lda, long ldb, hipStream_t s, int tile, int slices) {
+  if (slices == 1) return launch_gemm_edge(g, lda, ldb, tile, 1, s);
+  GemmArgs p = g;
+  p.epilogue = EPI_PARTIAL;
+  p.outf = g.workspace;
+  hipError_t e = launch_gemm_edge(p, lda, ldb, tile, slices, s);
+  if (e != hipSuccess) return e;
+  finish_split_k<MODE>(g, slices, (size_t)g.M * g.N, s, &e);
+  return e;
+}
+
 template <int MODE>
 hipError_t run_shape(const GemmArgs& g, long lda, long ldb, hipStream_t s, bool* taken) {
   *taken = true;
   hipError_t e = hipSuccess;
+  int tile = 0, slices = 1;
+  double edge_us = 1e30;
+  // a LayerNorm on the output's rows, which the launch that adds K slices takes over (finish_split_k)
+  const bool rides = g.ln_done && g.N <= 8192 && (MODE == EPI_BIAS_RESID ? g.ln_mode == 1 : MODE == EPI_STORE && g.ln_mode == 2);
+  if (g.N % 8 == 0)
+    choose_edge(g.M, g.N, g.K, g.workspace ? g.workspace_floats : 0, rides, &tile, &slices, &edge_us);
+  // Sizes that the 256-column tiles take stay with them unless the other tiles are clearly shorter: 256 x 1024 x
+  // 1024 16 -> 7.5 us, 512 x 768 x 3072 26 -> 14, 1024 x 1536 x 1536 23 -> 12; 1024 x 4096 x 4096 52 against 53.
+  if (g.K % 64 != 0 || g.M % 128 != 0 || g.N % BN != 0 || edge_us < 0.9 * big_tile_us(g, rides)) {
+    if (tile) return run_edge_shape<MODE>(g, lda, ldb, s, tile, slices);
+    *taken = false;
+    return hipSuccess;
+  }
   if (try_split_k<MODE>(g, lda, ldb, s, &e)) return e;
   if (try_tail_split<MODE>(g, lda, ldb, s, &e)) return e;
   if (g.N % BN == 0) {
@@ -680,8 +734,9 @@ template <typename T> hipError_t launch_wgrad_multi_mfma(const WgradMultiArgs& w
 template <> hipError_t launch_wgrad_multi_mfma<bf16_t>(const WgradMultiArgs& w, hipStream_t s, bool* taken) {
   *taken = false;
   if (w.nprob < 1 || w.nprob > kWgradMaxProblems || w.ngroup < 1 || w.ngroup > kGemmGroupMax ||
-      w.nprob * w.ngroup > kWgradMaxPairs || w.K <= 0 || w.K % 64 != 0)
+      w.nprob * w.ngroup > kWgradMaxPairs || w.K <= 0)
     return hipSuccess;
+  if (w.K % 64 != 0) return launch_wgrad_multi_edge(w, s, taken);
   WgradTable tb{};
   tb.nprob = w.nprob;
   tb.ngroup = w.ngroup;
@@ -689,7 +744,8 @@ template <> hipError_t launch_wgrad_multi_mfma<bf16_t>(const WgradMultiArgs& w, 
   long t256 = 0, t128 = 0;
   for (int q = 0; q < w.nprob; ++q) {
     const int M = w.M[q], N = w.N[q];
-    if (M <= 0 || N <= 0 || M % 128 != 0 || N % BN != 0 || !aligned16(w.outf[q])) return hipSuccess;
+    if (M <= 0 || N <= 0 || M % 128 != 0 || N % BN != 0 || !aligned16(w.outf[q]))
+      return launch_wgrad_multi_edge(w, s, taken);
     tb.M[q] = M; tb.N[q] = N; tb.outf[q] = w.outf[q];
     tb.bias[q] = w.bias_done ? w.bias[q] : nullptr;
     all256 = all256 && M % 256 == 0;
@@ -740,7 +796,7 @@ template <> hipError_t launch_gemm_mfma<bf16_t>(const GemmArgs& g, hipStream_t s
   // forward X[M,K] * W[K,N]; dgrad dY[M,K'] * Wt[K',N']: A K-contiguous, B row-contiguous
   if (g.a_sk != 1 || !(g.b_sn == 1 && g.b_sk != 1)) return hipSuccess;
   const long lda = g.a_sm, ldb = g.b_sk;
-  if (g.K % 64 != 0 || lda % 8 != 0 || ldb % 8 != 0 || !aligned16(g.A) || !aligned16(g.B)) return hipSuccess;
+  if (g.K % 8 != 0 || lda % 8 != 0 || ldb % 8 != 0 || !aligned16(g.A) || !aligned16(g.B)) return hipSuccess;
   if (g.epilogue == EPI_BIAS) return run_shape<EPI_BIAS>(g, lda, ldb, s, taken);
   if (g.epilogue == EPI_BIAS_RESID) return run_shape<EPI_BIAS_RESID>(g, lda, ldb, s, taken);
   if (g.epilogue == EPI_BIAS_GELU) return run_shape<EPI_BIAS_GELU>(g, lda, ldb, s, taken);

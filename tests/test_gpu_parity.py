@@ -424,3 +424,23 @@ def test_shape_sweep(cfg):
     hidden, heads, ffn, seq, b, layers, dtype = cfg
     w = W("sweep", dtype, layers, hidden, heads, ffn, seq, b, 4, 1, 3, "H2", seed=101 + hidden + seq)
     run_and_compare(w)
+
+
+EDGES = [
+    # hidden, heads, ffn, seq, b, layers       what is cut where
+    (600, 8, 1208, 77, 2, 2),     # head size 75 (odd: rows at 2-byte addresses), every width and the 154 tokens ragged
+    (72, 3, 136, 33, 1, 2),       # head size 24, widths below one tile, one row past a 32-row block
+    (400, 4, 1608, 130, 1, 1),    # head size 100; two rows past two 64-row tiles
+    (96, 12, 264, 65, 3, 1),      # head size 8, the smallest the matrix-core kernels take
+    (56, 8, 72, 50, 1, 1),        # head size 7, below it
+    (256, 2, 1032, 129, 1, 1),    # head size 128, one row past a whole 128-row block
+    (264, 3, 1024, 1, 1, 1),      # head size 88, a single token
+    (1032, 8, 4104, 520, 2, 1),   # head size 129, above the matrix-core kernels; K cut into slices with a short last one
+    (768, 12, 3072, 512, 1, 1),   # whole tiles of every kind, but too few of the large ones
+]
+
+
+@pytest.mark.parametrize("cfg", EDGES, ids=lambda c: "h%d_a%d_f%d_s%d_b%d_L%d" % c)
+def test_edge_tiles(cfg):
+    hidden, heads, ffn, seq, b, layers = cfg
+    run_and_compare(W("edges", "bf16", layers, hidden, heads, ffn, seq, b, 4, 1, 3, "H2", seed=301 + hidden + seq))
