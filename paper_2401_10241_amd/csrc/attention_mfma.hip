@@ -1,5 +1,5 @@
 // Causal multi-head attention on the gfx950 matrix cores (bf16 in, fp32 accumulate), forward and
-// backward, for head sizes 64 / 96 / 128 and sequence lengths that are multiples of 128.
+// backward, for head sizes from 8 to 128 and any sequence length.
 //
 // All products are formed "transposed" so that a lane owns one query (forward, dQ) or one key
 // (dK/dV) and softmax statistics never cross lanes except for one exchange between lane l and l+32:
@@ -7,8 +7,20 @@
 //             O^T += V^T P^T        (P taken straight from the S^T accumulators as an MFMA operand)
 //   dQ pass   S^T, dP^T = V dO^T,   dS^T = P^T o (dP^T - D),   dQ^T += K^T dS^T
 //   dK/dV     S = Q K^T, dP = dO V^T (lane = key),  dV^T += dO^T P,  dK^T += Q^T dS
-// dQ and dK/dV are separate kernels (each recomputes S), so no floating-point atomics are needed and
-// results do not depend on scheduling.
+// dQ and dK/dV are separate workgroups of one launch (each recomputes S), so no floating-point atomics are
+// needed and results do not depend on scheduling.
+//
+// Two forms of every kernel.  EDGE = false: head size 64, whole 128-row blocks.  EDGE = true: a head of d columns
+// is padded with zeros to D = 32 / 64 / 96 / 128 on its way into registers and LDS, rows past the end of the
+// sequence are zeros as well (a zero query or output gradient adds nothing; a key past the end is always behind
+// the diagonal), and P and dS go into their products as two bf16 terms, hi + lo, i.e. with 16 bits of mantissa:
+// the vector-ALU kernels that took these shapes before kept them in fp32.
+//
+// What bounds them: a workgroup is a chain of dependent tiles (LDS read -> MFMA -> exponentials -> MFMA), and
+// the shapes that come here have few heads, so most of the chip is idle; the launch therefore uses 64-row blocks
+// (two waves) unless 128-row blocks already give every CU two.  Measured: 16 heads of 75 columns, 777 tokens
+// 326 us forward and 1323 us backward on the vector ALUs; with these kernels the whole stage iteration they
+// sit in went from 13.7 to 2.8 ms.
 //
 // A 32x32 accumulator tile holds, in lane l and element v, row 8*(v/4) + 4*(l>>5) + v%4 and column
 // l&31.  Used directly as the k-operand of the next MFMA (16 rows per instruction: elements 0-7,
@@ -27,7 +39,6 @@ hipError_t launch_attention_bwd_d128(const AttnArgs& a, hipStream_t s);
 
 namespace {
 
-constexpr int QB = 128;  // rows owned by a workgroup (4 waves x 32)
 constexpr int KB = 64;   // rows of the inner-loop tile
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -36,27 +47,63 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 
-template <int D> struct AT {
+template <int D, int NW = 4> struct AT {
   static constexpr int PITCH = D + 16;
-  static constexpr int CH = KB * D / 8 / 256;  // 16-byte chunks per thread per tile
+  static constexpr int CH = KB * D / 8 / (64 * NW);  // 16-byte chunks per thread per tile
   static constexpr int TILE = KB * PITCH;      // elements
 };
 
-template <int D, int CH>
-__device__ __forceinline__ void gload_tile(u32x4 (&reg)[CH], const bf16_t* __restrict__ base, long ld) {
+// Columns c0 .. c0+7 of a row of d columns (d >= 8), zeros from column d on; reads inside the row only, at any
+// even address.
+typedef u32x4 __attribute__((aligned(2))) u32x4_any;
+__device__ __forceinline__ u32x4 load_chunk(const bf16_t* __restrict__ row, int c0, int d) {
+  const int at = min(c0, d - 8);
+  u32x4 v = *reinterpret_cast<const u32x4_any*>(row + at);
+  if (c0 != at) {  // the tail chunk, read from column d - 8: move it down by c0 - at elements
+    const int sh = c0 - at;
+    unsigned __int128 x = __builtin_bit_cast(unsigned __int128, v);
+    x = sh < 8 ? x >> (16 * sh) : 0;
+    v = __builtin_bit_cast(u32x4, x);
+  }
+  return v;
+}
+
+// rows [0, KB) of a tile whose first `rows` exist (the others are zeros), NW * 64 threads
+template <int D, int NW, bool EDGE, int CH>
+__device__ __forceinline__ void gload_tile(u32x4 (&reg)[CH], const bf16_t* __restrict__ base, long ld, int rows, int d) {
 #pragma unroll
   for (int j = 0; j < CH; ++j) {
-    const int c = threadIdx.x + 256 * j;
+    const int c = threadIdx.x + 64 * NW * j;
     const int row = c / (D / 8), dc = c % (D / 8);
-    reg[j] = *reinterpret_cast<const u32x4*>(base + (long)row * ld + dc * 8);
+    if constexpr (EDGE) {
+      reg[j] = load_chunk(base + (long)min(row, rows - 1) * ld, dc * 8, d);
+      if (row >= rows) reg[j] = u32x4{0, 0, 0, 0};
+    } else {
+      reg[j] = *reinterpret_cast<const u32x4*>(base + (long)row * ld + dc * 8);
+    }
   }
 }
-template <int D, int CH> __device__ __forceinline__ void lstore_tile(const u32x4 (&reg)[CH], bf16_t* __restrict__ s) {
+template <int D, int NW, int CH>
+__device__ __forceinline__ void lstore_tile(const u32x4 (&reg)[CH], bf16_t* __restrict__ s) {
 #pragma unroll
   for (int j = 0; j < CH; ++j) {
-    const int c = threadIdx.x + 256 * j;
+    const int c = threadIdx.x + 64 * NW * j;
     const int row = c / (D / 8), dc = c % (D / 8);
     *reinterpret_cast<u32x4*>(s + row * AT<D>::PITCH + ((dc ^ ((row >> 2) & 1)) << 3)) = reg[j];
+  }
+}
+// the row's k-operand fragments (columns kk*16 + hi*8 ..) straight from memory
+template <int D, bool EDGE>
+__device__ __forceinline__ void load_row_frags(bf16x8 (&f)[D / 16], const bf16_t* __restrict__ row, int hi, bool valid, int d) {
+#pragma unroll
+  for (int kk = 0; kk < D / 16; ++kk) {
+    if constexpr (EDGE) {
+      u32x4 v = load_chunk(row, kk * 16 + hi * 8, d);
+      if (!valid) v = u32x4{0, 0, 0, 0};
+      f[kk] = __builtin_bit_cast(bf16x8, v);
+    } else {
+      f[kk] = *reinterpret_cast<const bf16x8*>(row + kk * 16 + hi * 8);
+    }
   }
 }
 
@@ -93,35 +140,58 @@ __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// what pack_half leaves behind, as a second bf16 operand
+__device__ __forceinline__ bf16x8 pack_rest(const f32x16& t, int half) {
+  bf16x8 r;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const float x = t[half * 8 + j];
+    r[j] = (bf16_t)(x - (float)(bf16_t)x);
+  }
+  return r;
+}
+
 __device__ __forceinline__ void store4(bf16_t* p, float a, float b, float c, float d) {
   bf16x4 t;
   t[0] = (bf16_t)a; t[1] = (bf16_t)b; t[2] = (bf16_t)c; t[3] = (bf16_t)d;
   *reinterpret_cast<bf16x4*>(p) = t;
 }
+// columns e .. e+3 of a row of d columns
+template <bool EDGE>
+__device__ __forceinline__ void store4_row(bf16_t* row, int e, int d, float a, float b, float c, float f) {
+  if (!EDGE || (d % 4 == 0 && e < d)) {
+    store4(row + e, a, b, c, f);
+  } else {
+    if (e < d) row[e] = (bf16_t)a;
+    if (e + 1 < d) row[e + 1] = (bf16_t)b;
+    if (e + 2 < d) row[e + 2] = (bf16_t)c;
+    if (e + 3 < d) row[e + 3] = (bf16_t)f;
+  }
+}
 
 // ------------------------------------------------------------------------------------------------
 // forward
 // ------------------------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256) void attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out,
-                                                       float* __restrict__ lse, int s, int a, float sl2) {
+template <int D, int NW, bool EDGE>
+__global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out,
+                                                           float* __restrict__ lse, int s, int a, int d, float sl2) {
+  constexpr int QB = 32 * NW;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   bf16_t* sK = reinterpret_cast<bf16_t*>(smem_raw);  // [2][TILE]
   bf16_t* sV = sK + 2 * AT<D>::TILE;
-  const int qb = gridDim.x - 1 - blockIdx.x, head = blockIdx.y, bi = blockIdx.z;  // heaviest blocks first
-  const int h = a * D;
+  const int qb = gridDim.z - 1 - blockIdx.z, head = blockIdx.x, bi = blockIdx.y;  // heaviest blocks first
+  if (!EDGE) d = D;
+  const int h = a * d;
   const long ld = 3L * h;
   const long tok0 = (long)bi * s;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int hi = lane >> 5, lq = lane & 31;
   const int qw0 = qb * QB + wave * 32;  // first query of this wave
 
+  const bool mine = !EDGE || qw0 + lq < s;  // this lane's query exists
+  const int row_q = mine ? qw0 + lq : s - 1;
   bf16x8 qf[D / 16];
-  {
-    const bf16_t* qp = qkv + (tok0 + qw0 + lq) * ld + head * D + hi * 8;
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qp + kk * 16);
-  }
+  load_row_frags<D, EDGE>(qf, qkv + (tok0 + row_q) * ld + head * d, hi, mine, d);
   f32x16 o[D / 32];
 #pragma unroll
   for (int et = 0; et < D / 32; ++et)
@@ -129,17 +199,17 @@ __global__ __launch_bounds__(256) void attn_fwd_kernel(const bf16_t* __restrict_
     for (int v = 0; v < 16; ++v) o[et][v] = 0.f;
   float m = -INFINITY, l = 0.f;
 
-  const int nkb = 2 * qb + 2;
-  const bf16_t* kbase = qkv + tok0 * ld + h + head * D;
+  const int nkb = EDGE ? (min((qb + 1) * QB, s) + KB - 1) / KB : (qb + 1) * QB / KB;
+  const bf16_t* kbase = qkv + tok0 * ld + h + head * d;
   const bf16_t* vbase = kbase + h;
-  u32x4 rk[AT<D>::CH], rv[AT<D>::CH];
-  gload_tile<D>(rk, kbase, ld);
-  gload_tile<D>(rv, vbase, ld);
-  lstore_tile<D>(rk, sK);
-  lstore_tile<D>(rv, sV);
+  u32x4 rk[AT<D, NW>::CH], rv[AT<D, NW>::CH];
+  gload_tile<D, NW, EDGE>(rk, kbase, ld, s, d);
+  gload_tile<D, NW, EDGE>(rv, vbase, ld, s, d);
+  lstore_tile<D, NW>(rk, sK);
+  lstore_tile<D, NW>(rv, sV);
   if (nkb > 1) {
-    gload_tile<D>(rk, kbase + (long)KB * ld, ld);
-    gload_tile<D>(rv, vbase + (long)KB * ld, ld);
+    gload_tile<D, NW, EDGE>(rk, kbase + (long)KB * ld, ld, s - KB, d);
+    gload_tile<D, NW, EDGE>(rv, vbase + (long)KB * ld, ld, s - KB, d);
   }
   __syncthreads();
 
@@ -200,57 +270,66 @@ __global__ __launch_bounds__(256) void attn_fwd_kernel(const bf16_t* __restrict_
       for (int kk = 0; kk < 4; ++kk) {
         if (kk < 2 || act1) {
 #pragma unroll
-          for (int et = 0; et < D / 32; ++et) o[et] = mfma(frag_tr<D>(vc, et * 32, kk * 16, lane), pf[kk], o[et]);
+          for (int et = 0; et < D / 32; ++et) {
+            const bf16x8 vf = frag_tr<D>(vc, et * 32, kk * 16, lane);
+            o[et] = mfma(vf, pf[kk], o[et]);
+            if constexpr (EDGE) o[et] = mfma(vf, pack_rest(st[kk >> 1], kk & 1), o[et]);
+          }
         }
       }
     }
     if (jb + 1 < nkb) {
-      lstore_tile<D>(rk, sK + ((jb + 1) & 1) * AT<D>::TILE);
-      lstore_tile<D>(rv, sV + ((jb + 1) & 1) * AT<D>::TILE);
+      lstore_tile<D, NW>(rk, sK + ((jb + 1) & 1) * AT<D>::TILE);
+      lstore_tile<D, NW>(rv, sV + ((jb + 1) & 1) * AT<D>::TILE);
     }
     __syncthreads();
     if (jb + 2 < nkb) {
-      gload_tile<D>(rk, kbase + (long)(jb + 2) * KB * ld, ld);
-      gload_tile<D>(rv, vbase + (long)(jb + 2) * KB * ld, ld);
+      gload_tile<D, NW, EDGE>(rk, kbase + (long)(jb + 2) * KB * ld, ld, s - (jb + 2) * KB, d);
+      gload_tile<D, NW, EDGE>(rv, vbase + (long)(jb + 2) * KB * ld, ld, s - (jb + 2) * KB, d);
     }
   }
 
   const float inv = 1.0f / l;
-  bf16_t* op = out + (tok0 + qw0 + lq) * h + head * D + hi * 4;
+  if (!mine) return;
+  bf16_t* op = out + (tok0 + qw0 + lq) * h + head * d;
 #pragma unroll
   for (int et = 0; et < D / 32; ++et)
 #pragma unroll
     for (int g = 0; g < 4; ++g)
-      store4(op + et * 32 + g * 8, o[et][4 * g] * inv, o[et][4 * g + 1] * inv, o[et][4 * g + 2] * inv,
+      store4_row<EDGE>(op, et * 32 + g * 8 + hi * 4, d, o[et][4 * g] * inv, o[et][4 * g + 1] * inv, o[et][4 * g + 2] * inv,
              o[et][4 * g + 3] * inv);
   if (hi == 0) lse[((long)bi * a + head) * s + qw0 + lq] = (m + __builtin_amdgcn_logf(l)) * kLn2;
 }
 
 // ------------------------------------------------------------------------------------------------
-// backward, step 0: D_i = dO_i . O_i     (one wavefront per (row, head))
+// backward, step 0: D_i = dO_i . O_i     (16 lanes per (row, head), 16 rows per workgroup)
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void attn_bwd_prep_kernel(const bf16_t* __restrict__ o, const bf16_t* __restrict__ dout,
-                                                           float* __restrict__ dvec, int s, int a, int d) {
-  const int i = blockIdx.x, head = blockIdx.y, bi = blockIdx.z;
-  const long off = ((long)bi * s + i) * a * d + head * d;
+__global__ __launch_bounds__(256) void attn_bwd_prep_kernel(const bf16_t* __restrict__ o, const bf16_t* __restrict__ dout,
+                                                            float* __restrict__ dvec, int s, int a, int d) {
+  const int i = blockIdx.x * 16 + (threadIdx.x >> 4), head = blockIdx.y, bi = blockIdx.z;
+  const int l16 = threadIdx.x & 15;
+  const long off = ((long)bi * s + min(i, s - 1)) * a * d + head * d;
   float acc = 0.f;
-  for (int e = threadIdx.x; e < d; e += 64) acc += (float)o[off + e] * (float)dout[off + e];
-  acc = wave_sum(acc);
-  if (threadIdx.x == 0) dvec[((long)bi * a + head) * s + i] = acc;
+#pragma unroll 8
+  for (int e = l16; e < d; e += 16) acc += (float)o[off + e] * (float)dout[off + e];
+#pragma unroll
+  for (int x = 8; x > 0; x >>= 1) acc += __shfl_xor(acc, x, 64);
+  if (l16 == 0 && i < s) dvec[((long)bi * a + head) * s + i] = acc;
 }
 
 // ------------------------------------------------------------------------------------------------
 // backward, dQ: workgroup = 128 queries, loop over key tiles up to the diagonal
 // ------------------------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256) void attn_bwd_dq_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
-                                                          const float* __restrict__ lse, const float* __restrict__ dvec,
-                                                          bf16_t* __restrict__ dqkv, int s, int a, float scale) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
+template <int D, int NW, bool EDGE>
+__device__ __forceinline__ void attn_bwd_dq_body(unsigned char* smem_raw, int qb, int head, int bi,
+                                                 const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
+                                                 const float* __restrict__ lse, const float* __restrict__ dvec,
+                                                 bf16_t* __restrict__ dqkv, int s, int a, int d, float scale) {
+  constexpr int QB = 32 * NW;
   bf16_t* sK = reinterpret_cast<bf16_t*>(smem_raw);
   bf16_t* sV = sK + 2 * AT<D>::TILE;
-  const int qb = gridDim.x - 1 - blockIdx.x, head = blockIdx.y, bi = blockIdx.z;
-  const int h = a * D;
+  if (!EDGE) d = D;
+  const int h = a * d;
   const long ld = 3L * h;
   const long tok0 = (long)bi * s;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -258,17 +337,12 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_kernel(const bf16_t* __restri
   const int qw0 = qb * QB + wave * 32;
   const float sl2 = scale * kLog2e;
 
+  const bool mine = !EDGE || qw0 + lq < s;
+  const int row_q = mine ? qw0 + lq : s - 1;
   bf16x8 qf[D / 16], dof[D / 16];
-  {
-    const bf16_t* qp = qkv + (tok0 + qw0 + lq) * ld + head * D + hi * 8;
-    const bf16_t* dp = dout + (tok0 + qw0 + lq) * h + head * D + hi * 8;
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) {
-      qf[kk] = *reinterpret_cast<const bf16x8*>(qp + kk * 16);
-      dof[kk] = *reinterpret_cast<const bf16x8*>(dp + kk * 16);
-    }
-  }
-  const long srow = ((long)bi * a + head) * s + qw0 + lq;
+  load_row_frags<D, EDGE>(qf, qkv + (tok0 + row_q) * ld + head * d, hi, mine, d);
+  load_row_frags<D, EDGE>(dof, dout + (tok0 + row_q) * h + head * d, hi, mine, d);
+  const long srow = ((long)bi * a + head) * s + row_q;
   const float lse2 = lse[srow] * kLog2e;
   const float Dq = dvec[srow];
   f32x16 dq[D / 32];
@@ -277,17 +351,17 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_kernel(const bf16_t* __restri
 #pragma unroll
     for (int v = 0; v < 16; ++v) dq[et][v] = 0.f;
 
-  const int nkb = 2 * qb + 2;
-  const bf16_t* kbase = qkv + tok0 * ld + h + head * D;
+  const int nkb = EDGE ? (min((qb + 1) * QB, s) + KB - 1) / KB : (qb + 1) * QB / KB;
+  const bf16_t* kbase = qkv + tok0 * ld + h + head * d;
   const bf16_t* vbase = kbase + h;
-  u32x4 rk[AT<D>::CH], rv[AT<D>::CH];
-  gload_tile<D>(rk, kbase, ld);
-  gload_tile<D>(rv, vbase, ld);
-  lstore_tile<D>(rk, sK);
-  lstore_tile<D>(rv, sV);
+  u32x4 rk[AT<D, NW>::CH], rv[AT<D, NW>::CH];
+  gload_tile<D, NW, EDGE>(rk, kbase, ld, s, d);
+  gload_tile<D, NW, EDGE>(rv, vbase, ld, s, d);
+  lstore_tile<D, NW>(rk, sK);
+  lstore_tile<D, NW>(rv, sV);
   if (nkb > 1) {
-    gload_tile<D>(rk, kbase + (long)KB * ld, ld);
-    gload_tile<D>(rv, vbase + (long)KB * ld, ld);
+    gload_tile<D, NW, EDGE>(rk, kbase + (long)KB * ld, ld, s - KB, d);
+    gload_tile<D, NW, EDGE>(rv, vbase + (long)KB * ld, ld, s - KB, d);
   }
   __syncthreads();
 
@@ -331,43 +405,49 @@ __global__ __launch_bounds__(256) void attn_bwd_dq_kernel(const bf16_t* __restri
       for (int kk = 0; kk < 4; ++kk) {
         if (kk < 2 || act1) {
 #pragma unroll
-          for (int et = 0; et < D / 32; ++et) dq[et] = mfma(frag_tr<D>(kc, et * 32, kk * 16, lane), dsf[kk], dq[et]);
+          for (int et = 0; et < D / 32; ++et) {
+            const bf16x8 kf = frag_tr<D>(kc, et * 32, kk * 16, lane);
+            dq[et] = mfma(kf, dsf[kk], dq[et]);
+            if constexpr (EDGE) dq[et] = mfma(kf, pack_rest(st[kk >> 1], kk & 1), dq[et]);
+          }
         }
       }
     }
     if (jb + 1 < nkb) {
-      lstore_tile<D>(rk, sK + ((jb + 1) & 1) * AT<D>::TILE);
-      lstore_tile<D>(rv, sV + ((jb + 1) & 1) * AT<D>::TILE);
+      lstore_tile<D, NW>(rk, sK + ((jb + 1) & 1) * AT<D>::TILE);
+      lstore_tile<D, NW>(rv, sV + ((jb + 1) & 1) * AT<D>::TILE);
     }
     __syncthreads();
     if (jb + 2 < nkb) {
-      gload_tile<D>(rk, kbase + (long)(jb + 2) * KB * ld, ld);
-      gload_tile<D>(rv, vbase + (long)(jb + 2) * KB * ld, ld);
+      gload_tile<D, NW, EDGE>(rk, kbase + (long)(jb + 2) * KB * ld, ld, s - (jb + 2) * KB, d);
+      gload_tile<D, NW, EDGE>(rv, vbase + (long)(jb + 2) * KB * ld, ld, s - (jb + 2) * KB, d);
     }
   }
-  bf16_t* op = dqkv + (tok0 + qw0 + lq) * ld + head * D + hi * 4;
+  if (!mine) return;
+  bf16_t* op = dqkv + (tok0 + qw0 + lq) * ld + head * d;
 #pragma unroll
   for (int et = 0; et < D / 32; ++et)
 #pragma unroll
     for (int g = 0; g < 4; ++g)
-      store4(op + et * 32 + g * 8, dq[et][4 * g] * scale, dq[et][4 * g + 1] * scale, dq[et][4 * g + 2] * scale,
+      store4_row<EDGE>(op, et * 32 + g * 8 + hi * 4, d, dq[et][4 * g] * scale, dq[et][4 * g + 1] * scale, dq[et][4 * g + 2] * scale,
              dq[et][4 * g + 3] * scale);
 }
 
 // ------------------------------------------------------------------------------------------------
 // backward, dK and dV: workgroup = 128 keys, loop over query tiles from the diagonal to the end
 // ------------------------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
-                                                           const float* __restrict__ lse, const float* __restrict__ dvec,
-                                                           bf16_t* __restrict__ dqkv, int s, int a, float scale) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
+template <int D, int NW, bool EDGE>
+__device__ __forceinline__ void attn_bwd_dkv_body(unsigned char* smem_raw, int kb, int head, int bi,
+                                                  const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
+                                                  const float* __restrict__ lse, const float* __restrict__ dvec,
+                                                  bf16_t* __restrict__ dqkv, int s, int a, int d, float scale) {
+  constexpr int QB = 32 * NW;
   bf16_t* sQ = reinterpret_cast<bf16_t*>(smem_raw);  // [2][TILE]
   bf16_t* sO = sQ + 2 * AT<D>::TILE;                 // dO tiles
   float* sL = reinterpret_cast<float*>(sO + 2 * AT<D>::TILE);  // [2][64] lse * log2(e)
   float* sD = sL + 2 * KB;                                     // [2][64] D
-  const int kb = blockIdx.x, head = blockIdx.y, bi = blockIdx.z;  // key block 0 has the most work and goes first
-  const int h = a * D;
+  if (!EDGE) d = D;
+  const int h = a * d;
   const long ld = 3L * h;
   const long tok0 = (long)bi * s;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -375,45 +455,43 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const bf16_t* __restr
   const int kw0 = kb * QB + wave * 32;  // first key of this wave
   const float sl2 = scale * kLog2e;
 
+  const bool mine = !EDGE || kw0 + lk < s;
+  const int row_k = mine ? kw0 + lk : s - 1;
   bf16x8 kf[D / 16], vf[D / 16];
-  {
-    const bf16_t* kp = qkv + (tok0 + kw0 + lk) * ld + h + head * D + hi * 8;
-#pragma unroll
-    for (int kk = 0; kk < D / 16; ++kk) {
-      kf[kk] = *reinterpret_cast<const bf16x8*>(kp + kk * 16);
-      vf[kk] = *reinterpret_cast<const bf16x8*>(kp + h + kk * 16);
-    }
-  }
+  load_row_frags<D, EDGE>(kf, qkv + (tok0 + row_k) * ld + h + head * d, hi, mine, d);
+  load_row_frags<D, EDGE>(vf, qkv + (tok0 + row_k) * ld + 2 * h + head * d, hi, mine, d);
   f32x16 dk[D / 32], dv[D / 32];
 #pragma unroll
   for (int et = 0; et < D / 32; ++et)
 #pragma unroll
     for (int v = 0; v < 16; ++v) dk[et][v] = dv[et][v] = 0.f;
 
-  const int ib0 = kb * (QB / KB), nib = s / KB;
-  const bf16_t* qbase = qkv + tok0 * ld + head * D;
-  const bf16_t* obase = dout + tok0 * h + head * D;
+  const int ib0 = kb * (QB / KB), nib = (s + KB - 1) / KB;
+  const bf16_t* qbase = qkv + tok0 * ld + head * d;
+  const bf16_t* obase = dout + tok0 * h + head * d;
   const float* lbase = lse + ((long)bi * a + head) * s;
   const float* dbase = dvec + ((long)bi * a + head) * s;
-  u32x4 rq[AT<D>::CH], ro[AT<D>::CH];
+  u32x4 rq[AT<D, NW>::CH], ro[AT<D, NW>::CH];
   float rs = 0.f;  // threads 0..63 stage lse, 64..127 stage D
   auto gload_stats = [&](int ib) {
-    if (threadIdx.x < KB) rs = lbase[ib * KB + threadIdx.x] * kLog2e;
-    else if (threadIdx.x < 2 * KB) rs = dbase[ib * KB + threadIdx.x - KB];
+    const int r = ib * KB + (threadIdx.x & (KB - 1));
+    if (EDGE && r >= s) rs = threadIdx.x < KB ? INFINITY : 0.f;  // 2^-inf: no weight
+    else if (threadIdx.x < KB) rs = lbase[r] * kLog2e;
+    else if (threadIdx.x < 2 * KB) rs = dbase[r];
   };
   auto lstore_stats = [&](int stage) {
     if (threadIdx.x < KB) sL[stage * KB + threadIdx.x] = rs;
     else if (threadIdx.x < 2 * KB) sD[stage * KB + threadIdx.x - KB] = rs;
   };
-  gload_tile<D>(rq, qbase + (long)ib0 * KB * ld, ld);
-  gload_tile<D>(ro, obase + (long)ib0 * KB * h, h);
+  gload_tile<D, NW, EDGE>(rq, qbase + (long)ib0 * KB * ld, ld, s - ib0 * KB, d);
+  gload_tile<D, NW, EDGE>(ro, obase + (long)ib0 * KB * h, h, s - ib0 * KB, d);
   gload_stats(ib0);
-  lstore_tile<D>(rq, sQ);
-  lstore_tile<D>(ro, sO);
+  lstore_tile<D, NW>(rq, sQ);
+  lstore_tile<D, NW>(ro, sO);
   lstore_stats(0);
   if (ib0 + 1 < nib) {
-    gload_tile<D>(rq, qbase + (long)(ib0 + 1) * KB * ld, ld);
-    gload_tile<D>(ro, obase + (long)(ib0 + 1) * KB * h, h);
+    gload_tile<D, NW, EDGE>(rq, qbase + (long)(ib0 + 1) * KB * ld, ld, s - (ib0 + 1) * KB, d);
+    gload_tile<D, NW, EDGE>(ro, obase + (long)(ib0 + 1) * KB * h, h, s - (ib0 + 1) * KB, d);
     gload_stats(ib0 + 1);
   }
   __syncthreads();
@@ -471,33 +549,54 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_kernel(const bf16_t* __restr
         if (kk >= 2 || act0) {
 #pragma unroll
           for (int et = 0; et < D / 32; ++et) {
-            dv[et] = mfma(frag_tr<D>(oc, et * 32, kk * 16, lane), pf[kk], dv[et]);
-            dk[et] = mfma(frag_tr<D>(qc, et * 32, kk * 16, lane), dsf[kk], dk[et]);
+            const bf16x8 of = frag_tr<D>(oc, et * 32, kk * 16, lane), qf = frag_tr<D>(qc, et * 32, kk * 16, lane);
+            dv[et] = mfma(of, pf[kk], dv[et]);
+            dk[et] = mfma(qf, dsf[kk], dk[et]);
+            if constexpr (EDGE) {
+              dv[et] = mfma(of, pack_rest(pt[kk >> 1], kk & 1), dv[et]);
+              dk[et] = mfma(qf, pack_rest(st[kk >> 1], kk & 1), dk[et]);
+            }
           }
         }
       }
     }
     if (ib + 1 < nib) {
-      lstore_tile<D>(rq, sQ + (stage ^ 1) * AT<D>::TILE);
-      lstore_tile<D>(ro, sO + (stage ^ 1) * AT<D>::TILE);
+      lstore_tile<D, NW>(rq, sQ + (stage ^ 1) * AT<D>::TILE);
+      lstore_tile<D, NW>(ro, sO + (stage ^ 1) * AT<D>::TILE);
       lstore_stats(stage ^ 1);
     }
     __syncthreads();
     if (ib + 2 < nib) {
-      gload_tile<D>(rq, qbase + (long)(ib + 2) * KB * ld, ld);
-      gload_tile<D>(ro, obase + (long)(ib + 2) * KB * h, h);
+      gload_tile<D, NW, EDGE>(rq, qbase + (long)(ib + 2) * KB * ld, ld, s - (ib + 2) * KB, d);
+      gload_tile<D, NW, EDGE>(ro, obase + (long)(ib + 2) * KB * h, h, s - (ib + 2) * KB, d);
       gload_stats(ib + 2);
     }
   }
-  bf16_t* kp = dqkv + (tok0 + kw0 + lk) * ld + h + head * D + hi * 4;
+  if (!mine) return;
+  bf16_t* kp = dqkv + (tok0 + kw0 + lk) * ld + h + head * d;
 #pragma unroll
   for (int et = 0; et < D / 32; ++et)
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      store4(kp + et * 32 + g * 8, dk[et][4 * g] * scale, dk[et][4 * g + 1] * scale, dk[et][4 * g + 2] * scale,
-             dk[et][4 * g + 3] * scale);
-      store4(kp + h + et * 32 + g * 8, dv[et][4 * g], dv[et][4 * g + 1], dv[et][4 * g + 2], dv[et][4 * g + 3]);
+      const int e = et * 32 + g * 8 + hi * 4;
+      store4_row<EDGE>(kp, e, d, dk[et][4 * g] * scale, dk[et][4 * g + 1] * scale, dk[et][4 * g + 2] * scale,
+                       dk[et][4 * g + 3] * scale);
+      store4_row<EDGE>(kp + h, e, d, dv[et][4 * g], dv[et][4 * g + 1], dv[et][4 * g + 2], dv[et][4 * g + 3]);
     }
+}
+
+// Both halves of the backward in one launch: they are independent, and each alone leaves most of the chip idle.
+// Even workgroups are key blocks, odd ones query blocks, those with the most tiles first.
+template <int D, int NW, bool EDGE>
+__global__ __launch_bounds__(64 * NW) void attn_bwd_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
+                                                           const float* __restrict__ lse, const float* __restrict__ dvec,
+                                                           bf16_t* __restrict__ dqkv, int s, int a, int d, float scale) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int blk = blockIdx.z >> 1, nblk = gridDim.z >> 1, head = blockIdx.x, bi = blockIdx.y;
+  if (blockIdx.z & 1)
+    attn_bwd_dq_body<D, NW, EDGE>(smem_raw, nblk - 1 - blk, head, bi, qkv, dout, lse, dvec, dqkv, s, a, d, scale);
+  else
+    attn_bwd_dkv_body<D, NW, EDGE>(smem_raw, blk, head, bi, qkv, dout, lse, dvec, dqkv, s, a, d, scale);
 }
 
 template <typename K> hipError_t set_smem(K kern, size_t smem, bool* done) {
@@ -508,42 +607,51 @@ template <typename K> hipError_t set_smem(K kern, size_t smem, bool* done) {
   return e;
 }
 
-template <int D> hipError_t run_fwd(const AttnArgs& a, hipStream_t s) {
+template <int D, int NW, bool EDGE> hipError_t run_fwd(const AttnArgs& a, hipStream_t s) {
   static bool done = false;
   constexpr size_t smem = (size_t)4 * AT<D>::TILE * sizeof(bf16_t);
-  hipError_t e = set_smem(attn_fwd_kernel<D>, smem, &done);
+  hipError_t e = set_smem(attn_fwd_kernel<D, NW, EDGE>, smem, &done);
   if (e != hipSuccess) return e;
-  dim3 grid(a.s / QB, a.a, a.b);
-  attn_fwd_kernel<D><<<grid, 256, smem, s>>>((const bf16_t*)a.qkv, (bf16_t*)a.out, a.lse, a.s, a.a,
-                                             kLog2e / sqrtf((float)D));
+  dim3 grid(a.a, a.b, (a.s + 32 * NW - 1) / (32 * NW));  // the last index is the slowest: heaviest blocks of all heads first
+  attn_fwd_kernel<D, NW, EDGE><<<grid, 64 * NW, smem, s>>>((const bf16_t*)a.qkv, (bf16_t*)a.out, a.lse, a.s, a.a, a.d,
+                                                          kLog2e / sqrtf((float)a.d));
   return hipGetLastError();
 }
 
-template <int D> hipError_t run_bwd(const AttnArgs& a, hipStream_t s) {
-  static bool done_q = false, done_kv = false;
-  constexpr size_t smem_q = (size_t)4 * AT<D>::TILE * sizeof(bf16_t);
-  constexpr size_t smem_kv = smem_q + 4 * KB * sizeof(float);
-  hipError_t e = set_smem(attn_bwd_dq_kernel<D>, smem_q, &done_q);
+template <int D, int NW, bool EDGE> hipError_t run_bwd(const AttnArgs& a, hipStream_t s) {
+  static bool done = false;
+  constexpr size_t smem = (size_t)4 * AT<D>::TILE * sizeof(bf16_t) + 4 * KB * sizeof(float);
+  hipError_t e = set_smem(attn_bwd_kernel<D, NW, EDGE>, smem, &done);
   if (e != hipSuccess) return e;
-  e = set_smem(attn_bwd_dkv_kernel<D>, smem_kv, &done_kv);
-  if (e != hipSuccess) return e;
-  const float scale = 1.0f / sqrtf((float)D);
-  dim3 grid1(a.s, a.a, a.b);
-  attn_bwd_prep_kernel<<<grid1, 64, 0, s>>>((const bf16_t*)a.o, (const bf16_t*)a.dout, a.dvec, a.s, a.a, D);
+  dim3 grid1((a.s + 15) / 16, a.a, a.b);
+  attn_bwd_prep_kernel<<<grid1, 256, 0, s>>>((const bf16_t*)a.o, (const bf16_t*)a.dout, a.dvec, a.s, a.a, a.d);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  dim3 grid(a.s / QB, a.a, a.b);
-  attn_bwd_dq_kernel<D><<<grid, 256, smem_q, s>>>((const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.dvec,
-                                                  (bf16_t*)a.dqkv, a.s, a.a, scale);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  attn_bwd_dkv_kernel<D><<<grid, 256, smem_kv, s>>>((const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.dvec,
-                                                    (bf16_t*)a.dqkv, a.s, a.a, scale);
+  dim3 grid(a.a, a.b, 2 * ((a.s + 32 * NW - 1) / (32 * NW)));
+  attn_bwd_kernel<D, NW, EDGE><<<grid, 64 * NW, smem, s>>>((const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.dvec,
+                                                          (bf16_t*)a.dqkv, a.s, a.a, a.d, 1.0f / sqrtf((float)a.d));
   return hipGetLastError();
 }
 
-inline bool mfma_shape(const AttnArgs& a) {
-  return a.s % QB == 0 && (a.d == 64 || a.d == 96 || a.d == 128);
+// whole tiles: head sizes 96 and 128 go to attention_mfma128.hip, 64 to the kernels above without edges
+inline bool whole_tiles(const AttnArgs& a) { return a.s % 128 == 0 && (a.d == 64 || a.d == 96 || a.d == 128); }
+// sizes the kernels above take (b and the row blocks are grid dimensions of 16 bits)
+inline bool mfma_shape(const AttnArgs& a) { return a.d >= 8 && a.d <= 128 && a.b < 65536 && a.a < 65536 && a.s <= (1 << 20); }
+// fewer than two 128-row blocks per CU: 64-row blocks
+inline bool narrow(const AttnArgs& a) { return (long)((a.s + 127) / 128) * a.a * a.b < 512; }
+
+template <template <int, int, bool> class Run, int D, bool EDGE> hipError_t run_nw(const AttnArgs& a, hipStream_t s) {
+  return narrow(a) ? Run<D, 2, EDGE>::run(a, s) : Run<D, 4, EDGE>::run(a, s);
+}
+template <int D, int NW, bool EDGE> struct Fwd { static hipError_t run(const AttnArgs& a, hipStream_t s) { return run_fwd<D, NW, EDGE>(a, s); } };
+template <int D, int NW, bool EDGE> struct Bwd { static hipError_t run(const AttnArgs& a, hipStream_t s) { return run_bwd<D, NW, EDGE>(a, s); } };
+
+template <template <int, int, bool> class Run> hipError_t run_shape(const AttnArgs& a, hipStream_t s) {
+  if (whole_tiles(a)) return run_nw<Run, 64, false>(a, s);
+  if (a.d <= 32) return run_nw<Run, 32, true>(a, s);
+  if (a.d <= 64) return run_nw<Run, 64, true>(a, s);
+  if (a.d <= 96) return run_nw<Run, 96, true>(a, s);
+  return run_nw<Run, 128, true>(a, s);
 }
 
 }  // namespace
@@ -559,12 +667,12 @@ template <typename T> hipError_t launch_attention_bwd_mfma(const AttnArgs& a, hi
 template <> hipError_t launch_attention_fwd_mfma<bf16_t>(const AttnArgs& a, hipStream_t s, bool* taken) {
   *taken = mfma_shape(a);
   if (!*taken) return hipSuccess;
-  return a.d == 64 ? run_fwd<64>(a, s) : launch_attention_fwd_d128(a, s);
+  return whole_tiles(a) && a.d != 64 ? launch_attention_fwd_d128(a, s) : run_shape<Fwd>(a, s);
 }
 template <> hipError_t launch_attention_bwd_mfma<bf16_t>(const AttnArgs& a, hipStream_t s, bool* taken) {
   *taken = mfma_shape(a);
   if (!*taken) return hipSuccess;
-  return a.d == 64 ? run_bwd<64>(a, s) : launch_attention_bwd_d128(a, s);
+  return whole_tiles(a) && a.d != 64 ? launch_attention_bwd_d128(a, s) : run_shape<Bwd>(a, s);
 }
 template hipError_t launch_attention_fwd_mfma<float>(const AttnArgs&, hipStream_t, bool*);
 template hipError_t launch_attention_bwd_mfma<float>(const AttnArgs&, hipStream_t, bool*);
