@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libzbstage.so")
 
-SOURCES = ["stage.hip", "kernels_rowwise.hip", "kernels_optimizer.hip", "gemm_generic.hip", "gemm_mfma.hip", "gemm_mfma_edge.hip",
+SOURCES = ["stage.hip", "kernels_rowwise.hip", "kernels_optimizer.hip", "gemm_generic.hip", "gemm_mfma.hip", "gemm_mfma_edge.hip", "gemm_f32.hip",
            "attention_generic.hip", "attention_mfma.hip", "attention_mfma128.hip", "autosched.hip",
            "kernels_endstage.hip"]
 

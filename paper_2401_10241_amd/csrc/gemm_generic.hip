@@ -1,7 +1,8 @@
 // Generic strided GEMM on the vector ALUs (fp32 accumulate): every shape, both data types, all
-// three operand forms (forward X*W, dgrad dY*W^T, wgrad X^T*dY).  It carries the fp32 workload and
-// any bf16 shape the MFMA kernel does not take.  64x64 output tile per 256-thread workgroup,
-// K walked in steps of 16 through LDS, 4x4 outputs per lane.
+// three operand forms (forward X*W, dgrad dY*W^T, wgrad X^T*dY).  It carries what the matrix-core kernels
+// do not take: contraction lengths or widths that do not allow 16-byte accesses (a vocabulary that is no
+// multiple of 4 in fp32, of 8 in bf16).  64x64 output tile per 256-thread workgroup, K walked in steps of 16
+// through LDS, 4x4 outputs per lane.
 #include "gemm_epilogue.h"
 
 namespace zb {
@@ -117,7 +118,7 @@ template <typename T> hipError_t launch_wgrad_multi(const WgradMultiArgs& w, hip
   bool taken = false;
   hipError_t e = launch_wgrad_multi_mfma<T>(w, s, &taken);
   if (taken) return e;
-  for (int q = 0; q < w.nprob; ++q) {  // problem by problem (fp32, or a shape the MFMA kernel does not take)
+  for (int q = 0; q < w.nprob; ++q) {  // problem by problem (a shape the matrix-core kernels do not take)
     GemmArgs g{};
     g.M = w.M[q]; g.N = w.N[q]; g.K = w.K;
     g.a_sm = 1; g.a_sk = w.M[q]; g.b_sk = w.N[q]; g.b_sn = 1;

@@ -721,16 +721,10 @@ hipError_t run_wgrad(WgradTable& tb, int K, hipStream_t s) {
 
 }  // namespace
 
-template <typename T> hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s, bool* taken) {
-  *taken = false;
-  return hipSuccess;
-}
+template <typename T> hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s, bool* taken);  // fp32: gemm_f32.hip
 
 // wgrad launch for the gradients of one W pass; *taken stays false if a shape is not one for the MFMA kernel
-template <typename T> hipError_t launch_wgrad_multi_mfma(const WgradMultiArgs& w, hipStream_t s, bool* taken) {
-  *taken = false;
-  return hipSuccess;
-}
+template <typename T> hipError_t launch_wgrad_multi_mfma(const WgradMultiArgs& w, hipStream_t s, bool* taken);
 template <> hipError_t launch_wgrad_multi_mfma<bf16_t>(const WgradMultiArgs& w, hipStream_t s, bool* taken) {
   *taken = false;
   if (w.nprob < 1 || w.nprob > kWgradMaxProblems || w.ngroup < 1 || w.ngroup > kGemmGroupMax ||
@@ -769,7 +763,6 @@ template <> hipError_t launch_wgrad_multi_mfma<bf16_t>(const WgradMultiArgs& w, 
   if (t128 > 256) return run_wgrad<128, 3, true>(tb, w.K, s);
   return run_wgrad<128, 5, true>(tb, w.K, s);
 }
-template hipError_t launch_wgrad_multi_mfma<float>(const WgradMultiArgs&, hipStream_t, bool*);
 
 namespace {
 
@@ -804,7 +797,5 @@ template <> hipError_t launch_gemm_mfma<bf16_t>(const GemmArgs& g, hipStream_t s
   if (g.epilogue == EPI_DGELU) return run_shape<EPI_DGELU>(g, lda, ldb, s, taken);
   return hipSuccess;
 }
-
-template hipError_t launch_gemm_mfma<float>(const GemmArgs&, hipStream_t, bool*);
 
 }  // namespace zb

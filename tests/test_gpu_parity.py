@@ -444,3 +444,30 @@ EDGES = [
 def test_edge_tiles(cfg):
     hidden, heads, ffn, seq, b, layers = cfg
     run_and_compare(W("edges", "bf16", layers, hidden, heads, ffn, seq, b, 4, 1, 3, "H2", seed=301 + hidden + seq))
+
+
+@pytest.mark.parametrize("cfg", [
+    (72, 3, 136, 33, 1, 2),      # widths and tokens cut every tile
+    (512, 4, 2048, 300, 2, 1),   # enough tiles for the 64 x 64 form, 600 tokens ragged
+    (40, 5, 8, 5, 1, 1),         # contractions shorter than one wave's block of 32
+], ids=lambda c: "h%d_a%d_f%d_s%d_b%d_L%d" % c)
+def test_fp32_tiles(cfg):
+    hidden, heads, ffn, seq, b, layers = cfg
+    run_and_compare(W("fp32_tiles", "fp32", layers, hidden, heads, ffn, seq, b, 4, 1, 3, "H2", seed=401 + hidden + seq))
+
+
+def test_fp32_grouped_w_has_the_bits_of_one_by_one_w():
+    import paper_2401_10241_amd as zb
+    w = W("grp32", "fp32", 2, 72, 3, 200, 50, 1, 4, 3, 6, "H1", seed=29)
+    params = zb_inputs.stage_params(w)
+    grads = []
+    for group in (True, False):
+        dev = make_device_stage(w, 6, group_w=group)
+        dev.set_params(params)
+        dev.begin_iteration(0, 6)
+        load_iteration(w, 0, 6, dev)
+        dev.run_schedule(4, 3, 6, "H1")   # ends in three consecutive W
+        dev.synchronize()
+        grads.append(dev.get_tensor(zb.T_FLAT_GRADS).copy())
+        dev.close()
+    assert np.abs(grads[0]).max() > 0 and grads[0].tobytes() == grads[1].tobytes()
