@@ -53,14 +53,16 @@ template <int D, int NW = 4> struct AT {
   static constexpr int TILE = KB * PITCH;      // elements
 };
 
-// Columns c0 .. c0+7 of a row of d columns (d >= 8), zeros from column d on; reads inside the row only, at any
-// even address.
+// Columns c0 .. c0+7 of a row of d columns (d >= 8): read inside the row only, at any even address; then, when
+// the load has arrived, zeros from column d on (`valid` false: all zeros).  Two steps so that a tile's loads are
+// all in flight before the first is waited for.
 typedef u32x4 __attribute__((aligned(2))) u32x4_any;
 __device__ __forceinline__ u32x4 load_chunk(const bf16_t* __restrict__ row, int c0, int d) {
-  const int at = min(c0, d - 8);
-  u32x4 v = *reinterpret_cast<const u32x4_any*>(row + at);
-  if (c0 != at) {  // the tail chunk, read from column d - 8: move it down by c0 - at elements
-    const int sh = c0 - at;
+  return *reinterpret_cast<const u32x4_any*>(row + min(c0, d - 8));
+}
+__device__ __forceinline__ u32x4 trim_chunk(u32x4 v, int c0, int d, bool valid) {
+  const int sh = valid ? c0 - min(c0, d - 8) : 8;
+  if (sh) {  // a tail chunk was read from column d - 8: move it down
     unsigned __int128 x = __builtin_bit_cast(unsigned __int128, v);
     x = sh < 8 ? x >> (16 * sh) : 0;
     v = __builtin_bit_cast(u32x4, x);
@@ -68,42 +70,39 @@ __device__ __forceinline__ u32x4 load_chunk(const bf16_t* __restrict__ row, int 
   return v;
 }
 
-// rows [0, KB) of a tile whose first `rows` exist (the others are zeros), NW * 64 threads
+// rows [0, KB) of a tile whose first `rows` exist, NW * 64 threads
 template <int D, int NW, bool EDGE, int CH>
 __device__ __forceinline__ void gload_tile(u32x4 (&reg)[CH], const bf16_t* __restrict__ base, long ld, int rows, int d) {
 #pragma unroll
   for (int j = 0; j < CH; ++j) {
     const int c = threadIdx.x + 64 * NW * j;
     const int row = c / (D / 8), dc = c % (D / 8);
-    if constexpr (EDGE) {
-      reg[j] = load_chunk(base + (long)min(row, rows - 1) * ld, dc * 8, d);
-      if (row >= rows) reg[j] = u32x4{0, 0, 0, 0};
-    } else {
-      reg[j] = *reinterpret_cast<const u32x4*>(base + (long)row * ld + dc * 8);
-    }
+    if constexpr (EDGE) reg[j] = load_chunk(base + (long)min(row, rows - 1) * ld, dc * 8, d);
+    else reg[j] = *reinterpret_cast<const u32x4*>(base + (long)row * ld + dc * 8);
   }
 }
-template <int D, int NW, int CH>
-__device__ __forceinline__ void lstore_tile(const u32x4 (&reg)[CH], bf16_t* __restrict__ s) {
+template <int D, int NW, bool EDGE, int CH>
+__device__ __forceinline__ void lstore_tile(const u32x4 (&reg)[CH], bf16_t* __restrict__ s, int rows, int d) {
 #pragma unroll
   for (int j = 0; j < CH; ++j) {
     const int c = threadIdx.x + 64 * NW * j;
     const int row = c / (D / 8), dc = c % (D / 8);
-    *reinterpret_cast<u32x4*>(s + row * AT<D>::PITCH + ((dc ^ ((row >> 2) & 1)) << 3)) = reg[j];
+    *reinterpret_cast<u32x4*>(s + row * AT<D>::PITCH + ((dc ^ ((row >> 2) & 1)) << 3)) =
+        EDGE ? trim_chunk(reg[j], dc * 8, d, row < rows) : reg[j];
   }
 }
 // the row's k-operand fragments (columns kk*16 + hi*8 ..) straight from memory
 template <int D, bool EDGE>
 __device__ __forceinline__ void load_row_frags(bf16x8 (&f)[D / 16], const bf16_t* __restrict__ row, int hi, bool valid, int d) {
+  if constexpr (EDGE) {
+    u32x4 v[D / 16];
 #pragma unroll
-  for (int kk = 0; kk < D / 16; ++kk) {
-    if constexpr (EDGE) {
-      u32x4 v = load_chunk(row, kk * 16 + hi * 8, d);
-      if (!valid) v = u32x4{0, 0, 0, 0};
-      f[kk] = __builtin_bit_cast(bf16x8, v);
-    } else {
-      f[kk] = *reinterpret_cast<const bf16x8*>(row + kk * 16 + hi * 8);
-    }
+    for (int kk = 0; kk < D / 16; ++kk) v[kk] = load_chunk(row, kk * 16 + hi * 8, d);
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk) f[kk] = __builtin_bit_cast(bf16x8, trim_chunk(v[kk], kk * 16 + hi * 8, d, valid));
+  } else {
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk) f[kk] = *reinterpret_cast<const bf16x8*>(row + kk * 16 + hi * 8);
   }
 }
 
@@ -205,8 +204,8 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const bf16_t* __restr
   u32x4 rk[AT<D, NW>::CH], rv[AT<D, NW>::CH];
   gload_tile<D, NW, EDGE>(rk, kbase, ld, s, d);
   gload_tile<D, NW, EDGE>(rv, vbase, ld, s, d);
-  lstore_tile<D, NW>(rk, sK);
-  lstore_tile<D, NW>(rv, sV);
+  lstore_tile<D, NW, EDGE>(rk, sK, s, d);
+  lstore_tile<D, NW, EDGE>(rv, sV, s, d);
   if (nkb > 1) {
     gload_tile<D, NW, EDGE>(rk, kbase + (long)KB * ld, ld, s - KB, d);
     gload_tile<D, NW, EDGE>(rv, vbase + (long)KB * ld, ld, s - KB, d);
@@ -279,8 +278,8 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const bf16_t* __restr
       }
     }
     if (jb + 1 < nkb) {
-      lstore_tile<D, NW>(rk, sK + ((jb + 1) & 1) * AT<D>::TILE);
-      lstore_tile<D, NW>(rv, sV + ((jb + 1) & 1) * AT<D>::TILE);
+      lstore_tile<D, NW, EDGE>(rk, sK + ((jb + 1) & 1) * AT<D>::TILE, s - (jb + 1) * KB, d);
+      lstore_tile<D, NW, EDGE>(rv, sV + ((jb + 1) & 1) * AT<D>::TILE, s - (jb + 1) * KB, d);
     }
     __syncthreads();
     if (jb + 2 < nkb) {
@@ -357,8 +356,8 @@ __device__ __forceinline__ void attn_bwd_dq_body(unsigned char* smem_raw, int qb
   u32x4 rk[AT<D, NW>::CH], rv[AT<D, NW>::CH];
   gload_tile<D, NW, EDGE>(rk, kbase, ld, s, d);
   gload_tile<D, NW, EDGE>(rv, vbase, ld, s, d);
-  lstore_tile<D, NW>(rk, sK);
-  lstore_tile<D, NW>(rv, sV);
+  lstore_tile<D, NW, EDGE>(rk, sK, s, d);
+  lstore_tile<D, NW, EDGE>(rv, sV, s, d);
   if (nkb > 1) {
     gload_tile<D, NW, EDGE>(rk, kbase + (long)KB * ld, ld, s - KB, d);
     gload_tile<D, NW, EDGE>(rv, vbase + (long)KB * ld, ld, s - KB, d);
@@ -414,8 +413,8 @@ __device__ __forceinline__ void attn_bwd_dq_body(unsigned char* smem_raw, int qb
       }
     }
     if (jb + 1 < nkb) {
-      lstore_tile<D, NW>(rk, sK + ((jb + 1) & 1) * AT<D>::TILE);
-      lstore_tile<D, NW>(rv, sV + ((jb + 1) & 1) * AT<D>::TILE);
+      lstore_tile<D, NW, EDGE>(rk, sK + ((jb + 1) & 1) * AT<D>::TILE, s - (jb + 1) * KB, d);
+      lstore_tile<D, NW, EDGE>(rv, sV + ((jb + 1) & 1) * AT<D>::TILE, s - (jb + 1) * KB, d);
     }
     __syncthreads();
     if (jb + 2 < nkb) {
@@ -486,8 +485,8 @@ __device__ __forceinline__ void attn_bwd_dkv_body(unsigned char* smem_raw, int k
   gload_tile<D, NW, EDGE>(rq, qbase + (long)ib0 * KB * ld, ld, s - ib0 * KB, d);
   gload_tile<D, NW, EDGE>(ro, obase + (long)ib0 * KB * h, h, s - ib0 * KB, d);
   gload_stats(ib0);
-  lstore_tile<D, NW>(rq, sQ);
-  lstore_tile<D, NW>(ro, sO);
+  lstore_tile<D, NW, EDGE>(rq, sQ, s - ib0 * KB, d);
+  lstore_tile<D, NW, EDGE>(ro, sO, s - ib0 * KB, d);
   lstore_stats(0);
   if (ib0 + 1 < nib) {
     gload_tile<D, NW, EDGE>(rq, qbase + (long)(ib0 + 1) * KB * ld, ld, s - (ib0 + 1) * KB, d);
@@ -561,8 +560,8 @@ __device__ __forceinline__ void attn_bwd_dkv_body(unsigned char* smem_raw, int k
       }
     }
     if (ib + 1 < nib) {
-      lstore_tile<D, NW>(rq, sQ + (stage ^ 1) * AT<D>::TILE);
-      lstore_tile<D, NW>(ro, sO + (stage ^ 1) * AT<D>::TILE);
+      lstore_tile<D, NW, EDGE>(rq, sQ + (stage ^ 1) * AT<D>::TILE, s - (ib + 1) * KB, d);
+      lstore_tile<D, NW, EDGE>(ro, sO + (stage ^ 1) * AT<D>::TILE, s - (ib + 1) * KB, d);
       lstore_stats(stage ^ 1);
     }
     __syncthreads();
@@ -656,14 +655,9 @@ template <template <int, int, bool> class Run> hipError_t run_shape(const AttnAr
 
 }  // namespace
 
-template <typename T> hipError_t launch_attention_fwd_mfma(const AttnArgs& a, hipStream_t s, bool* taken) {
-  *taken = false;
-  return hipSuccess;
-}
-template <typename T> hipError_t launch_attention_bwd_mfma(const AttnArgs& a, hipStream_t s, bool* taken) {
-  *taken = false;
-  return hipSuccess;
-}
+// fp32: attention_f32.hip
+template <typename T> hipError_t launch_attention_fwd_mfma(const AttnArgs& a, hipStream_t s, bool* taken);
+template <typename T> hipError_t launch_attention_bwd_mfma(const AttnArgs& a, hipStream_t s, bool* taken);
 template <> hipError_t launch_attention_fwd_mfma<bf16_t>(const AttnArgs& a, hipStream_t s, bool* taken) {
   *taken = mfma_shape(a);
   if (!*taken) return hipSuccess;
