@@ -15,7 +15,7 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libzbstage.so")
 
 SOURCES = ["stage.hip", "kernels_rowwise.hip", "kernels_optimizer.hip", "gemm_generic.hip", "gemm_mfma.hip", "gemm_mfma_edge.hip", "gemm_f32.hip",
-           "attention_generic.hip", "attention_mfma.hip", "attention_mfma128.hip", "autosched.hip",
+           "attention_generic.hip", "attention_mfma.hip", "attention_mfma128.hip", "attention_f32.hip", "autosched.hip",
            "kernels_endstage.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

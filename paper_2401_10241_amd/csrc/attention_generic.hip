@@ -1,6 +1,6 @@
 // Causal multi-head attention, forward and backward, on the vector ALUs: one wavefront per
-// (sample, head, row).  Any head size and sequence length; fp32 arithmetic.  It carries the fp32
-// workload and any bf16 shape the MFMA attention kernels do not take.
+// (sample, head, row).  Any head size and sequence length; fp32 arithmetic.  It carries what the matrix-core
+// kernels do not take: head sizes below 8 and above 128, in fp32 also those that are no multiple of 4.
 //
 // forward (per query row i):   s_j = q_i.k_j / sqrt(d) for j <= i;  p = softmax(s);  o_i = sum_j p_j v_j;
 //                              lse_i = log sum_j exp(s_j)  (kept for the backward)

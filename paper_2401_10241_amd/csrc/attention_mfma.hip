@@ -668,7 +668,5 @@ template <> hipError_t launch_attention_bwd_mfma<bf16_t>(const AttnArgs& a, hipS
   if (!*taken) return hipSuccess;
   return whole_tiles(a) && a.d != 64 ? launch_attention_bwd_d128(a, s) : run_shape<Bwd>(a, s);
 }
-template hipError_t launch_attention_fwd_mfma<float>(const AttnArgs&, hipStream_t, bool*);
-template hipError_t launch_attention_bwd_mfma<float>(const AttnArgs&, hipStream_t, bool*);
 
 }  // namespace zb

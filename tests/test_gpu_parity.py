@@ -450,6 +450,11 @@ def test_edge_tiles(cfg):
     (72, 3, 136, 33, 1, 2),      # widths and tokens cut every tile
     (512, 4, 2048, 300, 2, 1),   # enough tiles for the 64 x 64 form, 600 tokens ragged
     (40, 5, 8, 5, 1, 1),         # contractions shorter than one wave's block of 32
+    (160, 8, 320, 161, 1, 1),    # head size 20, six blocks of 32 rows (a wave takes two), the last one row long
+    (384, 4, 768, 97, 2, 1),     # head size 96
+    (200, 2, 400, 64, 1, 1),     # head size 100
+    (152, 2, 304, 40, 1, 1),     # head size 76; 152 / 8 = 19 below
+    (152, 8, 304, 40, 1, 1),     # head size 19: one wavefront per row
 ], ids=lambda c: "h%d_a%d_f%d_s%d_b%d_L%d" % c)
 def test_fp32_tiles(cfg):
     hidden, heads, ffn, seq, b, layers = cfg
