@@ -273,6 +273,56 @@ __device__ __forceinline__ void layernorm_bwd_param_body(int bx, int by, const T
   }
 }
 
+// The same column sums over all rows, straight onto dgamma / dbeta: 32 columns per workgroup, 256 threads = 4
+// column-lanes (8 consecutive columns each) x 64 row groups; row groups are added in a fixed order.
+template <typename T>
+__device__ __forceinline__ void layernorm_bwd_param_whole(int bx, const T* __restrict__ g, const T* __restrict__ x,
+                                                          const float* __restrict__ stats, float* __restrict__ dgamma,
+                                                          float* __restrict__ dbeta, int rows, int h) {
+  __shared__ float red[64][65];
+  __shared__ float red4[4][64];
+  const int cl = threadIdx.x & 3, rg = threadIdx.x >> 2;
+  const int col = bx * 32 + cl * 8;
+  float ag[8], ab[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ag[e] = ab[e] = 0.f;
+  if (col < h) {
+    const bool second = col + 4 < h;  // h is a multiple of 4
+#pragma unroll 4
+    for (int r = rg; r < rows; r += 64) {
+      const float mean = stats[r * 2], rstd = stats[r * 2 + 1];
+      const size_t off = (size_t)r * h + col;
+      float gv[2][4], xv[2][4];
+      Vec4<T>::load(g + off, gv[0]);
+      Vec4<T>::load(x + off, xv[0]);
+      Vec4<T>::load(g + off + (second ? 4 : 0), gv[1]);
+      Vec4<T>::load(x + off + (second ? 4 : 0), xv[1]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        ag[e] += gv[e >> 2][e & 3] * ((xv[e >> 2][e & 3] - mean) * rstd);
+        ab[e] += gv[e >> 2][e & 3];
+      }
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    red[rg][cl * 8 + e] = ag[e];
+    red[rg][32 + cl * 8 + e] = ab[e];
+  }
+  __syncthreads();
+  const int t = threadIdx.x & 63, part = threadIdx.x >> 6;
+  float sum = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) sum += red[part * 16 + r][t];
+  red4[part][t] = sum;
+  __syncthreads();
+  const int c = bx * 32 + (t & 31);
+  if (part == 0 && c < h) {
+    float* __restrict__ d = t < 32 ? dgamma : dbeta;
+    d[c] += (red4[0][t] + red4[1][t]) + (red4[2][t] + red4[3][t]);
+  }
+}
+
 // LayerNorm backward fused with the end of the split-K dgrad GEMM that produces its incoming gradient g: one
 // row per workgroup; g = the sum of the `slices` planes (slice order), rounded to T and stored (the gamma /
 // beta sums read it afterwards); dx as in layernorm_bwd_dx_body, from the same registers.
@@ -348,6 +398,23 @@ __global__ __launch_bounds__(kThreads) void layernorm_bwd_kernel(const T* __rest
     const int q = blockIdx.x - dx_rows;
     layernorm_bwd_param_body<T>(q % col_blocks, q / col_blocks, g, x, stats, partials, rows, h, rows_per_slice);
   }
+}
+
+// Few rows: the parameter sums are finished by this launch too (its first `pblocks` workgroups, the longer ones).
+// A launch of its own for the sums of row slices costs 3 us and the gap before it (128 rows of 256: 4.4 + 3.0 us ->
+// 4.1), but one workgroup's walk over all rows grows with them: 1024 rows of 2304 take 14.4 us against 4.8 + 4.7,
+// 777 of 1200 12.2, 512 of 768 the same as both together.
+constexpr int kParamRows = 256;
+template <typename T, int NCH>
+__global__ __launch_bounds__(kThreads) void layernorm_bwd_whole_kernel(const T* __restrict__ g, const T* __restrict__ x,
+                                                                       const float* __restrict__ stats,
+                                                                       const float* __restrict__ gamma,
+                                                                       const T* __restrict__ resid, T* __restrict__ dx,
+                                                                       float* __restrict__ dgamma,
+                                                                       float* __restrict__ dbeta, int rows, int h,
+                                                                       int pblocks) {
+  if ((int)blockIdx.x < pblocks) layernorm_bwd_param_whole<T>(blockIdx.x, g, x, stats, dgamma, dbeta, rows, h);
+  else layernorm_bwd_dx_body<T, NCH>(blockIdx.x - pblocks, g, x, stats, gamma, resid, dx, h);
 }
 
 // dgamma[c] += sum_b partials[b][0][c]; dbeta[c] += sum_b partials[b][1][c], always in the same order:
@@ -523,7 +590,13 @@ hipError_t launch_layernorm_fwd(const T* x, const float* gamma, const float* bet
 
 template <typename T, int NCH>
 hipError_t run_ln_bwd(const T* g, const T* x, const float* stats, const float* gamma, const T* resid, T* dx,
-                      float* partials, int rows, int h, int slices, hipStream_t s) {
+                      float* dgamma, float* dbeta, float* partials, int rows, int h, int slices, hipStream_t s) {
+  if (rows <= kParamRows) {
+    const int pblocks = (h + 31) / 32;
+    layernorm_bwd_whole_kernel<T, NCH><<<pblocks + rows, kThreads, 0, s>>>(g, x, stats, gamma, resid, dx, dgamma, dbeta,
+                                                                          rows, h, pblocks);
+    return hipGetLastError();
+  }
   const int rows_per_slice = (rows + slices - 1) / slices, col_blocks = (h + 127) / 128;
   layernorm_bwd_kernel<T, NCH><<<rows + col_blocks * slices, kThreads, 0, s>>>(g, x, stats, gamma, resid, dx, partials,
                                                                              rows, h, rows_per_slice, col_blocks, rows);
@@ -541,15 +614,15 @@ hipError_t launch_layernorm_bwd(const T* g, const T* x, const float* stats, cons
   if (slices > kLnBwdSlices) slices = kLnBwdSlices;
   hipError_t e;
   switch (nch) {
-    case 1: e = run_ln_bwd<T, 1>(g, x, stats, gamma, resid, dx, partials, rows, h, slices, s); break;
-    case 2: e = run_ln_bwd<T, 2>(g, x, stats, gamma, resid, dx, partials, rows, h, slices, s); break;
-    case 3: e = run_ln_bwd<T, 3>(g, x, stats, gamma, resid, dx, partials, rows, h, slices, s); break;
-    case 4: e = run_ln_bwd<T, 4>(g, x, stats, gamma, resid, dx, partials, rows, h, slices, s); break;
-    case 5: e = run_ln_bwd<T, 5>(g, x, stats, gamma, resid, dx, partials, rows, h, slices, s); break;
-    case 6: e = run_ln_bwd<T, 6>(g, x, stats, gamma, resid, dx, partials, rows, h, slices, s); break;
-    default: e = run_ln_bwd<T, 8>(g, x, stats, gamma, resid, dx, partials, rows, h, slices, s); break;
+    case 1: e = run_ln_bwd<T, 1>(g, x, stats, gamma, resid, dx, dgamma, dbeta, partials, rows, h, slices, s); break;
+    case 2: e = run_ln_bwd<T, 2>(g, x, stats, gamma, resid, dx, dgamma, dbeta, partials, rows, h, slices, s); break;
+    case 3: e = run_ln_bwd<T, 3>(g, x, stats, gamma, resid, dx, dgamma, dbeta, partials, rows, h, slices, s); break;
+    case 4: e = run_ln_bwd<T, 4>(g, x, stats, gamma, resid, dx, dgamma, dbeta, partials, rows, h, slices, s); break;
+    case 5: e = run_ln_bwd<T, 5>(g, x, stats, gamma, resid, dx, dgamma, dbeta, partials, rows, h, slices, s); break;
+    case 6: e = run_ln_bwd<T, 6>(g, x, stats, gamma, resid, dx, dgamma, dbeta, partials, rows, h, slices, s); break;
+    default: e = run_ln_bwd<T, 8>(g, x, stats, gamma, resid, dx, dgamma, dbeta, partials, rows, h, slices, s); break;
   }
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || rows <= kParamRows) return e;
   layernorm_bwd_reduce_kernel<<<(h + 63) / 64, 256, 0, s>>>(partials, dgamma, dbeta, slices, h);
   return hipGetLastError();
 }
@@ -576,8 +649,12 @@ hipError_t launch_splitk_layernorm_bwd(const float* planes, int slices, size_t p
 #define ZB_RUN(N)                                                                                                   \
   splitk_layernorm_bwd_kernel<T, N><<<rows, kThreads, 0, s>>>(planes, slices, plane, g_out, x, stats, gamma, resid,  \
                                                               dx, h);                                               \
-  layernorm_bwd_kernel<T, N><<<col_blocks * pslices, kThreads, 0, s>>>(g_out, x, stats, gamma, resid, dx, partials,  \
-                                                                       rows, h, rows_per_slice, col_blocks, 0)
+  if (rows <= kParamRows)                                                                                           \
+    layernorm_bwd_whole_kernel<T, N><<<(h + 31) / 32, kThreads, 0, s>>>(g_out, x, stats, gamma, resid, dx, dgamma,   \
+                                                                        dbeta, rows, h, (h + 31) / 32);              \
+  else                                                                                                              \
+    layernorm_bwd_kernel<T, N><<<col_blocks * pslices, kThreads, 0, s>>>(g_out, x, stats, gamma, resid, dx, partials, \
+                                                                         rows, h, rows_per_slice, col_blocks, 0)
   switch (nch) {
     case 1: ZB_RUN(1); break;
     case 2: ZB_RUN(2); break;
@@ -589,7 +666,7 @@ hipError_t launch_splitk_layernorm_bwd(const float* planes, int slices, size_t p
   }
 #undef ZB_RUN
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || rows <= kParamRows) return e;
   layernorm_bwd_reduce_kernel<<<(h + 63) / 64, 256, 0, s>>>(partials, dgamma, dbeta, pslices, h);
   return hipGetLastError();
 }
