@@ -81,6 +81,34 @@ __device__ __forceinline__ int xcd_run(int id, int nblk) {
 
 constexpr int ST = 4;  // LDS stages
 
+// epilogue_tile for a tile that the last row cuts: all reads first (from the last row where a row does not exist), or
+// every row would wait for a read of its own behind the store before it
+template <int MODE>
+__device__ __forceinline__ void epilogue_edge(const EpiParams& e, int m0, int M, int n, const f32x16& acc) {
+  size_t idx[16];
+  float a[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) idx[v] = (size_t)min(m0 + (v >> 2) * 8 + (v & 3), M - 1) * e.N + n;
+  if (MODE == EPI_BIAS_RESID || MODE == EPI_DGELU) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) a[v] = to_f32(((const bf16_t*)e.aux)[idx[v]]);
+  }
+  const float b = MODE == EPI_BIAS || MODE == EPI_BIAS_RESID || MODE == EPI_BIAS_GELU ? e.bias[n] : 0.f;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    if (m0 + (v >> 2) * 8 + (v & 3) >= M) continue;
+    const float f = acc[v] + b;
+    if (MODE == EPI_PARTIAL) {
+      e.outf[idx[v]] = acc[v];
+    } else if (MODE == EPI_DGELU) {
+      ((bf16_t*)e.out0)[idx[v]] = (bf16_t)(acc[v] * gelu_grad_f(a[v]));
+    } else {
+      ((bf16_t*)e.out0)[idx[v]] = (bf16_t)(MODE == EPI_BIAS_RESID ? f + a[v] : f);
+      if (MODE == EPI_BIAS_GELU) ((bf16_t*)e.out1)[idx[v]] = (bf16_t)gelu_f(f);
+    }
+  }
+}
+
 template <int BM, int BN, int NWM, int NWN, int MODE>
 __global__ __launch_bounds__(64 * NWM * NWN) void gemm_edge_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
                                                                   int M, int N, int K, long lda, long ldb, EpiParams epi,
@@ -194,13 +222,7 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_edge_kernel(const bf16_t*
       if (mb + 32 <= M && nb + 32 <= N) {
         epilogue_tile<bf16_t, MODE>(epi, mb + lhi, nb + lrow, acc[i][j]);
       } else if (nb + lrow < N) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int m = mb + lhi + (v >> 2) * 8 + (v & 3);
-          if (m >= M) continue;
-          if (MODE == EPI_PARTIAL) epi.outf[(size_t)m * epi.N + nb + lrow] = acc[i][j][v];
-          else epilogue_one<bf16_t, MODE>(epi, m, nb + lrow, acc[i][j][v]);
-        }
+        epilogue_edge<MODE>(epi, mb + lhi, M, nb + lrow, acc[i][j]);
       }
     }
 }
