@@ -39,12 +39,12 @@ struct LayerOff {  // byte offsets inside one slot of each pool
 };
 
 enum KClass {
-  KC_GEMM_FWD = 0, KC_GEMM_DGRAD, KC_GEMM_WGRAD, KC_ATTN_FWD, KC_ATTN_BWD, KC_LN_FWD, KC_LN_BWD, KC_COLSUM,
+  KC_GEMM_FWD = 0, KC_GEMM_DGRAD, KC_GEMM_WGRAD, KC_ATTN_FWD, KC_ATTN_BWD, KC_LN_FWD, KC_LN_BWD,
   KC_FILL, KC_SUMSQ, KC_ADAMW_STEP, KC_ADAMW_ROLLBACK, KC_ADAMW_RESTEP, KC_TRANSPOSE, KC_EMBED, KC_LOSS, KC_COUNT
 };
 const char* const kClassNames[KC_COUNT] = {
     "gemm_fwd", "gemm_dgrad", "gemm_wgrad", "attention_fwd", "attention_bwd", "layernorm_fwd", "layernorm_bwd",
-    "bias_grad_colsum", "grad_zero_fill", "grad_sumsq", "adamw_step", "adamw_rollback", "adamw_restep",
+    "grad_zero_fill", "grad_sumsq", "adamw_step", "adamw_rollback", "adamw_restep",
     "weight_transpose", "embedding", "cross_entropy"};
 
 struct ProfRec {
@@ -280,12 +280,7 @@ size_t layout(zb_stage* st, void* arena) {
   }
   st->tmp = bp.take<char>(T * h * E);
   st->dvec = bp.take<float>((size_t)st->b * st->a * st->s * sizeof(float));
-  {  // LayerNorm-backward partials; the bias-gradient column sums reuse it for their row slices
-    size_t need = (size_t)kLnBwdSlices * 2 * h;
-    const size_t all_dy = (size_t)h + f + h + 3 * h;  // the four dY of a layer side by side
-    if ((size_t)kColsumSlices * all_dy > need) need = (size_t)kColsumSlices * all_dy;
-    st->ln_partials = bp.take<float>(need * sizeof(float));
-  }
+  st->ln_partials = bp.take<float>((size_t)kLnBwdSlices * 2 * h * sizeof(float));
   size_t stg = h * f;
   if (h * 3 * h > stg) stg = h * 3 * h;
   if (T * h > stg) stg = T * h;
@@ -626,8 +621,7 @@ template <typename T> struct Exec {
   // GEMMs of as many whole layers as one launch takes (tiles of equal duration, so the partly filled last
   // round of workgroups is paid once per launch, not once per weight matrix), each summing its n operand
   // pairs in the order given.  The bias gradients (column sums of the same dY operands, microbatch by
-  // microbatch in the same order) are taken by extra workgroups of that launch where the MFMA kernel runs it,
-  // by the column-sum kernels otherwise.
+  // microbatch in the same order) are taken by extra workgroups of that launch.
   static zb_status wgrad_layers(zb_stage* st, const int* mbs, int n, int l_hi, int l_lo) {
     const int h = st->h, f = st->ffn, T_ = st->T;
     hipStream_t s = st->stream;
@@ -649,7 +643,6 @@ template <typename T> struct Exec {
     int per_launch = kWgradMaxPairs / (4 * n);  // whole layers per launch
     if (per_launch > kWgradMaxProblems / 4) per_launch = kWgradMaxProblems / 4;
     if (per_launch < 1) per_launch = 1;
-    std::vector<char> bias_in_launch(st->L, 0);
     for (int l1 = l_hi; l1 >= l_lo; l1 -= per_launch) {
       const int l0 = l1 - per_launch + 1 > l_lo ? l1 - per_launch + 1 : l_lo;
       WgradMultiArgs w{};
@@ -675,21 +668,7 @@ template <typename T> struct Exec {
         ProfScope ps(st, KC_GEMM_WGRAD, flops, bytes);
         ZB_HIP(st, launch_wgrad_multi<T>(w, s));
       }
-      if (bias_done)
-        for (int l = l1; l >= l0; --l) bias_in_launch[l] = 1;
-    }
-    for (int l = l_hi; l >= l_lo; --l) {
-      if (bias_in_launch[l]) continue;  // the wgrad launch summed the columns of its dY operands itself
-      Lin lins[4];
-      lins_of(l, lins);
-      for (int i = 0; i < n; ++i) {  // the four bias gradients: column sums of the same dY's
-        const void* dys[4];
-        float* dbs[4];
-        int ns[4];
-        for (int q = 0; q < 4; ++q) { dys[q] = dy_of(lins[q], mbs[i]); dbs[q] = st->G(l, lins[q].bi); ns[q] = lins[q].nout; }
-        ProfScope ps(st, KC_COLSUM, 0, E * T_ * (double)(ns[0] + ns[1] + ns[2] + ns[3]));
-        ZB_HIP(st, launch_colsum_accum_multi<T>(dys, dbs, ns, 4, st->ln_partials, T_, s));
-      }
+      if (!bias_done) return fail(st, ZB_EDEVICE, "no W kernel takes these operands");  // every valid stage has one
     }
     return ZB_OK;
   }

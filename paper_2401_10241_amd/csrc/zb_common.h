@@ -109,7 +109,8 @@ struct WgradMultiArgs {
   const void* a[kWgradMaxPairs];  // pair g of problem q at [q * ngroup + g]
   const void* b[kWgradMaxPairs];
   // optional: bias[q] (N[q] floats) += column sums of problem q's b operands, pair by pair in the order given.
-  // *bias_done is set if the launch did it (extra workgroups of the same launch); otherwise the caller does.
+  // *bias_done is set if the launch did it (extra workgroups of the same launch); the problem-by-problem
+  // fallback for a head of odd width does not, and its caller asks for none.
   float* bias[kWgradMaxProblems];
   bool* bias_done;
 };
@@ -158,21 +159,6 @@ template <typename T>
 hipError_t launch_splitk_layernorm_bwd(const float* planes, int slices, size_t plane, T* g_out, const T* x,
                                        const float* stats, const float* gamma, const T* resid, T* dx, float* dgamma,
                                        float* dbeta, float* partials, int rows, int h, hipStream_t s);
-
-// bias gradients: db[q][c] += sum_rows dy[q][r, c] for `count` <= 4 matrices dy[q] of [rows, n[q]] in one launch
-// pair; row slices are added in a fixed order; scratch holds kColsumSlices * (n[0] + ... + n[count-1]) floats
-constexpr int kColsumSlices = 8;
-struct ColsumSegs {
-  const void* dy[4];
-  float* db[4];
-  int n[4];
-  int blk0[4];  // first column block of each matrix in the launch
-  int col0[4];  // first column of each matrix in the scratch rows
-  int total;    // n[0] + ... + n[count-1]
-};
-template <typename T>
-hipError_t launch_colsum_accum_multi(const void* const* dy, float* const* db, const int* n, int count,
-                                     float* scratch, int rows, hipStream_t s);
 
 hipError_t launch_fill_f32(float* p, size_t n, float v, hipStream_t s);
 hipError_t launch_transpose_bf16(const bf16_t* src, bf16_t* dst, int rows, int cols, hipStream_t s);
