@@ -5,10 +5,12 @@
 // straight from memory into registers (one block of 32 k ahead), and the waves' partial tiles are added through
 // LDS in wave order.  What bounds the products that come here (hundreds of tokens, widths up to a few thousand)
 // is latency: with the K range walked in steps of 16 through LDS by a 64 x 64 tile, 128 x 256 x 1024 took 64
-// dependent steps on 8 CUs; here it is 4 on 32.  Tiles are 32 x 32 with eight waves while those do not give every
-// CU four workgroups, else 64 x 64 with four waves (half the reads per product, twice the chain).  Measured on
+// dependent steps on 8 CUs; here it is 4 on 32.  Tiles are 32 x 32 with eight waves or 64 x 64 with four (half the
+// reads per product, twice the chain); the rules are at `kWideTiles` and `wide_wgrad`.  Measured on
 // the stage of hidden 256 with 128 tokens: N = 256 products 103-111 us -> 10-15 us, a W pass 215 us in eight
 // launches plus column sums -> 17 us in one, the iteration 4.97 -> 1.09 ms.
+#include <algorithm>
+
 #include "gemm_epilogue.h"
 
 namespace zb {
@@ -203,9 +205,25 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_wgrad_kernel(F32WgradTable t
   }
 }
 
-constexpr long kWideTiles = 1024;  // four workgroups per CU: from here on the 64 x 64 tile fills the chip, too
-
 inline long tiles_of(int M, int N, int t) { return (long)((M + t - 1) / t) * ((N + t - 1) / t); }
+
+// Forward / dgrad: 64 x 64 tiles with four waves from four 32 x 32 tiles per CU on.  Measured, us with 32 x 32 / 64 x 64
+// tiles: 512 x 1024 x 256 (512 tiles) 7.6 / 10.5, 512 x 1536 x 512 (768) 20.9 / 16.5, 512 x 2048 x 512 (1024) 29.2 /
+// 18.6, 600 x 2048 x 512 (1216) 36.8 / 29.3, its dgrad 28.3 / 32.8, 1024 x 4096 x 1024 (4096) 220 / 98.
+constexpr long kWideTiles = 1024;
+
+// W: the two forms split K over eight and four waves, i.e. add in different orders, so the choice may rest only on what
+// is the same in every launch of a stage - the tokens and the largest gradient of a layer - and not on how many layers
+// share the launch: the gradients keep their bits in every grouping.  The wide form pays with at most one 32-k block
+// per wave and gradients that fill half the chip.  Measured, us with 32 x 32 / 64 x 64 tiles, hidden h, ffn 4 h: 128 tokens
+// h 128 (largest gradient 64 tiles of 32 x 32) one layer 4.4 / 8.3, four 12.8 / 8.8; h 192 (144) one 6.9 / 8.5, two 12.7 / 8.9;
+// h 256 (256) one 10.9 / 8.7, four 41 / 27; h 1024 128 / 88; h 256, two layers 64 tokens 18.7 / 15.4, 136 tokens 23.6 / 26.4,
+// 512 tokens 39 / 104; h 1024, 512 tokens 256 / 531.
+inline bool wide_wgrad(const WgradMultiArgs& w) {
+  long most = 0;
+  for (int q = 0; q < w.nprob; ++q) most = std::max(most, tiles_of(w.M[q], w.N[q], 32));
+  return w.K <= 4 * KB && most >= 128;
+}
 
 template <bool BKC, int MODE> hipError_t run_f32(const GemmArgs& g, long lda, long ldb, hipStream_t s) {
   const long small = tiles_of(g.M, g.N, 32);
@@ -248,7 +266,7 @@ template <> hipError_t launch_wgrad_multi_mfma<float>(const WgradMultiArgs& w, h
     small += tiles_of(w.M[q], w.N[q], 32);
   }
   if (small >= (1L << 30)) return hipSuccess;
-  const bool wide = small >= kWideTiles;
+  const bool wide = wide_wgrad(w);
   int tiles = 0, strips = 0;
   for (int q = 0; q < w.nprob; ++q) {
     tb.M[q] = w.M[q]; tb.N[q] = w.N[q]; tb.outf[q] = w.outf[q];

@@ -476,3 +476,42 @@ def test_fp32_grouped_w_has_the_bits_of_one_by_one_w():
         grads.append(dev.get_tensor(zb.T_FLAT_GRADS).copy())
         dev.close()
     assert np.abs(grads[0]).max() > 0 and grads[0].tobytes() == grads[1].tobytes()
+
+
+@pytest.mark.parametrize("hidden,heads,ffn,seq,layers,groups", [
+    (256, 4, 1024, 160, 2, (9, 1)),  # nine and more microbatches: one layer per W launch instead of both
+    (256, 4, 1024, 128, 2, (9, 1)),  # the same at 128 tokens: 64 x 64 tiles
+    (160, 5, 640, 160, 4, (5, 5)),   # five microbatches: three layers and one instead of all four
+], ids=["h256_s160_L2", "h256_s128_L2", "h160_s160_L4"])
+def test_fp32_w_bits_do_not_depend_on_the_layers_per_launch(hidden, heads, ffn, seq, layers, groups):
+    # how many layers share a W launch follows from the number of microbatches and from the pass (the single
+    # backward takes one layer at a time); at 160 tokens the waves of a workgroup split K unevenly
+    import paper_2401_10241_amd as zb
+    m = sum(groups)
+    w = W("fp32_bits", "fp32", layers, hidden, heads, ffn, seq, 1, 4, 2, m, "1F1B", seed=37)
+    params = zb_inputs.stage_params(w)
+    grads = []
+    for mode in ("one by one", "groups", "fused"):
+        dev = make_device_stage(w, m, pools=(m, m, m))
+        dev.set_params(params)
+        dev.begin_iteration(0, m)
+        load_iteration(w, 0, m, dev)
+        for k in range(m):
+            dev.forward(k)
+            if mode == "fused":
+                dev.backward_fused(k)
+            else:
+                dev.backward_input(k)
+                if mode == "one by one":
+                    dev.backward_weight(k)
+        if mode == "groups":
+            k = 0
+            for n in groups:
+                dev.backward_weight_group(list(range(k, k + n))) if n > 1 else dev.backward_weight(k)
+                k += n
+        dev.synchronize()
+        grads.append(dev.get_tensor(zb.T_FLAT_GRADS).copy())
+        dev.close()
+    assert np.abs(grads[0]).max() > 0
+    for g in grads[1:]:
+        assert np.array_equal(g.view(np.uint32), grads[0].view(np.uint32))
