@@ -9,13 +9,13 @@
 // contracts the two rows that a lane pair holds in element v: P and dS go into the next product as they are, in
 // fp32, and the other operand is one float per lane, 32 consecutive columns of a row at a time, from memory.
 // Columns past the head size are zeros in the products over them; rows past the end of the sequence are fetched
-// from the last row and masked.
+// from the last row and masked.  Rows whose result is not finite are taken again from attention_rows.h.
 //
 // What bounds it: latency.  The fp32 stages are small (128 tokens of 4 heads: 512 rows), one wavefront per row
 // walked up to 128 dependent steps; here a wave has one 32 x 32 block.  Both halves of the backward are one launch
 // and D = rowsum(dO * O) is formed where it is used.  Measured (rocprof, 4 heads of 64, 128 tokens): forward 14.5 -> 11.6 us,
 // backward 13.4 + 20.3 -> 16.9 us; the iteration 1.07 -> 0.89 ms.
-#include "zb_common.h"
+#include "attention_rows.h"
 
 namespace zb {
 
@@ -100,10 +100,14 @@ template <int D> __device__ __forceinline__ void put(float* sm, const f32x16 (&o
 __device__ __forceinline__ int at(int r, int e) {
   return ((e >> 5) * 16 + ((e & 31) >> 3) * 4 + (e & 3)) * P + r + ((e >> 2) & 1) * 32;
 }
+// Rows whose result is not finite (attention_rows.h); cleared before the barrier that precedes the results
+__device__ __forceinline__ void clear_flags(int* bad) {
+  if (threadIdx.x < 32) bad[threadIdx.x] = 0;
+}
 // rows [0, min(32, rows)) x d columns = scale * (sum over the waves, in order); ends with a barrier
 template <int D>
 __device__ __forceinline__ void sum_out(float* sm, const f32x16 (&o)[D / 32], float* __restrict__ out, long ld, int rows, int d,
-                                        float scale, int wave, int lane) {
+                                        float scale, int wave, int lane, int* bad) {
   put<D>(sm, o, wave, lane);
   __syncthreads();
   for (int t = threadIdx.x; t < 32 * d; t += 64 * NW) {
@@ -113,6 +117,7 @@ __device__ __forceinline__ void sum_out(float* sm, const f32x16 (&o)[D / 32], fl
 #pragma unroll
     for (int w = 1; w < NW; ++w) x += sm[w * kState<D> + at(r, e)];
     out[(long)r * ld + e] = x * scale;
+    if (!isfinite(x * scale)) bad[r] = 1;
   }
   __syncthreads();
 }
@@ -121,6 +126,7 @@ template <int D>
 __global__ __launch_bounds__(64 * NW) void attn_fwd_f32_kernel(const float* __restrict__ qkv, float* __restrict__ out,
                                                                float* __restrict__ lse, int s, int a, int d, float scale) {
   extern __shared__ float sm[];           // [NW] states, then [NW][2][32] maxima and sums
+  __shared__ int bad[32];
   float* xm = sm + NW * kState<D>;
   const int qb = gridDim.z - 1 - blockIdx.z, head = blockIdx.x, bi = blockIdx.y;  // longest rows first
   const int h = a * d, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, hi = lane >> 5, l31 = lane & 31;
@@ -161,6 +167,7 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_f32_kernel(const float* __re
     add_rows<D>(o, base + 2 * h, ld, k0, s, d, st, lane);
   }
   put<D>(sm, o, wave, lane);
+  clear_flags(bad);
   if (hi == 0) { xm[wave * 64 + l31] = m; xm[wave * 64 + 32 + l31] = l; }
   __syncthreads();
   // a wave without a block has m = -inf, l = 0, o = 0: its factor is 0 (wave 0 always has key 0)
@@ -179,12 +186,16 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_f32_kernel(const float* __re
       sum += f * xm[w * 64 + 32 + r];
     }
     op[(long)r * h + e] = x / sum;
+    if (!isfinite(x / sum)) bad[r] = 1;
     if (e == 0) lse[((long)bi * a + head) * s + qb * 32 + r] = mm + logf(sum);
   }
+  __syncthreads();
+  for (int r = wave; r < 32; r += NW)
+    if (bad[r]) attn_row_fwd<float>(qb * 32 + r, head, bi, qkv, out, lse, s, a, d, scale);
 }
 
 template <int D>
-__device__ __forceinline__ void dq_body(float* sm, int qb, int head, int bi, const float* __restrict__ qkv,
+__device__ __forceinline__ void dq_body(float* sm, int* bad, int qb, int head, int bi, const float* __restrict__ qkv,
                                         const float* __restrict__ o, const float* __restrict__ dout,
                                         const float* __restrict__ lse, float* __restrict__ dqkv, int s, int a, int d,
                                         float scale) {
@@ -219,11 +230,14 @@ __device__ __forceinline__ void dq_body(float* sm, int qb, int head, int bi, con
     }
     add_rows<D>(dq, base + h, ld, k0, s, d, ds, lane);
   }
-  sum_out<D>(sm, dq, dqkv + (tok0 + qb * 32) * ld + head * d, ld, s - qb * 32, d, scale, wave, lane);
+  clear_flags(bad);
+  sum_out<D>(sm, dq, dqkv + (tok0 + qb * 32) * ld + head * d, ld, s - qb * 32, d, scale, wave, lane, bad);
+  for (int r = wave; r < 32; r += NW)
+    if (bad[r]) attn_row_dq<float>(qb * 32 + r, head, bi, qkv, o, dout, lse, dqkv, s, a, d, scale);
 }
 
 template <int D>
-__device__ __forceinline__ void dkv_body(float* sm, int kb, int head, int bi, const float* __restrict__ qkv,
+__device__ __forceinline__ void dkv_body(float* sm, int* bad, int kb, int head, int bi, const float* __restrict__ qkv,
                                          const float* __restrict__ o, const float* __restrict__ dout,
                                          const float* __restrict__ lse, float* __restrict__ dqkv, int s, int a, int d,
                                          float scale) {
@@ -268,8 +282,11 @@ __device__ __forceinline__ void dkv_body(float* sm, int kb, int head, int bi, co
     add_rows<D>(dk, base, ld, q0, s, d, ds, lane);
   }
   float* op = dqkv + (tok0 + kb * 32) * ld + h + head * d;
-  sum_out<D>(sm, dk, op, ld, s - kb * 32, d, scale, wave, lane);
-  sum_out<D>(sm, dv, op + h, ld, s - kb * 32, d, 1.0f, wave, lane);
+  clear_flags(bad);
+  sum_out<D>(sm, dk, op, ld, s - kb * 32, d, scale, wave, lane, bad);
+  sum_out<D>(sm, dv, op + h, ld, s - kb * 32, d, 1.0f, wave, lane, bad);
+  for (int r = wave; r < 32; r += NW)
+    if (bad[r]) attn_row_dkv<float>(kb * 32 + r, head, bi, qkv, o, dout, lse, dqkv, s, a, d, scale);
 }
 
 template <int D>
@@ -277,9 +294,10 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_f32_kernel(const float* __re
                                                                const float* __restrict__ dout, const float* __restrict__ lse,
                                                                float* __restrict__ dqkv, int s, int a, int d, float scale) {
   extern __shared__ float sm[];
+  __shared__ int bad[32];
   const int blk = blockIdx.z >> 1, nb = gridDim.z >> 1;  // the blocks with the longest walks first
-  if (blockIdx.z & 1) dq_body<D>(sm, nb - 1 - blk, blockIdx.x, blockIdx.y, qkv, o, dout, lse, dqkv, s, a, d, scale);
-  else dkv_body<D>(sm, blk, blockIdx.x, blockIdx.y, qkv, o, dout, lse, dqkv, s, a, d, scale);
+  if (blockIdx.z & 1) dq_body<D>(sm, bad, nb - 1 - blk, blockIdx.x, blockIdx.y, qkv, o, dout, lse, dqkv, s, a, d, scale);
+  else dkv_body<D>(sm, bad, blk, blockIdx.x, blockIdx.y, qkv, o, dout, lse, dqkv, s, a, d, scale);
 }
 
 template <typename K> hipError_t set_smem(K kern, size_t smem, bool* done) {
