@@ -14,7 +14,8 @@
 // is padded with zeros to D = 32 / 64 / 96 / 128 on its way into registers and LDS, rows past the end of the
 // sequence are zeros as well (a zero query or output gradient adds nothing; a key past the end is always behind
 // the diagonal), and P and dS go into their products as two bf16 terms, hi + lo, i.e. with 16 bits of mantissa:
-// the vector-ALU kernels that took these shapes before kept them in fp32.
+// the vector-ALU kernels that took these shapes before kept them in fp32.  Rows whose result is not finite are taken
+// again from attention_rows.h.
 //
 // What bounds them: a workgroup is a chain of dependent tiles (LDS read -> MFMA -> exponentials -> MFMA), and
 // the shapes that come here have few heads, so most of the chip is idle; the launch therefore uses 64-row blocks
@@ -30,7 +31,7 @@
 // LDS tiles are [64 rows][D + 16] bf16 (rows = keys or queries, D contiguous); the 16-byte chunk c of
 // row r sits at chunk position c ^ ((r >> 2) & 1), which keeps both the 16-byte row reads and the
 // transposing reads free of bank conflicts.
-#include "zb_common.h"
+#include "attention_rows.h"
 
 namespace zb {
 
@@ -155,6 +156,20 @@ __device__ __forceinline__ void store4(bf16_t* p, float a, float b, float c, flo
   t[0] = (bf16_t)a; t[1] = (bf16_t)b; t[2] = (bf16_t)c; t[3] = (bf16_t)d;
   *reinterpret_cast<bf16x4*>(p) = t;
 }
+// one of this lane's 16 x N values is infinite or NaN
+template <int N> __device__ __forceinline__ bool not_finite(const f32x16 (&t)[N]) {
+  float z = 0.f;
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) z = fmaf(t[i][v], 0.f, z);
+  return z != 0.f;
+}
+// bit r: the row of lanes r and r + 32 is one that either lane calls bad
+__device__ __forceinline__ unsigned bad_rows(bool bad) {
+  const unsigned long long b = __ballot(bad);
+  return (unsigned)(b | (b >> 32));
+}
 // columns e .. e+3 of a row of d columns
 template <bool EDGE>
 __device__ __forceinline__ void store4_row(bf16_t* row, int e, int d, float a, float b, float c, float f) {
@@ -173,7 +188,7 @@ __device__ __forceinline__ void store4_row(bf16_t* row, int e, int d, float a, f
 // ------------------------------------------------------------------------------------------------
 template <int D, int NW, bool EDGE>
 __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out,
-                                                           float* __restrict__ lse, int s, int a, int d, float sl2) {
+                                                           float* __restrict__ lse, int s, int a, int d, float scale) {
   constexpr int QB = 32 * NW;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   bf16_t* sK = reinterpret_cast<bf16_t*>(smem_raw);  // [2][TILE]
@@ -186,6 +201,7 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const bf16_t* __restr
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int hi = lane >> 5, lq = lane & 31;
   const int qw0 = qb * QB + wave * 32;  // first query of this wave
+  const float sl2 = scale * kLog2e;
 
   const bool mine = !EDGE || qw0 + lq < s;  // this lane's query exists
   const int row_q = mine ? qw0 + lq : s - 1;
@@ -289,15 +305,23 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const bf16_t* __restr
   }
 
   const float inv = 1.0f / l;
-  if (!mine) return;
-  bf16_t* op = out + (tok0 + qw0 + lq) * h + head * d;
 #pragma unroll
   for (int et = 0; et < D / 32; ++et)
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
-      store4_row<EDGE>(op, et * 32 + g * 8 + hi * 4, d, o[et][4 * g] * inv, o[et][4 * g + 1] * inv, o[et][4 * g + 2] * inv,
-             o[et][4 * g + 3] * inv);
-  if (hi == 0) lse[((long)bi * a + head) * s + qw0 + lq] = (m + __builtin_amdgcn_logf(l)) * kLn2;
+    for (int v = 0; v < 16; ++v) o[et][v] *= inv;
+  unsigned bad = 0;
+  if constexpr (EDGE) bad = bad_rows(mine && not_finite(o));
+  if (mine && !(bad >> lq & 1)) {
+    bf16_t* op = out + (tok0 + qw0 + lq) * h + head * d;
+#pragma unroll
+    for (int et = 0; et < D / 32; ++et)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        store4_row<EDGE>(op, et * 32 + g * 8 + hi * 4, d, o[et][4 * g], o[et][4 * g + 1], o[et][4 * g + 2], o[et][4 * g + 3]);
+    if (hi == 0) lse[((long)bi * a + head) * s + qw0 + lq] = (m + __builtin_amdgcn_logf(l)) * kLn2;
+  }
+  if constexpr (EDGE)
+    for (; bad; bad &= bad - 1) attn_row_fwd<bf16_t>(qw0 + __builtin_ctz(bad), head, bi, qkv, out, lse, s, a, d, scale);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -321,9 +345,9 @@ __global__ __launch_bounds__(256) void attn_bwd_prep_kernel(const bf16_t* __rest
 // ------------------------------------------------------------------------------------------------
 template <int D, int NW, bool EDGE>
 __device__ __forceinline__ void attn_bwd_dq_body(unsigned char* smem_raw, int qb, int head, int bi,
-                                                 const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
-                                                 const float* __restrict__ lse, const float* __restrict__ dvec,
-                                                 bf16_t* __restrict__ dqkv, int s, int a, int d, float scale) {
+                                                 const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
+                                                 const bf16_t* __restrict__ dout, const float* __restrict__ lse,
+                                                 const float* __restrict__ dvec, bf16_t* __restrict__ dqkv, int s, int a, int d, float scale) {
   constexpr int QB = 32 * NW;
   bf16_t* sK = reinterpret_cast<bf16_t*>(smem_raw);
   bf16_t* sV = sK + 2 * AT<D>::TILE;
@@ -422,14 +446,20 @@ __device__ __forceinline__ void attn_bwd_dq_body(unsigned char* smem_raw, int qb
       gload_tile<D, NW, EDGE>(rv, vbase + (long)(jb + 2) * KB * ld, ld, s - (jb + 2) * KB, d);
     }
   }
-  if (!mine) return;
-  bf16_t* op = dqkv + (tok0 + qw0 + lq) * ld + head * d;
+  unsigned bad = 0;
+  if constexpr (EDGE) bad = bad_rows(mine && not_finite(dq));
+  if (mine && !(bad >> lq & 1)) {
+    bf16_t* op = dqkv + (tok0 + qw0 + lq) * ld + head * d;
 #pragma unroll
-  for (int et = 0; et < D / 32; ++et)
+    for (int et = 0; et < D / 32; ++et)
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
-      store4_row<EDGE>(op, et * 32 + g * 8 + hi * 4, d, dq[et][4 * g] * scale, dq[et][4 * g + 1] * scale, dq[et][4 * g + 2] * scale,
-             dq[et][4 * g + 3] * scale);
+      for (int g = 0; g < 4; ++g)
+        store4_row<EDGE>(op, et * 32 + g * 8 + hi * 4, d, dq[et][4 * g] * scale, dq[et][4 * g + 1] * scale,
+                         dq[et][4 * g + 2] * scale, dq[et][4 * g + 3] * scale);
+  }
+  if constexpr (EDGE)
+    for (; bad; bad &= bad - 1)
+      attn_row_dq<bf16_t>(qw0 + __builtin_ctz(bad), head, bi, qkv, o, dout, lse, dqkv, s, a, d, scale);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -437,9 +467,9 @@ __device__ __forceinline__ void attn_bwd_dq_body(unsigned char* smem_raw, int qb
 // ------------------------------------------------------------------------------------------------
 template <int D, int NW, bool EDGE>
 __device__ __forceinline__ void attn_bwd_dkv_body(unsigned char* smem_raw, int kb, int head, int bi,
-                                                  const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
-                                                  const float* __restrict__ lse, const float* __restrict__ dvec,
-                                                  bf16_t* __restrict__ dqkv, int s, int a, int d, float scale) {
+                                                  const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
+                                                  const bf16_t* __restrict__ dout, const float* __restrict__ lse,
+                                                  const float* __restrict__ dvec, bf16_t* __restrict__ dqkv, int s, int a, int d, float scale) {
   constexpr int QB = 32 * NW;
   bf16_t* sQ = reinterpret_cast<bf16_t*>(smem_raw);  // [2][TILE]
   bf16_t* sO = sQ + 2 * AT<D>::TILE;                 // dO tiles
@@ -571,31 +601,37 @@ __device__ __forceinline__ void attn_bwd_dkv_body(unsigned char* smem_raw, int k
       gload_stats(ib + 2);
     }
   }
-  if (!mine) return;
-  bf16_t* kp = dqkv + (tok0 + kw0 + lk) * ld + h + head * d;
+  unsigned bad = 0;
+  if constexpr (EDGE) bad = bad_rows(mine && (not_finite(dk) || not_finite(dv)));
+  if (mine && !(bad >> lk & 1)) {
+    bf16_t* kp = dqkv + (tok0 + kw0 + lk) * ld + h + head * d;
 #pragma unroll
-  for (int et = 0; et < D / 32; ++et)
+    for (int et = 0; et < D / 32; ++et)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int e = et * 32 + g * 8 + hi * 4;
-      store4_row<EDGE>(kp, e, d, dk[et][4 * g] * scale, dk[et][4 * g + 1] * scale, dk[et][4 * g + 2] * scale,
-                       dk[et][4 * g + 3] * scale);
-      store4_row<EDGE>(kp + h, e, d, dv[et][4 * g], dv[et][4 * g + 1], dv[et][4 * g + 2], dv[et][4 * g + 3]);
-    }
+      for (int g = 0; g < 4; ++g) {
+        const int e = et * 32 + g * 8 + hi * 4;
+        store4_row<EDGE>(kp, e, d, dk[et][4 * g] * scale, dk[et][4 * g + 1] * scale, dk[et][4 * g + 2] * scale,
+                         dk[et][4 * g + 3] * scale);
+        store4_row<EDGE>(kp + h, e, d, dv[et][4 * g], dv[et][4 * g + 1], dv[et][4 * g + 2], dv[et][4 * g + 3]);
+      }
+  }
+  if constexpr (EDGE)
+    for (; bad; bad &= bad - 1)
+      attn_row_dkv<bf16_t>(kw0 + __builtin_ctz(bad), head, bi, qkv, o, dout, lse, dqkv, s, a, d, scale);
 }
 
 // Both halves of the backward in one launch: they are independent, and each alone leaves most of the chip idle.
 // Even workgroups are key blocks, odd ones query blocks, those with the most tiles first.
 template <int D, int NW, bool EDGE>
-__global__ __launch_bounds__(64 * NW) void attn_bwd_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
-                                                           const float* __restrict__ lse, const float* __restrict__ dvec,
-                                                           bf16_t* __restrict__ dqkv, int s, int a, int d, float scale) {
+__global__ __launch_bounds__(64 * NW) void attn_bwd_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
+                                                           const bf16_t* __restrict__ dout, const float* __restrict__ lse,
+                                                           const float* __restrict__ dvec, bf16_t* __restrict__ dqkv, int s, int a, int d, float scale) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int blk = blockIdx.z >> 1, nblk = gridDim.z >> 1, head = blockIdx.x, bi = blockIdx.y;
   if (blockIdx.z & 1)
-    attn_bwd_dq_body<D, NW, EDGE>(smem_raw, nblk - 1 - blk, head, bi, qkv, dout, lse, dvec, dqkv, s, a, d, scale);
+    attn_bwd_dq_body<D, NW, EDGE>(smem_raw, nblk - 1 - blk, head, bi, qkv, o, dout, lse, dvec, dqkv, s, a, d, scale);
   else
-    attn_bwd_dkv_body<D, NW, EDGE>(smem_raw, blk, head, bi, qkv, dout, lse, dvec, dqkv, s, a, d, scale);
+    attn_bwd_dkv_body<D, NW, EDGE>(smem_raw, blk, head, bi, qkv, o, dout, lse, dvec, dqkv, s, a, d, scale);
 }
 
 template <typename K> hipError_t set_smem(K kern, size_t smem, bool* done) {
@@ -613,7 +649,7 @@ template <int D, int NW, bool EDGE> hipError_t run_fwd(const AttnArgs& a, hipStr
   if (e != hipSuccess) return e;
   dim3 grid(a.a, a.b, (a.s + 32 * NW - 1) / (32 * NW));  // the last index is the slowest: heaviest blocks of all heads first
   attn_fwd_kernel<D, NW, EDGE><<<grid, 64 * NW, smem, s>>>((const bf16_t*)a.qkv, (bf16_t*)a.out, a.lse, a.s, a.a, a.d,
-                                                          kLog2e / sqrtf((float)a.d));
+                                                          1.0f / sqrtf((float)a.d));
   return hipGetLastError();
 }
 
@@ -627,8 +663,8 @@ template <int D, int NW, bool EDGE> hipError_t run_bwd(const AttnArgs& a, hipStr
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   dim3 grid(a.a, a.b, 2 * ((a.s + 32 * NW - 1) / (32 * NW)));
-  attn_bwd_kernel<D, NW, EDGE><<<grid, 64 * NW, smem, s>>>((const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.dvec,
-                                                          (bf16_t*)a.dqkv, a.s, a.a, a.d, 1.0f / sqrtf((float)a.d));
+  attn_bwd_kernel<D, NW, EDGE><<<grid, 64 * NW, smem, s>>>((const bf16_t*)a.qkv, (const bf16_t*)a.o, (const bf16_t*)a.dout, a.lse,
+                                                          a.dvec, (bf16_t*)a.dqkv, a.s, a.a, a.d, 1.0f / sqrtf((float)a.d));
   return hipGetLastError();
 }
 

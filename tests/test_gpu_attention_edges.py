@@ -14,6 +14,9 @@ SHAPES = [
     # dtype, hidden, heads, seq, mb_size      which kernel
     ("fp32", 128, 2, 100, 1),       # head size 64, four blocks of 32 rows, the last one cut
     ("fp32", 128, 4, 161, 2),       # head size 32, six blocks: a wave takes two
+    ("bf16", 600, 8, 77, 1),        # head size 75, two 64-row tiles
+    ("bf16", 128, 4, 130, 2),       # head size 32, two rows past two tiles
+    ("bf16", 256, 2, 200, 1),       # head size 128
 ]
 IDS = ["%s_h%d_a%d_s%d_b%d" % c for c in SHAPES]
 
