@@ -13,8 +13,8 @@
 // Two forms of every kernel.  EDGE = false: head size 64, whole 128-row blocks.  EDGE = true: a head of d columns
 // is padded with zeros to D = 32 / 64 / 96 / 128 on its way into registers and LDS, rows past the end of the
 // sequence are zeros as well (a zero query or output gradient adds nothing; a key past the end is always behind
-// the diagonal), and P and dS go into their products as two bf16 terms, hi + lo, i.e. with 16 bits of mantissa:
-// the vector-ALU kernels that took these shapes before kept them in fp32.  Rows whose result is not finite are taken
+// the diagonal), and P and dS, fp32 values, go into their products as three bf16 terms, which hold all 24 bits of
+// their mantissas (the whole-tile form rounds them to one).  Rows whose result is not finite are taken
 // again from attention_rows.h.
 //
 // What bounds them: a workgroup is a chain of dependent tiles (LDS read -> MFMA -> exponentials -> MFMA), and
@@ -140,16 +140,30 @@ __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-// what pack_half leaves behind, as a second bf16 operand
-__device__ __forceinline__ bf16x8 pack_rest(const f32x16& t, int half) {
-  bf16x8 r;
+// Elements 8*half .. 8*half+7 of an accumulator tile as a k-operand: rounded to bf16 or, with edges, all of them in
+// three terms (x - hi and x - hi - mid are exact)
+template <bool EDGE> struct Weights { bf16x8 t[EDGE ? 3 : 1]; };
+template <bool EDGE> __device__ __forceinline__ Weights<EDGE> weights(const f32x16& t, int half) {
+  Weights<EDGE> w;
+  w.t[0] = pack_half(t, half);
+  if constexpr (EDGE) {
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const float x = t[half * 8 + j];
-    r[j] = (bf16_t)(x - (float)(bf16_t)x);
+    for (int j = 0; j < 8; ++j) {
+      const float r = t[half * 8 + j] - (float)w.t[0][j];
+      w.t[1][j] = (bf16_t)r;
+      w.t[2][j] = (bf16_t)(r - (float)w.t[1][j]);
+    }
   }
-  return r;
+  return w;
 }
+template <bool EDGE> __device__ __forceinline__ f32x16 mfma(bf16x8 a, const Weights<EDGE>& w, f32x16 c) {
+#pragma unroll
+  for (const bf16x8& t : w.t) c = mfma(a, t, c);
+  return c;
+}
+// The softmax: in powers of two on whole tiles, in powers of e with edges
+template <bool EDGE> __device__ __forceinline__ float exp_of(float x) { return EDGE ? expf(x) : __builtin_amdgcn_exp2f(x); }
+template <bool EDGE> __device__ __forceinline__ float units(float x) { return EDGE ? x : x * kLog2e; }
 
 __device__ __forceinline__ void store4(bf16_t* p, float a, float b, float c, float d) {
   bf16x4 t;
@@ -201,7 +215,7 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const bf16_t* __restr
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int hi = lane >> 5, lq = lane & 31;
   const int qw0 = qb * QB + wave * 32;  // first query of this wave
-  const float sl2 = scale * kLog2e;
+  const float su = units<EDGE>(scale);
 
   const bool mine = !EDGE || qw0 + lq < s;  // this lane's query exists
   const int row_q = mine ? qw0 + lq : s - 1;
@@ -251,7 +265,7 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const bf16_t* __restr
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          float x = st[t][v] * sl2;
+          float x = st[t][v] * su;
           if (diag) {
             const int key = key0 + t * 32 + (v >> 2) * 8 + hi * 4 + (v & 3);
             if (key > myq) x = -INFINITY;
@@ -261,13 +275,13 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const bf16_t* __restr
         }
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
       const float m_new = fmaxf(m, mx);
-      const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+      const float alpha = exp_of<EDGE>(m - m_new);
       float rs = 0.f;
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          const float p = __builtin_amdgcn_exp2f(st[t][v] - m_new);
+          const float p = exp_of<EDGE>(st[t][v] - m_new);
           st[t][v] = p;
           rs += p;
         }
@@ -278,17 +292,14 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const bf16_t* __restr
       for (int et = 0; et < D / 32; ++et)
 #pragma unroll
         for (int v = 0; v < 16; ++v) o[et][v] *= alpha;
-      bf16x8 pf[4];
-      pf[0] = pack_half(st[0], 0); pf[1] = pack_half(st[0], 1);
-      pf[2] = pack_half(st[1], 0); pf[3] = pack_half(st[1], 1);
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
         if (kk < 2 || act1) {
+          const Weights<EDGE> pf = weights<EDGE>(st[kk >> 1], kk & 1);
 #pragma unroll
           for (int et = 0; et < D / 32; ++et) {
             const bf16x8 vf = frag_tr<D>(vc, et * 32, kk * 16, lane);
-            o[et] = mfma(vf, pf[kk], o[et]);
-            if constexpr (EDGE) o[et] = mfma(vf, pack_rest(st[kk >> 1], kk & 1), o[et]);
+            o[et] = mfma(vf, pf, o[et]);
           }
         }
       }
@@ -318,7 +329,7 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const bf16_t* __restr
 #pragma unroll
       for (int g = 0; g < 4; ++g)
         store4_row<EDGE>(op, et * 32 + g * 8 + hi * 4, d, o[et][4 * g], o[et][4 * g + 1], o[et][4 * g + 2], o[et][4 * g + 3]);
-    if (hi == 0) lse[((long)bi * a + head) * s + qw0 + lq] = (m + __builtin_amdgcn_logf(l)) * kLn2;
+    if (hi == 0) lse[((long)bi * a + head) * s + qw0 + lq] = EDGE ? m + logf(l) : (m + __builtin_amdgcn_logf(l)) * kLn2;
   }
   if constexpr (EDGE)
     for (; bad; bad &= bad - 1) attn_row_fwd<bf16_t>(qw0 + __builtin_ctz(bad), head, bi, qkv, out, lse, s, a, d, scale);
@@ -358,7 +369,7 @@ __device__ __forceinline__ void attn_bwd_dq_body(unsigned char* smem_raw, int qb
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int hi = lane >> 5, lq = lane & 31;
   const int qw0 = qb * QB + wave * 32;
-  const float sl2 = scale * kLog2e;
+  const float su = units<EDGE>(scale);
 
   const bool mine = !EDGE || qw0 + lq < s;
   const int row_q = mine ? qw0 + lq : s - 1;
@@ -366,7 +377,7 @@ __device__ __forceinline__ void attn_bwd_dq_body(unsigned char* smem_raw, int qb
   load_row_frags<D, EDGE>(qf, qkv + (tok0 + row_q) * ld + head * d, hi, mine, d);
   load_row_frags<D, EDGE>(dof, dout + (tok0 + row_q) * h + head * d, hi, mine, d);
   const long srow = ((long)bi * a + head) * s + row_q;
-  const float lse2 = lse[srow] * kLog2e;
+  const float lse_u = units<EDGE>(lse[srow]);
   const float Dq = dvec[srow];
   f32x16 dq[D / 32];
 #pragma unroll
@@ -414,24 +425,21 @@ __device__ __forceinline__ void attn_bwd_dq_body(unsigned char* smem_raw, int qb
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          float p = __builtin_amdgcn_exp2f(st[t][v] * sl2 - lse2);
+          float p = exp_of<EDGE>(st[t][v] * su - lse_u);
           if (diag) {
             const int key = key0 + t * 32 + (v >> 2) * 8 + hi * 4 + (v & 3);
             if (key > myq) p = 0.f;
           }
           st[t][v] = p * (dpt[t][v] - Dq);
         }
-      bf16x8 dsf[4];
-      dsf[0] = pack_half(st[0], 0); dsf[1] = pack_half(st[0], 1);
-      dsf[2] = pack_half(st[1], 0); dsf[3] = pack_half(st[1], 1);
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
         if (kk < 2 || act1) {
+          const Weights<EDGE> dsf = weights<EDGE>(st[kk >> 1], kk & 1);
 #pragma unroll
           for (int et = 0; et < D / 32; ++et) {
             const bf16x8 kf = frag_tr<D>(kc, et * 32, kk * 16, lane);
-            dq[et] = mfma(kf, dsf[kk], dq[et]);
-            if constexpr (EDGE) dq[et] = mfma(kf, pack_rest(st[kk >> 1], kk & 1), dq[et]);
+            dq[et] = mfma(kf, dsf, dq[et]);
           }
         }
       }
@@ -473,7 +481,7 @@ __device__ __forceinline__ void attn_bwd_dkv_body(unsigned char* smem_raw, int k
   constexpr int QB = 32 * NW;
   bf16_t* sQ = reinterpret_cast<bf16_t*>(smem_raw);  // [2][TILE]
   bf16_t* sO = sQ + 2 * AT<D>::TILE;                 // dO tiles
-  float* sL = reinterpret_cast<float*>(sO + 2 * AT<D>::TILE);  // [2][64] lse * log2(e)
+  float* sL = reinterpret_cast<float*>(sO + 2 * AT<D>::TILE);  // [2][64] lse in units of the softmax
   float* sD = sL + 2 * KB;                                     // [2][64] D
   if (!EDGE) d = D;
   const int h = a * d;
@@ -482,7 +490,7 @@ __device__ __forceinline__ void attn_bwd_dkv_body(unsigned char* smem_raw, int k
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int hi = lane >> 5, lk = lane & 31;
   const int kw0 = kb * QB + wave * 32;  // first key of this wave
-  const float sl2 = scale * kLog2e;
+  const float su = units<EDGE>(scale);
 
   const bool mine = !EDGE || kw0 + lk < s;
   const int row_k = mine ? kw0 + lk : s - 1;
@@ -504,8 +512,8 @@ __device__ __forceinline__ void attn_bwd_dkv_body(unsigned char* smem_raw, int k
   float rs = 0.f;  // threads 0..63 stage lse, 64..127 stage D
   auto gload_stats = [&](int ib) {
     const int r = ib * KB + (threadIdx.x & (KB - 1));
-    if (EDGE && r >= s) rs = threadIdx.x < KB ? INFINITY : 0.f;  // 2^-inf: no weight
-    else if (threadIdx.x < KB) rs = lbase[r] * kLog2e;
+    if (EDGE && r >= s) rs = threadIdx.x < KB ? INFINITY : 0.f;  // exp(-inf): no weight
+    else if (threadIdx.x < KB) rs = units<EDGE>(lbase[r]);
     else if (threadIdx.x < 2 * KB) rs = dbase[r];
   };
   auto lstore_stats = [&](int stage) {
@@ -561,30 +569,22 @@ __device__ __forceinline__ void attn_bwd_dkv_body(unsigned char* smem_raw, int k
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
             const int v = g * 4 + i;
-            float p = __builtin_amdgcn_exp2f(st[t][v] * sl2 - l4[i]);
+            float p = exp_of<EDGE>(st[t][v] * su - l4[i]);
             if (diag && mykey > q0 + qi + i) p = 0.f;
             if (t == 0 && !act0) p = 0.f;
             pt[t][v] = p;
             st[t][v] = p * (dpt[t][v] - d4[i]);
           }
         }
-      bf16x8 pf[4], dsf[4];
-      pf[0] = pack_half(pt[0], 0); pf[1] = pack_half(pt[0], 1);
-      pf[2] = pack_half(pt[1], 0); pf[3] = pack_half(pt[1], 1);
-      dsf[0] = pack_half(st[0], 0); dsf[1] = pack_half(st[0], 1);
-      dsf[2] = pack_half(st[1], 0); dsf[3] = pack_half(st[1], 1);
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
         if (kk >= 2 || act0) {
+          const Weights<EDGE> pf = weights<EDGE>(pt[kk >> 1], kk & 1), dsf = weights<EDGE>(st[kk >> 1], kk & 1);
 #pragma unroll
           for (int et = 0; et < D / 32; ++et) {
             const bf16x8 of = frag_tr<D>(oc, et * 32, kk * 16, lane), qf = frag_tr<D>(qc, et * 32, kk * 16, lane);
-            dv[et] = mfma(of, pf[kk], dv[et]);
-            dk[et] = mfma(qf, dsf[kk], dk[et]);
-            if constexpr (EDGE) {
-              dv[et] = mfma(of, pack_rest(pt[kk >> 1], kk & 1), dv[et]);
-              dk[et] = mfma(qf, pack_rest(st[kk >> 1], kk & 1), dk[et]);
-            }
+            dv[et] = mfma(of, pf, dv[et]);
+            dk[et] = mfma(qf, dsf, dk[et]);
           }
         }
       }

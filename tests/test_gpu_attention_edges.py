@@ -1,5 +1,5 @@
 """GPU: what the attention kernels of any sequence length and head size keep of the arithmetic of a softmax taken
-row by row: masked entries have no part in it, whatever they hold."""
+row by row: masked entries have no part in it, whatever they hold, and its weights are fp32."""
 import numpy as np
 import pytest
 
@@ -103,3 +103,58 @@ def test_a_token_that_is_not_finite_stays_causal(shape, bad):
         assert np.isfinite(dx[keep]).all(), f"dX after token {t} is not finite"
         assert rel_fro(dx[keep], dx0[keep]) <= TOL[dtype]
         assert not np.isfinite(dx[:t + 1]).all(axis=1).any()
+
+
+def bf16_half_ulp(x):
+    return 2.0 ** (np.floor(np.log2(np.maximum(np.abs(x), 1e-38))) - 8)
+
+
+@pytest.mark.parametrize("shape", [s for s in SHAPES if s[0] == "bf16"], ids=IDS[2:])
+def test_probabilities_keep_24_bits_in_the_products(shape):
+    # Every column of W_qkv picks one input feature and W_o is a permutation, so Q, K, V and dO are columns of the
+    # stashed LayerNorm output and output gradient, exactly, and the attention's results have a reference in 64 bits
+    # from the device's own operands.  Beyond the rounding of the stored bf16 value an fp32 softmax leaves on a weight
+    # the roundings of the scaled score, the log-sum-exp (both below 8: 2^-22 each), the exponential and the sum, 2^-21
+    # together, and on dP - D those of two sums, 2^-23 of their absolute terms.  Weights of 16 bits (a bf16 and its
+    # bf16 remainder) exceed these bounds 1.4 to 5 times, weights of 8 bits hundreds of times.
+    import paper_2401_10241_amd as zb
+    _, hidden, heads, seq, b = shape
+    w = W("bits", "bf16", 1, hidden, heads, 4 * hidden, seq, b, 4, 0, 1, "H1", seed=61)
+    params = zb_inputs.stage_params(w)
+    rng = np.random.default_rng(67)
+    pick = np.concatenate([rng.permutation(hidden) for _ in range(3)])
+    params[0]["wqkv"] = np.zeros((hidden, 3 * hidden), np.float32)
+    params[0]["wqkv"][pick, np.arange(3 * hidden)] = 1.0
+    perm = rng.permutation(hidden)
+    params[0]["wo"] = np.zeros((hidden, hidden), np.float32)
+    params[0]["wo"][np.arange(hidden), perm] = 1.0
+    dev = run_once(w, params, zb_inputs.stage_input(w, 0, 0), zb_inputs.upstream_grad(w, 0, 0))
+    cols = np.arange(hidden)
+    qkv = dev.get_stash_columns(zb.S_QKV_IN, 0, 0, cols).astype(np.float64)[:, pick]
+    do = dev.get_stash_columns(zb.S_PROJ_DOUT, 0, 0, cols).astype(np.float64)[:, perm]
+    out = dev.get_stash_columns(zb.S_PROJ_IN, 0, 0, cols).astype(np.float64)
+    dqkv = np.hstack([dev.get_stash_columns(zb.S_QKV_DOUT, 0, 0, cols + k * hidden) for k in range(3)]).astype(np.float64)
+    dev.close()
+    d = hidden // heads
+    masked = np.triu(np.ones((seq, seq), bool), 1)
+    worst = {}
+    for i in range(b):
+        rows = slice(i * seq, (i + 1) * seq)
+        for hd in range(heads):
+            c = [slice(k * hidden + hd * d, k * hidden + (hd + 1) * d) for k in range(3)]
+            q, k, v, o, g = qkv[rows, c[0]], qkv[rows, c[1]], qkv[rows, c[2]], out[rows, c[0]], do[rows, c[0]]
+            x = np.where(masked, -np.inf, q @ k.T / np.sqrt(d))
+            assert np.abs(x[~masked]).max() < 8.0
+            p = np.exp(x - x.max(axis=1, keepdims=True))
+            p /= p.sum(axis=1, keepdims=True)
+            ds = p * (g @ v.T - (g * o).sum(axis=1, keepdims=True))
+            tds = 2.0 ** -21 * np.abs(ds) + 2.0 ** -23 * p * (np.abs(g) @ np.abs(v).T + np.abs(g * o).sum(axis=1, keepdims=True))
+            for name, dev_, ref, bound in (
+                    ("O", o, p @ v, 2.0 ** -21 * p @ np.abs(v)),
+                    ("dQ", dqkv[rows, c[0]], ds @ k / np.sqrt(d), tds @ np.abs(k) / np.sqrt(d)),
+                    ("dK", dqkv[rows, c[1]], ds.T @ q / np.sqrt(d), tds.T @ np.abs(q) / np.sqrt(d)),
+                    ("dV", dqkv[rows, c[2]], p.T @ g, 2.0 ** -21 * p.T @ np.abs(g))):
+                beyond = np.abs(dev_ - ref) - bf16_half_ulp(dev_)
+                worst[name] = max(worst.get(name, 0.0), float((beyond / (bound + 1e-300)).max()))
+    print(f"[{shape}] largest error beyond the stored value's rounding, of its bound: {worst}", flush=True)
+    assert max(worst.values()) <= 1.0, worst
