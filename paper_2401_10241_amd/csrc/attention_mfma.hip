@@ -18,10 +18,8 @@
 // again from attention_rows.h.
 //
 // What bounds them: a workgroup is a chain of dependent tiles (LDS read -> MFMA -> exponentials -> MFMA), and
-// the shapes that come here have few heads, so most of the chip is idle; the launch therefore uses 64-row blocks
-// (two waves) unless 128-row blocks already give every CU two.  Measured: 16 heads of 75 columns, 777 tokens
-// 326 us forward and 1323 us backward on the vector ALUs; with these kernels the whole stage iteration they
-// sit in went from 13.7 to 2.8 ms.
+// the shapes that come here have few heads, so most of the chip is idle (row blocks: the rule at `narrow_fwd`).
+// Measured: 16 heads of 75 columns, 777 tokens 315 us forward and 1292 us backward on the vector ALUs, 64 and 95 here.
 //
 // A 32x32 accumulator tile holds, in lane l and element v, row 8*(v/4) + 4*(l>>5) + v%4 and column
 // l&31.  Used directly as the k-operand of the next MFMA (16 rows per instruction: elements 0-7,
@@ -352,7 +350,7 @@ __global__ __launch_bounds__(256) void attn_bwd_prep_kernel(const bf16_t* __rest
 }
 
 // ------------------------------------------------------------------------------------------------
-// backward, dQ: workgroup = 128 queries, loop over key tiles up to the diagonal
+// backward, dQ: workgroup = 32 NW queries, loop over key tiles up to the diagonal
 // ------------------------------------------------------------------------------------------------
 template <int D, int NW, bool EDGE>
 __device__ __forceinline__ void attn_bwd_dq_body(unsigned char* smem_raw, int qb, int head, int bi,
@@ -471,7 +469,7 @@ __device__ __forceinline__ void attn_bwd_dq_body(unsigned char* smem_raw, int qb
 }
 
 // ------------------------------------------------------------------------------------------------
-// backward, dK and dV: workgroup = 128 keys, loop over query tiles from the diagonal to the end
+// backward, dK and dV: workgroup = 32 NW keys, loop over query tiles from the diagonal to the end
 // ------------------------------------------------------------------------------------------------
 template <int D, int NW, bool EDGE>
 __device__ __forceinline__ void attn_bwd_dkv_body(unsigned char* smem_raw, int kb, int head, int bi,
@@ -672,21 +670,44 @@ template <int D, int NW, bool EDGE> hipError_t run_bwd(const AttnArgs& a, hipStr
 inline bool whole_tiles(const AttnArgs& a) { return a.s % 128 == 0 && (a.d == 64 || a.d == 96 || a.d == 128); }
 // sizes the kernels above take (b and the row blocks are grid dimensions of 16 bits)
 inline bool mfma_shape(const AttnArgs& a) { return a.d >= 8 && a.d <= 128 && a.b < 65536 && a.a < 65536 && a.s <= (1 << 20); }
-// fewer than two 128-row blocks per CU: 64-row blocks
-inline bool narrow(const AttnArgs& a) { return (long)((a.s + 127) / 128) * a.a * a.b < 512; }
-
-template <template <int, int, bool> class Run, int D, bool EDGE> hipError_t run_nw(const AttnArgs& a, hipStream_t s) {
-  return narrow(a) ? Run<D, 2, EDGE>::run(a, s) : Run<D, 4, EDGE>::run(a, s);
+// Row blocks per workgroup: 128 (four waves) or 64 (two).  Two waves share the staging of a tile between fewer rows but
+// leave less idle at the diagonal and pack the CUs more evenly.  Measured, us with 64 / 128 rows, and blocks = 128-row
+// blocks of the launch:
+//   forward, whole tiles  16 heads x 128 tokens (16 blocks) 6.6 / 7.2, 12 x 512 (48) 18.5 / 18.9, 64 x 512 (256) 19.9 / 20.2,
+//                         128 x 512 (512) 22.2 / 21.8, 128 x 1024 (1024) 54 / 50, 64 x 2048 (1024) 99 / 82
+//   forward, edges        head 75: 16 x 130 (32) 19.9 / 18.7, 16 x 777 (112) 72 / 65, 96 x 777 (672) 116 / 89; head 128 at
+//                         128 x 257 (384) 32 / 39, 96 x 520 (480) 57 / 67, 96 x 777 (672) 112 / 120, but 64 x 520 (320) 53 / 48
+//                         and 64 x 1100 (576) 132 / 129
+//   backward, whole tiles 12 x 512 (48) 25.7 / 26.7, 256 x 256 (512) 44 / 52, 64 x 1024 (512) 99 / 105, 128 x 2048 (2048) 704 /
+//                         708; 128 rows are ahead, by at most 4 %, between 96 and 256 blocks of 1024 and more tokens
+//   backward, edges       head 75: 16 x 777 (112) 103 / 96, 128 x 257 (384) 74 / 93, 96 x 777 (672) 253 / 273, 64 x 1500 (768)
+//                         500 / 483, but 16 x 130 (32) 31 / 34; head 40: 64 x 384 (192) 39 / 38, 96 x 256 (192) 29 / 31
+inline long blocks128(const AttnArgs& a) { return (long)((a.s + 127) / 128) * a.a * a.b; }
+template <int D, bool EDGE> bool narrow_fwd(const AttnArgs& a) {
+  if (!EDGE) return blocks128(a) < 512;
+  return D == 128 && a.s < 1024 && blocks128(a) >= 352;
 }
-template <int D, int NW, bool EDGE> struct Fwd { static hipError_t run(const AttnArgs& a, hipStream_t s) { return run_fwd<D, NW, EDGE>(a, s); } };
-template <int D, int NW, bool EDGE> struct Bwd { static hipError_t run(const AttnArgs& a, hipStream_t s) { return run_bwd<D, NW, EDGE>(a, s); } };
+template <int D> bool narrow_bwd_edge(const AttnArgs& a) {
+  return (a.s < 1024 && blocks128(a) >= 192) || (D == 96 && a.s <= 256);
+}
+template <int D, bool EDGE> struct Fwd {
+  static hipError_t run(const AttnArgs& a, hipStream_t s) {
+    return narrow_fwd<D, EDGE>(a) ? run_fwd<D, 2, EDGE>(a, s) : run_fwd<D, 4, EDGE>(a, s);
+  }
+};
+template <int D, bool EDGE> struct Bwd {
+  static hipError_t run(const AttnArgs& a, hipStream_t s) {
+    if constexpr (!EDGE) return run_bwd<D, 2, EDGE>(a, s);
+    else return narrow_bwd_edge<D>(a) ? run_bwd<D, 2, EDGE>(a, s) : run_bwd<D, 4, EDGE>(a, s);
+  }
+};
 
-template <template <int, int, bool> class Run> hipError_t run_shape(const AttnArgs& a, hipStream_t s) {
-  if (whole_tiles(a)) return run_nw<Run, 64, false>(a, s);
-  if (a.d <= 32) return run_nw<Run, 32, true>(a, s);
-  if (a.d <= 64) return run_nw<Run, 64, true>(a, s);
-  if (a.d <= 96) return run_nw<Run, 96, true>(a, s);
-  return run_nw<Run, 128, true>(a, s);
+template <template <int, bool> class Run> hipError_t run_shape(const AttnArgs& a, hipStream_t s) {
+  if (whole_tiles(a)) return Run<64, false>::run(a, s);
+  if (a.d <= 32) return Run<32, true>::run(a, s);
+  if (a.d <= 64) return Run<64, true>::run(a, s);
+  if (a.d <= 96) return Run<96, true>::run(a, s);
+  return Run<128, true>::run(a, s);
 }
 
 }  // namespace

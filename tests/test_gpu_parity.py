@@ -447,6 +447,18 @@ def test_edge_tiles(cfg):
 
 
 @pytest.mark.parametrize("cfg", [
+    # hidden, heads, ffn, seq, b       the attention's row blocks per workgroup that only many heads reach
+    (256, 4, 512, 128, 128),     # head size 64, 512 whole blocks: 128 rows forward, 64 backward
+    (512, 4, 512, 130, 44),      # head size 128, 352 blocks with edges: 64 rows forward and backward
+    (72, 3, 136, 33, 64),        # head size 24, 192 blocks: 64 rows backward
+    (120, 3, 248, 70, 64),       # head size 40, likewise
+], ids=lambda c: "h%d_a%d_f%d_s%d_b%d" % c)
+def test_attention_with_many_heads(cfg):
+    hidden, heads, ffn, seq, b = cfg
+    run_and_compare(W("many", "bf16", 1, hidden, heads, ffn, seq, b, 4, 1, 1, "H1", seed=501 + hidden))
+
+
+@pytest.mark.parametrize("cfg", [
     (72, 3, 136, 33, 1, 2),      # widths and tokens cut every tile
     (512, 4, 2048, 300, 2, 1),   # enough tiles for the 64 x 64 form, 600 tokens ragged
     (40, 5, 8, 5, 1, 1),         # contractions shorter than one wave's block of 32
