@@ -328,8 +328,10 @@ template <int D> hipError_t bwd_f32(const AttnArgs& a, hipStream_t s) {
 }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-// rows of a head at 16-byte addresses; b and the row blocks are grid dimensions of 16 bits
-inline bool takes(const AttnArgs& a) { return a.d % 4 == 0 && a.d <= 128 && a.b < 65536 && a.s <= (1 << 20) && aligned16(a.qkv); }
+// rows of a head at 16-byte addresses; b and the row blocks (two per 32 rows in the backward) are grid dimensions of 16 bits
+inline bool takes(const AttnArgs& a) {
+  return a.d % 4 == 0 && a.d <= 128 && a.b < 65536 && 2 * ((a.s + 31) / 32) < 65536 && aligned16(a.qkv);
+}
 
 }  // namespace
 

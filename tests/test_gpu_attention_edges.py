@@ -158,3 +158,16 @@ def test_probabilities_keep_24_bits_in_the_products(shape):
                 worst[name] = max(worst.get(name, 0.0), float((beyond / (bound + 1e-300)).max()))
     print(f"[{shape}] largest error beyond the stored value's rounding, of its bound: {worst}", flush=True)
     assert max(worst.values()) <= 1.0, worst
+
+
+def test_fp32_sequence_beyond_the_grid_is_refused():
+    # 2^20 tokens: two workgroups per 32 rows of the backward are one more than a grid's last dimension takes.  The
+    # forward already refuses, so no pass runs on a sequence whose B could not be launched.
+    import paper_2401_10241_amd as zb
+    w = W("long", "fp32", 1, 8, 2, 8, 1 << 20, 1, 4, 0, 1, "H1", seed=71)
+    dev = make_device_stage(w, 1, pools=(1, 1, 1), journal=False)
+    dev.begin_iteration(0, 1)
+    with pytest.raises(zb.ZbError) as e:
+        dev.forward(0)
+    assert e.value.status == zb.EDEVICE
+    dev.close()
