@@ -85,11 +85,12 @@ def compare(w, role, dev, orc, m):
 
 CASES = [
     # role, dtype, layers, hidden, heads, ffn, seq, b, vocab, m      what the shape reaches
-    ("first", "fp32", 1, 64, 2, 256, 32, 2, 97, 3),          # generic kernels, odd vocabulary
+    ("first", "fp32", 1, 64, 2, 256, 32, 2, 97, 3),          # fp32, odd vocabulary
     ("first", "bf16", 2, 256, 4, 1024, 128, 1, 1000, 4),     # MFMA layers; ids repeat within a microbatch
-    ("last", "fp32", 1, 64, 2, 256, 32, 2, 97, 3),           # generic GEMMs for the head (vocab 97)
+    ("last", "fp32", 1, 64, 2, 256, 32, 2, 97, 3),           # the head's dgrad on the vector ALUs (vocab 97)
     ("last", "bf16", 2, 256, 4, 1024, 128, 1, 1024, 4),      # head on the MFMA kernels (vocab a multiple of 256)
-    ("last", "bf16", 1, 512, 4, 2048, 256, 2, 5000, 2),      # bf16 head on the generic kernels (vocab 5000)
+    ("last", "bf16", 1, 512, 4, 2048, 256, 2, 5000, 2),      # head on the tiles with edges (vocab a multiple of 8)
+    ("last", "bf16", 1, 256, 4, 1024, 128, 1, 1003, 4),      # head on the vector ALUs: all three products, W in a group
 ]
 
 
@@ -137,13 +138,12 @@ def test_end_stage_parity(case):
     dev.close()
 
 
-@pytest.mark.parametrize("role", ["first", "last"])
-def test_end_stage_gradients_are_bitwise_identical_across_orders_and_groupings(role):
+@pytest.mark.parametrize("role,vocab", [("first", 512), ("last", 512), ("last", 1003)])   # 1003: head on the vector ALUs
+def test_end_stage_gradients_are_bitwise_identical_across_orders_and_groupings(role, vocab):
     import paper_2401_10241_amd as zb
     m, p = 6, 4
     sigma = 0 if role == "first" else p - 1
     w = W("end_det", "bf16", 2, 256, 4, 1024, 128, 1, p, sigma, m, "H1", seed=67)
-    vocab = 512
     results = []
     flat = [(0, k) for k in range(m)] + [(1, k) for k in range(m)] + [(2, k) for k in range(m)]
     for mode in ("H1 grouped", "H1 one by one", "flat", "1F1B fused", "W in aligned groups of 2"):

@@ -50,7 +50,7 @@ def test_small_bf16_mfma_shapes():
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
-def test_ragged_shapes_generic_kernels(dtype):
+def test_ragged_shapes(dtype):
     # nothing is a multiple of a tile: seq 80, hidden 72 (3 heads of 24), ffn 200, two sequences per microbatch
     w = W("ragged", dtype, 2, 72, 3, 200, 80, 2, 3, 1, 4, "H1", seed=5)
     run_and_compare(w)
@@ -123,10 +123,10 @@ def test_accumulation_is_bitwise_identical_across_orders():
     dev.close()
 
 
-@pytest.mark.parametrize("shape", [(256, 4, 1024, 128), (72, 3, 200, 80)], ids=["mfma", "generic"])
+@pytest.mark.parametrize("shape", [(256, 4, 1024, 128), (72, 3, 200, 80)], ids=["whole_tiles", "edges"])
 def test_grouped_w_has_the_bits_of_one_by_one_w(shape):
     # consecutive W passes of an order run as one grouped W: every gradient must keep every bit, whether the
-    # grouped MFMA kernel takes the shape (hidden 256) or the group falls back to single launches (hidden 72)
+    # kernel of whole tiles takes the shape (hidden 256) or the one with edges (hidden 72)
     import paper_2401_10241_amd as zb
     hidden, heads, ffn, seq = shape
     m = 6
@@ -407,15 +407,19 @@ def test_algorithm_1_rollback_without_journal_is_close_but_not_exact():
 
 SWEEP = [
     # hidden, heads, ffn, seq, b, layers, dtype      which kernels the shape reaches
-    (128, 2, 512, 64, 2, 2, "bf16"),      # head size 64, N = 384 / 128 not multiples of 256: generic GEMMs
-    (512, 4, 2048, 256, 1, 2, "bf16"),    # head size 128, every GEMM on the MFMA kernel, 256-token tiles
-    (768, 12, 3072, 128, 3, 1, "bf16"),   # head size 64, 384 tokens: 128-row tiles only
-    (320, 4, 1280, 96, 1, 2, "bf16"),     # head size 80 and 96 tokens: generic attention, mixed GEMMs
-    (1024, 8, 4096, 200, 1, 1, "bf16"),   # head size 128 but a ragged sequence: generic attention, 200-token GEMMs
+    (128, 2, 512, 64, 2, 2, "bf16"),      # head size 64, N = 384 / 128 not multiples of 256: GEMM tiles with edges
+    (512, 4, 2048, 256, 1, 2, "bf16"),    # head size 128, 256 tokens: small GEMM tiles
+    (768, 12, 3072, 128, 3, 1, "bf16"),   # head size 64, 384 tokens: small GEMM tiles
+    (320, 4, 1280, 96, 1, 2, "bf16"),     # head size 80 and 96 tokens: attention with edges, mixed GEMMs
+    (1024, 8, 4096, 200, 1, 1, "bf16"),   # head size 128 but a ragged sequence: attention with edges, 200-token GEMMs
     (384, 4, 1536, 192, 2, 1, "bf16"),    # head size 96
     (256, 2, 1024, 320, 1, 1, "fp32"),    # fp32 arithmetic everywhere
     (2048, 16, 8192, 512, 1, 1, "bf16"),  # split-K shapes with 512 tokens
     (1536, 12, 6144, 256, 1, 1, "bf16"),  # wgrad on 128-row tiles, two workgroups per CU (288 tiles for FC1 / FC2)
+    (768, 12, 16384, 128, 3, 1, "bf16"),  # 384 tokens, FC1 and its backward on 192 tiles of 128 x 256
+    (512, 8, 24576, 128, 3, 1, "bf16"),   # the same on 288, two workgroups per CU
+    (1536, 24, 1024, 128, 11, 1, "bf16"), # 1408 tokens, QKV on 198 tiles of 128 x 256
+    (2304, 36, 1024, 128, 11, 1, "bf16"), # the same on 297
 ]
 
 
