@@ -77,7 +77,7 @@ def auto_schedule_report(zb, st, w, m, class_ms):
     memory of 1F1B (p M_B) and twice that."""
     t_f = (class_ms.get("gemm_fwd", 0) + class_ms.get("attention_fwd", 0) + class_ms.get("layernorm_fwd", 0)) / m
     t_b = (class_ms.get("gemm_dgrad", 0) + class_ms.get("attention_bwd", 0) + class_ms.get("layernorm_bwd", 0)) / m
-    t_w = (class_ms.get("gemm_wgrad", 0) + class_ms.get("bias_grad_colsum", 0)) / m
+    t_w = class_ms.get("gemm_wgrad", 0) / m
     elem = 2 if w.dtype == "bf16" else 4
     t_comm = w.seq * w.mb_size * w.hidden * elem / (XGMI_LINK_GBS * 1e9) * 1e3
     m_b, m_w = st.stash_bytes()
@@ -145,7 +145,7 @@ def grouped_w_report(zb, st, w, m, kind, group, flops, auto, class_ms):
         return sum(1 for i, (c, _) in enumerate(o) if c == 2 and (i == 0 or o[i - 1][0] != 2))
 
     r0, r1 = runs_of_w(base_ops), runs_of_w(ops)
-    T0, T1 = class_ms["gemm_wgrad"] + class_ms.get("bias_grad_colsum", 0), wg["total_ms"]
+    T0, T1 = class_ms["gemm_wgrad"], wg["total_ms"]
     rep = {"group": group, "value": round(flops / (ms * 1e-3) / 1e12, 2), "unit": "TFLOP/s",
            "ms_per_step": round(ms, 3), "steps": n,
            "gemm_wgrad": {"launches": wg["launches"], "total_ms": round(wg["total_ms"], 3),

@@ -38,6 +38,7 @@
 #include <type_traits>
 
 #include "gemm_epilogue.h"
+#include "gemm_lds.h"
 
 namespace zb {
 
@@ -55,14 +56,6 @@ constexpr int NTHREADS = 512;
 constexpr int WN = 64;   // wave tile columns
 constexpr int LB = BN / 128;  // DMA instructions per wave per B tile
 
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef const __attribute__((address_space(1))) void* gptr_t;
-typedef __attribute__((address_space(3))) void* lptr_t;
-
-// s_waitcnt immediate that waits for vmcnt <= n and nothing else (gfx9 encoding)
-constexpr int vmcnt_imm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
-
 // Direct-to-LDS loads.  Every DMA instruction of a wave writes one 1 KB run of the tile (run index
 // blk = j * 8 + wave); which 16-byte global chunk a lane fetches implements the LDS swizzle.  The address
 // splits into a part that is the same for the whole wave (tile origin, k offset, run) and a per-lane byte
@@ -74,8 +67,7 @@ constexpr int vmcnt_imm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >>
 template <int R> __device__ __forceinline__ unsigned dma_tr_lane_off(long ld, int wave, int lane) {
   constexpr int CPL = R / 8, LPB = 64 / CPL;  // chunks per k-line, k-lines per run
   const int kl = lane / CPL;
-  const int k3 = (wave * LPB + kl) & 3;  // (k & 3): the runs of one wave are 8*LPB (a multiple of 4) lines apart
-  const int c = (lane % CPL) ^ (k3 << 2);
+  const int c = (lane % CPL) ^ swz_tr<R>(wave * LPB + kl);  // the runs of one wave are 8*LPB (a multiple of 4) lines apart
   return (unsigned)((kl * ld + c * 8) * (long)sizeof(bf16_t));
 }
 // p0 = the tile's first element (k0, r0)
@@ -86,7 +78,7 @@ __device__ __forceinline__ void dma_tr(const bf16_t* __restrict__ p0, long ld, u
   for (int j = 0; j < R / 128; ++j) {
     const int blk = j * 8 + wave;
     const char* base = reinterpret_cast<const char*>(p0 + (long)(blk * LPB) * ld);
-    __builtin_amdgcn_global_load_lds((gptr_t)(base + lane_off), (lptr_t)(s + blk * 512), 16, 0, 0);
+    dma16(base + lane_off, s + blk * 512);
   }
 }
 // [R][64 k] tile of a K-contiguous operand (element (r, k) at p[r*ld + k]): run blk holds rows blk*8 .. +7.
@@ -101,27 +93,8 @@ __device__ __forceinline__ void dma_rows(const bf16_t* __restrict__ p0, long ld,
   for (int j = 0; j < R / 64; ++j) {
     const int blk = j * 8 + wave;
     const char* base = reinterpret_cast<const char*>(p0 + (long)(blk * 8) * ld);
-    __builtin_amdgcn_global_load_lds((gptr_t)(base + lane_off), (lptr_t)(s + blk * 512), 16, 0, 0);
+    dma16(base + lane_off, s + blk * 512);
   }
-}
-
-// fragment of a [32][R] tile: operand rows rb..rb+31, k = kk*16 .. kk*16+15 (kk = 0, 1)
-template <int R> __device__ __forceinline__ bf16x8 frag_tr(const bf16_t* __restrict__ s, int rb, int kk, int lane) {
-  const int blk = lane >> 4, a = lane & 15;
-  const int row = rb + ((blk & 1) << 4) + ((a & 3) << 2);
-  const int k = kk * 16 + ((blk >> 1) << 3) + (a >> 2);
-  typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
-  const bf16_t* p0 = s + k * R + ((((row >> 3) ^ ((k & 3) << 2)) << 3) | (row & 7));
-  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0));
-  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0 + 4 * R));  // k + 4: same swizzle
-  s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-  return __builtin_bit_cast(bf16x8, v);
-}
-// fragment of a [R][64] tile: rows rb..rb+31, k = kk*16 .. kk*16+15 (kk = 0..3)
-__device__ __forceinline__ bf16x8 frag_rows(const bf16_t* __restrict__ s, int rb, int kk, int lane) {
-  const int r = rb + (lane & 31);
-  const int chunk = kk * 2 + (lane >> 5);
-  return *reinterpret_cast<const bf16x8*>(s + r * 64 + ((chunk ^ ((r >> 1) & 7)) << 3));
 }
 
 // Number of even step indices in [it-BS+2, it-1] for a (large) step index of the given parity: the
@@ -233,7 +206,7 @@ __global__ __launch_bounds__(NTHREADS, (BM == 128 && BS == 3) ? 4 : 2) void gemm
 #pragma unroll
     for (int i = 0; i < MT; ++i) af[i] = frag_rows(a_s, wm + i * 32, parity * 2 + kk, lane);
 #pragma unroll
-    for (int j = 0; j < NT; ++j) bfr[j] = frag_tr<BN>(b_s, wn + j * 32, kk, lane);
+    for (int j = 0; j < NT; ++j) bfr[j] = frag_tr<BN>(b_s, wn + j * 32, kk * 16, lane);
   };
   auto mfmas = [&](const bf16x8 (&af)[MT], const bf16x8 (&bfr)[NT]) {
 #pragma unroll
@@ -480,9 +453,9 @@ __global__ __launch_bounds__(512, (BM == 128 && BS == 3) ? 4 : 2) void gemm_wgra
     const bf16_t* a_s = sA + (it % BS) * C::A_ELEMS;
     const bf16_t* b_s = sB + (it % BS) * C::B_ELEMS;
 #pragma unroll
-    for (int i = 0; i < MT; ++i) af[i] = frag_tr<BM>(a_s, wm + i * 32, kk, lane);
+    for (int i = 0; i < MT; ++i) af[i] = frag_tr<BM>(a_s, wm + i * 32, kk * 16, lane);
 #pragma unroll
-    for (int j = 0; j < NT; ++j) bfr[j] = frag_tr<BN>(b_s, wn + j * 32, kk, lane);
+    for (int j = 0; j < NT; ++j) bfr[j] = frag_tr<BN>(b_s, wn + j * 32, kk * 16, lane);
   };
   auto mfmas = [&](const bf16x8 (&af)[MT], const bf16x8 (&bfr)[NT]) {
 #pragma unroll
@@ -667,27 +640,18 @@ hipError_t run_shape(const GemmArgs& g, long lda, long ldb, hipStream_t s, bool*
   }
   if (try_split_k<MODE>(g, lda, ldb, s, &e)) return e;
   if (try_tail_split<MODE>(g, lda, ldb, s, &e)) return e;
-  if (g.N % BN == 0) {
-    // Rounds of tiles over the 256 CUs times the tile height; the taller tile does about 1.25x the
-    // work per cycle, so it wins only when it does not cost an extra, mostly empty round.
-    const long t256 = g.M % 256 == 0 ? (long)(g.M / 256) * (g.N / BN) : 0;
-    const long t128 = g.M % 128 == 0 ? (long)(g.M / 128) * (g.N / BN) : 0;
-    const double c256 = t256 ? (double)((t256 + 255) / 256) * 256.0 / 1.25 : 1e30;
-    const double c128 = t128 ? (double)((t128 + 255) / 256) * 128.0 : 1e30;
-    if (t256 && c256 <= c128) return run_cfg<256, 4, MODE, 3>(g, lda, ldb, s);
-    if (t128) {
-      // more tiles than CUs: a three-stage ring (<= 80 KB) lets two workgroups share a CU, so one's
-      // epilogue and pipeline fill hide behind the other's MFMAs; otherwise one workgroup per CU with a
-      // deeper ring
-      if (t128 > 256) return run_cfg<128, 3, MODE>(g, lda, ldb, s);
-      return run_cfg<128, 5, MODE>(g, lda, ldb, s);
-    }
-  }
-  *taken = false;
-  return hipSuccess;
+  // Rounds of tiles over the 256 CUs times the tile height; the taller tile does about 1.25x the
+  // work per cycle, so it wins only when it does not cost an extra, mostly empty round.
+  const long t256 = g.M % 256 == 0 ? (long)(g.M / 256) * (g.N / BN) : 0;
+  const long t128 = (long)(g.M / 128) * (g.N / BN);
+  const double c256 = t256 ? (double)((t256 + 255) / 256) * 256.0 / 1.25 : 1e30;
+  if (c256 <= (double)((t128 + 255) / 256) * 128.0) return run_cfg<256, 4, MODE, 3>(g, lda, ldb, s);
+  // more tiles than CUs: a three-stage ring (<= 80 KB) lets two workgroups share a CU, so one's
+  // epilogue and pipeline fill hide behind the other's MFMAs; otherwise one workgroup per CU with a
+  // deeper ring
+  if (t128 > 256) return run_cfg<128, 3, MODE>(g, lda, ldb, s);
+  return run_cfg<128, 5, MODE>(g, lda, ldb, s);
 }
-
-inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 template <int BM, int BS, bool XB>
 hipError_t run_wgrad(WgradTable& tb, int K, hipStream_t s) {

@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "gemm_epilogue.h"
+#include "gemm_lds.h"
 
 namespace zb {
 
@@ -28,41 +29,7 @@ double split_cost(int M, int N, int slices, bool rides);
 
 namespace {
 
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-typedef const __attribute__((address_space(1))) void* gptr_t;
-typedef __attribute__((address_space(3))) void* lptr_t;
-
 __device__ const uint4 kZeroChunk = {0, 0, 0, 0};
-
-constexpr int vmcnt_imm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
-
-__device__ __forceinline__ void dma16(const void* g, bf16_t* s) {
-  __builtin_amdgcn_global_load_lds((gptr_t)g, (lptr_t)s, 16, 0, 0);
-}
-
-// Chunk position of chunk c of k-line k in a [k][R] tile (16-byte chunks).  The transposing read takes 64 bytes
-// from each of four consecutive k-lines at a time; the swizzle puts them in different quarters of the 64 banks
-// (R = 128: a line is all banks; R = 64: a line is half of them, so k & 1 already separates two).
-template <int R> __device__ __forceinline__ int swz_tr(int k) { return R == 128 ? (k & 3) << 2 : ((k >> 1) & 1) << 2; }
-
-// operand rows rb..rb+31, k = k0 .. k0+15 of a [k][R] tile
-template <int R> __device__ __forceinline__ bf16x8 frag_tr(const bf16_t* __restrict__ s, int rb, int k0, int lane) {
-  const int blk = lane >> 4, a = lane & 15;
-  const int row = rb + ((blk & 1) << 4) + ((a & 3) << 2);
-  const int k = k0 + ((blk >> 1) << 3) + (a >> 2);
-  typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
-  const bf16_t* p0 = s + k * R + ((((row >> 3) ^ swz_tr<R>(k)) << 3) | (row & 7));
-  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0));
-  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0 + 4 * R));  // k + 4: same swizzle
-  return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-}
-// operand rows rb..rb+31, k = kk*16 .. kk*16+15 of a [R][64] tile (chunk c of row r at position c ^ ((r >> 1) & 7))
-__device__ __forceinline__ bf16x8 frag_rows(const bf16_t* __restrict__ s, int rb, int kk, int lane) {
-  const int r = rb + (lane & 31);
-  const int chunk = kk * 2 + (lane >> 5);
-  return *reinterpret_cast<const bf16x8*>(s + r * 64 + ((chunk ^ ((r >> 1) & 7)) << 3));
-}
 
 // XCD-aware renumbering (ids go round the 8 XCDs) and bands of G tile rows, M fastest within a band
 __device__ __forceinline__ void tile_of(int pid, int tiles_m, int tiles_n, int G, int* tm, int* tn) {
@@ -472,8 +439,6 @@ __global__ __launch_bounds__(256, 2) void gemm_wgrad_edge_kernel(EdgeWgradTable 
       }
     }
 }
-
-inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 }  // namespace
 

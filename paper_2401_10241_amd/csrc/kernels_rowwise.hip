@@ -1,7 +1,7 @@
 // Bandwidth-bound row-wise and elementwise kernels: LayerNorm forward / backward-input
-// (with the gamma/beta gradients, which this build produces in the B pass), bias-gradient
-// column sums (W pass), fills and type conversions.  One wavefront = 64 lanes; reductions
-// use cross-lane shuffles, then LDS across the four waves of a 256-thread workgroup.
+// (with the gamma/beta gradients, which the B pass produces), fills and type conversions.
+// One wavefront = 64 lanes; reductions use cross-lane shuffles, then LDS across the four
+// waves of a 256-thread workgroup.
 #include <cstdint>
 
 #include "zb_common.h"

@@ -101,7 +101,7 @@ template <typename T> hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 // The accumulate GEMMs of one W pass in one launch: dW[q] (fp32 [M[q], N[q]], row stride N[q]) +=
 // sum over g < ngroup of X[q][g]^T dY[q][g], X [K, M[q]] and dY [K, N[q]] of type T, dense, for q < nprob.
 // Every dW[q] and bias gradient keeps its bits however many whole layers share a launch and however the pairs
-// are spread over launches (in bf16 they are also launch_gemm's, problem by problem).
+// are spread over launches.
 constexpr int kWgradMaxProblems = 16, kWgradMaxPairs = 64;
 struct WgradMultiArgs {
   int nprob, ngroup, K;  // nprob * ngroup <= kWgradMaxPairs, ngroup <= kGemmGroupMax
