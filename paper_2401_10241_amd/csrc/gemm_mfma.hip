@@ -594,7 +594,8 @@ bool try_tail_split(const GemmArgs& g, long lda, long ldb, hipStream_t s, hipErr
 
 // Microseconds the 256-column tiles below are expected to take where they do not fill the chip even once (at most
 // 128 tiles of 256 x 256): a step of 32 k takes 0.66 us with few 256-row tiles and 0.90 with one per CU (128-row
-// tiles: 0.40 and 0.70); same measurements as edge_cost's.  A larger product is theirs without asking.
+// tiles: 0.40 and 0.70).  Against 27 of edge_cost's shapes -9 to +17 %, but for 1024 x 6144 x 1536 (33.0 against 24.9),
+// where the choice is the right one all the same.  A larger product is theirs without asking.
 double big_tile_us(const GemmArgs& g, bool rides) {
   if ((long)g.M * g.N > 128L * 256 * BN) return 0;
   const int steps = g.K / KS;
@@ -632,7 +633,8 @@ hipError_t run_shape(const GemmArgs& g, long lda, long ldb, hipStream_t s, bool*
   if (g.N % 8 == 0)
     choose_edge(g.M, g.N, g.K, g.workspace ? g.workspace_floats : 0, rides, &tile, &slices, &edge_us);
   // Sizes that the 256-column tiles take stay with them unless the other tiles are clearly shorter: 256 x 1024 x
-  // 1024 16 -> 7.5 us, 512 x 768 x 3072 26 -> 14, 1024 x 1536 x 1536 23 -> 12; 1024 x 4096 x 4096 52 against 53.
+  // 1024 15.6 -> 7.5 us, 512 x 768 x 3072 25.7 -> 12.9, 1024 x 1536 x 1536 22.7 -> 11.8, 1024 x 2304 x 2304 34.2 -> 26.1 (28.0
+  // and 31.2 expected); 1024 x 4096 x 4096 stays, 50.0 against 51.3.
   if (g.K % 64 != 0 || g.M % 128 != 0 || g.N % BN != 0 || edge_us < 0.9 * big_tile_us(g, rides)) {
     if (tile) return run_edge_shape<MODE>(g, lda, ldb, s, tile, slices);
     *taken = false;

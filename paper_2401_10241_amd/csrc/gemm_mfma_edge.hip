@@ -16,8 +16,9 @@
 // What bounds them: at these sizes a GEMM is a chain of K / 64 steps on a chip that is filled once or less, so
 // the latency of a step (global -> LDS -> fragments -> MFMA, with three later steps in flight) times the number
 // of steps is the time; smaller tiles and K slices shorten the chain or use more CUs (the rule is at
-// `edge_cost`).  Measured: 777 x 4808 x 1200 580 us on the vector ALUs -> 27 us here, 777 x 1200 x 4808 650 -> 32,
-// 256 x 1024 x 1024 15.6 us on the 256-column tiles -> 7.5, 512 x 768 x 3072 26 -> 14.
+// `edge_cost`).  Measured (M x N x K with a bias epilogue, us per launch back to back, the launch that adds K slices
+// included; before: the vector ALUs or the 256-column tiles): 777 x 4808 x 1200 245 -> 26, 777 x 1200 x 4808 1041 -> 28,
+// 777 x 1200 x 1200 264 -> 10, 256 x 1024 x 1024 15.6 -> 7.5, 512 x 768 x 3072 25.7 -> 12.9, 512 x 2048 x 2048 25.6 -> 13.6.
 #include <type_traits>
 
 #include "gemm_epilogue.h"
@@ -221,10 +222,12 @@ template <int MODE> hipError_t run_edge_tile(const GemmArgs& g, long lda, long l
 }  // namespace
 
 // Microseconds the kernel above is expected to take with this tile and number of K slices, the launch that adds
-// the planes included (`rides`: a LayerNorm that has to run anyway does it).  Fitted to single launches on
-// N(0,1)-like operands, 40 shapes from 256 x 1024 x 1024 to 1024 x 6144 x 6144, all within 20 %: a step of 64 k
+// the planes included (`rides`: a LayerNorm that has to run anyway does it).  Fitted to single launches: a step of 64 k
 // takes 0.31 us with one 64 x 64 workgroup per CU and 0.44 with two (0.57 and 0.79 for a 128 x 128 tile on a
-// nearly empty and on a full chip), 3 us go to the start, the fill of the ring and the epilogue.
+// nearly empty and on a full chip), 3 us go to the start, the fill of the ring and the epilogue.  Against 39 shapes from
+// 1 x 64 x 72 to 6144 x 2304 x 2304, 76 unsliced points: -20 to +15 %, but for three products under 12 us (100 x 96 x 96,
+// 1 x 64 x 72, 333 x 264 x 520: up to 59 % short).  218 sliced points: 43 more than 20 % short, up to 42 % (512 x 3072 x 768 in
+// four slices: 7.0 against 12.1; the planes' stores are not in the step), so slices are taken a little too readily.
 double edge_cost(int M, int N, int K, int tile, int slices, bool rides) {
   const long tiles = (long)((M + tile - 1) / tile) * ((N + tile - 1) / tile) * slices;
   const int steps = ((K + 63) / 64 + slices - 1) / slices;
@@ -237,8 +240,8 @@ double edge_cost(int M, int N, int K, int tile, int slices, bool rides) {
   return us;
 }
 
-// Cheapest tile and number of K slices (within the workspace); both measured at 512 x 768 x 3072: 18.3 us whole,
-// 8.7 us in four slices (26.3 us on the 256-column tiles).
+// Cheapest tile and number of K slices (within the workspace); 512 x 768 x 3072: 17.9 us whole, 8.3 in four slices and
+// 4.6 for the launch that adds them (25.7 on the 256-column tiles).
 void choose_edge(int M, int N, int K, size_t workspace_floats, bool rides, int* tile, int* slices, double* us) {
   *us = 1e30;
   const int blocks = (K + 63) / 64;
