@@ -17,6 +17,7 @@ namespace zb {
 
 template <typename T> hipError_t launch_gemm_mfma(const GemmArgs& g, hipStream_t s, bool* taken);
 template <typename T> hipError_t launch_wgrad_multi_mfma(const WgradMultiArgs& w, hipStream_t s, bool* taken);
+template <typename T> hipError_t launch_gemm_generic(const GemmArgs& g, hipStream_t s);
 
 namespace {
 
@@ -214,15 +215,27 @@ constexpr long kWideTiles = 1024;
 
 // W: the two forms split K over eight and four waves, i.e. add in different orders, so the choice may rest only on what
 // is the same in every launch of a stage - the tokens and the largest gradient of a layer - and not on how many layers
-// share the launch: the gradients keep their bits in every grouping.  The wide form pays with at most one 32-k block
+// share the launch (nor may `valu_wgrad`): the gradients keep their bits in every grouping.  The wide form pays with at most one 32-k block
 // per wave and gradients that fill half the chip.  Measured, us with 32 x 32 / 64 x 64 tiles, hidden h, ffn 4 h: 128 tokens
 // h 128 (largest gradient 64 tiles of 32 x 32) one layer 4.4 / 8.3, four 12.8 / 8.8; h 192 (144) one 6.9 / 8.5, two 12.7 / 8.9;
 // h 256 (256) one 10.9 / 8.7, four 41 / 27; h 1024 128 / 88; h 256, two layers 64 tokens 18.7 / 15.4, 136 tokens 23.6 / 26.4,
 // 512 tokens 39 / 104; h 1024, 512 tokens 256 / 531.
-inline bool wide_wgrad(const WgradMultiArgs& w) {
+inline long largest_tiles(const WgradMultiArgs& w) {
   long most = 0;
   for (int q = 0; q < w.nprob; ++q) most = std::max(most, tiles_of(w.M[q], w.N[q], 32));
-  return w.K <= 4 * KB && most >= 128;
+  return most;
+}
+inline bool wide_wgrad(const WgradMultiArgs& w) { return w.K <= 4 * KB && largest_tiles(w) >= 128; }
+
+// Large gradients are bound by their own turn-around, and these tiles, whose waves wait for each other's partial sums,
+// keep too few loads in flight for it: the vector-ALU kernel takes the products there, one launch each, and only the
+// strips stay here.  Measured with the bias sums, us of one layer, matrix cores / vector ALUs (hidden h, ffn 4 h; the
+// largest gradient is h^2 / 256 tiles): h 768 17 tokens 45 / 50, h 1024 17: 77 / 58, 64: 76 / 73, 128: 82 / 110, 136: 148 /
+// 116, 220: 152 / 158 (four layers 668 / 628), 256: 153 / 180; h 1536 64: 160 / 124, 128: 172 / 187, 220: 335 / 286, 512: 523 /
+// 580; h 2048 17: 277 / 128, 128: 304 / 253, 256: 600 / 440, 1024: 1607 / 1560.
+inline bool valu_wgrad(const WgradMultiArgs& w) {
+  const long most = largest_tiles(w);
+  return most >= 16384 || (most >= 4096 && (w.K <= 64 || (w.K > 4 * KB && w.K < 224)));
 }
 
 template <bool BKC, int MODE> hipError_t run_f32(const GemmArgs& g, long lda, long ldb, hipStream_t s) {
@@ -266,14 +279,14 @@ template <> hipError_t launch_wgrad_multi_mfma<float>(const WgradMultiArgs& w, h
     small += tiles_of(w.M[q], w.N[q], 32);
   }
   if (small >= (1L << 30)) return hipSuccess;
-  const bool wide = wide_wgrad(w);
+  const bool valu = valu_wgrad(w), wide = !valu && wide_wgrad(w);
   int tiles = 0, strips = 0;
   for (int q = 0; q < w.nprob; ++q) {
     tb.M[q] = w.M[q]; tb.N[q] = w.N[q]; tb.outf[q] = w.outf[q];
     tb.bias[q] = w.bias_done ? w.bias[q] : nullptr;
     tb.tile0[q] = tiles;
     tb.strip0[q] = strips;
-    tiles += (int)tiles_of(w.M[q], w.N[q], wide ? 64 : 32);
+    if (!valu) tiles += (int)tiles_of(w.M[q], w.N[q], wide ? 64 : 32);
     if (tb.bias[q]) strips += (w.N[q] + 63) / 64;
     for (int g = 0; g < w.ngroup; ++g) {
       tb.a[q * w.ngroup + g] = (const float*)w.a[q * w.ngroup + g];
@@ -284,6 +297,16 @@ template <> hipError_t launch_wgrad_multi_mfma<float>(const WgradMultiArgs& w, h
   tb.ntiles = tiles;
   *taken = true;
   if (w.bias_done) *w.bias_done = true;
+  if (valu)
+    for (int i = 0; i < w.nprob * w.ngroup; ++i) {
+      const int q = i / w.ngroup;
+      GemmArgs g{};
+      g.A = w.a[i]; g.B = w.b[i]; g.M = w.M[q]; g.N = w.N[q]; g.K = w.K;
+      g.a_sm = 1; g.a_sk = g.M; g.b_sk = g.N; g.b_sn = 1; g.epilogue = EPI_ACCUM_F32; g.outf = w.outf[q];
+      hipError_t e = launch_gemm_generic<float>(g, s);
+      if (e != hipSuccess) return e;
+    }
+  if (tiles + strips == 0) return hipSuccess;
   if (wide) gemm_f32_wgrad_kernel<64, 64, 4><<<tiles + strips, 256, 0, s>>>(tb, w.K);
   else gemm_f32_wgrad_kernel<32, 32, 8><<<tiles + strips, 512, 0, s>>>(tb, w.K);
   return hipGetLastError();

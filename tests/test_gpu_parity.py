@@ -471,6 +471,7 @@ def test_attention_with_many_heads(cfg):
     (200, 2, 400, 64, 1, 1),     # head size 100
     (152, 2, 304, 40, 1, 1),     # head size 76; 152 / 8 = 19 below
     (152, 8, 304, 40, 1, 1),     # head size 19: one wavefront per row
+    (1024, 8, 4096, 17, 1, 1),   # gradients on the vector ALUs, bias sums in a launch of their own
 ], ids=lambda c: "h%d_a%d_f%d_s%d_b%d_L%d" % c)
 def test_fp32_tiles(cfg):
     hidden, heads, ffn, seq, b, layers = cfg
@@ -498,7 +499,8 @@ def test_fp32_grouped_w_has_the_bits_of_one_by_one_w():
     (256, 4, 1024, 160, 2, (9, 1)),  # nine and more microbatches: one layer per W launch instead of both
     (256, 4, 1024, 128, 2, (9, 1)),  # the same at 128 tokens: 64 x 64 tiles
     (160, 5, 640, 160, 4, (5, 5)),   # five microbatches: three layers and one instead of all four
-], ids=["h256_s160_L2", "h256_s128_L2", "h160_s160_L4"])
+    (1024, 8, 4096, 17, 2, (9, 1)),  # gradients on the vector ALUs, bias sums in a launch of their own
+], ids=["h256_s160_L2", "h256_s128_L2", "h160_s160_L4", "h1024_s17_L2"])
 def test_fp32_w_bits_do_not_depend_on_the_layers_per_launch(hidden, heads, ffn, seq, layers, groups):
     # how many layers share a W launch follows from the number of microbatches and from the pass (the single
     # backward takes one layer at a time); at 160 tokens the waves of a workgroup split K unevenly
