@@ -151,11 +151,11 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_f32_kernel(const float* __re
       mx = fmaxf(mx, st[v]);
     }
     mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    const float m_new = fmaxf(m, mx), alpha = expf(m - m_new);
+    const float m_new = fmaxf(m, mx), ref = softmax_ref(m_new), alpha = expf(m - ref);
     float rs = 0.f;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      st[v] = expf(st[v] - m_new);
+      st[v] = expf(st[v] - ref);
       rs += st[v];
     }
     l = l * alpha + rs + __shfl_xor(rs, 32, 64);
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_f32_kernel(const float* __re
       sum += f * xm[w * 64 + 32 + r];
     }
     op[(long)r * h + e] = x / sum;
-    if (!isfinite(x / sum)) bad[r] = 1;
+    if (!isfinite(x / sum) && sum == sum) bad[r] = 1;
     if (e == 0) lse[((long)bi * a + head) * s + qb * 32 + r] = mm + logf(sum);
   }
   __syncthreads();
@@ -231,9 +231,10 @@ __device__ __forceinline__ void dq_body(float* sm, int* bad, int qb, int head, i
     add_rows<D>(dq, base + h, ld, k0, s, d, ds, lane);
   }
   clear_flags(bad);
+  const bool lost = lq != lq || Dq != Dq;  // no weight or no gradient is a number: neither is the row
   sum_out<D>(sm, dq, dqkv + (tok0 + qb * 32) * ld + head * d, ld, s - qb * 32, d, scale, wave, lane, bad);
   for (int r = wave; r < 32; r += NW)
-    if (bad[r]) attn_row_dq<float>(qb * 32 + r, head, bi, qkv, o, dout, lse, dqkv, s, a, d, scale);
+    if (bad[r] && !__shfl((int)lost, r, 64)) attn_row_dq<float>(qb * 32 + r, head, bi, qkv, o, dout, lse, dqkv, s, a, d, scale);
 }
 
 template <int D>

@@ -272,14 +272,14 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const bf16_t* __restr
           mx = fmaxf(mx, x);
         }
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float m_new = fmaxf(m, mx);
-      const float alpha = exp_of<EDGE>(m - m_new);
+      const float m_new = fmaxf(m, mx), ref = EDGE ? softmax_ref(m_new) : m_new;
+      const float alpha = exp_of<EDGE>(m - ref);
       float rs = 0.f;
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          const float p = exp_of<EDGE>(st[t][v] - m_new);
+          const float p = exp_of<EDGE>(st[t][v] - ref);
           st[t][v] = p;
           rs += p;
         }
@@ -319,7 +319,7 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const bf16_t* __restr
 #pragma unroll
     for (int v = 0; v < 16; ++v) o[et][v] *= inv;
   unsigned bad = 0;
-  if constexpr (EDGE) bad = bad_rows(mine && not_finite(o));
+  if constexpr (EDGE) bad = bad_rows(mine && l == l && not_finite(o));
   if (mine && !(bad >> lq & 1)) {
     bf16_t* op = out + (tok0 + qw0 + lq) * h + head * d;
 #pragma unroll
@@ -453,7 +453,7 @@ __device__ __forceinline__ void attn_bwd_dq_body(unsigned char* smem_raw, int qb
     }
   }
   unsigned bad = 0;
-  if constexpr (EDGE) bad = bad_rows(mine && not_finite(dq));
+  if constexpr (EDGE) bad = bad_rows(mine && lse_u == lse_u && Dq == Dq && not_finite(dq));  // else every term is NaN
   if (mine && !(bad >> lq & 1)) {
     bf16_t* op = dqkv + (tok0 + qw0 + lq) * ld + head * d;
 #pragma unroll
