@@ -14,7 +14,7 @@
 // What bounds it: latency.  The fp32 stages are small (128 tokens of 4 heads: 512 rows), one wavefront per row
 // walked up to 128 dependent steps; here a wave has one 32 x 32 block.  Both halves of the backward are one launch
 // and D = rowsum(dO * O) is formed where it is used.  Measured (rocprof, 4 heads of 64, 128 tokens): forward 14.5 -> 11.6 us,
-// backward 13.4 + 20.3 -> 16.9 us; the iteration 1.07 -> 0.89 ms.
+// backward 13.4 + 20.3 -> 16.9 us; the iteration 1.07 -> 0.90 ms.
 #include "attention_rows.h"
 
 namespace zb {
