@@ -1,4 +1,4 @@
-// bf16 GEMM on the gfx950 matrix cores (v_mfma_f32_32x32x16_bf16), fp32 accumulation.
+// bf16 GEMM on the gfx950 matrix cores (v_mfma_f32_16x16x32_bf16), fp32 accumulation.
 //
 //   C[M,N] (epilogue)= A * B, with B always given "row-contiguous" ([k][n] in memory, n contiguous: the
 //   weight W[in][out] in the forward GEMM, the transposed weight copy in the dgrad GEMM, dY in the wgrad
@@ -12,31 +12,37 @@
 // bytes land at consecutive LDS addresses, no registers in between) into rings of LDS stages, several
 // steps ahead of the MFMAs.  Per step: wait until this wave's loads of the current tiles have landed
 // (s_waitcnt vmcnt with the number of younger loads that may stay in flight), one barrier (all waves'
-// loads landed, all waves done with the stage about to be refilled), issue the loads for the step
-// BS-1 ahead, then fragments + MFMAs.
+// loads landed, all waves done with the stage about to be refilled), then the step's MFMAs in two halves; between
+// them, one at a time, stand the fragment reads of the half step to come and the loads for the step BS-1 ahead.
+//
+// What bounds the loop, and why it looks like this:
+//   - Per step the matrix pipe takes 1024 cycles and the 32 load instructions 512 cycles of the load unit.  Issued in a
+//     block (after the barrier or before it) the loads hold up the MFMAs behind them: in a probe of loads and MFMAs alone a
+//     step took 1475 (loads first) and 1385 cycles (last), 1220 with a load after every fourth MFMA.
+//   - On real operands the chip lowers its clock under the power of the matrix cores.  16x16x32 instructions, each
+//     sharing an operand with the one before it, sustain 2.00-2.08 PFLOP/s on N(0,1) operands where 32x32x16 ones
+//     sustain 1.79-1.82 (both 2.4 on zeros), and give the same bits.
+// Before -> after on one box, N(0,1) operands: 1024 x 15360 x 5120 194 -> 175 us, 6144 x 6912 x 2304 209 -> 187, 6144 x
+// 2304 x 9216 258 -> 227; W of h 5120, 1024 tokens 963 -> 896, of h 4096 in pairs 994 -> 888, of h 2304, 6144 tokens,
+// three layers 2506 -> 2209.  All zeros: 1024 x 15360 x 5120 126 -> 121, 6144 x 2304 x 9216 188 -> 165.
 //
 // LDS layouts (no padding: the DMA writes 1 KB runs; bank conflicts are avoided by choosing WHICH global
 // chunk each lane fetches).  The LDS has 64 banks of 4 bytes; 16-byte accesses go 16 lanes at a time,
 // 8-byte accesses 32 lanes at a time.
 //   row-contiguous source: ring of BS stages of [32 k][R]; chunk c (16 B) of k-line k sits at position
-//     c ^ ((k & 3) << 2).  Read back with the transposing LDS load ds_read_b64_tr_b16: within 16 lanes,
+//     c ^ swz16_tr(k).  Read back with the transposing LDS load ds_read_b64_tr_b16 (frag16_tr): within 16 lanes,
 //     lane a points at 4 consecutive rows (a & 3) * 4 of k-line (a >> 2) and receives, as lane r, the 4 k
-//     values of row r.  32 lanes read 64 B from each of four k-lines; the swizzle puts those in
-//     different quarters of the banks.
+//     values of row r.
 //   K-contiguous source: 64 k at a time (128-byte rows, so every fetched cache line is used whole), two or
-//     three stages of [BM][64] refilled every other step; chunk c of row r sits at position
+//     three stages of [BM][64]; chunk c of row r sits at position
 //     c ^ ((r >> 1) & 7): 16 consecutive rows reading the same k cover all banks.
 //
-// Ring shape for the 256-row tile: 3 A stages (96 KB) + 4 B stages (64 KB) = the whole 160 KB.  Loads come
-// back in order, so an A tile (activations, L2 hits) waits behind the B tiles (weights, streamed from
-// HBM) issued before it; fetching A two tiles (four steps) ahead and B three steps ahead balances the two
-// (about 1 % faster than 2 + 5 stages, which has more bytes of B in flight but A only two steps ahead).
+// Ring shape for the 256-row tile: 3 A stages (96 KB) + 4 B stages (64 KB) = the whole 160 KB; A is fetched four and
+// three steps ahead (half a stage on each step, so that every step issues four loads per wave) and B three.
 //
-// MFMA 32x32x16 operand layout: lane l supplies row (l & 31) of its operand and the 8 consecutive k
-// starting at 8 * (l >> 5); it receives column (l & 31) and rows 8*(v/4) + 4*(l >> 5) + v%4 of the
-// 32 x 32 result in accumulator element v.
-#include <type_traits>
-
+// MFMA 16x16x32 operand layout: lane l supplies row (l & 15) of its operand and the 8 consecutive k
+// starting at 8 * (l >> 4); it receives column (l & 15) and rows 4 * (l >> 4) + v of the 16 x 16 result in accumulator
+// element v.
 #include "gemm_epilogue.h"
 #include "gemm_lds.h"
 
@@ -67,19 +73,16 @@ constexpr int LB = BN / 128;  // DMA instructions per wave per B tile
 template <int R> __device__ __forceinline__ unsigned dma_tr_lane_off(long ld, int wave, int lane) {
   constexpr int CPL = R / 8, LPB = 64 / CPL;  // chunks per k-line, k-lines per run
   const int kl = lane / CPL;
-  const int c = (lane % CPL) ^ swz_tr<R>(wave * LPB + kl);  // the runs of one wave are 8*LPB (a multiple of 4) lines apart
+  static_assert(R == 128 || R == 256, "a wave's runs must be a multiple of 16 k-lines apart, where the swizzle repeats");
+  const int c = (lane % CPL) ^ swz16_tr(wave * LPB + kl);
   return (unsigned)((kl * ld + c * 8) * (long)sizeof(bf16_t));
 }
-// p0 = the tile's first element (k0, r0)
+// run j of the tile whose first element (k0, r0) is *p0
 template <int R>
-__device__ __forceinline__ void dma_tr(const bf16_t* __restrict__ p0, long ld, unsigned lane_off, bf16_t* s, int wave) {
+__device__ __forceinline__ void dma_tr(const bf16_t* __restrict__ p0, long ld, unsigned lane_off, bf16_t* s, int wave, int j) {
   constexpr int LPB = 64 / (R / 8);
-#pragma unroll
-  for (int j = 0; j < R / 128; ++j) {
-    const int blk = j * 8 + wave;
-    const char* base = reinterpret_cast<const char*>(p0 + (long)(blk * LPB) * ld);
-    dma16(base + lane_off, s + blk * 512);
-  }
+  const int blk = j * 8 + wave;
+  dma16_at(p0 + (long)(blk * LPB) * ld, lane_off, s + blk * 512);
 }
 // [R][64 k] tile of a K-contiguous operand (element (r, k) at p[r*ld + k]): run blk holds rows blk*8 .. +7.
 __device__ __forceinline__ unsigned dma_rows_lane_off(long ld, int wave, int lane) {
@@ -87,44 +90,130 @@ __device__ __forceinline__ unsigned dma_rows_lane_off(long ld, int wave, int lan
   const int c = (lane & 7) ^ ((((wave & 1) << 2) | (lane >> 4)) & 7);  // ((r >> 1) & 7), r = blk*8 + rl
   return (unsigned)((rl * ld + c * 8) * (long)sizeof(bf16_t));
 }
-template <int R>
-__device__ __forceinline__ void dma_rows(const bf16_t* __restrict__ p0, long ld, unsigned lane_off, bf16_t* s, int wave) {
-#pragma unroll
-  for (int j = 0; j < R / 64; ++j) {
-    const int blk = j * 8 + wave;
-    const char* base = reinterpret_cast<const char*>(p0 + (long)(blk * 8) * ld);
-    dma16(base + lane_off, s + blk * 512);
-  }
+__device__ __forceinline__ void dma_rows(const bf16_t* __restrict__ p0, long ld, unsigned lane_off, bf16_t* s, int wave, int j) {
+  const int blk = j * 8 + wave;
+  dma16_at(p0 + (long)(blk * 8) * ld, lane_off, s + blk * 512);
 }
 
-// Number of even step indices in [it-BS+2, it-1] for a (large) step index of the given parity: the
-// steps whose A refill (K-contiguous A is refilled on even steps only) is younger than B tile `it`.
-constexpr int even_steps_in_window(int BS, int parity) {
-  int n = 0;
-  for (int i = 1000 + parity - BS + 2; i <= 1000 + parity - 1; ++i) n += (i % 2 == 0);
-  return n;
-}
-
-// AS = LDS stages of a K-contiguous A (64 k each, refilled on even steps AS-1 tiles ahead); a row-contiguous A
-// travels with B in the BS-stage ring.
+// AS = LDS stages of a K-contiguous A (64 k each); with three or more a stage is refilled half on the even and half on
+// the odd step, 2(AS-1) steps ahead, with two it is refilled whole on even steps.  A row-contiguous A travels with B in
+// the BS-stage ring.
 template <int BM, int BS, bool ATR, int AS = 2> struct Cfg {
+  static constexpr bool HALVES = !ATR && AS >= 3;
   static constexpr int A_ELEMS = ATR ? KS * BM : BM * 64;      // per A stage
   static constexpr int A_STAGES = ATR ? BS : AS;
   static constexpr int B_ELEMS = KS * BN;
-  static constexpr int LA = ATR ? BM / 128 : BM / 64;           // DMA instructions per wave per A refill
+  static constexpr int LA = ATR ? BM / 128 : HALVES ? BM / 128 : BM / 64;  // DMA instructions per wave per refill of A
   static constexpr size_t SMEM = ((size_t)A_STAGES * A_ELEMS + (size_t)BS * B_ELEMS) * sizeof(bf16_t);
-  // younger loads that may still be in flight when step `it` starts computing
+  static_assert(!HALVES || 2 * AS >= BS + 2, "the second half of an A stage must not be younger than B of the same step");
+  // younger loads that may still be in flight when step `it` starts computing: the refills of the BS-2 steps since the
+  // one that fetched B tile `it` (the last part of A tile it/2 is no younger)
   static constexpr int allowed(int parity) {
-    if (ATR) return (BS - 2) * (LA + LB);
-    // after B tile `it`: the refills of steps it-BS+2 .. it-1
-    const int wrt_b = (BS - 2) * LB + LA * even_steps_in_window(BS, parity);
+    if (ATR || HALVES) return (BS - 2) * (LA + LB);
+    int even = 0;  // even steps among them
+    for (int i = 1000 + parity - BS + 2; i <= 1000 + parity - 1; ++i) even += (i % 2 == 0);
+    const int wrt_b = (BS - 2) * LB + LA * even;
     if (parity) return wrt_b;               // the A tile of this pair was checked on the even step
-    // after A tile it/2 (issued on step it-2(AS-1), before that step's B): the B tiles of steps
-    // it-2(AS-1) .. it-1 and the A tiles of the AS-2 even steps between
     const int wrt_a = 2 * (AS - 1) * LB + (AS - 2) * LA;
     return wrt_b < wrt_a ? wrt_b : wrt_a;
   }
 };
+
+// Half a step: the products of MH row fragments with NT column fragments.  After MFMA e the e-th fragment of the half
+// step to come is read from LDS (NR of them), and the ND refills are spread evenly over the MFMAs.  The order is pinned:
+// left to itself the compiler reads fragments right before their use and issues all refills together, and then the
+// matrix pipe waits for the LDS and for the load unit (which takes 16 cycles per 1 KB instruction, 512 for the 32 of a
+// step).  Each MFMA shares an operand with the one before it.
+template <int NR, int ND, int MH, int NT, class R, class D>
+__device__ __forceinline__ void half_step(f32x4 (*acc)[NT], const bf16x8 (&fa)[MH], const bf16x8 (&fb)[NT], R&& read,
+                                          D&& dma) {
+  constexpr int H = MH * NT;
+  static_assert(NR <= H && ND <= H, "one read and one refill at most after an MFMA");
+#pragma unroll
+  for (int e = 0; e < H; ++e) {
+    const int i = e / NT, j = (i & 1) ? NT - 1 - e % NT : e % NT;
+    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);  // a wait for this MFMA's operands must not take in the read that follows
+    if (e < NR) read(e);
+#pragma unroll
+    for (int d = 0; d < ND; ++d)
+      if ((d + 1) * H / (ND > 0 ? ND : 1) - 1 == e) dma(d);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// What one wave's steps share.  it counts steps of 32 k; L holds the first MH row fragments of a step, H the others.
+// read_a(it, i) and read_b(it, j) fetch fragments, dma(it, d, guard) issues refill d < ND of step it, wait(it, guard)
+// waits for the tiles of step it (and meets the other waves), fetched() follows the last refill of a step.
+// guard: near the end, where tiles past the end are not fetched and fewer loads are in flight than allowed() assumes.
+template <int MH, int NT, int ND, class RA, class RB, class DM, class WA, class FE>
+__device__ __forceinline__ void pipelined_steps(f32x4 (*acc)[NT], int nk, int safe, RA&& read_a, RB&& read_b, DM&& dma,
+                                                WA&& wait, FE&& fetched) {
+  constexpr int N0 = ND / 2, N1 = ND - N0;  // refills of a step issued before / after the MFMAs of its first half
+  bf16x8 aL[MH], aH[MH], b0[NT], b1[NT];
+  // order of the fragments of a step's start: b0 a0, the other columns, the other rows
+  auto read_start = [&](int it, int r, bf16x8 (&b)[NT]) {
+    if (r == 0) b[0] = read_b(it, 0);
+    else if (r == 1) aL[0] = read_a(it, 0);
+    else if (r <= NT) b[r - 1] = read_b(it, r - 1);
+    else aL[r - NT] = read_a(it, r - NT);
+  };
+  // From step it to step it + 1: the MFMAs of the first half of step it run while the row fragments of its second half
+  // are read; then the next step's tiles are waited for, and the second half's MFMAs run while the first fragments of
+  // the next step are read.  A wave so reaches the barrier with matrix work queued and holds the fragments of half a step.
+  auto advance = [&](int it, bool guard, const bf16x8 (&b)[NT], bf16x8 (&bn)[NT]) {
+    half_step<MH, N1>(acc, aL, b, [&](int r) { aH[r] = read_a(it, MH + r); }, [&](int d) { dma(it, N0 + d, guard); });
+    fetched();
+    // these LDS reads must have completed before the barrier lets another wave refill the stage
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0) only
+    wait(it + 1, guard);
+    half_step<MH + NT, N0>(acc + MH, aH, b, [&](int r) { read_start(it + 1, r, bn); },
+                           [&](int d) { dma(it + 1, d, guard); });
+  };
+  wait(0, true);
+#pragma unroll
+  for (int r = 0; r < MH + NT; ++r) read_start(0, r, b0);
+#pragma unroll
+  for (int d = 0; d < N0; ++d) dma(0, d, true);
+  int it = 0;
+  for (; it < safe; it += 2) {  // every refill of steps it .. it + 2 exists
+    advance(it, false, b0, b1);
+    advance(it + 1, false, b1, b0);
+  }
+  for (; it + 2 < nk; it += 2) {
+    advance(it, true, b0, b1);
+    advance(it + 1, true, b1, b0);
+  }
+  advance(it, true, b0, b1);
+  half_step<MH, 0>(acc, aL, b1, [&](int r) { aH[r] = read_a(nk - 1, MH + r); }, [](int) {});
+  half_step<0, 0>(acc + MH, aH, b1, [](int) {}, [](int) {});
+}
+
+// The steps with two workgroups per CU (three-stage ring, half the registers): the other workgroup fills the gaps.
+template <int MH, int NT, int ND, class RA, class RB, class DM, class WA, class FE>
+__device__ __forceinline__ void plain_steps(f32x4 (*acc)[NT], int nk, RA&& read_a, RB&& read_b, DM&& dma, WA&& wait,
+                                            FE&& fetched) {
+  for (int it = 0; it < nk; ++it) {
+    wait(it, true);
+#pragma unroll
+    for (int d = 0; d < ND; ++d) dma(it, d, true);
+    fetched();
+    bf16x8 a[MH], b[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) b[j] = read_b(it, j);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int i = 0; i < MH; ++i) a[i] = read_a(it, h * MH + i);
+#pragma unroll
+      for (int i = 0; i < MH; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+          acc[h * MH + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[h * MH + i][j], 0, 0, 0);
+    }
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the reads are done before the next barrier
+  }
+}
 
 template <int BM, int BS, int MODE, int AS>
 __global__ __launch_bounds__(NTHREADS, (BM == 128 && BS == 3) ? 4 : 2) void gemm_mfma_kernel(const bf16_t* __restrict__ A,
@@ -135,7 +224,7 @@ __global__ __launch_bounds__(NTHREADS, (BM == 128 && BS == 3) ? 4 : 2) void gemm
   bf16_t* sA = reinterpret_cast<bf16_t*>(smem_raw);
   bf16_t* sB = sA + C::A_STAGES * C::A_ELEMS;
   constexpr int WM = BM / 2;
-  constexpr int MT = WM / 32, NT = WN / 32;
+  constexpr int MT = WM / 16, NT = WN / 16;
 
   // Consecutive workgroup ids go to different XCDs (8, each with its own L2): renumber so that every
   // XCD gets a contiguous run of tiles, M fastest, and tiles that share a weight block share an L2.
@@ -173,91 +262,51 @@ __global__ __launch_bounds__(NTHREADS, (BM == 128 && BS == 3) ? 4 : 2) void gemm
   const bf16_t* a_tile = A + (long)m0 * lda;  // + k
   const bf16_t* b_tile = B + n0;              // + k * ldb
 
-  f32x16 acc[MT][NT];
+  f32x4 acc[MT][NT];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   const int nk = K / KS;  // even
 
-  // refills issued by step `it` (also used, with negative it, for the pipeline fill so that the order of
-  // loads is the same from the first step on)
-  auto issue = [&](int it) {
-    if ((it & 1) == 0) {
-      const int j = (it >> 1) + AS - 1;  // A tile j covers steps 2j, 2j+1 (negative early in the fill: nothing)
-      if (j >= 0 && 2 * j < nk) dma_rows<BM>(a_tile + j * 64, lda, a_off, sA + (j % AS) * C::A_ELEMS, wave);
-    }
+  // Refills of step `it` (also used, with negative it, for the pipeline fill so that the order of loads is the same from
+  // the first step on), as single DMA instructions: 0 .. LA-1 of A, then LB of B.  A tile j covers steps 2j, 2j+1.
+  auto refill_a = [&](int it, int d, bool guard) {
+    const int j = (it >> 1) + AS - 1;
+    if (!C::HALVES && (it & 1)) return;
+    if (guard && !(j >= 0 && 2 * j < nk)) return;
+    dma_rows(a_tile + j * 64, lda, a_off, sA + (j % AS) * C::A_ELEMS, wave, C::HALVES ? (it & 1) * C::LA + d : d);
+  };
+  auto refill_b = [&](int it, int d, bool guard) {
     const int nt = it + BS - 1;
-    if (nt >= 0 && nt < nk)
-      dma_tr<BN>(b_tile + (long)(nt * KS) * ldb, ldb, b_off, sB + (nt % BS) * C::B_ELEMS, wave);
+    if (guard && !(nt >= 0 && nt < nk)) return;
+    dma_tr<BN>(b_tile + (long)(nt * KS) * ldb, ldb, b_off, sB + (nt % BS) * C::B_ELEMS, wave, d);
   };
-  // With one workgroup per CU (BS > 3) the MFMAs of the second half of every tile are issued after the
-  // NEXT step's barrier: a wave then reaches the barrier with matrix work still queued, and the matrix
-  // pipe stays busy while the waves re-synchronise and the first fragments of the new tile come out of
-  // LDS.  With two workgroups per CU the other workgroup fills those gaps and registers are scarce.
-  constexpr bool XBAR = BS > 3;
-  bf16x8 af1[MT], bf1[NT];  // fragments of the current tile's second half, kept across the barrier
-  auto load_frags = [&](int it, int parity, int kk, bf16x8 (&af)[MT], bf16x8 (&bfr)[NT]) {
-    const bf16_t* b_s = sB + (it % BS) * C::B_ELEMS;
-    const bf16_t* a_s = sA + ((it >> 1) % AS) * C::A_ELEMS;
-#pragma unroll
-    for (int i = 0; i < MT; ++i) af[i] = frag_rows(a_s, wm + i * 32, parity * 2 + kk, lane);
-#pragma unroll
-    for (int j = 0; j < NT; ++j) bfr[j] = frag_tr<BN>(b_s, wn + j * 32, kk * 16, lane);
+  auto read_a = [&](int it, int i) { return frag16_rows(sA + ((it >> 1) % AS) * C::A_ELEMS, wm + i * 16, it & 1, lane); };
+  auto read_b = [&](int it, int j) { return frag16_tr<BN>(sB + (it % BS) * C::B_ELEMS, wn + j * 16, lane); };
+  constexpr int AHEAD = (BS - 2) > (2 * AS - 3) ? (BS - 2) : (2 * AS - 3);  // last step whose refills all exist
+  auto dma = [&](int it, int d, bool guard) {
+    if (d < C::LA) refill_a(it, d, guard);
+    else refill_b(it, d - C::LA, guard);
   };
-  auto mfmas = [&](const bf16x8 (&af)[MT], const bf16x8 (&bfr)[NT]) {
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-      for (int j = 0; j < NT; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-  };
-  auto step = [&](int it, auto parity_tag) {
-    constexpr int parity = decltype(parity_tag)::value;
-    // near the end fewer loads were issued than the constant assumes: wait for everything
-    constexpr int AHEAD = (BS - 2) > (2 * AS - 3) ? (BS - 2) : (2 * AS - 3);  // last step whose refills all exist
-    if (it + AHEAD < nk) __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::allowed(parity)));
-    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+  auto wait = [&](int it, bool guard) {
+    if (guard && it + AHEAD >= nk) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    else if (it & 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::allowed(1)));
+    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::allowed(0)));
     __builtin_amdgcn_s_barrier();
-    // The refill of the stage that step it-1 used may be issued any time after the barrier; with the deep
-    // ring it goes after the fragment reads so that the matrix pipe gets its work first.
-    if constexpr (!XBAR) issue(it);  // shallow ring, two workgroups per CU: refill at once
-    bf16x8 af0[MT], bf0[NT];
-    load_frags(it, parity, 0, af0, bf0);
-    if constexpr (XBAR) {
-      if (it > 0) mfmas(af1, bf1);  // second half of tile it-1
-      mfmas(af0, bf0);
-      load_frags(it, parity, 1, af1, bf1);
-      issue(it);
-      // these LDS reads must have completed before the next barrier lets another wave refill the stage
-      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0) only
-    } else {
-      mfmas(af0, bf0);
-      load_frags(it, parity, 1, af1, bf1);
-      mfmas(af1, bf1);
-    }
   };
-
   // pipeline fill: the same sequence of refills as in the loop, from the first step that issues anything
   constexpr int FILL0 = (1 - BS) < -2 * (AS - 1) ? (1 - BS) : -2 * (AS - 1);
 #pragma unroll
-  for (int it = FILL0; it < 0; ++it) issue(it);
-  for (int it = 0; it < nk; it += 2) {
-    step(it, std::integral_constant<int, 0>());
-    step(it + 1, std::integral_constant<int, 1>());
+  for (int it = FILL0; it < 0; ++it) {
+#pragma unroll
+    for (int d = 0; d < C::LA + LB; ++d) dma(it, d, true);
   }
-  if constexpr (XBAR) mfmas(af1, bf1);
+  if constexpr (BS > 3) pipelined_steps<MT / 2, NT, C::LA + LB>(acc, nk, nk - AHEAD - 3, read_a, read_b, dma, wait, [] {});
+  else plain_steps<MT / 2, NT, C::LA + LB>(acc, nk, read_a, read_b, dma, wait, [] {});
 
-  const int lrow = lane & 31, lhi = (lane >> 5) * 4;
-#pragma unroll
-  for (int i = 0; i < MT; ++i)
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      epilogue_tile<bf16_t, MODE>(epi, m0 + wm + i * 32 + lhi, n0 + wn + j * 32 + lrow, acc[i][j]);
-    }
+  epilogue_wave<MODE, MT, NT>(epi, m0 + wm, n0 + wn, lane, acc);
 }
 
 // ldo: row stride of the outputs when the GEMM covers a column range of a wider matrix (0: g.N)
@@ -383,14 +432,14 @@ __device__ __forceinline__ void wgrad_bias_strip(const WgradTable& tb, int sid, 
   if (threadIdx.x < BN) bias[n0 + threadIdx.x] = run;
 }
 
-template <int BM, int BS, bool XB>
+template <int BM, int BS>
 __global__ __launch_bounds__(512, (BM == 128 && BS == 3) ? 4 : 2) void gemm_wgrad_kernel(WgradTable tb, int Kc) {
   extern __shared__ __align__(1024) unsigned char smem_raw[];
   typedef Cfg<BM, BS, true> C;
   bf16_t* sA = reinterpret_cast<bf16_t*>(smem_raw);
   bf16_t* sB = sA + C::A_STAGES * C::A_ELEMS;
   constexpr int WM = BM / 2;
-  constexpr int MT = WM / 32, NT = WN / 32;
+  constexpr int MT = WM / 16, NT = WN / 16;
 
   const int nblk = tb.ntiles;
   int pid = blockIdx.x;
@@ -422,86 +471,71 @@ __global__ __launch_bounds__(512, (BM == 128 && BS == 3) ? 4 : 2) void gemm_wgra
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int wm = (wave >> 2) * WM, wn = (wave & 3) * WN;
-  const int lrow = lane & 31, lhi = (lane >> 5) * 4;
+  const unsigned c_off = rows8_lane_off(N, lane);
   const unsigned a_off = dma_tr_lane_off<BM>(lda, wave, lane), b_off = dma_tr_lane_off<BN>(ldb, wave, lane);
 
-  f32x16 acc[MT][NT];
+  f32x4 acc[MT][NT];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      const float* p0 = outf + (size_t)(m0 + wm + i * 32 + lhi) * N + n0 + wn + j * 32 + lrow;
+    for (int j = 0; j < NT; j += 2) {
+      const float* p0 = outf + (size_t)(m0 + wm + i * 16) * N + n0 + wn + j * 16;
+      f32x8 c;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = __builtin_nontemporal_load(p0 + (size_t)((v >> 2) * 8 + (v & 3)) * N);
-      __builtin_amdgcn_sched_barrier(0);  // one tile's addresses at a time
+      for (int v = 0; v < 8; ++v) c[v] = __builtin_nontemporal_load(at_lane(p0 + (size_t)v * N, c_off));
+      from_rows8(c, &acc[i][j], &acc[i][j + 1]);
     }
 
   const int spc = Kc / KS;        // steps per operand pair
   const int nk = ngroup * spc;
-  int g_next = 0, k_next = 0;  // operand pair and k offset of the next tile to fetch (tiles are fetched in order)
-  auto issue = [&](int it) {
+  // the next tile to fetch (tiles are fetched in order): its operand pair, k offset and addresses
+  int g_next = 0, k_next = 0;
+  const bf16_t* a_next = tb.a[pair0] + m0;
+  const bf16_t* b_next = tb.b[pair0] + n0;
+  auto dma = [&](int it, int d, bool guard) {
     const int nt = it + BS - 1;
-    if (nt < nk) {
-      dma_tr<BM>(tb.a[pair0 + g_next] + (long)k_next * lda + m0, lda, a_off, sA + (nt % BS) * C::A_ELEMS, wave);
-      dma_tr<BN>(tb.b[pair0 + g_next] + (long)k_next * ldb + n0, ldb, b_off, sB + (nt % BS) * C::B_ELEMS, wave);
-      k_next += KS;
-      if (k_next == Kc) { k_next = 0; ++g_next; }
+    if (guard && nt >= nk) return;
+    if (d < C::LA) dma_tr<BM>(a_next, lda, a_off, sA + (nt % BS) * C::A_ELEMS, wave, d);
+    else dma_tr<BN>(b_next, ldb, b_off, sB + (nt % BS) * C::B_ELEMS, wave, d - C::LA);
+  };
+  auto next_tile = [&]() {
+    a_next += (long)KS * lda;
+    b_next += (long)KS * ldb;
+    k_next += KS;
+    if (k_next == Kc && ++g_next < ngroup) {
+      k_next = 0;
+      a_next = tb.a[pair0 + g_next] + m0;
+      b_next = tb.b[pair0 + g_next] + n0;
     }
   };
-  bf16x8 af1[MT], bf1[NT];  // XB: fragments of a tile's second half, carried across the next barrier
-  auto load_frags = [&](int it, int kk, bf16x8 (&af)[MT], bf16x8 (&bfr)[NT]) {
-    const bf16_t* a_s = sA + (it % BS) * C::A_ELEMS;
-    const bf16_t* b_s = sB + (it % BS) * C::B_ELEMS;
-#pragma unroll
-    for (int i = 0; i < MT; ++i) af[i] = frag_tr<BM>(a_s, wm + i * 32, kk * 16, lane);
-#pragma unroll
-    for (int j = 0; j < NT; ++j) bfr[j] = frag_tr<BN>(b_s, wn + j * 32, kk * 16, lane);
-  };
-  auto mfmas = [&](const bf16x8 (&af)[MT], const bf16x8 (&bfr)[NT]) {
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-      for (int j = 0; j < NT; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-  };
-
-#pragma unroll
-  for (int it = 1 - BS; it < 0; ++it) issue(it);
-  for (int it = 0; it < nk; ++it) {
-    if (it + BS - 2 < nk) __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::allowed(0)));
-    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+  auto read_a = [&](int it, int i) { return frag16_tr<BM>(sA + (it % BS) * C::A_ELEMS, wm + i * 16, lane); };
+  auto read_b = [&](int it, int j) { return frag16_tr<BN>(sB + (it % BS) * C::B_ELEMS, wn + j * 16, lane); };
+  auto wait = [&](int it, bool guard) {
+    if (guard && it + BS - 2 >= nk) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::allowed(0)));
     __builtin_amdgcn_s_barrier();
-    bf16x8 af0[MT], bf0[NT];
-    if constexpr (XB) {
-      // the MFMAs of a step's second half are issued after the next step's barrier (one workgroup per CU:
-      // the matrix pipe keeps work queued while the waves re-synchronise)
-      load_frags(it, 0, af0, bf0);
-      if (it > 0) mfmas(af1, bf1);
-      mfmas(af0, bf0);
-      load_frags(it, 1, af1, bf1);
-      issue(it);
-      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): fragment reads done before the next barrier
-    } else {
-      issue(it);
-      load_frags(it, 0, af0, bf0);
-      mfmas(af0, bf0);
-      load_frags(it, 1, af1, bf1);
-      mfmas(af1, bf1);
-    }
+  };
+#pragma unroll
+  for (int it = 1 - BS; it < 0; ++it) {
+#pragma unroll
+    for (int d = 0; d < C::LA + LB; ++d) dma(it, d, true);
+    next_tile();
   }
-  if constexpr (XB) mfmas(af1, bf1);
+  if constexpr (BS > 3) pipelined_steps<MT / 2, NT, C::LA + LB>(acc, nk, nk - BS - 1, read_a, read_b, dma, wait, next_tile);
+  else plain_steps<MT / 2, NT, C::LA + LB>(acc, nk, read_a, read_b, dma, wait, next_tile);
 
   // the store addresses are worked out again here (from a copy of the tile origin the compiler cannot
-  // connect with the one used for the loads), or the address pairs would stay in registers across the loop
+  // connect with the one used for the loads), or they would stay in registers across the loop
   int m0s = m0, n0s = n0;
   asm volatile("" : "+s"(m0s), "+s"(n0s));
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      float* p0 = outf + (size_t)(m0s + wm + i * 32 + lhi) * N + n0s + wn + j * 32 + lrow;
+    for (int j = 0; j < NT; j += 2) {
+      float* p0 = outf + (size_t)(m0s + wm + i * 16) * N + n0s + wn + j * 16;
+      const f32x8 c = rows8(acc[i][j], acc[i][j + 1]);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) __builtin_nontemporal_store(acc[i][j][v], p0 + (size_t)((v >> 2) * 8 + (v & 3)) * N);
-      __builtin_amdgcn_sched_barrier(0);
+      for (int v = 0; v < 8; ++v) __builtin_nontemporal_store(c[v], at_lane(p0 + (size_t)v * N, c_off));
     }
 }
 
@@ -655,9 +689,9 @@ hipError_t run_shape(const GemmArgs& g, long lda, long ldb, hipStream_t s, bool*
   return run_cfg<128, 5, MODE>(g, lda, ldb, s);
 }
 
-template <int BM, int BS, bool XB>
+template <int BM, int BS>
 hipError_t run_wgrad(WgradTable& tb, int K, hipStream_t s) {
-  auto kern = gemm_wgrad_kernel<BM, BS, XB>;
+  auto kern = gemm_wgrad_kernel<BM, BS>;
   constexpr size_t smem = Cfg<BM, BS, true>::SMEM;
   static_assert(smem <= 160 * 1024, "LDS budget");
   static bool attr_set = false;
@@ -725,9 +759,9 @@ template <> hipError_t launch_wgrad_multi_mfma<bf16_t>(const WgradMultiArgs& w, 
   // 256-row tiles (one workgroup per CU, four-stage ring) when they fill most of the chip; else 128-row
   // tiles, two workgroups per CU with a three-stage ring if there are more tiles than CUs, one with a
   // five-stage ring otherwise.  The choice does not change the result (see the kernel).
-  if (all256 && t256 >= 192) return run_wgrad<256, 4, true>(tb, w.K, s);
-  if (t128 > 256) return run_wgrad<128, 3, true>(tb, w.K, s);
-  return run_wgrad<128, 5, true>(tb, w.K, s);
+  if (all256 && t256 >= 192) return run_wgrad<256, 4>(tb, w.K, s);
+  if (t128 > 256) return run_wgrad<128, 3>(tb, w.K, s);
+  return run_wgrad<128, 5>(tb, w.K, s);
 }
 
 namespace {

@@ -451,6 +451,22 @@ def test_edge_tiles(cfg):
 
 
 @pytest.mark.parametrize("cfg", [
+    # hidden, heads, ffn, seq, b       products of few steps of 32 k on the large tiles (the pipeline's fill and end)
+    (64, 1, 2048, 64, 68),       # FC1 and FC2's backward: two steps on 256-row tiles
+    (128, 2, 2048, 64, 68),      # four
+    (192, 3, 2048, 64, 68),      # six
+    (64, 1, 2048, 64, 66),       # two on 128-row tiles, two workgroups per CU
+    (256, 4, 24576, 64, 1),      # W: two steps on 256-row tiles
+    (256, 4, 24576, 64, 3),      # six
+    (256, 4, 17920, 64, 1),      # two on 128-row tiles, two workgroups per CU
+    (256, 4, 1024, 64, 5),       # ten on 128-row tiles, one per CU
+], ids=lambda c: "h%d_a%d_f%d_s%d_b%d" % c)
+def test_few_steps_of_the_large_tiles(cfg):
+    hidden, heads, ffn, seq, b = cfg
+    run_and_compare(W("few", "bf16", 1, hidden, heads, ffn, seq, b, 4, 1, 2, "H2", seed=601 + hidden + b))
+
+
+@pytest.mark.parametrize("cfg", [
     # hidden, heads, ffn, seq, b       the attention's row blocks per workgroup that only many heads reach
     (256, 4, 512, 128, 128),     # head size 64, 512 whole blocks: 128 rows forward, 64 backward
     (512, 4, 512, 130, 44),      # head size 128, 352 blocks with edges: 64 rows forward and backward
