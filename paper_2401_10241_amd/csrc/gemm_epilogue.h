@@ -33,9 +33,9 @@ __device__ __forceinline__ void epilogue_one(const EpiParams& e, int m, int n, f
   } else if (MODE == EPI_BIAS_GELU) {
     const float f = acc + e.bias[n];
     ((T*)e.out0)[idx] = from_f32<T>(f);
-    ((T*)e.out1)[idx] = from_f32<T>(gelu_f(f));
+    ((T*)e.out1)[idx] = from_f32<T>(gelu<T>(f));
   } else if (MODE == EPI_DGELU) {
-    ((T*)e.out0)[idx] = from_f32<T>(acc * gelu_grad_f(to_f32(((const T*)e.aux)[idx])));
+    ((T*)e.out0)[idx] = from_f32<T>(acc * gelu_grad<T>(to_f32(((const T*)e.aux)[idx])));
   } else {  // EPI_ACCUM_F32
     e.outf[idx] += acc;
   }
@@ -60,14 +60,14 @@ __device__ __forceinline__ void epilogue_tile(const EpiParams& e, int m0, int n,
     const float b = MODE == EPI_BIAS_RESID ? e.bias[n] : 0.f;
 #pragma unroll
     for (int v = 0; v < 16; ++v)
-      ((T*)e.out0)[idx[v]] = from_f32<T>(MODE == EPI_BIAS_RESID ? acc[v] + b + a[v] : acc[v] * gelu_grad_f(a[v]));
+      ((T*)e.out0)[idx[v]] = from_f32<T>(MODE == EPI_BIAS_RESID ? acc[v] + b + a[v] : acc[v] * gelu_grad<T>(a[v]));
   } else if (MODE == EPI_BIAS_GELU) {
     const float b = e.bias[n];
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const float f = acc[v] + b;
       ((T*)e.out0)[idx[v]] = from_f32<T>(f);
-      ((T*)e.out1)[idx[v]] = from_f32<T>(gelu_f(f));
+      ((T*)e.out1)[idx[v]] = from_f32<T>(gelu<T>(f));
     }
   } else {
     const float b = MODE == EPI_BIAS ? e.bias[n] : 0.f;
@@ -147,9 +147,9 @@ __device__ __forceinline__ void epilogue_wave(const EpiParams& e, int m0, int n0
         const size_t at = row + (size_t)v * e.N + q * 32;
         const float f = c[v] + b[q];
         if (MODE == EPI_PARTIAL) *at_lane(e.outf + at, off) = c[v];  // e.outf already points at this K slice's [M,N] plane
-        else if (MODE == EPI_DGELU) *at_lane((bf16_t*)e.out0 + at, off) = (bf16_t)(c[v] * gelu_grad_f(a[q][v]));
+        else if (MODE == EPI_DGELU) *at_lane((bf16_t*)e.out0 + at, off) = (bf16_t)(c[v] * gelu_grad<bf16_t>(a[q][v]));
         else *at_lane((bf16_t*)e.out0 + at, off) = (bf16_t)(MODE == EPI_BIAS_RESID ? f + a[q][v] : MODE == EPI_STORE ? c[v] : f);
-        if (MODE == EPI_BIAS_GELU) *at_lane((bf16_t*)e.out1 + at, off) = (bf16_t)gelu_f(f);
+        if (MODE == EPI_BIAS_GELU) *at_lane((bf16_t*)e.out1 + at, off) = (bf16_t)gelu<bf16_t>(f);
       }
     }
   }

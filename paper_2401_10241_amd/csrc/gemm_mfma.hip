@@ -347,7 +347,7 @@ __global__ __launch_bounds__(256) void gemm_splitk_fixup_kernel(const float* __r
   } else if (MODE == EPI_DGELU) {
     const bf16x4 a = *reinterpret_cast<const bf16x4*>((const bf16_t*)epi.aux + i4);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o0[e] = (bf16_t)(acc[e] * gelu_grad_f((float)a[e]));
+    for (int e = 0; e < 4; ++e) o0[e] = (bf16_t)(acc[e] * gelu_grad<bf16_t>((float)a[e]));
   } else {
     const f32x4 b = *reinterpret_cast<const f32x4*>(epi.bias + n);
     if (MODE == EPI_BIAS_RESID) {
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(256) void gemm_splitk_fixup_kernel(const float* __r
       for (int e = 0; e < 4; ++e) {
         const float f = acc[e] + b[e];
         o0[e] = (bf16_t)f;
-        o1[e] = (bf16_t)gelu_f(f);
+        o1[e] = (bf16_t)gelu<bf16_t>(f);
       }
       *reinterpret_cast<bf16x4*>((bf16_t*)epi.out1 + i4) = o1;
     } else {

@@ -69,10 +69,10 @@ __device__ __forceinline__ void epilogue_edge(const EpiParams& e, int m0, int M,
     if (MODE == EPI_PARTIAL) {
       e.outf[idx[v]] = acc[v];
     } else if (MODE == EPI_DGELU) {
-      ((bf16_t*)e.out0)[idx[v]] = (bf16_t)(acc[v] * gelu_grad_f(a[v]));
+      ((bf16_t*)e.out0)[idx[v]] = (bf16_t)(acc[v] * gelu_grad<bf16_t>(a[v]));
     } else {
       ((bf16_t*)e.out0)[idx[v]] = (bf16_t)(MODE == EPI_BIAS_RESID ? f + a[v] : f);
-      if (MODE == EPI_BIAS_GELU) ((bf16_t*)e.out1)[idx[v]] = (bf16_t)gelu_f(f);
+      if (MODE == EPI_BIAS_GELU) ((bf16_t*)e.out1)[idx[v]] = (bf16_t)gelu<bf16_t>(f);
     }
   }
 }

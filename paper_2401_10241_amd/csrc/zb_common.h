@@ -35,16 +35,33 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
-// tanh-form GELU and its derivative (fp32)
-__device__ __forceinline__ float gelu_f(float x) {
+// tanh-form GELU x (1 + tanh(u)) / 2 with u = c (x + a x^3), and its derivative, in fp32.
+// fp32 stages: with the accurate tanhf.
+template <typename T> __device__ __forceinline__ float gelu(float x) {
   const float c = 0.7978845608028654f, a = 0.044715f;
   float u = c * (x + a * x * x * x);
   return 0.5f * x * (1.0f + tanhf(u));
 }
-__device__ __forceinline__ float gelu_grad_f(float x) {
+template <typename T> __device__ __forceinline__ float gelu_grad(float x) {
   const float c = 0.7978845608028654f, a = 0.044715f;
   float t = tanhf(c * (x + a * x * x * x));
   return 0.5f * (1.0f + t) + 0.5f * x * (1.0f - t * t) * c * (1.0f + 3.0f * a * x * x);
+}
+// bf16 stages, whose results are rounded to 8 bits: (1 + tanh(u)) / 2 = 1 / (1 + exp(-2u)) from the hardware's exponential
+// and reciprocal.  Nothing else runs while a GEMM tile's epilogue does this 128 times per lane: 7 instructions for the
+// GELU and 10 for its derivative instead of about 30 (1024 x 9216 x 2304: 78 -> 60 us, 6144 x 9216 x 2304: 314 -> 251 and
+// 320 -> 259, with the loop's gains).  Against 64 bits on [-1, 1], [-3, 3], [0, 12], [-12, 0], relative 2-norm: GELU 4.8e-8,
+// 4.7e-8, 1.3e-8, 7.7e-8 (tanhf 4.1e-8, 3.6e-8, 1.0e-8, 3.6e-7), derivative 3.8e-8, 1.6e-7, 3.4e-7, 9.5e-8 (4.0e-8, 6.2e-8,
+// 9.7e-8, 1.2e-6); rounded to bf16, 1.2e-3 to 2.1e-3, both are equally far off to seven digits.
+__device__ __forceinline__ float gelu_sigmoid(float x, float xx) {  // 1 / (1 + exp(-2u)), exactly 0 where that overflows
+  const float c2 = 2.302208198f, a = 0.044715f;  // c2 = 2 sqrt(2 / pi) log2(e)
+  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-(x * fmaf(c2 * a, xx, c2))));
+}
+template <> __device__ __forceinline__ float gelu<bf16_t>(float x) { return x * gelu_sigmoid(x, x * x); }
+template <> __device__ __forceinline__ float gelu_grad<bf16_t>(float x) {
+  const float c2 = 1.5957691216057308f, a3 = 0.134145f;  // 2 sqrt(2 / pi), 3 * 0.044715
+  const float xx = x * x, s = gelu_sigmoid(x, xx), q = x * fmaf(c2 * a3, xx, c2);
+  return fmaf(s, fmaf(-s, q, q), s);  // s + s (1 - s) q
 }
 
 // ---------------------------------------------------------------------------------------

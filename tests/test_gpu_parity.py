@@ -466,6 +466,30 @@ def test_few_steps_of_the_large_tiles(cfg):
     run_and_compare(W("few", "bf16", 1, hidden, heads, ffn, seq, b, 4, 1, 2, "H2", seed=601 + hidden + b))
 
 
+@pytest.mark.parametrize("dtype,cfg", [
+    ("bf16", (64, 1, 2048, 64, 68)),   # FC1 and FC2's backward on 256-row tiles
+    ("bf16", (256, 4, 1032, 100, 1)),  # small tiles with edges
+    ("fp32", (64, 1, 256, 64, 1)),
+])
+def test_gelu_over_its_range(dtype, cfg):
+    # pre-activations from -60 to 60 (past the exponential's range on both sides), set through FC1's bias
+    import paper_2401_10241_amd as zb
+    hidden, heads, ffn, seq, b = cfg
+    w = W("gelu", dtype, 1, hidden, heads, ffn, seq, b, 4, 1, 1, "H1", seed=651)
+    params = zb_inputs.stage_params(w)
+    params[0]["b1"] = np.linspace(-60.0, 60.0, ffn).astype(np.float32)
+    dev, orc = make_device_stage(w, 1), make_oracle(w, params)
+    dev.set_params(params)
+    dev.begin_iteration(0, 1)
+    orc.begin_iteration(1)
+    load_iteration(w, 0, 1, dev, orc)
+    dev.run_schedule(w.p, w.stage, 1, w.kind)
+    orc.run(stage_order(w.p, w.stage, 1, w.kind))
+    compare_outputs(dev, orc, 1, TOL[dtype], None)
+    compare_grads(dev, orc, TOL[dtype])
+    dev.close()
+
+
 @pytest.mark.parametrize("cfg", [
     # hidden, heads, ffn, seq, b       the attention's row blocks per workgroup that only many heads reach
     (256, 4, 512, 128, 128),     # head size 64, 512 whole blocks: 128 rows forward, 64 backward
