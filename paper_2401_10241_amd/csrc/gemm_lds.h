@@ -27,39 +27,20 @@ __device__ __forceinline__ void dma16_at(const bf16_t* base, unsigned lane_off, 
   __builtin_amdgcn_global_load_lds((gptr_t)(p + (size_t)lane_off), (lptr_t)s, 16, 0, 0);
 }
 
-// What chunk c of k-line k is exclusive-or'ed with in a [k][R] tile.  The transposing read takes 64 bytes from each of
-// four consecutive k-lines at a time; the swizzle puts them in different quarters of the 64 banks (R >= 128: a line is all
-// banks; R = 64: a line is half of them, so k & 1 already separates two).
-template <int R> __device__ __forceinline__ int swz_tr(int k) { return R >= 128 ? (k & 3) << 2 : ((k >> 1) & 1) << 2; }
-
-// operand rows rb..rb+31, k = k0 .. k0+15 of a [k][R] tile
-template <int R> __device__ __forceinline__ bf16x8 frag_tr(const bf16_t* __restrict__ s, int rb, int k0, int lane) {
-  const int blk = lane >> 4, a = lane & 15;
-  const int row = rb + ((blk & 1) << 4) + ((a & 3) << 2);
-  const int k = k0 + ((blk >> 1) << 3) + (a >> 2);
-  typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
-  const bf16_t* p0 = s + k * R + ((((row >> 3) ^ swz_tr<R>(k)) << 3) | (row & 7));
-  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0));
-  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0 + 4 * R));  // k + 4: same swizzle
-  return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+// Operands of v_mfma_f32_16x16x32_bf16 are 16 rows of 32 k: lane l holds row (l & 15), k = 8 * (l >> 4)
+// and the seven after it.  A [k][R] tile is read 32 bytes from each of eight k-lines (0-3 and 8-11, then 4-7 and 12-15,
+// then 16 more) by half a wave at a time; its swizzle puts those in different eighths of the banks (R = 64: a line is half
+// of the banks, so k & 1 already separates two).
+template <int R> __device__ __forceinline__ int swz16_tr(int k) {
+  return R >= 128 ? ((k & 3) | ((k >> 1) & 4)) << 1 : (((k >> 1) & 1) | ((k >> 2) & 2)) << 1;
 }
-// operand rows rb..rb+31, k = kk*16 .. kk*16+15 of a [R][64] tile (chunk c of row r at position c ^ ((r >> 1) & 7))
-__device__ __forceinline__ bf16x8 frag_rows(const bf16_t* __restrict__ s, int rb, int kk, int lane) {
-  const int r = rb + (lane & 31);
-  const int chunk = kk * 2 + (lane >> 5);
-  return *reinterpret_cast<const bf16x8*>(s + r * 64 + ((chunk ^ ((r >> 1) & 7)) << 3));
-}
-
-// The same for v_mfma_f32_16x16x32_bf16, whose operands are 16 rows of 32 k: lane l holds row (l & 15), k = 8 * (l >> 4)
-// and the seven after it.  A [32 k][R] tile is read 32 bytes from each of eight k-lines (0-3 and 8-11, then 4-7 and 12-15,
-// then 16 more) by half a wave at a time; its swizzle puts those in different eighths of the banks.
-__device__ __forceinline__ int swz16_tr(int k) { return ((k & 3) | ((k >> 1) & 4)) << 1; }
-template <int R> __device__ __forceinline__ bf16x8 frag16_tr(const bf16_t* __restrict__ s, int rb, int lane) {
+// rows rb..rb+15, k = k0 .. k0+31 of a [k][R] tile
+template <int R> __device__ __forceinline__ bf16x8 frag16_tr(const bf16_t* __restrict__ s, int rb, int k0, int lane) {
   const int a = lane & 15;
   const int row = rb + ((a & 3) << 2);
-  const int k = ((lane >> 4) << 3) + (a >> 2);
+  const int k = k0 + ((lane >> 4) << 3) + (a >> 2);
   typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
-  const bf16_t* p0 = s + k * R + ((((row >> 3) ^ swz16_tr(k)) << 3) | (row & 7));
+  const bf16_t* p0 = s + k * R + ((((row >> 3) ^ swz16_tr<R>(k)) << 3) | (row & 7));
   const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0));
   const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p0 + 4 * R));  // k + 4: same swizzle
   return __builtin_bit_cast(bf16x8, (s16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));

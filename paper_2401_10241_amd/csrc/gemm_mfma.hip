@@ -74,7 +74,7 @@ template <int R> __device__ __forceinline__ unsigned dma_tr_lane_off(long ld, in
   constexpr int CPL = R / 8, LPB = 64 / CPL;  // chunks per k-line, k-lines per run
   const int kl = lane / CPL;
   static_assert(R == 128 || R == 256, "a wave's runs must be a multiple of 16 k-lines apart, where the swizzle repeats");
-  const int c = (lane % CPL) ^ swz16_tr(wave * LPB + kl);
+  const int c = (lane % CPL) ^ swz16_tr<R>(wave * LPB + kl);
   return (unsigned)((kl * ld + c * 8) * (long)sizeof(bf16_t));
 }
 // run j of the tile whose first element (k0, r0) is *p0
@@ -284,7 +284,7 @@ __global__ __launch_bounds__(NTHREADS, (BM == 128 && BS == 3) ? 4 : 2) void gemm
     dma_tr<BN>(b_tile + (long)(nt * KS) * ldb, ldb, b_off, sB + (nt % BS) * C::B_ELEMS, wave, d);
   };
   auto read_a = [&](int it, int i) { return frag16_rows(sA + ((it >> 1) % AS) * C::A_ELEMS, wm + i * 16, it & 1, lane); };
-  auto read_b = [&](int it, int j) { return frag16_tr<BN>(sB + (it % BS) * C::B_ELEMS, wn + j * 16, lane); };
+  auto read_b = [&](int it, int j) { return frag16_tr<BN>(sB + (it % BS) * C::B_ELEMS, wn + j * 16, 0, lane); };
   constexpr int AHEAD = (BS - 2) > (2 * AS - 3) ? (BS - 2) : (2 * AS - 3);  // last step whose refills all exist
   auto dma = [&](int it, int d, bool guard) {
     if (d < C::LA) refill_a(it, d, guard);
@@ -508,8 +508,8 @@ __global__ __launch_bounds__(512, (BM == 128 && BS == 3) ? 4 : 2) void gemm_wgra
       b_next = tb.b[pair0 + g_next] + n0;
     }
   };
-  auto read_a = [&](int it, int i) { return frag16_tr<BM>(sA + (it % BS) * C::A_ELEMS, wm + i * 16, lane); };
-  auto read_b = [&](int it, int j) { return frag16_tr<BN>(sB + (it % BS) * C::B_ELEMS, wn + j * 16, lane); };
+  auto read_a = [&](int it, int i) { return frag16_tr<BM>(sA + (it % BS) * C::A_ELEMS, wm + i * 16, 0, lane); };
+  auto read_b = [&](int it, int j) { return frag16_tr<BN>(sB + (it % BS) * C::B_ELEMS, wn + j * 16, 0, lane); };
   auto wait = [&](int it, bool guard) {
     if (guard && it + BS - 2 >= nk) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     else __builtin_amdgcn_s_waitcnt(vmcnt_imm(C::allowed(0)));
@@ -627,9 +627,9 @@ bool try_tail_split(const GemmArgs& g, long lda, long ldb, hipStream_t s, hipErr
 }
 
 // Microseconds the 256-column tiles below are expected to take where they do not fill the chip even once (at most
-// 128 tiles of 256 x 256): a step of 32 k takes 0.66 us with few 256-row tiles and 0.90 with one per CU (128-row
-// tiles: 0.40 and 0.70).  Against 27 of edge_cost's shapes -9 to +17 %, but for 1024 x 6144 x 1536 (33.0 against 24.9),
-// where the choice is the right one all the same.  A larger product is theirs without asking.
+// 128 tiles of 256 x 256): a step of 32 k takes 0.42 us with few 256-row tiles and 0.85 with one per CU (128-row
+// tiles: 0.35 and 0.60).  A larger product is theirs without asking: 1024 x 9216 x 2304 (144 tiles) 55.3 us on them and
+// 55.5 on 128 x 128 ones, 6144 x 2304 x 2304 65.8 and 74.5.
 double big_tile_us(const GemmArgs& g, bool rides) {
   if ((long)g.M * g.N > 128L * 256 * BN) return 0;
   const int steps = g.K / KS;
@@ -637,10 +637,10 @@ double big_tile_us(const GemmArgs& g, bool rides) {
     const long tiles = (long)(g.M / 256) * (g.N / BN);
     const int slices = (int)(256 / tiles) < 4 ? (int)(256 / tiles) : 4;
     if ((size_t)slices * g.M * g.N <= g.workspace_floats)
-      return 3.0 + (double)(steps / slices) * (0.66 + 0.24 * tiles * slices / 256) + split_cost(g.M, g.N, slices, rides);
+      return 3.0 + (double)(steps / slices) * (0.42 + 0.43 * tiles * slices / 256) + split_cost(g.M, g.N, slices, rides);
   }
   const long t128 = (long)(g.M / 128) * (g.N / BN);  // at most 256: one round
-  return 3.0 + steps * (0.40 + 0.30 * t128 / 256);
+  return 3.0 + steps * (0.35 + 0.25 * t128 / 256);
 }
 
 // The other tiles (gemm_mfma_edge.hip)
@@ -667,8 +667,7 @@ hipError_t run_shape(const GemmArgs& g, long lda, long ldb, hipStream_t s, bool*
   if (g.N % 8 == 0)
     choose_edge(g.M, g.N, g.K, g.workspace ? g.workspace_floats : 0, rides, &tile, &slices, &edge_us);
   // Sizes that the 256-column tiles take stay with them unless the other tiles are clearly shorter: 256 x 1024 x
-  // 1024 15.6 -> 7.5 us, 512 x 768 x 3072 25.7 -> 12.9, 1024 x 1536 x 1536 22.7 -> 11.8, 1024 x 2304 x 2304 34.2 -> 26.1 (28.0
-  // and 31.2 expected); 1024 x 4096 x 4096 stays, 50.0 against 51.3.
+  // 1024 15.6 -> 6.8 us, 1024 x 2304 x 2304 34.2 -> 18.5, 1024 x 4096 x 4096 49.0 -> 34.4, 3072 x 2304 x 2304 51.5 -> 37.5.
   if (g.K % 64 != 0 || g.M % 128 != 0 || g.N % BN != 0 || edge_us < 0.9 * big_tile_us(g, rides)) {
     if (tile) return run_edge_shape<MODE>(g, lda, ldb, s, tile, slices);
     *taken = false;

@@ -7,20 +7,20 @@
 //   wgrad            both operands row-contiguous ([k][m], [k][n]), 32 k per step, tile 128 x 128 (4 waves), the
 //                    accumulators start from the old gradient as in gemm_mfma.hip
 //
-// Tiles travel global memory -> LDS directly, four stages deep.  Nothing out of range is ever read: rows and
+// Tiles travel global memory -> LDS directly, five stages deep.  Nothing out of range is ever read: rows and
 // columns past the edge are fetched from the last valid one (their products are never stored), and 16-byte
 // chunks whose k lies past the end are fetched from a chunk of zeros, so that the last step adds exact zeros
 // whatever the neighbouring memory holds (infinities and NaN included).  Which chunk a lane fetches also
 // implements the LDS swizzle.
 //
 // What bounds them: at these sizes a GEMM is a chain of K / 64 steps on a chip that is filled once or less, so
-// the latency of a step (global -> LDS -> fragments -> MFMA, with three later steps in flight) times the number
-// of steps is the time; smaller tiles and K slices shorten the chain or use more CUs (the rule is at
-// `edge_cost`).  Measured (M x N x K with a bias epilogue, us per launch back to back, the launch that adds K slices
-// included; before: the vector ALUs or the 256-column tiles): 777 x 4808 x 1200 245 -> 26, 777 x 1200 x 4808 1041 -> 28,
-// 777 x 1200 x 1200 264 -> 10, 256 x 1024 x 1024 15.6 -> 7.5, 512 x 768 x 3072 25.7 -> 12.9, 512 x 2048 x 2048 25.6 -> 13.6.
-#include <type_traits>
-
+// the latency of a step (barrier, LDS -> fragments, MFMA) times the number of steps is the time, and with two 64 x 64
+// workgroups on a CU what it can fetch from L2 (about 100 GB/s); smaller tiles and K slices shorten the chain or use
+// more CUs (the rule is at `edge_cost`).  The steps overlap as `ring_steps` says.  Measured (M x N x K with a bias
+// epilogue, us per launch back to back; fragments read and used in the same step, 32x32x16 MFMAs -> now): 1024 x 2304 x 2304
+// 25.7 -> 18.3, 512 x 2048 x 2048 13.7 -> 10.4, 256 x 3072 x 2048 12.8 -> 10.4, 777 x 3600 x 1200 17.1 -> 14.6, 1024 x 4096 x
+// 4096 (256-column tiles and the launch that adds four slices) 49.0 -> 34.4; W of h 1200, 777 tokens, two layers 143 -> 117.
+// A ring of seven or nine stages: the same or slower (256 x 3072 x 1024 7.3 -> 7.9 and 8.3).
 #include "gemm_epilogue.h"
 #include "gemm_lds.h"
 
@@ -47,34 +47,98 @@ __device__ __forceinline__ int xcd_run(int id, int nblk) {
   return x * per + min(x, rem) + (id >> 3);
 }
 
-constexpr int ST = 4;  // LDS stages
+constexpr int ST = 5;  // LDS stages
 
-// epilogue_tile for a tile that the last row cuts: all reads first (from the last row where a row does not exist), or
-// every row would wait for a read of its own behind the store before it
-template <int MODE>
-__device__ __forceinline__ void epilogue_edge(const EpiParams& e, int m0, int M, int n, const f32x16& acc) {
-  size_t idx[16];
-  float a[16];
+// The steps of a chain.  While a step's NM MFMAs run, the NR fragments of the next one are read from LDS and the ND loads
+// of the tile ST-1 ahead are issued, singly and in this order, so that a step is one barrier and its MFMAs: read and used
+// in the same step, the fragments' way out of LDS and a chain of dependent MFMAs stood in the open (0.31 us per 64-k
+// step of a 64 x 64 tile where the MFMAs take 0.06).
+// read(it, r, f) fetches fragment r of step it, dma(t, d, guard) issues load d of tile t (tiles in order; guard: the tile
+// may be past the end or cut by it), fetched() follows the last load of a tile, mma(f, e) is MFMA e.
+template <int NM, int NR, int ND, class F, class R, class D, class FE, class MM>
+__device__ __forceinline__ void ring_steps(int nk, F& f0, F& f1, R&& read, D&& dma, FE&& fetched, MM&& mma) {
+  auto advance = [&](int it, bool guard, const F& cur, F& nxt) {
+    // this wave's loads of tile it + 1 have landed (those of the ST-3 tiles after it may stay in flight)
+    if (guard && it + ST - 2 >= nk) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    else __builtin_amdgcn_s_waitcnt(vmcnt_imm((ST - 3) * ND));
+    __builtin_amdgcn_s_barrier();  // everybody's; and everybody is done with tile it - 1, whose stage is refilled
 #pragma unroll
-  for (int v = 0; v < 16; ++v) idx[v] = (size_t)min(m0 + (v >> 2) * 8 + (v & 3), M - 1) * e.N + n;
-  if (MODE == EPI_BIAS_RESID || MODE == EPI_DGELU) {
+    for (int e = 0; e < NM; ++e) {
+      mma(cur, e);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int v = 0; v < 16; ++v) a[v] = to_f32(((const bf16_t*)e.aux)[idx[v]]);
-  }
-  const float b = MODE == EPI_BIAS || MODE == EPI_BIAS_RESID || MODE == EPI_BIAS_GELU ? e.bias[n] : 0.f;
+      for (int r = 0; r < NR; ++r)
+        if (r * NM / NR == e) read(it + 1, r, nxt);
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    if (m0 + (v >> 2) * 8 + (v & 3) >= M) continue;
-    const float f = acc[v] + b;
-    if (MODE == EPI_PARTIAL) {
-      e.outf[idx[v]] = acc[v];
-    } else if (MODE == EPI_DGELU) {
-      ((bf16_t*)e.out0)[idx[v]] = (bf16_t)(acc[v] * gelu_grad<bf16_t>(a[v]));
-    } else {
-      ((bf16_t*)e.out0)[idx[v]] = (bf16_t)(MODE == EPI_BIAS_RESID ? f + a[v] : f);
-      if (MODE == EPI_BIAS_GELU) ((bf16_t*)e.out1)[idx[v]] = (bf16_t)gelu<bf16_t>(f);
+      for (int d = 0; d < ND; ++d)
+        if ((d + 1) * NM / ND - 1 == e) dma(it + ST - 1, d, guard);
+      __builtin_amdgcn_sched_barrier(0);
     }
+    fetched();
+  };
+#pragma unroll
+  for (int t = 0; t < ST - 1; ++t) {
+#pragma unroll
+    for (int d = 0; d < ND; ++d) dma(t, d, true);
+    fetched();
   }
+  if (nk >= ST - 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm((ST - 2) * ND));
+  else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+  __builtin_amdgcn_s_barrier();
+#pragma unroll
+  for (int r = 0; r < NR; ++r) read(0, r, f0);
+  int it = 0;
+  for (; it + 1 < nk - ST; it += 2) {  // the tiles fetched meanwhile are whole
+    advance(it, false, f0, f1);
+    advance(it + 1, false, f1, f0);
+  }
+  for (; it + 2 < nk; it += 2) {
+    advance(it, true, f0, f1);
+    advance(it + 1, true, f1, f0);
+  }
+  if (it + 1 < nk) {
+    advance(it, true, f0, f1);
+    f0 = f1;
+  }
+#pragma unroll
+  for (int e = 0; e < NM; ++e) mma(f0, e);
+}
+
+// epilogue_wave for a tile that the last row or column cuts: all reads of 8 rows first (from the last row where a row does
+// not exist), or every row would wait for a read of its own behind the store before it
+template <int MODE, int MT, int NT>
+__device__ __forceinline__ void epilogue_edge(const EpiParams& e, int m0, int M, int n0, int N, int lane,
+                                              const f32x4 (&acc)[MT][NT]) {
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int q = 0; q < NT / 2; ++q) {
+      const f32x8 c = rows8(acc[i][2 * q], acc[i][2 * q + 1]);
+      const int m = m0 + i * 16 + (lane >> 5) * 8, n = n0 + q * 32 + (lane & 31);
+      if (n >= N) continue;
+      size_t idx[8];
+      float a[8];
+#pragma unroll
+      for (int v = 0; v < 8; ++v) idx[v] = (size_t)min(m + v, M - 1) * e.N + n;
+      if (MODE == EPI_BIAS_RESID || MODE == EPI_DGELU) {
+#pragma unroll
+        for (int v = 0; v < 8; ++v) a[v] = to_f32(((const bf16_t*)e.aux)[idx[v]]);
+      }
+      const float b = MODE == EPI_BIAS || MODE == EPI_BIAS_RESID || MODE == EPI_BIAS_GELU ? e.bias[n] : 0.f;
+#pragma unroll
+      for (int v = 0; v < 8; ++v) {
+        if (m + v >= M) continue;
+        const float f = c[v] + b;
+        if (MODE == EPI_PARTIAL) {
+          e.outf[idx[v]] = c[v];
+        } else if (MODE == EPI_DGELU) {
+          ((bf16_t*)e.out0)[idx[v]] = (bf16_t)(c[v] * gelu_grad<bf16_t>(a[v]));
+        } else {
+          ((bf16_t*)e.out0)[idx[v]] = (bf16_t)(MODE == EPI_BIAS_RESID ? f + a[v] : f);
+          if (MODE == EPI_BIAS_GELU) ((bf16_t*)e.out1)[idx[v]] = (bf16_t)gelu<bf16_t>(f);
+        }
+      }
+    }
 }
 
 template <int BM, int BN, int NWM, int NWN, int MODE>
@@ -82,7 +146,7 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_edge_kernel(const bf16_t*
                                                                   int M, int N, int K, long lda, long ldb, EpiParams epi,
                                                                   int slices) {
   constexpr int NW = NWM * NWN;
-  constexpr int WM = BM / NWM, WN = BN / NWN, MT = WM / 32, NT = WN / 32;
+  constexpr int WM = BM / NWM, WN = BN / NWN, MT = WM / 16, NT = WN / 16;
   constexpr int LA = BM / 8 / NW;        // 1 KB runs (8 rows of 64 k) per wave per A tile
   constexpr int CPL = BN / 8, LPB = 64 / CPL;  // chunks per k-line of B, k-lines per run
   constexpr int LB = 64 / LPB / NW;
@@ -121,78 +185,47 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_edge_kernel(const bf16_t*
 #pragma unroll
   for (int j = 0; j < LB; ++j) {
     kb[j] = (j * NW + wave) * LPB + lane / CPL;
-    const int c = (lane % CPL) ^ swz_tr<BN>(kb[j]);
+    const int c = (lane % CPL) ^ swz16_tr<BN>(kb[j]);
     pb[j] = B + (long)kb[j] * ldb + min(n0 + c * 8, N - 8);
   }
 
-  f32x16 acc[MT][NT];
+  f32x4 acc[MT][NT];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
-    for (int j = 0; j < NT; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   const int nk = (K + 63) / 64;
-  auto issue = [&](int t) {  // tile t into its stage; every k-block before the last is whole
-    if (t >= nk) return;
-    bf16_t* a_s = sA + (t % ST) * (BM * 64);
-    bf16_t* b_s = sB + (t % ST) * (BN * 64);
+  auto dma = [&](int t, int d, bool guard) {  // every tile before the last is whole
+    if (guard && t >= nk) return;
     const int k0 = t * 64;
-    const bool whole = k0 + 64 <= K;
-#pragma unroll
-    for (int j = 0; j < LA; ++j) {
-      const void* p = pa[j] + k0;
-      if (!whole && k0 + ka[j] >= K) p = &kZeroChunk;
-      dma16(p, a_s + (j * NW + wave) * 512);
-    }
-#pragma unroll
-    for (int j = 0; j < LB; ++j) {
+    if (d < LA) {
+      const void* p = pa[d] + k0;
+      if (guard && k0 + ka[d] >= K) p = &kZeroChunk;
+      dma16(p, sA + (t % ST) * (BM * 64) + (d * NW + wave) * 512);
+    } else {
+      const int j = d - LA;
       const void* p = pb[j] + (long)k0 * ldb;
-      if (!whole && k0 + kb[j] >= K) p = &kZeroChunk;
-      dma16(p, b_s + (j * NW + wave) * 512);
+      if (guard && k0 + kb[j] >= K) p = &kZeroChunk;
+      dma16(p, sB + (t % ST) * (BN * 64) + (j * NW + wave) * 512);
     }
   };
-#pragma unroll
-  for (int t = 0; t < ST - 1; ++t) issue(t);
-  for (int it = 0; it < nk; ++it) {
-    // this wave's loads of tile `it` have landed (those of the ST-2 tiles after it may stay in flight)
-    if (it + ST - 2 < nk) __builtin_amdgcn_s_waitcnt(vmcnt_imm((ST - 2) * (LA + LB)));
-    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    __builtin_amdgcn_s_barrier();
-    const bf16_t* a_s = sA + (it % ST) * (BM * 64);
-    const bf16_t* b_s = sB + (it % ST) * (BN * 64);
-    bf16x8 af[4][MT], bf[4][NT];
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-#pragma unroll
-      for (int i = 0; i < MT; ++i) af[kk][i] = frag_rows(a_s, wm + i * 32, kk, lane);
-#pragma unroll
-      for (int j = 0; j < NT; ++j) bf[kk][j] = frag_tr<BN>(b_s, wn + j * 32, kk * 16, lane);
-    }
-    issue(it + ST - 1);  // into the stage that step it-1 read
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk][i], bf[kk][j], acc[i][j], 0, 0, 0);
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this stage's reads are done before the next barrier
-  }
+  struct Frags {
+    bf16x8 a[2][MT], b[2][NT];  // of both halves of the 64 k
+  } f0, f1;
+  auto read = [&](int it, int r, Frags& f) {
+    const int kk = r / (MT + NT), q = r % (MT + NT);  // columns first
+    if (q < NT) f.b[kk][q] = frag16_tr<BN>(sB + (it % ST) * (BN * 64), wn + q * 16, kk * 32, lane);
+    else f.a[kk][q - NT] = frag16_rows(sA + (it % ST) * (BM * 64), wm + (q - NT) * 16, kk, lane);
+  };
+  auto mma = [&](const Frags& f, int e) {
+    const int kk = e / (MT * NT), i = e % (MT * NT) / NT, j = (i & 1) ? NT - 1 - e % NT : e % NT;
+    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[kk][i], f.b[kk][j], acc[i][j], 0, 0, 0);
+  };
+  ring_steps<2 * MT * NT, 2 * (MT + NT), LA + LB>(nk, f0, f1, read, dma, [] {}, mma);
 
-  const int lrow = lane & 31, lhi = (lane >> 5) * 4;
-#pragma unroll
-  for (int i = 0; i < MT; ++i)
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-      const int mb = m0 + wm + i * 32, nb = n0 + wn + j * 32;
-      if (mb + 32 <= M && nb + 32 <= N) {
-        epilogue_tile<bf16_t, MODE>(epi, mb + lhi, nb + lrow, acc[i][j]);
-      } else if (nb + lrow < N) {
-        epilogue_edge<MODE>(epi, mb + lhi, M, nb + lrow, acc[i][j]);
-      }
-    }
+  if (m0 + wm + WM <= M && n0 + wn + WN <= N) epilogue_wave<MODE, MT, NT>(epi, m0 + wm, n0 + wn, lane, acc);
+  else epilogue_edge<MODE, MT, NT>(epi, m0 + wm, M, n0 + wn, N, lane, acc);
 }
 
 template <int BM, int BN, int NWM, int NWN, int MODE>
@@ -223,25 +256,27 @@ template <int MODE> hipError_t run_edge_tile(const GemmArgs& g, long lda, long l
 
 // Microseconds the kernel above is expected to take with this tile and number of K slices, the launch that adds
 // the planes included (`rides`: a LayerNorm that has to run anyway does it).  Fitted to single launches: a step of 64 k
-// takes 0.31 us with one 64 x 64 workgroup per CU and 0.44 with two (0.57 and 0.79 for a 128 x 128 tile on a
-// nearly empty and on a full chip), 3 us go to the start, the fill of the ring and the epilogue.  Against 39 shapes from
-// 1 x 64 x 72 to 6144 x 2304 x 2304, 76 unsliced points: -20 to +15 %, but for three products under 12 us (100 x 96 x 96,
-// 1 x 64 x 72, 333 x 264 x 520: up to 59 % short).  218 sliced points: 43 more than 20 % short, up to 42 % (512 x 3072 x 768 in
-// four slices: 7.0 against 12.1; the planes' stores are not in the step), so slices are taken a little too readily.
+// takes 0.21 us with one 64 x 64 workgroup on few CUs, 0.26 on all, 0.46 with two (what a CU can fetch from L2 then bounds
+// it), and 0.37 to 0.50 for a 128 x 128 tile; 3 us go to the start, the fill of the ring and the epilogue.  Over 49 shapes
+// from 1 x 64 x 72 to 6144 x 2304 x 2304 with one to four slices the choice it makes costs 0.6 % more than the best
+// measured one on average without a LayerNorm, 3 % with one (most: 100 x 96 x 96 and 1152 x 1536 x 512, 7.6 against 6.6).
 double edge_cost(int M, int N, int K, int tile, int slices, bool rides) {
   const long tiles = (long)((M + tile - 1) / tile) * ((N + tile - 1) / tile) * slices;
   const int steps = ((K + 63) / 64 + slices - 1) / slices;
   const long at_once = tile == 128 ? 256 : 512;
-  const double full = tile == 128 ? 0.79 : 0.44, empty = tile == 128 ? 0.57 : 0.31;
+  auto step = [&](long r) {  // with r workgroups on the chip
+    if (tile == 128) return 0.37 + 0.13 * r / 256;
+    return r <= 256 ? 0.21 + 0.05 * r / 256 : 0.37 + 0.09 * (r - 256) / 256;
+  };
   const long rounds = tiles / at_once, rest = tiles % at_once;
-  double us = 3.0 + steps * full * rounds;
-  if (rest) us += steps * (empty + (full - empty) * rest / at_once);
+  double us = 3.0 + steps * step(at_once) * rounds;
+  if (rest) us += steps * step(rest);
   if (slices > 1) us += split_cost(M, N, slices, rides);
   return us;
 }
 
-// Cheapest tile and number of K slices (within the workspace); 512 x 768 x 3072: 17.9 us whole, 8.3 in four slices and
-// 4.6 for the launch that adds them (25.7 on the 256-column tiles).
+// Cheapest tile and number of K slices (within the workspace); 512 x 768 x 3072: 13.6 us whole, 8.5 in four slices and
+// 4.5 for the launch that adds them (25.7 on the 256-column tiles).
 void choose_edge(int M, int N, int K, size_t workspace_floats, bool rides, int* tile, int* slices, double* us) {
   *us = 1e30;
   const int blocks = (K + 63) / 64;
@@ -255,9 +290,9 @@ void choose_edge(int M, int N, int K, size_t workspace_floats, bool rides, int* 
     }
 }
 
-// Microseconds that cutting a product into K slices adds: the planes are read back at about 4 TB/s, by a launch of
+// Microseconds that cutting a product into K slices adds: the planes are written and read back, by a launch of
 // its own unless a LayerNorm that runs anyway takes it over.
-double split_cost(int M, int N, int slices, bool rides) { return (rides ? 0.0 : 4.5) + (double)slices * M * N * 1e-6; }
+double split_cost(int M, int N, int slices, bool rides) { return (rides ? 0.0 : 4.5) + (double)slices * M * N * 1.6e-6; }
 
 // forward / dgrad GEMM with the given tile (128 or 64); slices > 1: the K slices' planes only (g.outf)
 hipError_t launch_gemm_edge(const GemmArgs& g, long lda, long ldb, int tile, int slices, hipStream_t s) {
@@ -354,20 +389,19 @@ __global__ __launch_bounds__(256, 2) void gemm_wgrad_edge_kernel(EdgeWgradTable 
   const int m0 = tm * WT, n0 = tn * WT;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
-  const int lrow = lane & 31, lhi = (lane >> 5) * 4;
+  const int row = m0 + wm + (lane >> 5) * 8, col = n0 + wn + (lane & 31);  // this lane's first row and column (rows8)
   float* __restrict__ outf = tb.outf[q];
 
-  f32x16 acc[2][2];
+  f32x4 acc[4][4];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {  // rows and columns past the edge: some valid element, never stored
-      const int n = min(n0 + wn + j * 32 + lrow, N - 1);
+    for (int j = 0; j < 4; j += 2) {  // rows and columns past the edge: some valid element, never stored
+      const int n = min(col + j * 16, N - 1);
+      f32x8 c;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int m = min(m0 + wm + i * 32 + lhi + (v >> 2) * 8 + (v & 3), M - 1);
-        acc[i][j][v] = __builtin_nontemporal_load(outf + (size_t)m * N + n);
-      }
+      for (int v = 0; v < 8; ++v) c[v] = __builtin_nontemporal_load(outf + (size_t)min(row + i * 16 + v, M - 1) * N + n);
+      from_rows8(c, &acc[i][j], &acc[i][j + 1]);
     }
 
   // run j of a tile: 4 k-lines of 16 chunks
@@ -376,69 +410,55 @@ __global__ __launch_bounds__(256, 2) void gemm_wgrad_edge_kernel(EdgeWgradTable 
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     kl[j] = (j * 4 + wave) * 4 + (lane >> 4);
-    const int c = ((lane & 15) ^ swz_tr<WT>(kl[j])) * 8;
+    const int c = ((lane & 15) ^ swz16_tr<WT>(kl[j])) * 8;
     oa[j] = (long)kl[j] * M + min(m0 + c, M - 8);
     ob[j] = (long)kl[j] * N + min(n0 + c, N - 8);
   }
   const int spc = (Kc + WKS - 1) / WKS, nk = ngroup * spc;
+  // the next tile to fetch: its operand pair, k offset and addresses
   int g_next = 0, k_next = 0;
-  auto issue = [&](int t) {  // tiles are fetched in order
-    if (t >= nk) return;
-    const bf16_t* pa = tb.a[pair0 + g_next] + (long)k_next * M;
-    const bf16_t* pb = tb.b[pair0 + g_next] + (long)k_next * N;
-    bf16_t* a_s = sA + (t % ST) * (WT * WKS);
-    bf16_t* b_s = sB + (t % ST) * (WT * WKS);
-    const bool whole = k_next + WKS <= Kc;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const bool out = !whole && k_next + kl[j] >= Kc;
-      const void* p = pa + oa[j];
-      const void* r = pb + ob[j];
-      if (out) p = r = &kZeroChunk;
-      dma16(p, a_s + (j * 4 + wave) * 512);
-      dma16(r, b_s + (j * 4 + wave) * 512);
-    }
-    k_next += WKS;
-    if (k_next >= Kc) { k_next = 0; ++g_next; }
+  const bf16_t *a_next = tb.a[pair0], *b_next = tb.b[pair0];
+  auto dma = [&](int t, int d, bool guard) {
+    if (guard && t >= nk) return;
+    const int j = d >> 1;
+    const void* p = (d & 1) ? b_next + ob[j] : a_next + oa[j];
+    if (k_next + kl[j] >= Kc) p = &kZeroChunk;  // a pair's last tile may be cut anywhere in the chain
+    dma16(p, ((d & 1) ? sB : sA) + (t % ST) * (WT * WKS) + (j * 4 + wave) * 512);
   };
-#pragma unroll
-  for (int t = 0; t < ST - 1; ++t) issue(t);
-  for (int it = 0; it < nk; ++it) {
-    if (it + ST - 2 < nk) __builtin_amdgcn_s_waitcnt(vmcnt_imm((ST - 2) * 4));
-    else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    __builtin_amdgcn_s_barrier();
-    const bf16_t* a_s = sA + (it % ST) * (WT * WKS);
-    const bf16_t* b_s = sB + (it % ST) * (WT * WKS);
-    bf16x8 af[2][2], bf[2][2];
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        af[kk][i] = frag_tr<WT>(a_s, wm + i * 32, kk * 16, lane);
-        bf[kk][i] = frag_tr<WT>(b_s, wn + i * 32, kk * 16, lane);
-      }
-    issue(it + ST - 1);
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk)
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk][i], bf[kk][j], acc[i][j], 0, 0, 0);
-    __builtin_amdgcn_s_waitcnt(0xC07F);
-  }
+  auto fetched = [&]() {
+    a_next += (long)WKS * M;
+    b_next += (long)WKS * N;
+    k_next += WKS;
+    if (k_next >= Kc && ++g_next < ngroup) {
+      k_next = 0;
+      a_next = tb.a[pair0 + g_next];
+      b_next = tb.b[pair0 + g_next];
+    }
+  };
+  struct Frags {
+    bf16x8 a[4], b[4];
+  } f0, f1;
+  auto read = [&](int it, int r, Frags& f) {
+    if (r & 1) f.a[r >> 1] = frag16_tr<WT>(sA + (it % ST) * (WT * WKS), wm + (r >> 1) * 16, 0, lane);
+    else f.b[r >> 1] = frag16_tr<WT>(sB + (it % ST) * (WT * WKS), wn + (r >> 1) * 16, 0, lane);
+  };
+  auto mma = [&](const Frags& f, int e) {
+    const int i = e >> 2, j = (i & 1) ? 3 - (e & 3) : e & 3;
+    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
+  };
+  ring_steps<16, 8, 4>(nk, f0, f1, read, dma, fetched, mma);
 
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int n = n0 + wn + j * 32 + lrow, mb = m0 + wm + i * 32 + lhi;
-      if (n < N) {
+    for (int j = 0; j < 4; j += 2) {
+      const f32x8 c = rows8(acc[i][j], acc[i][j + 1]);
+      const int n = col + j * 16;
+      if (n >= N) continue;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int m = mb + (v >> 2) * 8 + (v & 3);
-          if (m < M) __builtin_nontemporal_store(acc[i][j][v], outf + (size_t)m * N + n);
-        }
+      for (int v = 0; v < 8; ++v) {
+        const int m = row + i * 16 + v;
+        if (m < M) __builtin_nontemporal_store(c[v], outf + (size_t)m * N + n);
       }
     }
 }
@@ -475,7 +495,14 @@ hipError_t launch_wgrad_multi_edge(const WgradMultiArgs& w, hipStream_t s, bool*
   for (int q = w.nprob; q <= kWgradMaxProblems; ++q) { tb.tile0[q] = (int)tiles; tb.strip0[q] = strips; }
   tb.ntiles = (int)tiles;
   constexpr size_t smem = (size_t)ST * 2 * WT * WKS * sizeof(bf16_t);
-  static_assert(smem <= 64 * 1024 && smem >= 16 * WT * sizeof(float), "no attribute needed; the strips' buffer fits");
+  static_assert(smem <= 80 * 1024 && smem >= 16 * WT * sizeof(float), "two workgroups per CU; the strips' buffer fits");
+  static bool attr_set = false;  // one device per process in this library
+  if (!attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_wgrad_edge_kernel),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
   *taken = true;
   if (w.bias_done) *w.bias_done = true;
   gemm_wgrad_edge_kernel<<<(unsigned)(tiles + strips), 256, smem, s>>>(tb, w.K);

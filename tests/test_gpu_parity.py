@@ -466,6 +466,13 @@ def test_few_steps_of_the_large_tiles(cfg):
     run_and_compare(W("few", "bf16", 1, hidden, heads, ffn, seq, b, 4, 1, 2, "H2", seed=601 + hidden + b))
 
 
+@pytest.mark.parametrize("steps", range(1, 8))
+def test_few_steps_of_the_small_tiles(steps):
+    # 1 to 7 steps of a ring of five stages, the last one cut: 64 k of the products, 32 tokens of W
+    hidden = 64 * steps - 8
+    run_and_compare(W("few_small", "bf16", 1, hidden, 8, 64 * steps + 8, 32 * steps - 3, 1, 4, 1, 2, "H2", seed=671 + steps))
+
+
 @pytest.mark.parametrize("dtype,cfg", [
     ("bf16", (64, 1, 2048, 64, 68)),   # FC1 and FC2's backward on 256-row tiles
     ("bf16", (256, 4, 1032, 100, 1)),  # small tiles with edges
