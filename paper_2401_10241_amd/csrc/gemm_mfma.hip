@@ -755,10 +755,14 @@ template <> hipError_t launch_wgrad_multi_mfma<bf16_t>(const WgradMultiArgs& w, 
   if (t128 >= (1L << 30)) return hipSuccess;
   *taken = true;
   if (w.bias_done) *w.bias_done = true;
-  // 256-row tiles (one workgroup per CU, four-stage ring) when they fill most of the chip; else 128-row
+  // 256-row tiles (one workgroup per CU, four-stage ring) when they fill most of the chip and the chain is long; else 128-row
   // tiles, two workgroups per CU with a three-stage ring if there are more tiles than CUs, one with a
-  // five-stage ring otherwise.  The choice does not change the result (see the kernel).
-  if (all256 && t256 >= 192) return run_wgrad<256, 4>(tb, w.K, s);
+  // five-stage ring otherwise.  With a short chain the gradient's way in and out is most of the time, and a second
+  // workgroup's loop hides it: 256 tokens of h 1024, two layers 50.7 us on 256-row tiles, 42.1 on 128-row ones, 2 x 192 of
+  // h 1280 51.4 and 45.7, 2 x 128 of h 2048 95.8 and 88.8, 512 of h 768, four layers 66.1 both, 1024 of h 4096 554 and 559,
+  // 6144 of h 2304 2018 and 2407.  The choice does not change the result (see the kernel).
+  const bool long_chain = (long)w.K * w.ngroup >= 512;
+  if (all256 && t256 >= 192 && (long_chain || t128 <= 256)) return run_wgrad<256, 4>(tb, w.K, s);
   if (t128 > 256) return run_wgrad<128, 3>(tb, w.K, s);
   return run_wgrad<128, 5>(tb, w.K, s);
 }
