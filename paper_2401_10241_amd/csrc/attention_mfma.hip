@@ -18,8 +18,10 @@
 // again from attention_rows.h.
 //
 // What bounds them: a workgroup is a chain of dependent tiles (LDS read -> MFMA -> exponentials -> MFMA), and
-// the shapes that come here have few heads, so most of the chip is idle (row blocks: the rule at `narrow_fwd`).
-// Measured: 16 heads of 75 columns, 777 tokens 315 us forward and 1292 us backward on the vector ALUs, 64 and 95 here.
+// the shapes that come here have few heads, so most of the chip is idle.  Where it is, two groups of waves share a
+// workgroup's rows and take its tiles in turn (the rule and figures at `Fwd`).
+// Measured: 16 heads of 75 columns, 777 tokens 315 us forward and 1292 us backward on the vector ALUs, 65 and 93 here
+// with one group, 44 and 60 with two.
 //
 // A 32x32 accumulator tile holds, in lane l and element v, row 8*(v/4) + 4*(l>>5) + v%4 and column
 // l&31.  Used directly as the k-operand of the next MFMA (16 rows per instruction: elements 0-7,
@@ -69,12 +71,33 @@ __device__ __forceinline__ u32x4 trim_chunk(u32x4 v, int c0, int d, bool valid) 
   return v;
 }
 
+// A workgroup is NG groups of NW waves that own the same rows and take the tiles of the other side in turn, each
+// with its own LDS stages; the second hands its sums to the first at the end.
+template <int NW> __device__ __forceinline__ int group_thread() { return threadIdx.x & (64 * NW - 1); }
+template <int NW> __device__ __forceinline__ int group_of() { return __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * NW)); }
+// this lane's place for n floats of its wave, 64 apart
+__device__ __forceinline__ float* hand_over(unsigned char* smem, int wave, int n, int lane) {
+  return reinterpret_cast<float*>(smem) + wave * n * 64 + lane;
+}
+template <int N> __device__ __forceinline__ void put(float* x, const f32x16 (&t)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) x[(i * 16 + v) * 64] = t[i][v];
+}
+template <int N> __device__ __forceinline__ void add(f32x16 (&t)[N], const float* x) {
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) t[i][v] += x[(i * 16 + v) * 64];
+}
+
 // rows [0, KB) of a tile whose first `rows` exist, NW * 64 threads
 template <int D, int NW, bool EDGE, int CH>
 __device__ __forceinline__ void gload_tile(u32x4 (&reg)[CH], const bf16_t* __restrict__ base, long ld, int rows, int d) {
 #pragma unroll
   for (int j = 0; j < CH; ++j) {
-    const int c = threadIdx.x + 64 * NW * j;
+    const int c = group_thread<NW>() + 64 * NW * j;
     const int row = c / (D / 8), dc = c % (D / 8);
     if constexpr (EDGE) reg[j] = load_chunk(base + (long)min(row, rows - 1) * ld, dc * 8, d);
     else reg[j] = *reinterpret_cast<const u32x4*>(base + (long)row * ld + dc * 8);
@@ -84,7 +107,7 @@ template <int D, int NW, bool EDGE, int CH>
 __device__ __forceinline__ void lstore_tile(const u32x4 (&reg)[CH], bf16_t* __restrict__ s, int rows, int d) {
 #pragma unroll
   for (int j = 0; j < CH; ++j) {
-    const int c = threadIdx.x + 64 * NW * j;
+    const int c = group_thread<NW>() + 64 * NW * j;
     const int row = c / (D / 8), dc = c % (D / 8);
     *reinterpret_cast<u32x4*>(s + row * AT<D>::PITCH + ((dc ^ ((row >> 2) & 1)) << 3)) =
         EDGE ? trim_chunk(reg[j], dc * 8, d, row < rows) : reg[j];
@@ -198,19 +221,20 @@ __device__ __forceinline__ void store4_row(bf16_t* row, int e, int d, float a, f
 // ------------------------------------------------------------------------------------------------
 // forward
 // ------------------------------------------------------------------------------------------------
-template <int D, int NW, bool EDGE>
-__global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out,
+template <int D, int NW, int NG, bool EDGE>
+__global__ __launch_bounds__(64 * NW * NG) void attn_fwd_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out,
                                                            float* __restrict__ lse, int s, int a, int d, float scale) {
   constexpr int QB = 32 * NW;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  bf16_t* sK = reinterpret_cast<bf16_t*>(smem_raw);  // [2][TILE]
+  const int grp = NG > 1 ? group_of<NW>() : 0;
+  bf16_t* sK = reinterpret_cast<bf16_t*>(smem_raw) + grp * 4 * AT<D>::TILE;  // [2][TILE]
   bf16_t* sV = sK + 2 * AT<D>::TILE;
   const int qb = gridDim.z - 1 - blockIdx.z, head = blockIdx.x, bi = blockIdx.y;  // heaviest blocks first
   if (!EDGE) d = D;
   const int h = a * d;
   const long ld = 3L * h;
   const long tok0 = (long)bi * s;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = group_thread<NW>() >> 6, lane = threadIdx.x & 63;
   const int hi = lane >> 5, lq = lane & 31;
   const int qw0 = qb * QB + wave * 32;  // first query of this wave
   const float su = units<EDGE>(scale);
@@ -230,21 +254,27 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const bf16_t* __restr
   const bf16_t* kbase = qkv + tok0 * ld + h + head * d;
   const bf16_t* vbase = kbase + h;
   u32x4 rk[AT<D, NW>::CH], rv[AT<D, NW>::CH];
-  gload_tile<D, NW, EDGE>(rk, kbase, ld, s, d);
-  gload_tile<D, NW, EDGE>(rv, vbase, ld, s, d);
-  lstore_tile<D, NW, EDGE>(rk, sK, s, d);
-  lstore_tile<D, NW, EDGE>(rv, sV, s, d);
-  if (nkb > 1) {
-    gload_tile<D, NW, EDGE>(rk, kbase + (long)KB * ld, ld, s - KB, d);
-    gload_tile<D, NW, EDGE>(rv, vbase + (long)KB * ld, ld, s - KB, d);
+  auto gload = [&](int jb) {
+    gload_tile<D, NW, EDGE>(rk, kbase + (long)jb * KB * ld, ld, s - jb * KB, d);
+    gload_tile<D, NW, EDGE>(rv, vbase + (long)jb * KB * ld, ld, s - jb * KB, d);
+  };
+  auto lstore = [&](int jb, int stage) {
+    lstore_tile<D, NW, EDGE>(rk, sK + stage * AT<D>::TILE, s - jb * KB, d);
+    lstore_tile<D, NW, EDGE>(rv, sV + stage * AT<D>::TILE, s - jb * KB, d);
+  };
+  if (grp < nkb) {
+    gload(grp);
+    lstore(grp, 0);
   }
+  if (grp + NG < nkb) gload(grp + NG);
   __syncthreads();
 
-  for (int jb = 0; jb < nkb; ++jb) {
-    const bf16_t* kc = sK + (jb & 1) * AT<D>::TILE;
-    const bf16_t* vc = sV + (jb & 1) * AT<D>::TILE;
+  for (int it = 0; it * NG < nkb; ++it) {
+    const int jb = it * NG + grp;  // this group's tile (none in the last step if past the end)
+    const bf16_t* kc = sK + (it & 1) * AT<D>::TILE;
+    const bf16_t* vc = sV + (it & 1) * AT<D>::TILE;
     const int key0 = jb * KB;
-    if (key0 <= qw0 + 31) {  // this wave still has unmasked keys in the tile
+    if (jb < nkb && key0 <= qw0 + 31) {  // this wave still has unmasked keys in the tile
       const bool act1 = key0 + 32 <= qw0 + 31;
       f32x16 st[2];
 #pragma unroll
@@ -302,17 +332,29 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_kernel(const bf16_t* __restr
         }
       }
     }
-    if (jb + 1 < nkb) {
-      lstore_tile<D, NW, EDGE>(rk, sK + ((jb + 1) & 1) * AT<D>::TILE, s - (jb + 1) * KB, d);
-      lstore_tile<D, NW, EDGE>(rv, sV + ((jb + 1) & 1) * AT<D>::TILE, s - (jb + 1) * KB, d);
-    }
+    if (jb + NG < nkb) lstore(jb + NG, (it + 1) & 1);
     __syncthreads();
-    if (jb + 2 < nkb) {
-      gload_tile<D, NW, EDGE>(rk, kbase + (long)(jb + 2) * KB * ld, ld, s - (jb + 2) * KB, d);
-      gload_tile<D, NW, EDGE>(rv, vbase + (long)(jb + 2) * KB * ld, ld, s - (jb + 2) * KB, d);
-    }
+    if (jb + 2 * NG < nkb) gload(jb + 2 * NG);
   }
 
+  if constexpr (NG > 1) {
+    float* x = hand_over(smem_raw, wave, D / 2 + 2, lane);
+    if (grp) {
+      x[0] = m;
+      x[64] = l;
+      put(x + 128, o);
+    }
+    __syncthreads();
+    if (grp) return;
+    const float m1 = x[0], m_new = fmaxf(m, m1), ref = EDGE ? softmax_ref(m_new) : m_new;
+    const float a0 = exp_of<EDGE>(m - ref), a1 = exp_of<EDGE>(m1 - ref);
+    l = l * a0 + x[64] * a1;
+    m = m_new;
+#pragma unroll
+    for (int et = 0; et < D / 32; ++et)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) o[et][v] = o[et][v] * a0 + x[(2 + et * 16 + v) * 64] * a1;
+  }
   const float inv = 1.0f / l;
 #pragma unroll
   for (int et = 0; et < D / 32; ++et)
@@ -352,19 +394,20 @@ __global__ __launch_bounds__(256) void attn_bwd_prep_kernel(const bf16_t* __rest
 // ------------------------------------------------------------------------------------------------
 // backward, dQ: workgroup = 32 NW queries, loop over key tiles up to the diagonal
 // ------------------------------------------------------------------------------------------------
-template <int D, int NW, bool EDGE>
+template <int D, int NW, int NG, bool EDGE>
 __device__ __forceinline__ void attn_bwd_dq_body(unsigned char* smem_raw, int qb, int head, int bi,
                                                  const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                                  const bf16_t* __restrict__ dout, const float* __restrict__ lse,
                                                  const float* __restrict__ dvec, bf16_t* __restrict__ dqkv, int s, int a, int d, float scale) {
   constexpr int QB = 32 * NW;
-  bf16_t* sK = reinterpret_cast<bf16_t*>(smem_raw);
+  const int grp = NG > 1 ? group_of<NW>() : 0;
+  bf16_t* sK = reinterpret_cast<bf16_t*>(smem_raw) + grp * 4 * AT<D>::TILE;
   bf16_t* sV = sK + 2 * AT<D>::TILE;
   if (!EDGE) d = D;
   const int h = a * d;
   const long ld = 3L * h;
   const long tok0 = (long)bi * s;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = group_thread<NW>() >> 6, lane = threadIdx.x & 63;
   const int hi = lane >> 5, lq = lane & 31;
   const int qw0 = qb * QB + wave * 32;
   const float su = units<EDGE>(scale);
@@ -387,21 +430,27 @@ __device__ __forceinline__ void attn_bwd_dq_body(unsigned char* smem_raw, int qb
   const bf16_t* kbase = qkv + tok0 * ld + h + head * d;
   const bf16_t* vbase = kbase + h;
   u32x4 rk[AT<D, NW>::CH], rv[AT<D, NW>::CH];
-  gload_tile<D, NW, EDGE>(rk, kbase, ld, s, d);
-  gload_tile<D, NW, EDGE>(rv, vbase, ld, s, d);
-  lstore_tile<D, NW, EDGE>(rk, sK, s, d);
-  lstore_tile<D, NW, EDGE>(rv, sV, s, d);
-  if (nkb > 1) {
-    gload_tile<D, NW, EDGE>(rk, kbase + (long)KB * ld, ld, s - KB, d);
-    gload_tile<D, NW, EDGE>(rv, vbase + (long)KB * ld, ld, s - KB, d);
+  auto gload = [&](int jb) {
+    gload_tile<D, NW, EDGE>(rk, kbase + (long)jb * KB * ld, ld, s - jb * KB, d);
+    gload_tile<D, NW, EDGE>(rv, vbase + (long)jb * KB * ld, ld, s - jb * KB, d);
+  };
+  auto lstore = [&](int jb, int stage) {
+    lstore_tile<D, NW, EDGE>(rk, sK + stage * AT<D>::TILE, s - jb * KB, d);
+    lstore_tile<D, NW, EDGE>(rv, sV + stage * AT<D>::TILE, s - jb * KB, d);
+  };
+  if (grp < nkb) {
+    gload(grp);
+    lstore(grp, 0);
   }
+  if (grp + NG < nkb) gload(grp + NG);
   __syncthreads();
 
-  for (int jb = 0; jb < nkb; ++jb) {
-    const bf16_t* kc = sK + (jb & 1) * AT<D>::TILE;
-    const bf16_t* vc = sV + (jb & 1) * AT<D>::TILE;
+  for (int it = 0; it * NG < nkb; ++it) {
+    const int jb = it * NG + grp;  // this group's tile (none in the last step if past the end)
+    const bf16_t* kc = sK + (it & 1) * AT<D>::TILE;
+    const bf16_t* vc = sV + (it & 1) * AT<D>::TILE;
     const int key0 = jb * KB;
-    if (key0 <= qw0 + 31) {
+    if (jb < nkb && key0 <= qw0 + 31) {
       const bool act1 = key0 + 32 <= qw0 + 31;
       f32x16 st[2], dpt[2];
 #pragma unroll
@@ -442,15 +491,16 @@ __device__ __forceinline__ void attn_bwd_dq_body(unsigned char* smem_raw, int qb
         }
       }
     }
-    if (jb + 1 < nkb) {
-      lstore_tile<D, NW, EDGE>(rk, sK + ((jb + 1) & 1) * AT<D>::TILE, s - (jb + 1) * KB, d);
-      lstore_tile<D, NW, EDGE>(rv, sV + ((jb + 1) & 1) * AT<D>::TILE, s - (jb + 1) * KB, d);
-    }
+    if (jb + NG < nkb) lstore(jb + NG, (it + 1) & 1);
     __syncthreads();
-    if (jb + 2 < nkb) {
-      gload_tile<D, NW, EDGE>(rk, kbase + (long)(jb + 2) * KB * ld, ld, s - (jb + 2) * KB, d);
-      gload_tile<D, NW, EDGE>(rv, vbase + (long)(jb + 2) * KB * ld, ld, s - (jb + 2) * KB, d);
-    }
+    if (jb + 2 * NG < nkb) gload(jb + 2 * NG);
+  }
+  if constexpr (NG > 1) {
+    float* x = hand_over(smem_raw, wave, D / 2, lane);
+    if (grp) put(x, dq);
+    __syncthreads();
+    if (grp) return;
+    add(dq, x);
   }
   unsigned bad = 0;
   if constexpr (EDGE) bad = bad_rows(mine && lse_u == lse_u && Dq == Dq && not_finite(dq));  // else every term is NaN
@@ -471,21 +521,22 @@ __device__ __forceinline__ void attn_bwd_dq_body(unsigned char* smem_raw, int qb
 // ------------------------------------------------------------------------------------------------
 // backward, dK and dV: workgroup = 32 NW keys, loop over query tiles from the diagonal to the end
 // ------------------------------------------------------------------------------------------------
-template <int D, int NW, bool EDGE>
+template <int D, int NW, int NG, bool EDGE>
 __device__ __forceinline__ void attn_bwd_dkv_body(unsigned char* smem_raw, int kb, int head, int bi,
                                                   const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                                   const bf16_t* __restrict__ dout, const float* __restrict__ lse,
                                                   const float* __restrict__ dvec, bf16_t* __restrict__ dqkv, int s, int a, int d, float scale) {
   constexpr int QB = 32 * NW;
-  bf16_t* sQ = reinterpret_cast<bf16_t*>(smem_raw);  // [2][TILE]
-  bf16_t* sO = sQ + 2 * AT<D>::TILE;                 // dO tiles
-  float* sL = reinterpret_cast<float*>(sO + 2 * AT<D>::TILE);  // [2][64] lse in units of the softmax
+  const int grp = NG > 1 ? group_of<NW>() : 0;
+  bf16_t* sQ = reinterpret_cast<bf16_t*>(smem_raw) + grp * 4 * AT<D>::TILE;  // [2][TILE]
+  bf16_t* sO = sQ + 2 * AT<D>::TILE;                                         // dO tiles
+  float* sL = reinterpret_cast<float*>(smem_raw + NG * 4 * AT<D>::TILE * sizeof(bf16_t)) + grp * 4 * KB;  // [2][64] lse in units of the softmax
   float* sD = sL + 2 * KB;                                     // [2][64] D
   if (!EDGE) d = D;
   const int h = a * d;
   const long ld = 3L * h;
   const long tok0 = (long)bi * s;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = group_thread<NW>() >> 6, lane = threadIdx.x & 63;
   const int hi = lane >> 5, lk = lane & 31;
   const int kw0 = kb * QB + wave * 32;  // first key of this wave
   const float su = units<EDGE>(scale);
@@ -508,37 +559,37 @@ __device__ __forceinline__ void attn_bwd_dkv_body(unsigned char* smem_raw, int k
   const float* dbase = dvec + ((long)bi * a + head) * s;
   u32x4 rq[AT<D, NW>::CH], ro[AT<D, NW>::CH];
   float rs = 0.f;  // threads 0..63 stage lse, 64..127 stage D
-  auto gload_stats = [&](int ib) {
-    const int r = ib * KB + (threadIdx.x & (KB - 1));
-    if (EDGE && r >= s) rs = threadIdx.x < KB ? INFINITY : 0.f;  // exp(-inf): no weight
-    else if (threadIdx.x < KB) rs = units<EDGE>(lbase[r]);
-    else if (threadIdx.x < 2 * KB) rs = dbase[r];
+  const int tid = group_thread<NW>();
+  auto gload = [&](int ib) {
+    gload_tile<D, NW, EDGE>(rq, qbase + (long)ib * KB * ld, ld, s - ib * KB, d);
+    gload_tile<D, NW, EDGE>(ro, obase + (long)ib * KB * h, h, s - ib * KB, d);
+    const int r = ib * KB + (tid & (KB - 1));
+    if (EDGE && r >= s) rs = tid < KB ? INFINITY : 0.f;  // exp(-inf): no weight
+    else if (tid < KB) rs = units<EDGE>(lbase[r]);
+    else if (tid < 2 * KB) rs = dbase[r];
   };
-  auto lstore_stats = [&](int stage) {
-    if (threadIdx.x < KB) sL[stage * KB + threadIdx.x] = rs;
-    else if (threadIdx.x < 2 * KB) sD[stage * KB + threadIdx.x - KB] = rs;
+  auto lstore = [&](int ib, int stage) {
+    lstore_tile<D, NW, EDGE>(rq, sQ + stage * AT<D>::TILE, s - ib * KB, d);
+    lstore_tile<D, NW, EDGE>(ro, sO + stage * AT<D>::TILE, s - ib * KB, d);
+    if (tid < KB) sL[stage * KB + tid] = rs;
+    else if (tid < 2 * KB) sD[stage * KB + tid - KB] = rs;
   };
-  gload_tile<D, NW, EDGE>(rq, qbase + (long)ib0 * KB * ld, ld, s - ib0 * KB, d);
-  gload_tile<D, NW, EDGE>(ro, obase + (long)ib0 * KB * h, h, s - ib0 * KB, d);
-  gload_stats(ib0);
-  lstore_tile<D, NW, EDGE>(rq, sQ, s - ib0 * KB, d);
-  lstore_tile<D, NW, EDGE>(ro, sO, s - ib0 * KB, d);
-  lstore_stats(0);
-  if (ib0 + 1 < nib) {
-    gload_tile<D, NW, EDGE>(rq, qbase + (long)(ib0 + 1) * KB * ld, ld, s - (ib0 + 1) * KB, d);
-    gload_tile<D, NW, EDGE>(ro, obase + (long)(ib0 + 1) * KB * h, h, s - (ib0 + 1) * KB, d);
-    gload_stats(ib0 + 1);
+  if (ib0 + grp < nib) {
+    gload(ib0 + grp);
+    lstore(ib0 + grp, 0);
   }
+  if (ib0 + grp + NG < nib) gload(ib0 + grp + NG);
   __syncthreads();
 
-  for (int ib = ib0; ib < nib; ++ib) {
-    const int stage = (ib - ib0) & 1;
+  for (int it = 0; ib0 + it * NG < nib; ++it) {
+    const int ib = ib0 + it * NG + grp;  // this group's tile (none in the last step if past the end)
+    const int stage = it & 1;
     const bf16_t* qc = sQ + stage * AT<D>::TILE;
     const bf16_t* oc = sO + stage * AT<D>::TILE;
     const float* lc = sL + stage * KB;
     const float* dc = sD + stage * KB;
     const int q0 = ib * KB;
-    if (q0 + KB - 1 >= kw0) {  // some query of the tile can see this wave's keys
+    if (ib < nib && q0 + KB - 1 >= kw0) {  // some query of the tile can see this wave's keys
       const bool act0 = q0 + 31 >= kw0;
       f32x16 st[2], dpt[2];
 #pragma unroll
@@ -587,17 +638,20 @@ __device__ __forceinline__ void attn_bwd_dkv_body(unsigned char* smem_raw, int k
         }
       }
     }
-    if (ib + 1 < nib) {
-      lstore_tile<D, NW, EDGE>(rq, sQ + (stage ^ 1) * AT<D>::TILE, s - (ib + 1) * KB, d);
-      lstore_tile<D, NW, EDGE>(ro, sO + (stage ^ 1) * AT<D>::TILE, s - (ib + 1) * KB, d);
-      lstore_stats(stage ^ 1);
+    if (ib + NG < nib) lstore(ib + NG, stage ^ 1);
+    __syncthreads();
+    if (ib + 2 * NG < nib) gload(ib + 2 * NG);
+  }
+  if constexpr (NG > 1) {
+    float* x = hand_over(smem_raw, wave, D, lane);
+    if (grp) {
+      put(x, dk);
+      put(x + D / 2 * 64, dv);
     }
     __syncthreads();
-    if (ib + 2 < nib) {
-      gload_tile<D, NW, EDGE>(rq, qbase + (long)(ib + 2) * KB * ld, ld, s - (ib + 2) * KB, d);
-      gload_tile<D, NW, EDGE>(ro, obase + (long)(ib + 2) * KB * h, h, s - (ib + 2) * KB, d);
-      gload_stats(ib + 2);
-    }
+    if (grp) return;
+    add(dk, x);
+    add(dv, x + D / 2 * 64);
   }
   unsigned bad = 0;
   if constexpr (EDGE) bad = bad_rows(mine && (not_finite(dk) || not_finite(dv)));
@@ -620,16 +674,16 @@ __device__ __forceinline__ void attn_bwd_dkv_body(unsigned char* smem_raw, int k
 
 // Both halves of the backward in one launch: they are independent, and each alone leaves most of the chip idle.
 // Even workgroups are key blocks, odd ones query blocks, those with the most tiles first.
-template <int D, int NW, bool EDGE>
-__global__ __launch_bounds__(64 * NW) void attn_bwd_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
+template <int D, int NW, int NG, bool EDGE>
+__global__ __launch_bounds__(64 * NW * NG) void attn_bwd_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                                            const bf16_t* __restrict__ dout, const float* __restrict__ lse,
                                                            const float* __restrict__ dvec, bf16_t* __restrict__ dqkv, int s, int a, int d, float scale) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int blk = blockIdx.z >> 1, nblk = gridDim.z >> 1, head = blockIdx.x, bi = blockIdx.y;
   if (blockIdx.z & 1)
-    attn_bwd_dq_body<D, NW, EDGE>(smem_raw, nblk - 1 - blk, head, bi, qkv, o, dout, lse, dvec, dqkv, s, a, d, scale);
+    attn_bwd_dq_body<D, NW, NG, EDGE>(smem_raw, nblk - 1 - blk, head, bi, qkv, o, dout, lse, dvec, dqkv, s, a, d, scale);
   else
-    attn_bwd_dkv_body<D, NW, EDGE>(smem_raw, blk, head, bi, qkv, o, dout, lse, dvec, dqkv, s, a, d, scale);
+    attn_bwd_dkv_body<D, NW, NG, EDGE>(smem_raw, blk, head, bi, qkv, o, dout, lse, dvec, dqkv, s, a, d, scale);
 }
 
 template <typename K> hipError_t set_smem(K kern, size_t smem, bool* done) {
@@ -640,28 +694,30 @@ template <typename K> hipError_t set_smem(K kern, size_t smem, bool* done) {
   return e;
 }
 
-template <int D, int NW, bool EDGE> hipError_t run_fwd(const AttnArgs& a, hipStream_t s) {
+template <int D, int NW, int NG, bool EDGE> hipError_t run_fwd(const AttnArgs& a, hipStream_t s) {
   static bool done = false;
-  constexpr size_t smem = (size_t)4 * AT<D>::TILE * sizeof(bf16_t);
-  hipError_t e = set_smem(attn_fwd_kernel<D, NW, EDGE>, smem, &done);
+  constexpr size_t smem = (size_t)NG * 4 * AT<D>::TILE * sizeof(bf16_t);
+  static_assert(smem <= 160 * 1024 && (NG == 1 || smem >= (size_t)NW * (D / 2 + 2) * 64 * sizeof(float)), "stages; what a group hands over");
+  hipError_t e = set_smem(attn_fwd_kernel<D, NW, NG, EDGE>, smem, &done);
   if (e != hipSuccess) return e;
   dim3 grid(a.a, a.b, (a.s + 32 * NW - 1) / (32 * NW));  // the last index is the slowest: heaviest blocks of all heads first
-  attn_fwd_kernel<D, NW, EDGE><<<grid, 64 * NW, smem, s>>>((const bf16_t*)a.qkv, (bf16_t*)a.out, a.lse, a.s, a.a, a.d,
+  attn_fwd_kernel<D, NW, NG, EDGE><<<grid, 64 * NW * NG, smem, s>>>((const bf16_t*)a.qkv, (bf16_t*)a.out, a.lse, a.s, a.a, a.d,
                                                           1.0f / sqrtf((float)a.d));
   return hipGetLastError();
 }
 
-template <int D, int NW, bool EDGE> hipError_t run_bwd(const AttnArgs& a, hipStream_t s) {
+template <int D, int NW, int NG, bool EDGE> hipError_t run_bwd(const AttnArgs& a, hipStream_t s) {
   static bool done = false;
-  constexpr size_t smem = (size_t)4 * AT<D>::TILE * sizeof(bf16_t) + 4 * KB * sizeof(float);
-  hipError_t e = set_smem(attn_bwd_kernel<D, NW, EDGE>, smem, &done);
+  constexpr size_t smem = (size_t)NG * (4 * AT<D>::TILE * sizeof(bf16_t) + 4 * KB * sizeof(float));
+  static_assert(smem <= 160 * 1024 && (NG == 1 || smem >= (size_t)NW * D * 64 * sizeof(float)), "stages; what a group hands over");
+  hipError_t e = set_smem(attn_bwd_kernel<D, NW, NG, EDGE>, smem, &done);
   if (e != hipSuccess) return e;
   dim3 grid1((a.s + 15) / 16, a.a, a.b);
   attn_bwd_prep_kernel<<<grid1, 256, 0, s>>>((const bf16_t*)a.o, (const bf16_t*)a.dout, a.dvec, a.s, a.a, a.d);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   dim3 grid(a.a, a.b, 2 * ((a.s + 32 * NW - 1) / (32 * NW)));
-  attn_bwd_kernel<D, NW, EDGE><<<grid, 64 * NW, smem, s>>>((const bf16_t*)a.qkv, (const bf16_t*)a.o, (const bf16_t*)a.dout, a.lse,
+  attn_bwd_kernel<D, NW, NG, EDGE><<<grid, 64 * NW * NG, smem, s>>>((const bf16_t*)a.qkv, (const bf16_t*)a.o, (const bf16_t*)a.dout, a.lse,
                                                           a.dvec, (bf16_t*)a.dqkv, a.s, a.a, a.d, 1.0f / sqrtf((float)a.d));
   return hipGetLastError();
 }
@@ -670,35 +726,53 @@ template <int D, int NW, bool EDGE> hipError_t run_bwd(const AttnArgs& a, hipStr
 inline bool whole_tiles(const AttnArgs& a) { return a.s % 128 == 0 && (a.d == 64 || a.d == 96 || a.d == 128); }
 // sizes the kernels above take (b and the row blocks are grid dimensions of 16 bits)
 inline bool mfma_shape(const AttnArgs& a) { return a.d >= 8 && a.d <= 128 && a.b < 65536 && a.a < 65536 && a.s <= (1 << 20); }
-// Row blocks per workgroup: 128 (four waves) or 64 (two).  Two waves share the staging of a tile between fewer rows but
-// leave less idle at the diagonal and pack the CUs more evenly.  Measured, us with 64 / 128 rows, and blocks = 128-row
-// blocks of the launch:
-//   forward, whole tiles  16 heads x 128 tokens (16 blocks) 6.6 / 7.2, 12 x 512 (48) 18.5 / 18.9, 64 x 512 (256) 19.9 / 20.2,
-//                         128 x 512 (512) 22.2 / 21.8, 128 x 1024 (1024) 54 / 50, 64 x 2048 (1024) 99 / 82
-//   forward, edges        head 75: 16 x 130 (32) 19.9 / 18.7, 16 x 777 (112) 72 / 65, 96 x 777 (672) 116 / 89; head 128 at
-//                         128 x 257 (384) 32 / 39, 96 x 520 (480) 57 / 67, 96 x 777 (672) 112 / 120, but 64 x 520 (320) 53 / 48
-//                         and 64 x 1100 (576) 132 / 129
-//   backward, whole tiles 12 x 512 (48) 25.7 / 26.7, 256 x 256 (512) 44 / 52, 64 x 1024 (512) 99 / 105, 128 x 2048 (2048) 704 /
-//                         708; 128 rows are ahead, by at most 4 %, between 96 and 256 blocks of 1024 and more tokens
-//   backward, edges       head 75: 16 x 777 (112) 103 / 96, 128 x 257 (384) 74 / 93, 96 x 777 (672) 253 / 273, 64 x 1500 (768)
-//                         500 / 483, but 16 x 130 (32) 31 / 34; head 40: 64 x 384 (192) 39 / 38, 96 x 256 (192) 29 / 31
+// Rows per workgroup: 128 (four waves) or 64 (two), and one or two groups of that many waves.  Two groups halve the chain
+// of tiles and put a second wave on each SIMD where the launch leaves the chip room for them; two waves share the staging
+// of a tile between fewer rows but leave less idle at the diagonal and pack the CUs more evenly.  Measured, us with 64 rows /
+// 128 rows / 64 rows, two groups / 128 rows, two groups (heads x tokens x samples; blocks = 128-row blocks of the launch):
+//   forward, whole tiles  16 x 256 (32) 10.6 / 11.2 / 7.5 / 8.2, 12 x 512 (48) 18.6 / 19.2 / 11.7 / 11.9, 12 x 1024 (96) 34.4 / 34.9 /
+//                         20.5 / 19.8, 16 x 256 x 8 (256) 11.7 / 11.8 / 8.6 / 8.8, 16 x 1024 x 3 (384) 37.1 / 35.6 / 25.5 / 21.3,
+//                         32 x 512 x 4 (512) 22.6 / 21.2 / 21.4 / 18.0, but 64 x 128 x 8 (512) 10.3 / 10.4 / 12.3 / 12.4, 64 x 1024 x 2
+//                         (1024) 59 / 50 / 61 / 52
+//   forward, edges        head 75: 16 x 130 (32) 20.2 / 18.9 / 16.5 / 16.5, 16 x 777 (112) 73 / 65 / 45 / 44, 16 x 777 x 4 (448) 77 / 68 /
+//                         94 / 61, 96 x 777 (672) 119 / 86 / 139 / 91; head 40: 16 x 500 x 4 (256) 35 / 33 / 21 / 22; head 128: 64 x
+//                         257 x 2 (384) 33 / 39 / 40 / 30; head 96: 64 x 130 x 3 (384) 18.6 / 18.6 / 25.8 / 22.7
+//   backward, whole tiles 16 x 256 (32) 15.7 / 17.1 / 12.0 / 15.5, 12 x 512 (48) 26.0 / 27.3 / 17.8 / 22.5, 8 x 2048 (128) 90 / 87 / 56 /
+//                         63, 12 x 512 x 3 (144) 29.1 / 28.4 / 27.1 / 24.4, 16 x 256 x 8 (256) 23.5 / 25.8 / 31.1 / 24.7, 64 x 512 (256)
+//                         34.2 / 36.0 / 42.3 / 32.6, 64 x 1024 x 2 (1024) 198 / 208 / 242 / 159
+//   backward, edges       head 75: 16 x 130 (32) 30 / 34 / 25 / -, 16 x 777 (112) 96 / 93 / 60 / -, 16 x 777 x 2 (224) 99 / 96 / 106 / -;
+//                         head 128: 18 x 1100 (162) 135 / 125 / 99 / -, 16 x 257 x 4 (192) 44.9 / 44.3 / 47.5 / -; one group: 128 x
+//                         257 (384) 74 / 93, 96 x 777 (672) 253 / 273, 64 x 1500 (768) 500 / 483, head 40 96 x 256 (192) 29 / 31
+//                         (- : 128 rows and two groups do not fit the registers)
+// With edges the second group also doubles the staging (zeros past the columns are put in on the way) or the LDS of wide heads,
+// which costs where other launches want the chip: three stages at once, us per iteration with one and two groups: 16 heads
+// of 75, 777 tokens 2340 / 2308 with a forward in two, / 2390 with the backward as well; 16 of 40, 178 tokens 1161 / 1184; 4 of
+// 48, 945 tokens 1168 / 1004.  So two groups from 256 tokens on, and in the backward of heads up to 64 columns.
 inline long blocks128(const AttnArgs& a) { return (long)((a.s + 127) / 128) * a.a * a.b; }
-template <int D, bool EDGE> bool narrow_fwd(const AttnArgs& a) {
-  if (!EDGE) return blocks128(a) < 512;
-  return D == 128 && a.s < 1024 && blocks128(a) >= 352;
-}
-template <int D> bool narrow_bwd_edge(const AttnArgs& a) {
-  return (a.s < 1024 && blocks128(a) >= 192) || (D == 96 && a.s <= 256);
-}
 template <int D, bool EDGE> struct Fwd {
   static hipError_t run(const AttnArgs& a, hipStream_t s) {
-    return narrow_fwd<D, EDGE>(a) ? run_fwd<D, 2, EDGE>(a, s) : run_fwd<D, 4, EDGE>(a, s);
+    const long n = blocks128(a);
+    if constexpr (!EDGE) {
+      if (n < 96) return run_fwd<D, 2, 2, EDGE>(a, s);
+      if (n < 512 || (n < 1024 && a.s >= 512)) return run_fwd<D, 4, 2, EDGE>(a, s);
+    } else {
+      if (n < 512 && a.s >= 256) return run_fwd<D, D <= 64 ? 2 : 4, 2, EDGE>(a, s);
+      if constexpr (D == 128)
+        if (a.s < 1024 && n >= 352) return run_fwd<D, 2, 1, EDGE>(a, s);
+    }
+    return run_fwd<D, 4, 1, EDGE>(a, s);
   }
 };
 template <int D, bool EDGE> struct Bwd {
   static hipError_t run(const AttnArgs& a, hipStream_t s) {
-    if constexpr (!EDGE) return run_bwd<D, 2, EDGE>(a, s);
-    else return narrow_bwd_edge<D>(a) ? run_bwd<D, 2, EDGE>(a, s) : run_bwd<D, 4, EDGE>(a, s);
+    const long n = blocks128(a);
+    if (n <= 128 && (!EDGE || (D <= 64 && a.s >= 256))) return run_bwd<D, 2, 2, EDGE>(a, s);
+    if constexpr (!EDGE) {
+      return a.s >= 512 ? run_bwd<D, 4, 2, EDGE>(a, s) : run_bwd<D, 2, 1, EDGE>(a, s);
+    } else {
+      const bool narrow = (a.s < 1024 && n >= 192) || (D == 96 && a.s <= 256);
+      return narrow ? run_bwd<D, 2, 1, EDGE>(a, s) : run_bwd<D, 4, 1, EDGE>(a, s);
+    }
   }
 };
 

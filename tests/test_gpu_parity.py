@@ -498,6 +498,21 @@ def test_gelu_over_its_range(dtype, cfg):
 
 
 @pytest.mark.parametrize("cfg", [
+    # hidden, heads, ffn, seq, b       row blocks and groups of waves of the attention (128-row blocks of a launch)
+    (256, 4, 512, 128, 3),       # head size 64, 12 whole blocks: 64 rows, two groups; the first blocks have one tile
+    (256, 4, 512, 512, 9),       # 144 of them: 128 rows, two groups, both ways
+    (256, 4, 512, 256, 20),      # 160 short ones: the backward with one group of 64 rows
+    (120, 3, 248, 300, 16),      # head size 40, 144 blocks with edges: the backward with one group of 128 rows
+    (80, 2, 160, 257, 2),        # five tiles, both ways with two groups of 64 rows
+    (200, 2, 400, 260, 1),       # head size 100: the forward with two groups of 128
+    (240, 2, 480, 321, 1),       # head size 120, six tiles
+], ids=lambda c: "h%d_a%d_f%d_s%d_b%d" % c)
+def test_attention_in_groups(cfg):
+    hidden, heads, ffn, seq, b = cfg
+    run_and_compare(W("groups", "bf16", 1, hidden, heads, ffn, seq, b, 4, 1, 1, "H1", seed=551 + hidden + seq))
+
+
+@pytest.mark.parametrize("cfg", [
     # hidden, heads, ffn, seq, b       the attention's row blocks per workgroup that only many heads reach
     (256, 4, 512, 128, 128),     # head size 64, 512 whole blocks: 128 rows forward, 64 backward
     (512, 4, 512, 130, 44),      # head size 128, 352 blocks with edges: 64 rows forward and backward
