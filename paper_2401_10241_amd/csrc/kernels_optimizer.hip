@@ -3,6 +3,7 @@
 // Every decision (step or not, gradient scale, rollback, redo) is taken by a one-thread kernel
 // that writes predicates into OptDevState; the heavy kernels read them and return at once when
 // switched off, so the host never waits between the steps of the protocol.
+#include <atomic>
 #include <mutex>
 
 #include "../../include/zb_stage.h"
@@ -16,23 +17,50 @@ __device__ __forceinline__ int nonfinite_bits(float v) {
   return (__float_as_uint(v) & 0x7F800000u) == 0x7F800000u ? 1 : 0;
 }
 
-// Level 1: kSumsqPerThread 16-byte elements per thread, a workgroup's threads side by side in each (workgroups
-// in index order sweep the gradient as one moving front), one partial sum and one non-finite flag per
-// workgroup.
+// Sum and flag of up to kSumsqFan partials, in a fixed order, by the first 256 threads of a workgroup; thread 0 writes
+// them.  take(i, &sq, &nf) reads partial i.
+template <class F> __device__ __forceinline__ void sumsq_tree(size_t count, F&& take, double* out_sq, int* out_nf) {
+  __shared__ double red[256];
+  __shared__ int redf[256];
+  constexpr int per = kSumsqFan / 256;
+  const int t = threadIdx.x;
+  if (t < 256) {
+    double acc = 0.0;
+    int bad = 0;
+#pragma unroll
+    for (int k = 0; k < per; ++k) {
+      const size_t i = (size_t)t * per + k;
+      if (i < count) {
+        double sq;
+        int nf;
+        take(i, &sq, &nf);
+        acc += sq;
+        bad |= nf;
+      }
+    }
+    red[t] = acc;
+    redf[t] = bad;
+  }
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if (t < o) { red[t] += red[t + o]; redf[t] |= redf[t + o]; }
+    __syncthreads();
+  }
+  if (t == 0) { *out_sq = red[0]; *out_nf = redf[0]; }
+}
+
+// sum of squares and non-finite flag of a workgroup's kSumsqPerThread * T 16-byte elements; every thread gets them
 constexpr int kSumsqPerThread = 4;
-constexpr size_t kSumsqWg4 = 256 * kSumsqPerThread;  // 16-byte elements per workgroup
-__global__ __launch_bounds__(256) void grad_sumsq_kernel(const float4* __restrict__ g, size_t n4,
-                                                         double* __restrict__ partial_sq,
-                                                         int* __restrict__ partial_nf) {
-  __shared__ double red[4];
-  __shared__ int redf[4];
+template <int T> __device__ __forceinline__ void sumsq_block(const float4* __restrict__ g, size_t n4, double* sum, int* flag) {
+  __shared__ double red[T / 64];
+  __shared__ int redf[T / 64];
   double acc = 0.0;
   int bad = 0;
-  const size_t i0 = (size_t)blockIdx.x * kSumsqWg4 + threadIdx.x;
+  const size_t i0 = (size_t)blockIdx.x * T * kSumsqPerThread + threadIdx.x;
   float4 v[kSumsqPerThread];
 #pragma unroll
   for (int k = 0; k < kSumsqPerThread; ++k) {
-    const size_t i = i0 + (size_t)k * 256;
+    const size_t i = i0 + (size_t)k * T;
     v[k] = i < n4 ? g[i] : make_float4(0.f, 0.f, 0.f, 0.f);
   }
 #pragma unroll
@@ -45,35 +73,59 @@ __global__ __launch_bounds__(256) void grad_sumsq_kernel(const float4* __restric
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   if (lane == 0) { red[wave] = acc; redf[wave] = bad; }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    partial_sq[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
-    partial_nf[blockIdx.x] = redf[0] | redf[1] | redf[2] | redf[3];
-  }
+  *sum = red[0];
+  *flag = redf[0];
+#pragma unroll
+  for (int w = 1; w < T / 64; ++w) { *sum += red[w]; *flag |= redf[w]; }
 }
 
-// Level 2: workgroup b adds partials [b * kSumsqFan, (b + 1) * kSumsqFan) in a fixed order.
+// Level 1: a workgroup's threads side by side in each of their elements (workgroups in index order sweep the gradient as
+// one moving front), one partial sum and one non-finite flag per workgroup.
+constexpr size_t kSumsqWg4 = 256 * kSumsqPerThread;  // 16-byte elements per workgroup
+__global__ __launch_bounds__(256) void grad_sumsq_kernel(const float4* __restrict__ g, size_t n4,
+                                                         double* __restrict__ partial_sq,
+                                                         int* __restrict__ partial_nf) {
+  double sum;
+  int flag;
+  sumsq_block<256>(g, n4, &sum, &flag);
+  if (threadIdx.x == 0) { partial_sq[blockIdx.x] = sum; partial_nf[blockIdx.x] = flag; }
+}
+
+// Level 2: workgroup b adds partials [b * kSumsqFan, (b + 1) * kSumsqFan).
 __global__ __launch_bounds__(256) void grad_sumsq_mid_kernel(const double* __restrict__ in_sq,
                                                              const int* __restrict__ in_nf, size_t count,
                                                              double* __restrict__ out_sq,
                                                              int* __restrict__ out_nf) {
-  __shared__ double red[256];
-  __shared__ int redf[256];
-  constexpr int per = kSumsqFan / 256;
-  double acc = 0.0;
-  int bad = 0;
-#pragma unroll
-  for (int k = 0; k < per; ++k) {
-    const size_t i = (size_t)blockIdx.x * kSumsqFan + (size_t)threadIdx.x * per + k;
-    if (i < count) { acc += in_sq[i]; bad |= in_nf[i]; }
+  const size_t b0 = (size_t)blockIdx.x * kSumsqFan;
+  sumsq_tree(count - b0, [&](size_t i, double* sq, int* nf) { *sq = in_sq[b0 + i]; *nf = in_nf[b0 + i]; },
+             out_sq + blockIdx.x, out_nf + blockIdx.x);
+}
+
+// The whole sum of up to kSumsqOnceWgs workgroups in one launch: the one that is through last (`done` counts them and goes
+// back to 0) adds the partials, which are written and read past the caches of the XCDs.  A second launch that waits for
+// the first costs 4 us; the count costs about 30 ns a workgroup, so these are of 1024 threads.  us per call, two launches /
+// one with 256 threads / one with 1024: 2^20 gradients 9.7 / 8.6 / 5.3, 2^22 - / 25.5 / 9.3, 2^16 - / 4.2 / 4.4.
+constexpr size_t kSumsqOnceWgs = 256, kSumsqOnceWg4 = 1024 * kSumsqPerThread;
+__global__ __launch_bounds__(1024) void grad_sumsq_once_kernel(const float4* __restrict__ g, size_t n4,
+                                                               double* __restrict__ partial_sq,
+                                                               int* __restrict__ partial_nf, unsigned* __restrict__ done,
+                                                               double* __restrict__ out_sq, int* __restrict__ out_nf) {
+  __shared__ bool last;
+  double sum;
+  int flag;
+  sumsq_block<1024>(g, n4, &sum, &flag);
+  if (threadIdx.x == 0) {
+    __hip_atomic_store(partial_sq + blockIdx.x, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(partial_nf + blockIdx.x, flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
   }
-  red[threadIdx.x] = acc;
-  redf[threadIdx.x] = bad;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) { red[threadIdx.x] += red[threadIdx.x + o]; redf[threadIdx.x] |= redf[threadIdx.x + o]; }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) { out_sq[blockIdx.x] = red[0]; out_nf[blockIdx.x] = redf[0]; }
+  if (!last) return;
+  sumsq_tree(gridDim.x, [&](size_t i, double* sq, int* nf) {
+    *sq = __hip_atomic_load(partial_sq + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *nf = __hip_atomic_load(partial_nf + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }, out_sq, out_nf);
+  if (threadIdx.x == 0) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // one workgroup; partial sums are added in a fixed order
@@ -275,28 +327,29 @@ size_t grad_sumsq_partials(size_t n) {
   return p1 + p2;
 }
 
-// the three levels; the result goes to *out_sq / *out_nf (device)
-static hipError_t sumsq_levels(const float* g, size_t n, double* partial_sq, int* partial_nf, double* out_sq,
+// one launch or the three levels; the result goes to *out_sq / *out_nf (device).  *done is 0 and is 0 again afterwards.
+static hipError_t sumsq_levels(const float* g, size_t n, double* partial_sq, int* partial_nf, unsigned* done, double* out_sq,
                                int* out_nf, hipStream_t s) {
   if (n % 4 != 0 || n == 0) return hipErrorInvalidValue;
   const size_t n4 = n / 4;
   const size_t p1 = (n4 + kSumsqWg4 - 1) / kSumsqWg4, p2 = (p1 + kSumsqFan - 1) / kSumsqFan;
   if (p1 > ((size_t)1 << 31) - 1) return hipErrorInvalidValue;
-  // A level whose single workgroup already has the whole sum writes the result itself (the levels after it would
-  // only add zeros: the same bits).  2^20 gradients, all launches: 12.7 us with three levels, 9 with two.
-  grad_sumsq_kernel<<<(unsigned)p1, 256, 0, s>>>((const float4*)g, n4, p1 == 1 ? out_sq : partial_sq,
-                                                 p1 == 1 ? out_nf : partial_nf);
+  if (n4 <= kSumsqOnceWgs * kSumsqOnceWg4) {  // (at most kSumsqOnceWgs <= p1 partials, or one)
+    const unsigned wgs = (unsigned)((n4 + kSumsqOnceWg4 - 1) / kSumsqOnceWg4);
+    grad_sumsq_once_kernel<<<wgs, 1024, 0, s>>>((const float4*)g, n4, partial_sq, partial_nf, done, out_sq, out_nf);
+    return hipGetLastError();
+  }
+  grad_sumsq_kernel<<<(unsigned)p1, 256, 0, s>>>((const float4*)g, n4, partial_sq, partial_nf);
   hipError_t e = hipGetLastError();
-  if (e != hipSuccess || p1 == 1) return e;
-  grad_sumsq_mid_kernel<<<(unsigned)p2, 256, 0, s>>>(partial_sq, partial_nf, p1, p2 == 1 ? out_sq : partial_sq + p1,
-                                                     p2 == 1 ? out_nf : partial_nf + p1);
-  if ((e = hipGetLastError()) != hipSuccess || p2 == 1) return e;
+  if (e != hipSuccess) return e;
+  grad_sumsq_mid_kernel<<<(unsigned)p2, 256, 0, s>>>(partial_sq, partial_nf, p1, partial_sq + p1, partial_nf + p1);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
   grad_sumsq_final_kernel<<<1, 256, 0, s>>>(partial_sq + p1, partial_nf + p1, (int)p2, out_sq, out_nf);
   return hipGetLastError();
 }
 hipError_t launch_grad_sumsq(const float* g, size_t n, double* partial_sq, int* partial_nf, OptDevState* st,
                              hipStream_t s) {
-  return sumsq_levels(g, n, partial_sq, partial_nf, &st->local_sq, &st->local_nonfinite, s);
+  return sumsq_levels(g, n, partial_sq, partial_nf, &st->sumsq_done, &st->local_sq, &st->local_nonfinite, s);
 }
 hipError_t launch_decide_optimistic(OptDevState* st, OptHyper hp, double prev_sq, int prev_nf, int force,
                                     hipStream_t s) {
@@ -369,7 +422,11 @@ constexpr size_t kStaticMaxFloats = (size_t)1 << 30;  // == ZB_GRAD_NORM_STATIC_
 constexpr size_t kStaticP1 = (kStaticMaxFloats / 4 + zb::kSumsqWg4 - 1) / zb::kSumsqWg4;
 constexpr size_t kStaticPartials = kStaticP1 + (kStaticP1 + zb::kSumsqFan - 1) / zb::kSumsqFan;
 constexpr size_t kStaticSqBytes = (kStaticPartials * sizeof(double) + 255) / 256 * 256;
-constexpr size_t kStaticBytes = kStaticSqBytes + kStaticPartials * sizeof(int);  // about 3.2 MB
+// Counters of calls that finish in one launch, taken in turn: each goes back to zero with its call, and calls that
+// overlap (and so spoil each other's partials) do not share one and leave nothing wrong behind.
+constexpr unsigned kDoneSlots = 256, kDoneStride = 64;
+constexpr size_t kStaticNfBytes = (kStaticPartials * sizeof(int) + 255) / 256 * 256;
+constexpr size_t kStaticBytes = kStaticSqBytes + kStaticNfBytes + kDoneSlots * kDoneStride;  // about 3.2 MB
 static_assert(kStaticMaxFloats == ZB_GRAD_NORM_STATIC_MAX_FLOATS, "header and kernel file disagree");
 
 static __device__ __align__(256) unsigned char scratch[kStaticBytes];
@@ -408,8 +465,13 @@ extern "C" zb_status zb_grad_norm_static(const float* grads, size_t n, double* s
   if (scratch_of_current_device(&base) != hipSuccess) return ZB_EDEVICE;
   double* partial_sq = reinterpret_cast<double*>(base);
   int* partial_nf = reinterpret_cast<int*>(reinterpret_cast<unsigned char*>(base) + kStaticSqBytes);
-  // every partial the later levels read is written by the level before it in the same call: nothing has to
-  // start at zero, whatever the previous call left behind
-  const hipError_t e = zb::sumsq_levels(grads, n, partial_sq, partial_nf, sq_out, nonfinite_out, (hipStream_t)hip_stream);
+  // every partial the later levels read is written by the level before it in the same call; only the counters
+  // start at zero (as the array does) and each is zero again when its call is through
+  static std::atomic<unsigned> next{0};
+  const unsigned slot = next.fetch_add(1, std::memory_order_relaxed) % kDoneSlots;
+  unsigned* done = reinterpret_cast<unsigned*>(reinterpret_cast<unsigned char*>(base) + kStaticSqBytes + kStaticNfBytes +
+                                               slot * kDoneStride);
+  const hipError_t e =
+      zb::sumsq_levels(grads, n, partial_sq, partial_nf, done, sq_out, nonfinite_out, (hipStream_t)hip_stream);
   return e == hipSuccess ? ZB_OK : ZB_EDEVICE;
 }

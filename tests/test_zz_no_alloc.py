@@ -75,3 +75,22 @@ def test_static_grad_norm_rejects_bad_sizes():
                                    nf.data_ptr(), None) == zb.EINVAL
     assert lib.zb_grad_norm_static(None, 64, sq.data_ptr(), nf.data_ptr(), None) == zb.EINVAL
     assert lib.zb_grad_norm_static(g.data_ptr() + 4, 60, sq.data_ptr(), nf.data_ptr(), None) == zb.EINVAL
+
+
+@pytest.mark.parametrize("n", [4, 1028, 16384, 16388, 1 << 20, (1 << 22) - 4, 1 << 22, (1 << 22) + 4])
+def test_static_grad_norm_at_the_edges_of_its_workgroups(n):
+    # one workgroup, two, the most that share a launch, and three launches; three times each, so that every call finds
+    # what the one before left behind, with a value that is not finite in the last element of the second
+    import torch
+    stream = torch.cuda.Stream(device="cuda:0")
+    rng = np.random.default_rng(n)
+    flat = rng.standard_normal(n).astype(np.float32)
+    want = float(np.sum(flat.astype(np.float64) ** 2))
+    poisoned = flat.copy()
+    poisoned[-1] = np.inf
+    first, nf = _static_norm(flat, stream)
+    assert nf == 0 and abs(first - want) <= 1e-12 * want   # fp64 sums of n <= 2^22 squares: n * 2^-53 at most
+    sq, nf = _static_norm(poisoned, stream)
+    assert nf == 1 and sq == np.inf
+    again, nf = _static_norm(flat, stream)
+    assert nf == 0 and again == first
