@@ -444,9 +444,56 @@ __global__ __launch_bounds__(256) void layernorm_bwd_reduce_kernel(const float* 
   }
 }
 
-// dst[c][r] = src[r][c] for a [rows][cols] bf16 matrix; 64 x 64 tiles through LDS
-__global__ __launch_bounds__(256) void transpose_bf16_kernel(const unsigned short* __restrict__ src,
-                                                             unsigned short* __restrict__ dst, int rows, int cols) {
+// dst[c][r] = src[r][c] for the bf16 matrices of a table, 64 x 64 tiles through LDS, 16-byte global accesses on both sides
+// (rows and cols multiples of 8, 16-byte aligned pointers; the last tiles may be cut).  LDS row pitch 66 elements: the
+// gather of 8 consecutive rows of one column by 8 x 8 lanes (stride 8 rows = 8 banks) touches every bank once.  One launch
+// for the matrices of several layers: an iteration of two layers of hidden 1200, ffn 4808 takes 2267 us against 2307 with
+// one launch each, and 2-byte accesses (21 us for 1200 x 4808) where a size is no multiple of 64.
+struct TransposeTable {
+  int n;
+  int tile0[kTransposeMax];  // first tile of each matrix in the launch
+  int rows[kTransposeMax], cols[kTransposeMax];
+  const unsigned short* src[kTransposeMax];
+  unsigned short* dst[kTransposeMax];
+};
+__global__ __launch_bounds__(256) void transpose_bf16_kernel(TransposeTable tb) {
+  constexpr int P = 66;
+  __shared__ __align__(4) unsigned short tile[64 * P];
+  int q = 0;
+#pragma unroll
+  for (int i = 1; i < kTransposeMax; ++i) q += (i < tb.n && (int)blockIdx.x >= tb.tile0[i]) ? 1 : 0;
+  const int rows = tb.rows[q], cols = tb.cols[q], tiles_c = (cols + 63) / 64, t = blockIdx.x - tb.tile0[q];
+  const unsigned short* __restrict__ src = tb.src[q];
+  unsigned short* __restrict__ dst = tb.dst[q];
+  const int r0 = t / tiles_c * 64, c0 = t % tiles_c * 64;
+  const int hi = threadIdx.x >> 3, lo = threadIdx.x & 7;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int r = hi + 32 * j;
+    if (r0 + r < rows && c0 + lo * 8 < cols) {
+      const uint4 v = *reinterpret_cast<const uint4*>(src + (size_t)(r0 + r) * cols + c0 + lo * 8);
+      unsigned* w = reinterpret_cast<unsigned*>(tile + r * P + lo * 8);
+      w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int c = hi + 32 * j;
+    if (c0 + c < cols && r0 + lo * 8 < rows) {
+      unsigned w[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const unsigned a = tile[(lo * 8 + 2 * k) * P + c], b = tile[(lo * 8 + 2 * k + 1) * P + c];
+        w[k] = a | (b << 16);
+      }
+      *reinterpret_cast<uint4*>(dst + (size_t)(c0 + c) * rows + r0 + lo * 8) = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+  }
+}
+// any size, 2 bytes at a time (a head whose vocabulary is no multiple of 8)
+__global__ __launch_bounds__(256) void transpose_bf16_any_kernel(const unsigned short* __restrict__ src,
+                                                                 unsigned short* __restrict__ dst, int rows, int cols) {
   __shared__ unsigned short tile[64][66];
   const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
@@ -458,37 +505,6 @@ __global__ __launch_bounds__(256) void transpose_bf16_kernel(const unsigned shor
   for (int i = ty; i < 64; i += 4) {
     const int c = c0 + i, r = r0 + tx;
     if (c < cols && r < rows) dst[(size_t)c * rows + r] = tile[tx][i];
-  }
-}
-
-// 64 x 64 tile with 16-byte global accesses on both sides (rows, cols multiples of 64, 16-byte aligned
-// pointers).  LDS row pitch 66 elements: the gather of 8 consecutive rows of one column by 8 x 8 lanes
-// (stride 8 rows = 8 banks) touches every bank once.
-__global__ __launch_bounds__(256) void transpose_bf16_wide_kernel(const unsigned short* __restrict__ src,
-                                                                  unsigned short* __restrict__ dst, int rows,
-                                                                  int cols) {
-  constexpr int P = 66;
-  __shared__ __align__(4) unsigned short tile[64 * P];
-  const size_t r0 = (size_t)blockIdx.y * 64, c0 = (size_t)blockIdx.x * 64;
-  const int hi = threadIdx.x >> 3, lo = threadIdx.x & 7;
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int r = hi + 32 * j;
-    const uint4 v = *reinterpret_cast<const uint4*>(src + (r0 + r) * cols + c0 + lo * 8);
-    unsigned* t = reinterpret_cast<unsigned*>(tile + r * P + lo * 8);
-    t[0] = v.x; t[1] = v.y; t[2] = v.z; t[3] = v.w;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int c = hi + 32 * j;
-    unsigned w[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const unsigned a = tile[(lo * 8 + 2 * k) * P + c], b = tile[(lo * 8 + 2 * k + 1) * P + c];
-      w[k] = a | (b << 16);
-    }
-    *reinterpret_cast<uint4*>(dst + (c0 + c) * rows + r0 + lo * 8) = make_uint4(w[0], w[1], w[2], w[3]);
   }
 }
 
@@ -614,13 +630,32 @@ hipError_t launch_splitk_layernorm_bwd(const float* planes, int slices, size_t p
   return hipGetLastError();
 }
 
-hipError_t launch_transpose_bf16(const bf16_t* src, bf16_t* dst, int rows, int cols, hipStream_t s) {
-  if (rows <= 0 || cols <= 0) return hipErrorInvalidValue;
-  dim3 grid((cols + 63) / 64, (rows + 63) / 64);
-  const bool wide = rows % 64 == 0 && cols % 64 == 0 &&
-                    ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst)) & 15) == 0;
-  if (wide) transpose_bf16_wide_kernel<<<grid, 256, 0, s>>>((const unsigned short*)src, (unsigned short*)dst, rows, cols);
-  else transpose_bf16_kernel<<<grid, 256, 0, s>>>((const unsigned short*)src, (unsigned short*)dst, rows, cols);
+hipError_t launch_transpose_bf16(const TransposeArgs* m, int n, hipStream_t s) {
+  if (n < 0 || n > kTransposeMax) return hipErrorInvalidValue;
+  TransposeTable tb{};
+  long tiles = 0;
+  for (int i = 0; i < n; ++i) {
+    const int rows = m[i].rows, cols = m[i].cols;
+    if (rows <= 0 || cols <= 0) return hipErrorInvalidValue;
+    const long mine = (long)((rows + 63) / 64) * ((cols + 63) / 64);
+    if (rows % 8 != 0 || cols % 8 != 0 || tiles + mine >= (1L << 31) ||
+        ((reinterpret_cast<uintptr_t>(m[i].src) | reinterpret_cast<uintptr_t>(m[i].dst)) & 15) != 0) {
+      dim3 grid((cols + 63) / 64, (rows + 63) / 64);
+      transpose_bf16_any_kernel<<<grid, 256, 0, s>>>((const unsigned short*)m[i].src, (unsigned short*)m[i].dst, rows, cols);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+      continue;
+    }
+    tb.tile0[tb.n] = (int)tiles;
+    tb.rows[tb.n] = rows;
+    tb.cols[tb.n] = cols;
+    tb.src[tb.n] = (const unsigned short*)m[i].src;
+    tb.dst[tb.n] = (unsigned short*)m[i].dst;
+    ++tb.n;
+    tiles += mine;
+  }
+  if (tb.n == 0) return hipSuccess;
+  transpose_bf16_kernel<<<(unsigned)tiles, 256, 0, s>>>(tb);
   return hipGetLastError();
 }
 

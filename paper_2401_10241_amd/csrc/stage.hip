@@ -337,13 +337,12 @@ void weight_dims(const zb_stage* st, int i, int* rows, int* cols) {
 }
 const int kMatrices[4] = {ZB_P_WQKV, ZB_P_WO, ZB_P_W1, ZB_P_W2};
 
-// refresh the transposed bf16 copy of one weight matrix (bf16 stages only)
-hipError_t refresh_transposed(zb_stage* st, int l, int i) {
-  if (!st->bf16) return hipSuccess;
+// the transposed bf16 copy of one weight matrix (bf16 stages only)
+TransposeArgs transposed_copy(zb_stage* st, int l, int i) {
   int rows, cols;
   weight_dims(st, i, &rows, &cols);
   const size_t off = st->poff[l * ZB_P_COUNT + i];
-  return launch_transpose_bf16(st->theta16 + off, st->theta16_t + off, rows, cols, st->stream);
+  return {st->theta16 + off, st->theta16_t + off, rows, cols};
 }
 
 // Layers a (virtual) microbatch runs through: all of them, or with two chunks the first half of the stack
@@ -1132,11 +1131,21 @@ zb_status zb_optimizer_step_validated(zb_stage* st, const zb_global_state* gs, z
   ZB_HIP(st, launch_clear_step(st->opt, s));
   if (st->bf16) {  // the dgrad GEMMs read the weights transposed
     ProfScope ps(st, KC_TRANSPOSE, 0, 4.0 * 12.0 * st->h * (double)st->h * st->L);
+    TransposeArgs m[kTransposeMax];
+    int n = 0;
     for (int l = 0; l < st->L; ++l)
-      for (int wi : kMatrices) ZB_HIP(st, refresh_transposed(st, l, wi));
-    if (st->role == ZB_ROLE_LAST)
-      ZB_HIP(st, launch_transpose_bf16(st->theta16 + st->spoff[ZB_SP_W_HEAD], st->theta16_t + st->spoff[ZB_SP_W_HEAD],
-                                       st->h, st->V, s));
+      for (int wi : kMatrices) {
+        if (n == kTransposeMax) {
+          ZB_HIP(st, launch_transpose_bf16(m, n, s));
+          n = 0;
+        }
+        m[n++] = transposed_copy(st, l, wi);
+      }
+    ZB_HIP(st, launch_transpose_bf16(m, n, s));
+    if (st->role == ZB_ROLE_LAST) {
+      const TransposeArgs head{st->theta16 + st->spoff[ZB_SP_W_HEAD], st->theta16_t + st->spoff[ZB_SP_W_HEAD], st->h, st->V};
+      ZB_HIP(st, launch_transpose_bf16(&head, 1, s));
+    }
   }
   if (report) {
     OptDevState h;
@@ -1194,9 +1203,10 @@ zb_status zb_set_tensor(zb_stage* st, int32_t what, int32_t layer, int32_t mb, c
     ZB_HIP(st, hipMemcpyAsync(r.ptr, host_src, bytes, hipMemcpyHostToDevice, s));
     if (r.is_param && st->bf16) {
       ZB_HIP(st, launch_convert_from_f32<bf16_t>((const float*)r.ptr, st->theta16 + r.flat_off, r.count, s));
-      if (r.matrix_rows)  // the dgrad GEMMs read this matrix transposed
-        ZB_HIP(st, launch_transpose_bf16(st->theta16 + r.flat_off, st->theta16_t + r.flat_off, r.matrix_rows,
-                                         r.matrix_cols, s));
+      if (r.matrix_rows) {  // the dgrad GEMMs read this matrix transposed
+        const TransposeArgs t{st->theta16 + r.flat_off, st->theta16_t + r.flat_off, r.matrix_rows, r.matrix_cols};
+        ZB_HIP(st, launch_transpose_bf16(&t, 1, s));
+      }
     }
   }
   ZB_HIP(st, hipStreamSynchronize(s));

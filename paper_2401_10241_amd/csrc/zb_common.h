@@ -179,7 +179,13 @@ hipError_t launch_splitk_layernorm_bwd(const float* planes, int slices, size_t p
                                        float* dbeta, float* partials, int rows, int h, hipStream_t s);
 
 hipError_t launch_fill_f32(float* p, size_t n, float v, hipStream_t s);
-hipError_t launch_transpose_bf16(const bf16_t* src, bf16_t* dst, int rows, int cols, hipStream_t s);
+struct TransposeArgs {  // dst [cols][rows] = src [rows][cols] transposed
+  const bf16_t* src;
+  bf16_t* dst;
+  int rows, cols;
+};
+constexpr int kTransposeMax = 32;  // matrices per launch
+hipError_t launch_transpose_bf16(const TransposeArgs* m, int n, hipStream_t s);
 template <typename T> hipError_t launch_convert_from_f32(const float* src, T* dst, size_t n, hipStream_t s);
 template <typename T> hipError_t launch_convert_to_f32(const T* src, float* dst, size_t n, hipStream_t s);
 template <typename T> hipError_t launch_poke(T* dst, size_t idx, float v, hipStream_t s);

@@ -473,6 +473,34 @@ def test_few_steps_of_the_small_tiles(steps):
     run_and_compare(W("few_small", "bf16", 1, hidden, 8, 64 * steps + 8, 32 * steps - 3, 1, 4, 1, 2, "H2", seed=671 + steps))
 
 
+@pytest.mark.parametrize("layers,cfg", [
+    (9, (72, 3, 200, 33, 1)),     # 36 weight matrices: two launches transpose them; no side a multiple of 64
+    (8, (64, 1, 128, 32, 1)),     # 32: one
+    (1, (136, 1, 8, 16, 2)),      # the smallest ffn
+], ids=lambda c: str(c))
+def test_weights_are_transposed_after_a_step(layers, cfg):
+    # the iteration after a step is bit for bit that of a stage that is given the stepped weights
+    import paper_2401_10241_amd as zb
+    hidden, heads, ffn, seq, b = cfg
+    w = W("transposed", "bf16", layers, hidden, heads, ffn, seq, b, 4, 1, 2, "H1", seed=711 + hidden, lr=0.05)
+    dev, other = make_device_stage(w), make_device_stage(w)
+    dev.set_params(zb_inputs.stage_params(w))
+    dev.begin_iteration(0, w.m)
+    load_iteration(w, 0, w.m, dev)
+    dev.run_schedule(w.p, w.stage, w.m, w.kind)
+    dev.optimizer_step_validated(0.0, 0.0)
+    other.set_params(dev.get_group(zb.T_PARAM))
+    got = []
+    for st in (dev, other):
+        st.begin_iteration(1, w.m)
+        load_iteration(w, 1, w.m, st)
+        st.run_schedule(w.p, w.stage, w.m, w.kind)
+        grads = st.get_group(zb.T_GRAD)
+        got.append([st.get_tensor(zb.T_OUTPUT_DX, 0, k) for k in range(w.m)] + [g[n] for g in grads for n in sorted(g)])
+        st.close()
+    assert all(np.array_equal(a, c) for a, c in zip(*got))
+
+
 @pytest.mark.parametrize("dtype,cfg", [
     ("bf16", (64, 1, 2048, 64, 68)),   # FC1 and FC2's backward on 256-row tiles
     ("bf16", (256, 4, 1032, 100, 1)),  # small tiles with edges
