@@ -2,13 +2,11 @@
 // all three operand forms: forward X*W, dgrad dY*W^T (W as stored, K-contiguous), wgrad X^T*dY.
 //
 // A workgroup owns one output tile and its waves split K between them, 32 k at a time in turn; fragments come
-// straight from memory into registers (one block of 32 k ahead), and the waves' partial tiles are added through
-// LDS in wave order.  What bounds the products that come here (hundreds of tokens, widths up to a few thousand)
-// is latency: with the K range walked in steps of 16 through LDS by a 64 x 64 tile, 128 x 256 x 1024 took 64
-// dependent steps on 8 CUs; here it is 4 on 32.  Tiles are 32 x 32 with eight waves or 64 x 64 with four (half the
-// reads per product, twice the chain); the rules are at `kWideTiles` and `wide_wgrad`.  Measured on
-// the stage of hidden 256 with 128 tokens: N = 256 products 103-111 us -> 10-15 us, a W pass 215 us in eight
-// launches plus column sums -> 17 us in one, the iteration 4.97 -> 1.09 ms.
+// straight from memory into registers, and the waves' partial tiles are added through LDS in wave order.  What bounds
+// the products that come here (hundreds of tokens, widths up to a few thousand) is latency, so a wave has the loads of two
+// to four of its blocks in flight before the first product: with one block ahead of the products 128 x 256 x 1024 took
+// 22.5 us (dgrad 12.3).  Small products take 16 x 16 tiles, four times the workgroups: 5.9 us.  The rules are at `kSmallTiles` and
+// `wide_wgrad`.
 #include <algorithm>
 
 #include "gemm_epilogue.h"
@@ -23,13 +21,26 @@ namespace {
 
 constexpr int KB = 32;  // k per block
 
-// One operand's rows (or columns) r0 + (lane & 31), k0 .. k0+31: element 4q + j is k = k0 + 8q + 4 (lane >> 5) + j.
-// KC: element (r, k) at p[r * ld + k], K and ld multiples of 4; else at p[k * ld + r].  k >= K: zero.
-template <bool KC>
-__device__ __forceinline__ void load_frag(f32x4 (&f)[4], const float* __restrict__ p, long ld, int r, int k0, int K, int hi) {
+// An MFMA tile is T x T: 32 x 32 (v_mfma_f32_32x32x2_f32) or 16 x 16 (v_mfma_f32_16x16x4_f32), the same rate.
+template <int T> struct Mfma;
+template <> struct Mfma<32> {
+  using Acc = f32x16;
+  static __device__ __forceinline__ void mac(float a, float b, Acc& c) { c = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+};
+template <> struct Mfma<16> {
+  using Acc = f32x4;
+  static __device__ __forceinline__ void mac(float a, float b, Acc& c) { c = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+};
+template <int T> using Acc = typename Mfma<T>::Acc;
+template <int T> using Frag = f32x4[KB * T / 256];
+
+// One operand's row (or column) r of this lane (lane % T), k0 .. k0+31: element 4q + j is k = k0 + (256 / T) q + 4 hi + j,
+// hi = lane / T.  KC: element (r, k) at p[r * ld + k], K and ld multiples of 4; else at p[k * ld + r].  k >= K: zero.
+template <int T, bool KC>
+__device__ __forceinline__ void load_frag(Frag<T>& f, const float* __restrict__ p, long ld, int r, int k0, int K, int hi) {
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int k = k0 + q * 8 + hi * 4;
+  for (int q = 0; q < KB * T / 256; ++q) {
+    const int k = k0 + q * (256 / T) + hi * 4;
     if constexpr (KC) {
       f[q] = *reinterpret_cast<const f32x4*>(p + (long)r * ld + min(k, K - 4));
       if (k >= K) f[q] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -43,63 +54,72 @@ __device__ __forceinline__ void load_frag(f32x4 (&f)[4], const float* __restrict
   }
 }
 
-// This wave's share of the tile at (m0, n0)
-template <int TM, int TN, int NW, bool AKC, bool BKC>
-__device__ __forceinline__ void wave_tile(f32x16 (&acc)[TM / 32][TN / 32], const float* __restrict__ A,
-                                          const float* __restrict__ B, int M, int N, int K, long lda, long ldb, int m0,
-                                          int n0, int wave, int lane) {
-  constexpr int MT = TM / 32, NT = TN / 32;
-  const int hi = lane >> 5;
+// ND blocks of a wave's share of a tile, `step` apart in k: all their loads are in flight before the first product
+template <int T, int MT, int NT, int ND, bool AKC, bool BKC>
+__device__ __forceinline__ void wave_blocks(Acc<T> (&acc)[MT][NT], const float* __restrict__ A, const float* __restrict__ B,
+                                            int K, long lda, long ldb, const int (&rm)[MT], const int (&rn)[NT], int k0,
+                                            int step, int hi) {
+  Frag<T> a[ND][MT], b[ND][NT];
 #pragma unroll
-  for (int i = 0; i < MT; ++i)
+  for (int d = 0; d < ND; ++d) {
 #pragma unroll
-    for (int j = 0; j < NT; ++j)
+    for (int i = 0; i < MT; ++i) load_frag<T, AKC>(a[d][i], A, lda, rm[i], k0 + d * step, K, hi);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-  f32x4 a[MT][4], b[NT][4];
-  auto load = [&](f32x4 (&x)[MT][4], f32x4 (&y)[NT][4], int k0) {
+    for (int j = 0; j < NT; ++j) load_frag<T, BKC>(b[d][j], B, ldb, rn[j], k0 + d * step, K, hi);
+  }
 #pragma unroll
-    for (int i = 0; i < MT; ++i) load_frag<AKC>(x[i], A, lda, min(m0 + i * 32 + (lane & 31), M - 1), k0, K, hi);
+  for (int d = 0; d < ND; ++d)
 #pragma unroll
-    for (int j = 0; j < NT; ++j) load_frag<BKC>(y[j], B, ldb, min(n0 + j * 32 + (lane & 31), N - 1), k0, K, hi);
-  };
-  int k0 = wave * KB;
-  if (k0 < K) load(a, b, k0);
-  for (; k0 < K; k0 += NW * KB) {
-    f32x4 a1[MT][4], b1[NT][4];
-    const bool more = k0 + NW * KB < K;
-    if (more) load(a1, b1, k0 + NW * KB);
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int q = 0; q < KB * T / 256; ++q)
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
         for (int i = 0; i < MT; ++i)
 #pragma unroll
-          for (int j = 0; j < NT; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][q][e], b[j][q][e], acc[i][j], 0, 0, 0);
-    if (more) {
+          for (int j = 0; j < NT; ++j) Mfma<T>::mac(a[d][i][q][e], b[d][j][q][e], acc[i][j]);
+}
+
+// This wave's share of the TM x TN tile at (m0, n0), ND (1, 2 or 4) blocks at a time
+template <int T, int TM, int TN, int NW, int ND, bool AKC, bool BKC>
+__device__ __forceinline__ void wave_tile(Acc<T> (&acc)[TM / T][TN / T], const float* __restrict__ A,
+                                          const float* __restrict__ B, int M, int N, int K, long lda, long ldb, int m0,
+                                          int n0, int wave, int lane) {
+  constexpr int MT = TM / T, NT = TN / T, step = NW * KB;
+  const int hi = lane / T;
+  int rm[MT], rn[NT];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+  for (int i = 0; i < MT; ++i) rm[i] = min(m0 + i * T + lane % T, M - 1);
 #pragma unroll
-        for (int i = 0; i < MT; ++i) a[i][q] = a1[i][q];
+  for (int j = 0; j < NT; ++j) rn[j] = min(n0 + j * T + lane % T, N - 1);
 #pragma unroll
-        for (int j = 0; j < NT; ++j) b[j][q] = b1[j][q];
-      }
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int v = 0; v < T * T / 64; ++v) acc[i][j][v] = 0.f;
+  int k0 = wave * KB;
+  for (; k0 + (ND - 1) * step < K; k0 += ND * step)
+    wave_blocks<T, MT, NT, ND, AKC, BKC>(acc, A, B, K, lda, ldb, rm, rn, k0, step, hi);
+  if constexpr (ND > 2)
+    if (k0 + step < K) {
+      wave_blocks<T, MT, NT, 2, AKC, BKC>(acc, A, B, K, lda, ldb, rm, rn, k0, step, hi);
+      k0 += 2 * step;
     }
-  }
+  if constexpr (ND > 1)
+    if (k0 < K) wave_blocks<T, MT, NT, 1, AKC, BKC>(acc, A, B, K, lda, ldb, rm, rn, k0, step, hi);
 }
 
 // The waves' partial tiles into LDS, then element `e` of this thread = the sum over the waves in order.
 // Element id x = tile (i, j), register v, lane, as the MFMA leaves them.
-template <int TM, int TN, int NW>
-__device__ __forceinline__ void put_partial(float* red, const f32x16 (&acc)[TM / 32][TN / 32], int wave, int lane) {
+template <int T, int TM, int TN, int NW>
+__device__ __forceinline__ void put_partial(float* red, const Acc<T> (&acc)[TM / T][TN / T], int wave, int lane) {
+  constexpr int R = T * T / 64;
 #pragma unroll
-  for (int i = 0; i < TM / 32; ++i)
+  for (int i = 0; i < TM / T; ++i)
 #pragma unroll
-    for (int j = 0; j < TN / 32; ++j)
+    for (int j = 0; j < TN / T; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) red[wave * TM * TN + ((i * (TN / 32) + j) * 16 + v) * 64 + lane] = acc[i][j][v];
+      for (int v = 0; v < R; ++v) red[wave * TM * TN + ((i * (TN / T) + j) * R + v) * 64 + lane] = acc[i][j][v];
 }
 template <int TM, int TN, int NW> __device__ __forceinline__ float sum_partial(const float* red, int x) {
   float t = red[x];
@@ -107,28 +127,30 @@ template <int TM, int TN, int NW> __device__ __forceinline__ float sum_partial(c
   for (int w = 1; w < NW; ++w) t += red[w * TM * TN + x];
   return t;
 }
-template <int TN> __device__ __forceinline__ void where(int x, int* m, int* n) {
-  const int lane = x & 63, v = (x >> 6) & 15, t = x >> 10;
-  *m = (t / (TN / 32)) * 32 + (v >> 2) * 8 + (lane >> 5) * 4 + (v & 3);
-  *n = (t % (TN / 32)) * 32 + (lane & 31);
+template <int T, int TN> __device__ __forceinline__ void where(int x, int* m, int* n) {
+  constexpr int R = T * T / 64;
+  const int lane = x & 63, v = x / 64 % R, t = x / 64 / R;
+  *m = (t / (TN / T)) * T + (v >> 2) * 8 + lane / T * 4 + (v & 3);
+  *n = (t % (TN / T)) * T + lane % T;
 }
 
-template <int TM, int TN, int NW, bool BKC, int MODE>
+template <int T, int TM, int TN, int NW, int ND, bool BKC, int MODE>
 __global__ __launch_bounds__(64 * NW) void gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ B, int M,
                                                            int N, int K, long lda, long ldb, EpiParams epi) {
   __shared__ float red[NW * TM * TN];
   const int tiles_m = (M + TM - 1) / TM;
   const int m0 = ((int)blockIdx.x % tiles_m) * TM, n0 = ((int)blockIdx.x / tiles_m) * TN;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  f32x16 acc[TM / 32][TN / 32];
-  wave_tile<TM, TN, NW, true, BKC>(acc, A, B, M, N, K, lda, ldb, m0, n0, wave, lane);
-  put_partial<TM, TN, NW>(red, acc, wave, lane);
+  Acc<T> acc[TM / T][TN / T];
+  wave_tile<T, TM, TN, NW, ND, true, BKC>(acc, A, B, M, N, K, lda, ldb, m0, n0, wave, lane);
+  put_partial<T, TM, TN, NW>(red, acc, wave, lane);
   __syncthreads();
 #pragma unroll
-  for (int e = 0; e < TM * TN / (64 * NW); ++e) {
+  for (int e = 0; e < (TM * TN + 64 * NW - 1) / (64 * NW); ++e) {
     const int x = threadIdx.x + e * 64 * NW;
+    if (x >= TM * TN) break;  // 16 x 16 tiles have fewer elements than threads
     int m, n;
-    where<TN>(x, &m, &n);
+    where<T, TN>(x, &m, &n);
     if (m0 + m < M && n0 + n < N) epilogue_one<float, MODE>(epi, m0 + m, n0 + n, sum_partial<TM, TN, NW>(red, x));
   }
 }
@@ -147,7 +169,7 @@ struct F32WgradTable {
 // All gradients of a W pass in one launch: C += A_0^T B_0, then += A_1^T B_1, ...  (each pair's product is
 // finished before it is added, so several pairs in one launch give the bits of one launch each), and the bias
 // gradients (column sums of the B operands, rows in a fixed order) in the workgroups after the tiles.
-template <int TM, int TN, int NW>
+template <int T, int TM, int TN, int NW, int ND>
 __global__ __launch_bounds__(64 * NW) void gemm_f32_wgrad_kernel(F32WgradTable tb, int K) {
   __shared__ float red[NW * TM * TN];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -186,13 +208,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_wgrad_kernel(F32WgradTable t
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
     int m, n;
-    where<TN>(threadIdx.x + e * 64 * NW, &m, &n);
+    where<T, TN>(threadIdx.x + e * 64 * NW, &m, &n);
     c[e] = tb.outf[q][(size_t)min(m0 + m, M - 1) * N + min(n0 + n, N - 1)];
   }
   for (int g = 0; g < ngroup; ++g) {
-    f32x16 acc[TM / 32][TN / 32];
-    wave_tile<TM, TN, NW, false, false>(acc, tb.a[q * ngroup + g], tb.b[q * ngroup + g], M, N, K, M, N, m0, n0, wave, lane);
-    put_partial<TM, TN, NW>(red, acc, wave, lane);
+    Acc<T> acc[TM / T][TN / T];
+    wave_tile<T, TM, TN, NW, ND, false, false>(acc, tb.a[q * ngroup + g], tb.b[q * ngroup + g], M, N, K, M, N, m0, n0, wave, lane);
+    put_partial<T, TM, TN, NW>(red, acc, wave, lane);
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < PER; ++e) c[e] += sum_partial<TM, TN, NW>(red, threadIdx.x + e * 64 * NW);
@@ -201,17 +223,20 @@ __global__ __launch_bounds__(64 * NW) void gemm_f32_wgrad_kernel(F32WgradTable t
 #pragma unroll
   for (int e = 0; e < PER; ++e) {
     int m, n;
-    where<TN>(threadIdx.x + e * 64 * NW, &m, &n);
+    where<T, TN>(threadIdx.x + e * 64 * NW, &m, &n);
     if (m0 + m < M && n0 + n < N) tb.outf[q][(size_t)(m0 + m) * N + n0 + n] = c[e];
   }
 }
 
 inline long tiles_of(int M, int N, int t) { return (long)((M + t - 1) / t) * ((N + t - 1) / t); }
 
-// Forward / dgrad: 64 x 64 tiles with four waves from four 32 x 32 tiles per CU on.  Measured, us with 32 x 32 / 64 x 64
-// tiles: 512 x 1024 x 256 (512 tiles) 7.6 / 10.5, 512 x 1536 x 512 (768) 20.9 / 16.5, 512 x 2048 x 512 (1024) 29.2 /
-// 18.6, 600 x 2048 x 512 (1216) 36.8 / 29.3, its dgrad 28.3 / 32.8, 1024 x 4096 x 1024 (4096) 220 / 98.
-constexpr long kWideTiles = 1024;
+// Forward / dgrad: 16 x 16 tiles up to half a 32 x 32 tile per CU, 64 x 64 tiles with four waves from eight of them on.
+// Measured, us with 16 x 16 / 32 x 32 / 64 x 64 tiles, weights as stored (dgrad in brackets), tokens x N x K:
+// 128 x 256 x 1024 (32 tiles of 32 x 32) 5.9 / 9.7 / 28 (5.8 / 10.4 / 28), 128 x 1024 x 256 (128) 3.7 / 4.2 / 11 (4.1 / 4.5 / 12),
+// 512 x 256 x 1024 (128) 8.4 / 10.0 / 31 (9.3 / 10.5 / 29), 200 x 1024 x 256 (224) 5.3 / 4.3 / 12 (5.8 / 4.8 / 12), 512 x 1024 x 1024
+// (512) 26 / 18 / 34 (31 / 23 / 33), 512 x 2048 x 512 (1024) 25 / 18 / 23 (32 / 20 / 22), 1024 x 1024 x 4096 (1024) 168 / 113 / 111
+// (225 / 123 / 101), 1024 x 2048 x 512 (2048) 47 / 31 / 32 (60 / 35 / 31), 1024 x 4096 x 1024 (4096) 184 / 113 / 98 (227 / 128 / 94).
+constexpr long kSmallTiles = 128, kWideTiles = 2048;
 
 // W: the two forms split K over eight and four waves, i.e. add in different orders, so the choice may rest only on what
 // is the same in every launch of a stage - the tokens and the largest gradient of a layer - and not on how many layers
@@ -242,11 +267,13 @@ template <bool BKC, int MODE> hipError_t run_f32(const GemmArgs& g, long lda, lo
   const long small = tiles_of(g.M, g.N, 32);
   if (small >= (1L << 31)) return hipErrorInvalidValue;
   const float *A = (const float*)g.A, *B = (const float*)g.B;
-  if (small < kWideTiles)
-    gemm_f32_kernel<32, 32, 8, BKC, MODE><<<(unsigned)small, 512, 0, s>>>(A, B, g.M, g.N, g.K, lda, ldb, make_epi(g));
+  const EpiParams epi = make_epi(g);
+  if (small <= kSmallTiles)
+    gemm_f32_kernel<16, 16, 16, 8, 4, BKC, MODE><<<(unsigned)tiles_of(g.M, g.N, 16), 512, 0, s>>>(A, B, g.M, g.N, g.K, lda, ldb, epi);
+  else if (small < kWideTiles)
+    gemm_f32_kernel<32, 32, 32, 8, 2, BKC, MODE><<<(unsigned)small, 512, 0, s>>>(A, B, g.M, g.N, g.K, lda, ldb, epi);
   else
-    gemm_f32_kernel<64, 64, 4, BKC, MODE><<<(unsigned)tiles_of(g.M, g.N, 64), 256, 0, s>>>(A, B, g.M, g.N, g.K, lda, ldb,
-                                                                                          make_epi(g));
+    gemm_f32_kernel<32, 64, 64, 4, 1, BKC, MODE><<<(unsigned)tiles_of(g.M, g.N, 64), 256, 0, s>>>(A, B, g.M, g.N, g.K, lda, ldb, epi);
   return hipGetLastError();
 }
 
@@ -307,8 +334,8 @@ template <> hipError_t launch_wgrad_multi_mfma<float>(const WgradMultiArgs& w, h
       if (e != hipSuccess) return e;
     }
   if (tiles + strips == 0) return hipSuccess;
-  if (wide) gemm_f32_wgrad_kernel<64, 64, 4><<<tiles + strips, 256, 0, s>>>(tb, w.K);
-  else gemm_f32_wgrad_kernel<32, 32, 8><<<tiles + strips, 512, 0, s>>>(tb, w.K);
+  if (wide) gemm_f32_wgrad_kernel<32, 64, 64, 4, 1><<<tiles + strips, 256, 0, s>>>(tb, w.K);
+  else gemm_f32_wgrad_kernel<32, 32, 32, 8, 2><<<tiles + strips, 512, 0, s>>>(tb, w.K);
   return hipGetLastError();
 }
 

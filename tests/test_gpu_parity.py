@@ -473,6 +473,21 @@ def test_few_steps_of_the_small_tiles(steps):
     run_and_compare(W("few_small", "bf16", 1, hidden, 8, 64 * steps + 8, 32 * steps - 3, 1, 4, 1, 2, "H2", seed=671 + steps))
 
 
+@pytest.mark.parametrize("cfg", [
+    # hidden, heads, ffn, seq, b       32-k blocks per wave (eight waves, four waves of the 64 x 64 tiles)
+    (40, 1, 200, 33, 1),         # 16 x 16 tiles: two waves with a block; seven, the last one cut
+    (264, 3, 520, 33, 1),        # two and one; three and two
+    (776, 2, 1032, 17, 1),       # four and three; five and four
+    (264, 3, 1032, 101, 5),      # 32 x 32 tiles: 17 x 9 and 17 x 33 of them, two and one blocks, five and four
+    (520, 2, 40, 150, 2),        # 10 x 17, three and two
+    (40, 1, 4104, 130, 4),       # 64 x 64 tiles: 9 x 65, two waves with a block
+    (136, 1, 4104, 130, 4),      # two and one
+], ids=lambda c: "h%d_a%d_f%d_s%d_b%d" % c)
+def test_few_blocks_of_the_fp32_products(cfg):
+    hidden, heads, ffn, seq, b = cfg
+    run_and_compare(W("f32", "fp32", 1, hidden, heads, ffn, seq, b, 4, 1, 2, "H1", seed=731 + hidden + ffn))
+
+
 @pytest.mark.parametrize("layers,cfg", [
     (9, (72, 3, 200, 33, 1)),     # 36 weight matrices: two launches transpose them; no side a multiple of 64
     (8, (64, 1, 128, 32, 1)),     # 32: one
