@@ -6,7 +6,7 @@
 // the products that come here (hundreds of tokens, widths up to a few thousand) is latency, so a wave has the loads of two
 // to four of its blocks in flight before the first product: with one block ahead of the products 128 x 256 x 1024 took
 // 22.5 us (dgrad 12.3).  Small products take 16 x 16 tiles, four times the workgroups: 5.9 us.  The rules are at `kSmallTiles` and
-// `wide_wgrad`.
+// `four_waves`.
 #include <algorithm>
 
 #include "gemm_epilogue.h"
@@ -238,19 +238,20 @@ inline long tiles_of(int M, int N, int t) { return (long)((M + t - 1) / t) * ((N
 // (225 / 123 / 101), 1024 x 2048 x 512 (2048) 47 / 31 / 32 (60 / 35 / 31), 1024 x 4096 x 1024 (4096) 184 / 113 / 98 (227 / 128 / 94).
 constexpr long kSmallTiles = 128, kWideTiles = 2048;
 
-// W: the two forms split K over eight and four waves, i.e. add in different orders, so the choice may rest only on what
-// is the same in every launch of a stage - the tokens and the largest gradient of a layer - and not on how many layers
-// share the launch (nor may `valu_wgrad`): the gradients keep their bits in every grouping.  The wide form pays with at most one 32-k block
-// per wave and gradients that fill half the chip.  Measured, us with 32 x 32 / 64 x 64 tiles, hidden h, ffn 4 h: 128 tokens
-// h 128 (largest gradient 64 tiles of 32 x 32) one layer 4.4 / 8.3, four 12.8 / 8.8; h 192 (144) one 6.9 / 8.5, two 12.7 / 8.9;
-// h 256 (256) one 10.9 / 8.7, four 41 / 27; h 1024 128 / 88; h 256, two layers 64 tokens 18.7 / 15.4, 136 tokens 23.6 / 26.4,
-// 512 tokens 39 / 104; h 1024, 512 tokens 256 / 531.
+// W: 32 x 32 tiles with eight waves, or with four where they have at most one 32-k block each (the idle four of eight
+// would only add zeros: the same bits) and the gradients fill half the chip.  Above that the two would add in different
+// orders, so the choice may rest only on what is the same in every launch of a stage - the tokens and the largest gradient of a layer
+// - and not on how many layers share the launch (nor may `valu_wgrad`): the gradients keep their bits in every grouping.
+// Measured with the bias sums, us with eight waves / four / 64 x 64 tiles with four, hidden h, ffn 4 h, 128 tokens: h 128
+// (largest gradient 64 tiles) one layer 4.2 / 4.3 / 7.9, four 7.6 / 6.7 / 8.2; h 192 (144) one 5.1 / 5.2 / 8.0, two 7.8 / 7.3 / 8.3; h 256
+// (256) one 6.5 / 6.4 / 8.1, two 10.4 / 9.5 / 11.2, four 20 / 17 / 18; h 1024 60 / 51 / 55; 17 tokens: h 256, four 16 / 12 / 15, h 1024
+// 46 / 31 / 50.  136 tokens: h 256, one 7.4 / 7.4 / 10.4.
 inline long largest_tiles(const WgradMultiArgs& w) {
   long most = 0;
   for (int q = 0; q < w.nprob; ++q) most = std::max(most, tiles_of(w.M[q], w.N[q], 32));
   return most;
 }
-inline bool wide_wgrad(const WgradMultiArgs& w) { return w.K <= 4 * KB && largest_tiles(w) >= 128; }
+inline bool four_waves(const WgradMultiArgs& w) { return w.K <= 4 * KB && largest_tiles(w) >= 128; }
 
 // Large gradients are bound by their own turn-around, and these tiles, whose waves wait for each other's partial sums,
 // keep too few loads in flight for it: the vector-ALU kernel takes the products there, one launch each, and only the
@@ -306,14 +307,14 @@ template <> hipError_t launch_wgrad_multi_mfma<float>(const WgradMultiArgs& w, h
     small += tiles_of(w.M[q], w.N[q], 32);
   }
   if (small >= (1L << 30)) return hipSuccess;
-  const bool valu = valu_wgrad(w), wide = !valu && wide_wgrad(w);
+  const bool valu = valu_wgrad(w), four = !valu && four_waves(w);
   int tiles = 0, strips = 0;
   for (int q = 0; q < w.nprob; ++q) {
     tb.M[q] = w.M[q]; tb.N[q] = w.N[q]; tb.outf[q] = w.outf[q];
     tb.bias[q] = w.bias_done ? w.bias[q] : nullptr;
     tb.tile0[q] = tiles;
     tb.strip0[q] = strips;
-    if (!valu) tiles += (int)tiles_of(w.M[q], w.N[q], wide ? 64 : 32);
+    if (!valu) tiles += (int)tiles_of(w.M[q], w.N[q], 32);
     if (tb.bias[q]) strips += (w.N[q] + 63) / 64;
     for (int g = 0; g < w.ngroup; ++g) {
       tb.a[q * w.ngroup + g] = (const float*)w.a[q * w.ngroup + g];
@@ -334,7 +335,7 @@ template <> hipError_t launch_wgrad_multi_mfma<float>(const WgradMultiArgs& w, h
       if (e != hipSuccess) return e;
     }
   if (tiles + strips == 0) return hipSuccess;
-  if (wide) gemm_f32_wgrad_kernel<32, 64, 64, 4, 1><<<tiles + strips, 256, 0, s>>>(tb, w.K);
+  if (four) gemm_f32_wgrad_kernel<32, 32, 32, 4, 1><<<tiles + strips, 256, 0, s>>>(tb, w.K);
   else gemm_f32_wgrad_kernel<32, 32, 32, 8, 2><<<tiles + strips, 512, 0, s>>>(tb, w.K);
   return hipGetLastError();
 }
