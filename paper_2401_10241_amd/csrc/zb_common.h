@@ -60,7 +60,8 @@ __device__ __forceinline__ float gelu_sigmoid(float x, float xx) {  // 1 / (1 + 
 template <> __device__ __forceinline__ float gelu<bf16_t>(float x) { return x * gelu_sigmoid(x, x * x); }
 template <> __device__ __forceinline__ float gelu_grad<bf16_t>(float x) {
   const float c2 = 1.5957691216057308f, a3 = 0.134145f;  // 2 sqrt(2 / pi), 3 * 0.044715
-  const float xx = x * x, s = gelu_sigmoid(x, xx), q = x * fmaf(c2 * a3, xx, c2);
+  // s (1 - s) is 0 long before the polynomial ends at 1e18; unbounded, q overflows from |x| = 1.2e13 on and 0 * q is NaN
+  const float xx = x * x, s = gelu_sigmoid(x, xx), q = x * fminf(fmaf(c2 * a3, xx, c2), 1e18f);
   return fmaf(s, fmaf(-s, q, q), s);  // s + s (1 - s) q
 }
 

@@ -540,6 +540,51 @@ def test_gelu_over_its_range(dtype, cfg):
     dev.close()
 
 
+# products with the GELU in their epilogue: 256-row tiles, small tiles with edges, K slices and the launch that adds them
+GELU_SHAPES = [(64, 1, 2048, 64, 68), (256, 4, 1032, 100, 1), (2048, 16, 256, 64, 1)]
+
+
+def gelu_by_column(cfg, b1, dy):
+    """G = gelu(b1) and dF = dG * gelu'(b1) of a bf16 stage, [tokens, ffn], as its epilogues make them: FC1's weights are
+    zero, and W2 makes dG = dy[:, 0] + dy[:, 1] / 256 in every column, exactly (16 bits)."""
+    import paper_2401_10241_amd as zb
+    hidden, heads, ffn, seq, b = cfg
+    w = W("gelu", "bf16", 1, hidden, heads, ffn, seq, b, 4, 1, 1, "H1", seed=653)
+    params = zb_inputs.stage_params(w)
+    params[0]["w1"][:] = 0.0
+    params[0]["b1"] = b1.astype(np.float32)
+    params[0]["w2"][:] = 0.0
+    params[0]["w2"][:, 0] = 1.0
+    params[0]["w2"][:, 1] = 2.0 ** -8
+    dY = np.zeros((seq * b, hidden), np.float32)
+    dY[:, :2] = dy
+    dev = make_device_stage(w, 1)
+    dev.set_params(params)
+    dev.begin_iteration(0, 1)
+    dev.set_tensor(zb.T_INPUT_X, 0, 0, zb_inputs.stage_input(w, 0, 0))
+    dev.set_tensor(zb.T_INPUT_DY, 0, 0, dY)
+    dev.forward(0)
+    dev.backward_input(0)
+    G, dF = (np.hstack([dev.get_stash_columns(what, 0, 0, np.arange(n, min(n + 32, ffn))) for n in range(0, ffn, 32)])
+             for what in (zb.S_FC2_IN, zb.S_FC1_DOUT))
+    y, dx = dev.get_tensor(zb.T_OUTPUT_Y, 0, 0), dev.get_tensor(zb.T_OUTPUT_DX, 0, 0)
+    dev.close()
+    assert np.isfinite(y).all() and np.isfinite(dx).all()
+    return G, dF
+
+
+@pytest.mark.parametrize("cfg", GELU_SHAPES, ids=lambda c: "h%d_a%d_f%d_s%d_b%d" % c)
+def test_gelu_of_pre_activations_whose_cube_overflows(cfg):
+    # finite pre-activations of any size: the GELU is x or 0 and its derivative 1 or 0.  x^3 leaves fp32 at 7e12, x^2 at 1.8e19
+    hidden, heads, ffn, seq, b = cfg
+    big = np.array([64.0, 2.0 ** 20, 2.0 ** 42, 2.0 ** 43, 2.0 ** 44, 2.0 ** 50, 2.0 ** 60, 2.0 ** 63], np.float32)
+    x = np.resize(np.concatenate([big, -big]), ffn)
+    dy = np.stack([2.0 ** (np.arange(seq * b) % 8), np.zeros(seq * b)], axis=1)
+    G, dF = gelu_by_column(cfg, x, dy)
+    assert np.array_equal(G, np.broadcast_to(np.maximum(x, 0.0), G.shape))
+    assert np.array_equal(dF, np.outer(dy[:, 0], x > 0))
+
+
 @pytest.mark.parametrize("cfg", [
     # hidden, heads, ffn, seq, b       row blocks and groups of waves of the attention (128-row blocks of a launch)
     (256, 4, 512, 128, 3),       # head size 64, 12 whole blocks: 64 rows, two groups; the first blocks have one tile
