@@ -302,7 +302,7 @@ __global__ __launch_bounds__(64 * NW * NG) void attn_fwd_kernel(const bf16_t* __
           mx = fmaxf(mx, x);
         }
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float m_new = fmaxf(m, mx), ref = EDGE ? softmax_ref(m_new) : m_new;
+      const float m_new = fmaxf(m, mx), ref = softmax_ref(m_new);
       const float alpha = exp_of<EDGE>(m - ref);
       float rs = 0.f;
 #pragma unroll
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(64 * NW * NG) void attn_fwd_kernel(const bf16_t* __
     }
     __syncthreads();
     if (grp) return;
-    const float m1 = x[0], m_new = fmaxf(m, m1), ref = EDGE ? softmax_ref(m_new) : m_new;
+    const float m1 = x[0], m_new = fmaxf(m, m1), ref = softmax_ref(m_new);
     const float a0 = exp_of<EDGE>(m - ref), a1 = exp_of<EDGE>(m1 - ref);
     l = l * a0 + x[64] * a1;
     m = m_new;

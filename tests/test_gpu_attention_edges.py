@@ -18,7 +18,12 @@ SHAPES = [
     ("bf16", 128, 4, 130, 2),       # head size 32, two rows past two tiles
     ("bf16", 256, 2, 200, 1),       # head size 128
 ]
-IDS = ["%s_h%d_a%d_s%d_b%d" % c for c in SHAPES]
+# whole tiles: the kernels without edges
+WHOLE = [
+    ("bf16", 128, 2, 128, 1),       # head size 64, two groups of waves with one tile each
+    ("bf16", 128, 2, 512, 1),       # eight tiles
+]
+IDS = ["%s_h%d_a%d_s%d_b%d" % c for c in SHAPES + WHOLE]
 
 
 def run_once(w, params, X, dY):
@@ -34,8 +39,9 @@ def run_once(w, params, X, dY):
     return dev
 
 
-@pytest.mark.parametrize("low,live", [((32, 64), 0), ((0, 64), 64)], ids=["second_block", "first_blocks"])
-@pytest.mark.parametrize("shape", SHAPES, ids=IDS)
+@pytest.mark.parametrize("low,live", [((32, 64), 0), ((0, 64), 64), ((64, 128), 0)],
+                         ids=["second_block", "first_blocks", "second_tile"])
+@pytest.mark.parametrize("shape", SHAPES + WHOLE, ids=IDS)
 def test_scores_of_minus_infinity_have_no_weight(shape, low, live):
     # feature 0 of a token is the sign of its scores with every query (1e38 and more, an infinity in fp32): tokens
     # `low` get -inf, the others exactly 0.  From query `live` on there is a finite score, and those rows are
@@ -54,22 +60,23 @@ def test_scores_of_minus_infinity_have_no_weight(shape, low, live):
     X[:, :2] = 0.0                               # rows of mean zero: feature 0 stays exactly 0 in the LayerNorm
     X[:, 2:] *= 1.0 + 0.25 * (np.arange(seq * b)[:, None] % 3)
     for i in range(b):
-        X[i * seq + low[0]:i * seq + low[1], 0] = -1.0
-        X[i * seq + low[0]:i * seq + low[1], 1] = 1.0
+        X[i * seq + low[0]:i * seq + min(low[1], seq), 0] = -1.0
+        X[i * seq + low[0]:i * seq + min(low[1], seq), 1] = 1.0
     X = X.astype(np.float32)
     orc = make_oracle(w, params)
     orc.begin_iteration(1)
     orc.set_input(0, X)
     orc.forward(0)
     dev = run_once(w, params, X, np.zeros_like(X))
-    y = dev.get_tensor(zb.T_OUTPUT_Y, 0, 0)
+    y, dx = dev.get_tensor(zb.T_OUTPUT_Y, 0, 0), dev.get_tensor(zb.T_OUTPUT_DX, 0, 0)
     dev.close()
     keep = np.concatenate([np.arange(i * seq + live, (i + 1) * seq) for i in range(b)])
     assert np.isfinite(y[keep]).all()
+    assert live or np.isfinite(dx).all()         # the backward's weights are made from the log-sum-exp
     assert rel_fro(y[keep], np.asarray(orc.Y[0])[keep]) <= TOL[dtype]
 
 
-@pytest.mark.parametrize("shape", SHAPES, ids=IDS)
+@pytest.mark.parametrize("shape", SHAPES, ids=IDS[:len(SHAPES)])
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")], ids=["nan", "inf"])
 def test_a_token_that_is_not_finite_stays_causal(shape, bad):
     import paper_2401_10241_amd as zb
@@ -109,7 +116,7 @@ def bf16_half_ulp(x):
     return 2.0 ** (np.floor(np.log2(np.maximum(np.abs(x), 1e-38))) - 8)
 
 
-@pytest.mark.parametrize("shape", [s for s in SHAPES if s[0] == "bf16"], ids=IDS[2:])
+@pytest.mark.parametrize("shape", [s for s in SHAPES if s[0] == "bf16"], ids=IDS[2:len(SHAPES)])
 def test_probabilities_keep_24_bits_in_the_products(shape):
     # Every column of W_qkv picks one input feature and W_o is a permutation, so Q, K, V and dO are columns of the
     # stashed LayerNorm output and output gradient, exactly, and the attention's results have a reference in 64 bits
