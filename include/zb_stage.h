@@ -311,8 +311,9 @@ zb_status zb_optimizer_step_validated(zb_stage* st, const zb_global_state* gs, z
  *   hip_stream     hipStream_t or NULL; the call only enqueues kernels (no synchronisation, no memset,
  *                  no hipMalloc / hipFree), so it may be captured into a graph
  * ZB_EINVAL for null pointers, misaligned grads or n outside the range above (nothing is launched then);
- * ZB_EDEVICE if a HIP call fails.  All calls on one GPU share the array: calls that overlap on one GPU
- * (different streams without ordering between them) race; calls on one stream are safe. */
+ * ZB_EDEVICE if a HIP call fails.  All calls on one GPU share the array: of calls that overlap on one GPU
+ * (different streams without ordering between them) any may write a wrong result or none; calls on one stream, and
+ * calls after such an overlap, are safe. */
 #define ZB_GRAD_NORM_STATIC_MAX_FLOATS ((size_t)1 << 30)
 zb_status zb_grad_norm_static(const float* grads, size_t n, double* sq_out, int32_t* nonfinite_out,
                               void* hip_stream);

@@ -3,7 +3,6 @@
 // Every decision (step or not, gradient scale, rollback, redo) is taken by a one-thread kernel
 // that writes predicates into OptDevState; the heavy kernels read them and return at once when
 // switched off, so the host never waits between the steps of the protocol.
-#include <atomic>
 #include <mutex>
 
 #include "../../include/zb_stage.h"
@@ -101,8 +100,10 @@ __global__ __launch_bounds__(256) void grad_sumsq_mid_kernel(const double* __res
              out_sq + blockIdx.x, out_nf + blockIdx.x);
 }
 
-// The whole sum of up to kSumsqOnceWgs workgroups in one launch: the one that is through last (`done` counts them and goes
-// back to 0) adds the partials, which are written and read past the caches of the XCDs.  A second launch that waits for
+// The whole sum of up to kSumsqOnceWgs workgroups in one launch: the one that is through last adds the partials, which are
+// written and read past the caches of the XCDs.  `done` counts the workgroups modulo their number in one atomic operation,
+// so it is 0 again after any number of launches of this size, also of launches that overlapped and whose counts were mixed.
+// A second launch that waits for
 // the first costs 4 us; the count costs about 30 ns a workgroup, so these are of 1024 threads.  us per call, two launches /
 // one with 256 threads / one with 1024: 2^20 gradients 9.7 / 8.6 / 5.3, 2^22 - / 25.5 / 9.3, 2^16 - / 4.2 / 4.4.
 constexpr size_t kSumsqOnceWgs = 256, kSumsqOnceWg4 = 1024 * kSumsqPerThread;
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(1024) void grad_sumsq_once_kernel(const float4* __r
   if (threadIdx.x == 0) {
     __hip_atomic_store(partial_sq + blockIdx.x, sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(partial_nf + blockIdx.x, flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+    last = __builtin_amdgcn_atomic_inc32(done, gridDim.x - 1, __ATOMIC_ACQ_REL, "agent") == gridDim.x - 1;
   }
   __syncthreads();
   if (!last) return;
@@ -125,7 +126,6 @@ __global__ __launch_bounds__(1024) void grad_sumsq_once_kernel(const float4* __r
     *sq = __hip_atomic_load(partial_sq + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     *nf = __hip_atomic_load(partial_nf + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }, out_sq, out_nf);
-  if (threadIdx.x == 0) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // one workgroup; partial sums are added in a fixed order
@@ -327,15 +327,19 @@ size_t grad_sumsq_partials(size_t n) {
   return p1 + p2;
 }
 
-// one launch or the three levels; the result goes to *out_sq / *out_nf (device).  *done is 0 and is 0 again afterwards.
+// workgroups of the single launch that n gradients take, 0: three launches
+static unsigned sumsq_once_wgs(size_t n) {
+  return n / 4 <= kSumsqOnceWgs * kSumsqOnceWg4 ? (unsigned)((n / 4 + kSumsqOnceWg4 - 1) / kSumsqOnceWg4) : 0;
+}
+// one launch or the three levels; the result goes to *out_sq / *out_nf (device).  *done belongs to launches of this many
+// workgroups alone; it is 0 and is 0 again afterwards.
 static hipError_t sumsq_levels(const float* g, size_t n, double* partial_sq, int* partial_nf, unsigned* done, double* out_sq,
                                int* out_nf, hipStream_t s) {
   if (n % 4 != 0 || n == 0) return hipErrorInvalidValue;
   const size_t n4 = n / 4;
   const size_t p1 = (n4 + kSumsqWg4 - 1) / kSumsqWg4, p2 = (p1 + kSumsqFan - 1) / kSumsqFan;
   if (p1 > ((size_t)1 << 31) - 1) return hipErrorInvalidValue;
-  if (n4 <= kSumsqOnceWgs * kSumsqOnceWg4) {  // (at most kSumsqOnceWgs <= p1 partials, or one)
-    const unsigned wgs = (unsigned)((n4 + kSumsqOnceWg4 - 1) / kSumsqOnceWg4);
+  if (const unsigned wgs = sumsq_once_wgs(n)) {  // (wgs <= p1 partials)
     grad_sumsq_once_kernel<<<wgs, 1024, 0, s>>>((const float4*)g, n4, partial_sq, partial_nf, done, out_sq, out_nf);
     return hipGetLastError();
   }
@@ -422,9 +426,10 @@ constexpr size_t kStaticMaxFloats = (size_t)1 << 30;  // == ZB_GRAD_NORM_STATIC_
 constexpr size_t kStaticP1 = (kStaticMaxFloats / 4 + zb::kSumsqWg4 - 1) / zb::kSumsqWg4;
 constexpr size_t kStaticPartials = kStaticP1 + (kStaticP1 + zb::kSumsqFan - 1) / zb::kSumsqFan;
 constexpr size_t kStaticSqBytes = (kStaticPartials * sizeof(double) + 255) / 256 * 256;
-// Counters of calls that finish in one launch, taken in turn: each goes back to zero with its call, and calls that
-// overlap (and so spoil each other's partials) do not share one and leave nothing wrong behind.
-constexpr unsigned kDoneSlots = 256, kDoneStride = 64;
+// One counter for each number of workgroups that a single launch may have: it is zero after any calls of that size, so
+// calls that overlap (and spoil each other's partials and counts) leave nothing wrong behind, and a call captured into a
+// graph may be replayed between any others.
+constexpr size_t kDoneSlots = zb::kSumsqOnceWgs, kDoneStride = 64;
 constexpr size_t kStaticNfBytes = (kStaticPartials * sizeof(int) + 255) / 256 * 256;
 constexpr size_t kStaticBytes = kStaticSqBytes + kStaticNfBytes + kDoneSlots * kDoneStride;  // about 3.2 MB
 static_assert(kStaticMaxFloats == ZB_GRAD_NORM_STATIC_MAX_FLOATS, "header and kernel file disagree");
@@ -467,10 +472,9 @@ extern "C" zb_status zb_grad_norm_static(const float* grads, size_t n, double* s
   int* partial_nf = reinterpret_cast<int*>(reinterpret_cast<unsigned char*>(base) + kStaticSqBytes);
   // every partial the later levels read is written by the level before it in the same call; only the counters
   // start at zero (as the array does) and each is zero again when its call is through
-  static std::atomic<unsigned> next{0};
-  const unsigned slot = next.fetch_add(1, std::memory_order_relaxed) % kDoneSlots;
+  const unsigned wgs = zb::sumsq_once_wgs(n);
   unsigned* done = reinterpret_cast<unsigned*>(reinterpret_cast<unsigned char*>(base) + kStaticSqBytes + kStaticNfBytes +
-                                               slot * kDoneStride);
+                                               (wgs ? wgs - 1 : 0) * kDoneStride);
   const hipError_t e =
       zb::sumsq_levels(grads, n, partial_sq, partial_nf, done, sq_out, nonfinite_out, (hipStream_t)hip_stream);
   return e == hipSuccess ? ZB_OK : ZB_EDEVICE;

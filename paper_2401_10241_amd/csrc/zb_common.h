@@ -235,7 +235,7 @@ struct OptDevState {
   int outcome;
   float step_coef;       // gradient scale of the next step kernel
   float bc1, bc2;        // 1 - beta1^t, 1 - beta2^t for the step / rollback at time t
-  unsigned sumsq_done;   // workgroups of the running sum of squares that are through; 0 between launches
+  unsigned sumsq_done;   // workgroups of the running sum of squares that are through (all sums of a stage have as many); 0 between launches
   int journal_current;   // the next step writes no journal: it comes after the validation (final), and after a rollback theta, m, v equal the journal anyway
 };
 

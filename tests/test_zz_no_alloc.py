@@ -94,3 +94,46 @@ def test_static_grad_norm_at_the_edges_of_its_workgroups(n):
     assert nf == 1 and sq == np.inf
     again, nf = _static_norm(flat, stream)
     assert nf == 0 and again == first
+
+
+def test_calls_that_overlap_leave_the_counters_at_zero():
+    # Calls on two streams without order between them: their own results are not defined, but every workgroup counts once
+    # and calls of one size share a counter that is taken modulo their workgroups, so the calls after them find it at zero.
+    # More of them than counters, of sizes that finish in one launch (17, 3, 256, 1 and 2 workgroups) and one that does not;
+    # then each size twice, once in a graph captured before the overlap and replayed after it.
+    import torch
+    import paper_2401_10241_amd as zb
+    streams = [torch.cuda.Stream(device="cuda:0") for _ in range(2)]
+    sizes = [17 * 16384 - 4, 3 * 16384, 1 << 22, 4, 16388, (1 << 22) + 4]
+    g = torch.randn(max(sizes), generator=torch.Generator(device="cuda").manual_seed(3), device="cuda")
+    sq = torch.zeros(3, dtype=torch.float64, device="cuda")
+    nf = torch.zeros(3, dtype=torch.int32, device="cuda")
+
+    def call(n, out, stream):
+        zb.binding.grad_norm_static(g.data_ptr(), n, sq.data_ptr() + 8 * out, nf.data_ptr() + 4 * out, stream.cuda_stream)
+
+    def result(out):
+        torch.cuda.synchronize()
+        got = float(sq[out].item()), int(nf[out].item())
+        sq[out], nf[out] = -1.0, -1
+        return got
+
+    torch.cuda.synchronize()
+    want, graphs = {}, {}
+    for n in sizes:
+        call(n, 2, streams[0])
+        want[n] = result(2)
+        assert want[n][1] == 0 and want[n][0] > 0
+        graphs[n] = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graphs[n], stream=streams[0]):
+            call(n, 2, streams[0])
+        torch.cuda.synchronize()
+    for k in range(300):
+        for i, stream in enumerate(streams):
+            call(sizes[(k * (i + 1)) % len(sizes)], i, stream)
+    result(0), result(1)
+    for n in sizes:
+        call(n, 2, streams[1])
+        assert result(2) == want[n], n
+        graphs[n].replay()
+        assert result(2) == want[n], n
