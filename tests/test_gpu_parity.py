@@ -585,6 +585,31 @@ def test_gelu_of_pre_activations_whose_cube_overflows(cfg):
     assert np.array_equal(dF, np.outer(dy[:, 0], x > 0))
 
 
+@pytest.mark.parametrize("cfg", GELU_SHAPES, ids=lambda c: "h%d_a%d_f%d_s%d_b%d" % c)
+def test_gelu_and_its_derivative_keep_24_bits(cfg):
+    # What is stored is a bf16, but where the exact value lies further from the middle of two bf16 than the fp32 value's
+    # error, that error decides nothing.  For x >= 0 both are sums of a term and a smaller one: 2^-24 for the rounding of the
+    # sum, as much for the smaller term's own, 2^-24 from the exponential (2^-23 of it, a quarter of which at most is in the
+    # sum), and for dF one more for the product with dG: 2^-22 in all.  (The derivative with s (1 - s) from 1 - s is up to
+    # 2e-6 off = 8 x 2^-22, one from an fp32 tanh 5.6e-7.)
+    hidden, heads, ffn, seq, b = cfg
+    rng = np.random.default_rng(659)
+    grid = np.concatenate([np.float32(2.0) ** e * (1.0 + np.arange(128, dtype=np.float32) / 128) for e in range(-6, 4)])
+    x = np.resize(rng.permutation(grid[grid < 12.0]), ffn)             # bf16 values: the backward reads the stored one
+    dy = 1.0 + rng.integers(0, 128, (seq * b, 2)) / 128.0
+    G, dF = gelu_by_column(cfg, x, dy)
+    X = x.astype(np.longdouble)
+    c, a = np.sqrt(2 / np.longdouble(np.pi)), np.longdouble("0.044715")
+    w = 1 / (1 + np.exp(2 * c * (X + a * X ** 3)))
+    slope = (1 - w) + 2 * X * w * (1 - w) * c * (1 + 3 * a * X ** 2)
+    for name, got, want in (("G", G, np.broadcast_to((X * (1 - w)).astype(np.float64), G.shape)),
+                            ("dF", dF, np.outer(dy[:, 0] + dy[:, 1] / 256, slope.astype(np.float64)))):
+        half_ulp = 2.0 ** (np.floor(np.log2(got.astype(np.float64))) - 8)
+        off = float((np.maximum(np.abs(got - want) - half_ulp, 0) / want).max())
+        print(f"[{cfg}] {name}: {off * 2 ** 22:.2f} x 2^-22 beyond the stored value's rounding", flush=True)
+        assert off <= 2.0 ** -22, (name, off)
+
+
 @pytest.mark.parametrize("cfg", [
     # hidden, heads, ffn, seq, b       row blocks and groups of waves of the attention (128-row blocks of a launch)
     (256, 4, 512, 128, 3),       # head size 64, 12 whole blocks: 64 rows, two groups; the first blocks have one tile
