@@ -9,7 +9,7 @@
 // rows reading the same columns (16-byte fragment reads) then hit 16 different positions, and the four
 // rows that 32 lanes of a transposing read (ds_read_b64_tr_b16, 64 B from each row) touch fall into the four
 // quarters of the banks.
-#include "zb_common.h"
+#include "attention_rows.h"
 
 namespace zb {
 
@@ -184,14 +184,14 @@ __global__ __launch_bounds__(512, 2) void attn_fwd128_kernel(const bf16_t* __res
           mx = fmaxf(mx, x);
         }
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float m_new = fmaxf(m, mx);
-      const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+      const float m_new = fmaxf(m, mx), ref = softmax_ref(m_new);
+      const float alpha = __builtin_amdgcn_exp2f(m - ref);
       float rs = 0.f;
 #pragma unroll
       for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-          const float p = __builtin_amdgcn_exp2f(st[t][v] - m_new);
+          const float p = __builtin_amdgcn_exp2f(st[t][v] - ref);
           st[t][v] = p;
           rs += p;
         }
@@ -233,8 +233,8 @@ __global__ __launch_bounds__(512, 2) void attn_fwd128_kernel(const bf16_t* __res
   {
     // a wave of group 1 that saw no unmasked key has m = -inf, l = 0, o = 0: its factor is 0
     const float m1 = xm[(wave * 2 + 0) * 64 + lane], l1 = xm[(wave * 2 + 1) * 64 + lane];
-    const float m_new = fmaxf(m, m1);  // group 0 always holds key 0: finite
-    const float a0 = __builtin_amdgcn_exp2f(m - m_new), a1 = __builtin_amdgcn_exp2f(m1 - m_new);
+    const float m_new = fmaxf(m, m1), ref = softmax_ref(m_new);
+    const float a0 = __builtin_amdgcn_exp2f(m - ref), a1 = __builtin_amdgcn_exp2f(m1 - ref);
     l = l * a0 + l1 * a1;
     m = m_new;
 #pragma unroll

@@ -22,6 +22,8 @@ SHAPES = [
 WHOLE = [
     ("bf16", 128, 2, 128, 1),       # head size 64, two groups of waves with one tile each
     ("bf16", 128, 2, 512, 1),       # eight tiles
+    ("bf16", 192, 2, 128, 1),       # head size 96
+    ("bf16", 256, 2, 384, 1),       # head size 128, six tiles
 ]
 IDS = ["%s_h%d_a%d_s%d_b%d" % c for c in SHAPES + WHOLE]
 
