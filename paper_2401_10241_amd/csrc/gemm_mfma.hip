@@ -49,8 +49,6 @@
 namespace zb {
 
 // gemm_mfma_edge.hip: other tiles for sizes that the 256-column tiles do not take or do not fill the chip with
-double split_cost(int M, int N, int slices, bool rides);
-void choose_edge(int M, int N, int K, size_t workspace_floats, bool rides, int* tile, int* slices, double* us);
 hipError_t launch_gemm_edge(const GemmArgs& g, long lda, long ldb, int tile, int slices, hipStream_t s);
 hipError_t launch_wgrad_multi_edge(const WgradMultiArgs& w, hipStream_t s, bool* taken);
 
@@ -565,46 +563,30 @@ void finish_split_k(const GemmArgs& g, int slices, size_t plane, hipStream_t s, 
   *err = hipGetLastError();
 }
 
-// Few tiles and a long K (the N = hidden GEMMs of a 1024-token microbatch): cut K into slices so that
-// every CU gets a workgroup.  Returns false if the shape is not one for split-K.
-template <int MODE>
-bool try_split_k(const GemmArgs& g, long lda, long ldb, hipStream_t s, hipError_t* err) {
-  if (g.M % 256 != 0 || g.N % BN != 0 || g.N % 4 != 0 || g.K < 2048 || !g.workspace) return false;
-  const long tiles = (long)(g.M / 256) * (g.N / BN);
-  if (tiles > 128) return false;
-  int slices = (int)(256 / tiles);
-  if (slices > 4) slices = 4;
-  const size_t plane = (size_t)g.M * g.N;
-  if (slices < 2 || (size_t)slices * plane > g.workspace_floats) return false;
-  GemmArgs p = g;
-  p.epilogue = EPI_PARTIAL;
-  p.outf = g.workspace;
-  *err = run_cfg<256, 4, EPI_PARTIAL, 3>(p, lda, ldb, s, slices);
-  if (*err != hipSuccess) return true;
-  finish_split_k<MODE>(g, slices, plane, s, err);
-  return true;
-}
-
 // A little more than a whole number of rounds of 256 x 256 tiles over the 256 CUs (N = ffn with 1024
 // tokens: 320 tiles): the full rounds run as they are and the tile columns left over are cut along K so
 // that they, too, fill every CU once instead of occupying a quarter of the chip for a whole round.
-template <int MODE>
-bool try_tail_split(const GemmArgs& g, long lda, long ldb, hipStream_t s, hipError_t* err) {
-  if (g.M % 256 != 0 || g.N % BN != 0 || g.K < 2048 || !g.workspace) return false;
+struct Tail {
+  int cols = 0, slices = 0;  // tile columns past the last full round (0: none worth it), the slices they are cut into
+};
+inline Tail tail_of(const GemmArgs& g) {
+  if (g.M % 256 != 0 || g.K < 2048 || !g.workspace) return {};
   const int tm = g.M / 256, tn = g.N / BN;
-  if ((long)tm * tn <= 256 || tm > 256 || 256 % tm != 0) return false;
-  const int cols_per_round = 256 / tm;
-  const int tail_cols = tn % cols_per_round;
-  if (tail_cols == 0 || tail_cols * tm > 128) return false;
-  int slices = 256 / (tail_cols * tm);
-  if (slices > 4) slices = 4;
-  const int n_main = (tn - tail_cols) * BN, n_tail = tail_cols * BN;
+  if ((long)tm * tn <= 256 || tm > 256 || 256 % tm != 0) return {};
+  const int cols = tn % (256 / tm);
+  if (cols == 0 || cols * tm > 128) return {};
+  const int slices = 256 / (cols * tm) < 4 ? 256 / (cols * tm) : 4;
+  return (size_t)slices * g.M * cols * BN > g.workspace_floats ? Tail{} : Tail{cols, slices};
+}
+template <int MODE>
+hipError_t run_tail_split(const GemmArgs& g, long lda, long ldb, hipStream_t s, Tail tail) {
+  const int slices = tail.slices;
+  const int n_tail = tail.cols * BN, n_main = g.N - n_tail;
   const size_t plane = (size_t)g.M * n_tail;
-  if ((size_t)slices * plane > g.workspace_floats) return false;
   GemmArgs a = g;
   a.N = n_main;
-  *err = run_cfg<256, 4, MODE, 3>(a, lda, ldb, s, 1, g.N);
-  if (*err != hipSuccess) return true;
+  hipError_t e = run_cfg<256, 4, MODE, 3>(a, lda, ldb, s, 1, g.N);
+  if (e != hipSuccess) return e;
   GemmArgs t = g;  // the same GEMM on columns n_main .. N-1
   t.N = n_tail;
   t.B = (const bf16_t*)g.B + n_main;
@@ -615,77 +597,110 @@ bool try_tail_split(const GemmArgs& g, long lda, long ldb, hipStream_t s, hipErr
   GemmArgs p = t;
   p.epilogue = EPI_PARTIAL;
   p.outf = g.workspace;
-  *err = run_cfg<256, 4, EPI_PARTIAL, 3>(p, lda, ldb, s, slices);
-  if (*err != hipSuccess) return true;
+  e = run_cfg<256, 4, EPI_PARTIAL, 3>(p, lda, ldb, s, slices);
+  if (e != hipSuccess) return e;
   EpiParams epi = make_epi(t);
   epi.N = g.N;
   const size_t threads = plane / 4;
   gemm_splitk_fixup_kernel<MODE><<<(unsigned)((threads + 255) / 256), 256, 0, s>>>(g.workspace, slices, plane, n_tail,
                                                                                  epi);
-  *err = hipGetLastError();
-  return true;
+  return hipGetLastError();
 }
 
-// Microseconds the 256-column tiles below are expected to take where they do not fill the chip even once (at most
-// 128 tiles of 256 x 256): a step of 32 k takes 0.42 us with few 256-row tiles and 0.85 with one per CU (128-row
-// tiles: 0.35 and 0.60).  A larger product is theirs without asking: 1024 x 9216 x 2304 (144 tiles) 55.3 us on them and
-// 55.5 on 128 x 128 ones, 6144 x 2304 x 2304 65.8 and 74.5.
-double big_tile_us(const GemmArgs& g, bool rides) {
-  if ((long)g.M * g.N > 128L * 256 * BN) return 0;
-  const int steps = g.K / KS;
-  if (g.M % 256 == 0 && g.K >= 2048 && g.workspace) {  // try_split_k's tiles
-    const long tiles = (long)(g.M / 256) * (g.N / BN);
-    const int slices = (int)(256 / tiles) < 4 ? (int)(256 / tiles) : 4;
-    if ((size_t)slices * g.M * g.N <= g.workspace_floats)
-      return 3.0 + (double)(steps / slices) * (0.42 + 0.43 * tiles * slices / 256) + split_cost(g.M, g.N, slices, rides);
+// The tiles that a product may be cut into, and the microseconds a launch of each takes: `start` for the launch and the
+// fill of its ring, then for every round of the workgroups that the chip holds at once the steps of a workgroup (`few`
+// with one on the chip, `all` with one on every CU; `over` with one more than that, `twice` with two on every CU; linear
+// between) and an epilogue (2.9 times as long where a second matrix is read or written; none where K slices leave planes), but
+// no less than the weights take to come from memory (us per 10^6 of them).  K slices add a launch that adds the planes (3.8 us,
+// or 2.6 if it takes a LayerNorm over that runs anyway) and 1.7 us per 10^6 floats of planes, written and read.
+//
+// Fitted to 22 000 timings, back to back: every tile with up to four slices for the products of stages of hidden 96 to 6144, 128
+// to 6144 tokens (2447 products, 757 of them with a LayerNorm behind).  The figures tell the time of a launch within 9 % on
+// average, and which is the shortest: what is chosen takes 0.4 % longer than the shortest on average, 2.6 % in one of 20
+// products, 22 % at most.  A rule that took 256-column tiles wherever they fill half the chip and asked for the cost of the
+// others alone took 2.3 % longer, 13 % in one of 20 (6144 x 320 x 320 6.9 -> 5.8 us, 192 x 512 x 2048 10.3 -> 8.6,
+// 512 x 15360 x 5120 102 -> 79).
+struct Tile {
+  int rows, cols, k, at_once;
+  double start, few, all, over, twice, epilogue, weights;
+};
+enum { kTile64, kTile128, kTile256, kTile128x256, kTile128x256Two, kTileTail };
+constexpr Tile kTiles[] = {
+    {64, 64, 64, 512, 1.6, 0.20, 0.29, 0.42, 0.48, 0.8, 0.63},   // gemm_mfma_edge.hip, any size
+    {128, 128, 64, 256, 2.7, 0.41, 0.53, 0, 0, 1.2, 0.21},       // likewise
+    {256, 256, 32, 256, 3.2, 0.53, 0.62, 0, 0, 4.1, 0.21},       // whole tiles, as the two below
+    {128, 256, 32, 256, 1.5, 0.36, 0.46, 0, 0, 2.2, 0.21},
+    {128, 256, 32, 512, 9.1, 0.45, 0.58, 0.82, 0.88, 0, 0.21},   // two workgroups per CU: one's loop hides the other's epilogue
+};
+double rounds_us(const Tile& t, long tiles, int steps, double epilogue) {
+  auto round = [&](long r) {  // with r workgroups on the chip
+    const double step = r <= 256 ? t.few + (t.all - t.few) * r / 256 : t.over + (t.twice - t.over) * (r - 256) / 256;
+    return steps * step + epilogue * t.epilogue;
+  };
+  return (tiles / t.at_once) * round(t.at_once) + (tiles % t.at_once ? round(tiles % t.at_once) : 0.0);
+}
+double planes_us(double floats, bool rides) { return (rides ? 2.6 : 3.8) + 1.7e-6 * floats; }
+
+struct Plan {
+  int tile = -1, slices = 1;  // tile -1: no tile takes the shape
+  Tail tail;                  // kTileTail: 256 x 256 tiles with the last columns in slices
+};
+// rides: a LayerNorm on the output's rows, which the launch that adds K slices takes over (finish_split_k)
+Plan choose_tile(const GemmArgs& g, int mode, bool rides) {
+  Plan best;
+  double us = 1e30;
+  auto take = [&](double c, int tile, int slices, Tail tail) {
+    if (c < us) { us = c; best.tile = tile; best.slices = slices; best.tail = tail; }
+  };
+  const bool whole = g.K % 64 == 0 && g.M % 128 == 0 && g.N % BN == 0;
+  const double epilogue = mode == EPI_STORE || mode == EPI_BIAS ? 1.0 : 2.9;
+  const size_t plane = (size_t)g.M * g.N, room = g.workspace ? g.workspace_floats : 0;
+  const int blocks = (g.K + 63) / 64;
+  for (int i = kTile64; i <= kTile128x256Two; ++i) {
+    const Tile& t = kTiles[i];
+    if (i <= kTile128 ? g.N % 8 != 0 : !whole || g.M % t.rows != 0) continue;
+    const long tiles = (long)((g.M + t.rows - 1) / t.rows) * ((g.N + t.cols - 1) / t.cols);
+    for (int sl = 1; sl <= (i <= kTile256 ? 4 : 1); ++sl) {
+      const int per = (blocks + sl - 1) / sl;
+      if (sl > 1 && (sl * plane > room || (sl - 1) * per >= blocks)) continue;  // no room; an empty slice
+      const double c = rounds_us(t, tiles * sl, per * (64 / t.k), sl > 1 ? 0.0 : epilogue);
+      const double mem = t.weights * 1e-6 * g.N * g.K;
+      take(t.start + (c > mem ? c : mem) + (sl > 1 ? planes_us((double)sl * plane, rides) : 0.0), i, sl, {});
+    }
   }
-  const long t128 = (long)(g.M / 128) * (g.N / BN);  // at most 256: one round
-  return 3.0 + steps * (0.35 + 0.25 * t128 / 256);
-}
-
-// The other tiles (gemm_mfma_edge.hip)
-template <int MODE>
-hipError_t run_edge_shape(const GemmArgs& g, long lda, long ldb, hipStream_t s, int tile, int slices) {
-  if (slices == 1) return launch_gemm_edge(g, lda, ldb, tile, 1, s);
-  GemmArgs p = g;
-  p.epilogue = EPI_PARTIAL;
-  p.outf = g.workspace;
-  hipError_t e = launch_gemm_edge(p, lda, ldb, tile, slices, s);
-  if (e != hipSuccess) return e;
-  finish_split_k<MODE>(g, slices, (size_t)g.M * g.N, s, &e);
-  return e;
+  const Tail tail = whole ? tail_of(g) : Tail{};
+  if (tail.cols) {
+    const Tile& t = kTiles[kTile256];
+    const int tm = g.M / 256;
+    take(2 * t.start + rounds_us(t, (long)tm * (g.N / BN - tail.cols), blocks * 2, epilogue) +
+             rounds_us(t, (long)tm * tail.cols * tail.slices, (blocks + tail.slices - 1) / tail.slices * 2, 0.0) +
+             planes_us((double)tail.slices * g.M * tail.cols * BN, false),
+         kTileTail, tail.slices, tail);
+  }
+  return best;
 }
 
 template <int MODE>
 hipError_t run_shape(const GemmArgs& g, long lda, long ldb, hipStream_t s, bool* taken) {
-  *taken = true;
-  hipError_t e = hipSuccess;
-  int tile = 0, slices = 1;
-  double edge_us = 1e30;
-  // a LayerNorm on the output's rows, which the launch that adds K slices takes over (finish_split_k)
   const bool rides = g.ln_done && g.N <= 8192 && (MODE == EPI_BIAS_RESID ? g.ln_mode == 1 : MODE == EPI_STORE && g.ln_mode == 2);
-  if (g.N % 8 == 0)
-    choose_edge(g.M, g.N, g.K, g.workspace ? g.workspace_floats : 0, rides, &tile, &slices, &edge_us);
-  // Sizes that the 256-column tiles take stay with them unless the other tiles are clearly shorter: 256 x 1024 x
-  // 1024 15.6 -> 6.8 us, 1024 x 2304 x 2304 34.2 -> 18.5, 1024 x 4096 x 4096 49.0 -> 34.4, 3072 x 2304 x 2304 51.5 -> 37.5.
-  if (g.K % 64 != 0 || g.M % 128 != 0 || g.N % BN != 0 || edge_us < 0.9 * big_tile_us(g, rides)) {
-    if (tile) return run_edge_shape<MODE>(g, lda, ldb, s, tile, slices);
-    *taken = false;
-    return hipSuccess;
+  const Plan plan = choose_tile(g, MODE, rides);
+  *taken = plan.tile >= 0;
+  if (!*taken) return hipSuccess;
+  const int edge = plan.tile == kTile64 ? 64 : 128;
+  if (plan.tile == kTileTail) return run_tail_split<MODE>(g, lda, ldb, s, plan.tail);
+  if (plan.slices > 1) {
+    GemmArgs p = g;
+    p.epilogue = EPI_PARTIAL;
+    p.outf = g.workspace;
+    hipError_t e = plan.tile == kTile256 ? run_cfg<256, 4, EPI_PARTIAL, 3>(p, lda, ldb, s, plan.slices)
+                                         : launch_gemm_edge(p, lda, ldb, edge, plan.slices, s);
+    if (e == hipSuccess) finish_split_k<MODE>(g, plan.slices, (size_t)g.M * g.N, s, &e);
+    return e;
   }
-  if (try_split_k<MODE>(g, lda, ldb, s, &e)) return e;
-  if (try_tail_split<MODE>(g, lda, ldb, s, &e)) return e;
-  // Rounds of tiles over the 256 CUs times the tile height; the taller tile does about 1.25x the
-  // work per cycle, so it wins only when it does not cost an extra, mostly empty round.
-  const long t256 = g.M % 256 == 0 ? (long)(g.M / 256) * (g.N / BN) : 0;
-  const long t128 = (long)(g.M / 128) * (g.N / BN);
-  const double c256 = t256 ? (double)((t256 + 255) / 256) * 256.0 / 1.25 : 1e30;
-  if (c256 <= (double)((t128 + 255) / 256) * 128.0) return run_cfg<256, 4, MODE, 3>(g, lda, ldb, s);
-  // more tiles than CUs: a three-stage ring (<= 80 KB) lets two workgroups share a CU, so one's
-  // epilogue and pipeline fill hide behind the other's MFMAs; otherwise one workgroup per CU with a
-  // deeper ring
-  if (t128 > 256) return run_cfg<128, 3, MODE>(g, lda, ldb, s);
-  return run_cfg<128, 5, MODE>(g, lda, ldb, s);
+  if (plan.tile == kTile256) return run_cfg<256, 4, MODE, 3>(g, lda, ldb, s);
+  if (plan.tile == kTile128x256) return run_cfg<128, 5, MODE>(g, lda, ldb, s);
+  if (plan.tile == kTile128x256Two) return run_cfg<128, 3, MODE>(g, lda, ldb, s);
+  return launch_gemm_edge(g, lda, ldb, edge, 1, s);
 }
 
 template <int BM, int BS>

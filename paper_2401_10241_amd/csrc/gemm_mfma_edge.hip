@@ -16,7 +16,7 @@
 // What bounds them: at these sizes a GEMM is a chain of K / 64 steps on a chip that is filled once or less, so
 // the latency of a step (barrier, LDS -> fragments, MFMA) times the number of steps is the time, and with two 64 x 64
 // workgroups on a CU what it can fetch from L2 (about 100 GB/s); smaller tiles and K slices shorten the chain or use
-// more CUs (the rule is at `edge_cost`).  The steps overlap as `ring_steps` says.  Measured (M x N x K with a bias
+// more CUs (the rule is at `kTiles` in gemm_mfma.hip).  The steps overlap as `ring_steps` says.  Measured (M x N x K with a bias
 // epilogue, us per launch back to back; fragments read and used in the same step, 32x32x16 MFMAs -> now): 1024 x 2304 x 2304
 // 25.7 -> 18.3, 512 x 2048 x 2048 13.7 -> 10.4, 256 x 3072 x 2048 12.8 -> 10.4, 777 x 3600 x 1200 17.1 -> 14.6, 1024 x 4096 x
 // 4096 (256-column tiles and the launch that adds four slices) 49.0 -> 34.4; W of h 1200, 777 tokens, two layers 143 -> 117.
@@ -25,8 +25,6 @@
 #include "gemm_lds.h"
 
 namespace zb {
-
-double split_cost(int M, int N, int slices, bool rides);
 
 namespace {
 
@@ -253,46 +251,6 @@ template <int MODE> hipError_t run_edge_tile(const GemmArgs& g, long lda, long l
 }
 
 }  // namespace
-
-// Microseconds the kernel above is expected to take with this tile and number of K slices, the launch that adds
-// the planes included (`rides`: a LayerNorm that has to run anyway does it).  Fitted to single launches: a step of 64 k
-// takes 0.21 us with one 64 x 64 workgroup on few CUs, 0.26 on all, 0.46 with two (what a CU can fetch from L2 then bounds
-// it), and 0.37 to 0.50 for a 128 x 128 tile; 3 us go to the start, the fill of the ring and the epilogue.  Over 49 shapes
-// from 1 x 64 x 72 to 6144 x 2304 x 2304 with one to four slices the choice it makes costs 0.6 % more than the best
-// measured one on average without a LayerNorm, 3 % with one (most: 100 x 96 x 96 and 1152 x 1536 x 512, 7.6 against 6.6).
-double edge_cost(int M, int N, int K, int tile, int slices, bool rides) {
-  const long tiles = (long)((M + tile - 1) / tile) * ((N + tile - 1) / tile) * slices;
-  const int steps = ((K + 63) / 64 + slices - 1) / slices;
-  const long at_once = tile == 128 ? 256 : 512;
-  auto step = [&](long r) {  // with r workgroups on the chip
-    if (tile == 128) return 0.37 + 0.13 * r / 256;
-    return r <= 256 ? 0.21 + 0.05 * r / 256 : 0.37 + 0.09 * (r - 256) / 256;
-  };
-  const long rounds = tiles / at_once, rest = tiles % at_once;
-  double us = 3.0 + steps * step(at_once) * rounds;
-  if (rest) us += steps * step(rest);
-  if (slices > 1) us += split_cost(M, N, slices, rides);
-  return us;
-}
-
-// Cheapest tile and number of K slices (within the workspace); 512 x 768 x 3072: 13.6 us whole, 8.5 in four slices and
-// 4.5 for the launch that adds them (25.7 on the 256-column tiles).
-void choose_edge(int M, int N, int K, size_t workspace_floats, bool rides, int* tile, int* slices, double* us) {
-  *us = 1e30;
-  const int blocks = (K + 63) / 64;
-  for (int t = 64; t <= 128; t += 64)
-    for (int sl = 1; sl <= 4; ++sl) {
-      if (sl > 1 && (size_t)sl * M * N > workspace_floats) break;
-      const int per = (blocks + sl - 1) / sl;
-      if ((sl - 1) * per >= blocks) continue;  // an empty slice
-      const double c = edge_cost(M, N, K, t, sl, rides);
-      if (c < *us) { *us = c; *tile = t; *slices = sl; }
-    }
-}
-
-// Microseconds that cutting a product into K slices adds: the planes are written and read back, by a launch of
-// its own unless a LayerNorm that runs anyway takes it over.
-double split_cost(int M, int N, int slices, bool rides) { return (rides ? 0.0 : 4.5) + (double)slices * M * N * 1.6e-6; }
 
 // forward / dgrad GEMM with the given tile (128 or 64); slices > 1: the K slices' planes only (g.outf)
 hipError_t launch_gemm_edge(const GemmArgs& g, long lda, long ldb, int tile, int slices, hipStream_t s) {

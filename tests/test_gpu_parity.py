@@ -466,6 +466,22 @@ def test_few_steps_of_the_large_tiles(cfg):
     run_and_compare(W("few", "bf16", 1, hidden, heads, ffn, seq, b, 4, 1, 2, "H2", seed=601 + hidden + b))
 
 
+@pytest.mark.parametrize("cfg", [
+    # hidden, heads, ffn, seq, b       each tile of the products at about the fewest steps that reach it
+    (512, 8, 64, 512, 11),       # QKV on 256 x 256 tiles, 16 steps of 32
+    (1280, 20, 64, 64, 52),      # QKV's backward on them in three slices, 40
+    (64, 1, 768, 64, 86),        # FC1 on 128 x 256 tiles, two
+    (128, 2, 1280, 64, 52),      # four
+    (192, 3, 1280, 64, 52),      # six
+    (64, 1, 1280, 64, 104),      # the same with two workgroups per CU, two
+    (128, 2, 832, 64, 40),       # FC1 on 128 x 128 tiles, two steps of 64
+    (832, 13, 64, 64, 20),       # QKV's backward on them in three slices, thirteen
+], ids=lambda c: "h%d_a%d_f%d_s%d_b%d" % c)
+def test_products_on_each_tile(cfg):
+    hidden, heads, ffn, seq, b = cfg
+    run_and_compare(W("tiles", "bf16", 1, hidden, heads, ffn, seq, b, 4, 1, 1, "H1", seed=691 + hidden + b))
+
+
 @pytest.mark.parametrize("steps", range(1, 8))
 def test_few_steps_of_the_small_tiles(steps):
     # 1 to 7 steps of a ring of five stages, the last one cut: 64 k of the products, 32 tokens of W
