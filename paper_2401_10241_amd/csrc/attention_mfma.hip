@@ -748,15 +748,19 @@ inline bool mfma_shape(const AttnArgs& a) { return a.d >= 8 && a.d <= 128 && a.b
 // which costs where other launches want the chip: three stages at once, us per iteration with one and two groups: 16 heads
 // of 75, 777 tokens 2340 / 2308 with a forward in two, / 2390 with the backward as well; 16 of 40, 178 tokens 1161 / 1184; 4 of
 // 48, 945 tokens 1168 / 1004.  So two groups from 256 tokens on, and in the backward of heads up to 64 columns.
+// Where launches of two groups come near filling the chip the second only shares it (heads x tokens x samples, us with one
+// group / two): forward, whole tiles 40 x 1024 x 3 (960) 46 / 51, 16 x 2048 x 3 (768) 71 / 65; backward 40 x 128 x 3 (120) 12.4 /
+// 14.8, 16 x 128 x 3 (48) 10.9 / 9.6; forward of heads whose columns are staged singly, head 75 40 x 257 x 3 (360) 30 / 35, but
+// 16 x 257 x 3 (144) 28 / 22, 40 x 257 x 3 of head 96 26 / 25.
 inline long blocks128(const AttnArgs& a) { return (long)((a.s + 127) / 128) * a.a * a.b; }
 template <int D, bool EDGE> struct Fwd {
   static hipError_t run(const AttnArgs& a, hipStream_t s) {
     const long n = blocks128(a);
     if constexpr (!EDGE) {
       if (n < 96) return run_fwd<D, 2, 2, EDGE>(a, s);
-      if (n < 512 || (n < 1024 && a.s >= 512)) return run_fwd<D, 4, 2, EDGE>(a, s);
+      if (n < 512 || (n < 896 && a.s >= 512)) return run_fwd<D, 4, 2, EDGE>(a, s);
     } else {
-      if (n < 512 && a.s >= 256) return run_fwd<D, D <= 64 ? 2 : 4, 2, EDGE>(a, s);
+      if (n < 512 && a.s >= (n >= 256 && a.d % 8 != 0 ? 512 : 256)) return run_fwd<D, D <= 64 ? 2 : 4, 2, EDGE>(a, s);
       if constexpr (D == 128)
         if (a.s < 1024 && n >= 352) return run_fwd<D, 2, 1, EDGE>(a, s);
     }
@@ -766,7 +770,7 @@ template <int D, bool EDGE> struct Fwd {
 template <int D, bool EDGE> struct Bwd {
   static hipError_t run(const AttnArgs& a, hipStream_t s) {
     const long n = blocks128(a);
-    if (n <= 128 && (!EDGE || (D <= 64 && a.s >= 256))) return run_bwd<D, 2, 2, EDGE>(a, s);
+    if (EDGE ? n <= 128 && D <= 64 && a.s >= 256 : n <= (a.s >= 256 ? 128 : 64)) return run_bwd<D, 2, 2, EDGE>(a, s);
     if constexpr (!EDGE) {
       return a.s >= 512 ? run_bwd<D, 4, 2, EDGE>(a, s) : run_bwd<D, 2, 1, EDGE>(a, s);
     } else {
