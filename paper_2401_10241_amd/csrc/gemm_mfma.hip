@@ -775,9 +775,12 @@ template <> hipError_t launch_wgrad_multi_mfma<bf16_t>(const WgradMultiArgs& w, 
   // five-stage ring otherwise.  With a short chain the gradient's way in and out is most of the time, and a second
   // workgroup's loop hides it: 256 tokens of h 1024, two layers 50.7 us on 256-row tiles, 42.1 on 128-row ones, 2 x 192 of
   // h 1280 51.4 and 45.7, 2 x 128 of h 2048 95.8 and 88.8, 512 of h 768, four layers 66.1 both, 1024 of h 4096 554 and 559,
-  // 6144 of h 2304 2018 and 2407.  The choice does not change the result (see the kernel).
-  const bool long_chain = (long)w.K * w.ngroup >= 512;
-  if (all256 && t256 >= 192 && (long_chain || t128 <= 256)) return run_wgrad<256, 4>(tb, w.K, s);
+  // 6144 of h 2304 2018 and 2407.  But with up to four steps the second workgroup has too little to hide behind where 256-row
+  // tiles make one round or all but fill two: 128 of h 1024 (192 tiles) 20.3 and 23.3, 192 of it 21.7 and 22.2, 128 of h
+  // 1536 (432) 45.5 and 47.6, of two layers of h 1024 (384) 45.4 and 37.3.  The choice does not change the result (see the kernel).
+  const long chain = (long)w.K * w.ngroup;
+  const bool full_rounds = t256 <= 256 || (t256 > 400 && t256 <= 512);
+  if (all256 && t256 >= 192 && (chain >= 512 || (chain <= 128 && full_rounds))) return run_wgrad<256, 4>(tb, w.K, s);
   if (t128 > 256) return run_wgrad<128, 3>(tb, w.K, s);
   return run_wgrad<128, 5>(tb, w.K, s);
 }

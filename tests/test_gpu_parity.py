@@ -163,6 +163,39 @@ def test_grouped_w_has_the_bits_of_one_by_one_w(shape):
         assert g.tobytes() == results[0].tobytes()
 
 
+@pytest.mark.parametrize("shape", [(1024, 8, 4096, 256, 1, 2), (1024, 8, 4096, 128, 2, 4), (1024, 8, 4096, 128, 1, 4)],
+                         ids=["h1024_s256", "h1024_s128_L2", "h1024_s128"])
+def test_w_bits_do_not_depend_on_the_tiles(shape):
+    # which tiles a W launch takes depends on tokens x microbatches and on the tiles of its layers: at 256 tokens one W
+    # alone runs on 128-row tiles and two together on 256-row ones (192 of them); at 128 tokens the other way round with
+    # one layer, and four together on 256-row ones again; with two layers (the single backward takes one at a time) too
+    import paper_2401_10241_amd as zb
+    hidden, heads, ffn, seq, layers, m = shape
+    w = W("tiles", "bf16", layers, hidden, heads, ffn, seq, 1, 4, 2, m, "1F1B", seed=41)
+    params = zb_inputs.stage_params(w)
+    grads = []
+    for mode in ("one by one", "two by two", "together", "fused"):
+        dev = make_device_stage(w, m, pools=(m, m, m))
+        dev.set_params(params)
+        dev.begin_iteration(0, m)
+        load_iteration(w, 0, m, dev)
+        for k in range(m):
+            dev.forward(k)
+            if mode == "fused":
+                dev.backward_fused(k)
+            else:
+                dev.backward_input(k)
+        n = {"one by one": 1, "two by two": 2, "together": m, "fused": 0}[mode]
+        for k in range(0, m, n) if n else ():
+            dev.backward_weight_group(list(range(k, k + n))) if n > 1 else dev.backward_weight(k)
+        dev.synchronize()
+        grads.append(dev.get_tensor(zb.T_FLAT_GRADS).copy())
+        dev.close()
+    assert np.abs(grads[0]).max() > 0
+    for g in grads[1:]:
+        assert np.array_equal(g.view(np.uint32), grads[0].view(np.uint32))
+
+
 @pytest.mark.parametrize("group", [2, 3])
 def test_w_grouped_order_has_the_bits_of_the_plain_order(group):
     # the order with its steady-state W passes `group` at a time (zb_order_group_w) through zb_run_order: the W of
@@ -414,12 +447,12 @@ SWEEP = [
     (1024, 8, 4096, 200, 1, 1, "bf16"),   # head size 128 but a ragged sequence: attention with edges, 200-token GEMMs
     (384, 4, 1536, 192, 2, 1, "bf16"),    # head size 96
     (256, 2, 1024, 320, 1, 1, "fp32"),    # fp32 arithmetic everywhere
-    (2048, 16, 8192, 512, 1, 1, "bf16"),  # split-K shapes with 512 tokens
+    (2048, 16, 8192, 512, 1, 1, "bf16"),  # 128 x 128 tiles, whole and in four slices
     (1536, 12, 6144, 256, 1, 1, "bf16"),  # wgrad on 128-row tiles, two workgroups per CU (288 tiles for FC1 / FC2)
     (768, 12, 16384, 128, 3, 1, "bf16"),  # 384 tokens, FC1 and its backward on 192 tiles of 128 x 256
     (512, 8, 24576, 128, 3, 1, "bf16"),   # the same on 288, two workgroups per CU
     (1536, 24, 1024, 128, 11, 1, "bf16"), # 1408 tokens, QKV on 198 tiles of 128 x 256
-    (2304, 36, 1024, 128, 11, 1, "bf16"), # the same on 297
+    (2304, 36, 1024, 128, 11, 1, "bf16"), # QKV on 594 of 128 x 128
 ]
 
 
@@ -452,13 +485,14 @@ def test_edge_tiles(cfg):
 
 @pytest.mark.parametrize("cfg", [
     # hidden, heads, ffn, seq, b       products of few steps of 32 k on the large tiles (the pipeline's fill and end)
-    (64, 1, 2048, 64, 68),       # FC1 and FC2's backward: two steps on 256-row tiles
+    (64, 1, 2048, 64, 68),       # FC1 and FC2's backward: two steps on 128-row tiles, two workgroups per CU
     (128, 2, 2048, 64, 68),      # four
     (192, 3, 2048, 64, 68),      # six
-    (64, 1, 2048, 64, 66),       # two on 128-row tiles, two workgroups per CU
+    (64, 1, 2048, 64, 66),       # two, an odd number of tiles
     (256, 4, 24576, 64, 1),      # W: two steps on 256-row tiles
-    (256, 4, 24576, 64, 3),      # six
-    (256, 4, 17920, 64, 1),      # two on 128-row tiles, two workgroups per CU
+    (256, 4, 24576, 64, 2),      # four
+    (256, 4, 24576, 64, 3),      # six on 128-row tiles, two workgroups per CU
+    (256, 4, 17920, 64, 1),      # two
     (256, 4, 1024, 64, 5),       # ten on 128-row tiles, one per CU
 ], ids=lambda c: "h%d_a%d_f%d_s%d_b%d" % c)
 def test_few_steps_of_the_large_tiles(cfg):
