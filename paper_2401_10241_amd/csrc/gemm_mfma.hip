@@ -616,10 +616,13 @@ hipError_t run_tail_split(const GemmArgs& g, long lda, long ldb, hipStream_t s, 
 //
 // Fitted to 22 000 timings, back to back: every tile with up to four slices for the products of stages of hidden 96 to 6144, 128
 // to 6144 tokens (2447 products, 757 of them with a LayerNorm behind).  The figures tell the time of a launch within 9 % on
-// average, and which is the shortest: what is chosen takes 0.4 % longer than the shortest on average, 2.6 % in one of 20
-// products, 22 % at most.  A rule that took 256-column tiles wherever they fill half the chip and asked for the cost of the
-// others alone took 2.3 % longer, 13 % in one of 20 (6144 x 320 x 320 6.9 -> 5.8 us, 192 x 512 x 2048 10.3 -> 8.6,
-// 512 x 15360 x 5120 102 -> 79).
+// average, and which is the shortest: what they choose takes 0.4 % longer than the shortest on average.  But a launch that
+// is a little shorter on much more of the chip costs the launches beside it (777 x 4808 x 1200 alone 22.3 us on 64 x 64
+// tiles, 27.3 on 128 x 128 ones; three stages at once, an iteration of hidden 1200 2370 and 2254 us), so half of what a launch takes of the
+// chip is added: 0.8 % longer than the shortest on average, 6.7 % in one of 20 products, 23 % at most, and 4 % less of the chip.  A rule that
+// took 256-column tiles wherever they fill half the chip and asked for the cost of the others alone took 2.3 % longer, 13 %
+// in one of 20.
+constexpr double kBusy = 0.5;
 struct Tile {
   int rows, cols, k, at_once;
   double start, few, all, over, twice, epilogue, weights;
@@ -639,6 +642,8 @@ double rounds_us(const Tile& t, long tiles, int steps, double epilogue) {
   };
   return (tiles / t.at_once) * round(t.at_once) + (tiles % t.at_once ? round(tiles % t.at_once) : 0.0);
 }
+// What the launch takes of the chip: the time it would have it busy alone if its workgroups were packed without gaps.
+double busy_us(const Tile& t, long tiles, int steps) { return tiles * steps * (t.at_once > 256 ? t.twice : t.all) / t.at_once; }
 double planes_us(double floats, bool rides) { return (rides ? 2.6 : 3.8) + 1.7e-6 * floats; }
 
 struct Plan {
@@ -665,16 +670,19 @@ Plan choose_tile(const GemmArgs& g, int mode, bool rides) {
       if (sl > 1 && (sl * plane > room || (sl - 1) * per >= blocks)) continue;  // no room; an empty slice
       const double c = rounds_us(t, tiles * sl, per * (64 / t.k), sl > 1 ? 0.0 : epilogue);
       const double mem = t.weights * 1e-6 * g.N * g.K;
-      take(t.start + (c > mem ? c : mem) + (sl > 1 ? planes_us((double)sl * plane, rides) : 0.0), i, sl, {});
+      take(t.start + (c > mem ? c : mem) + (sl > 1 ? planes_us((double)sl * plane, rides) : 0.0) +
+               kBusy * busy_us(t, tiles * sl, per * (64 / t.k)),
+           i, sl, {});
     }
   }
   const Tail tail = whole ? tail_of(g) : Tail{};
   if (tail.cols) {
     const Tile& t = kTiles[kTile256];
-    const int tm = g.M / 256;
-    take(2 * t.start + rounds_us(t, (long)tm * (g.N / BN - tail.cols), blocks * 2, epilogue) +
-             rounds_us(t, (long)tm * tail.cols * tail.slices, (blocks + tail.slices - 1) / tail.slices * 2, 0.0) +
-             planes_us((double)tail.slices * g.M * tail.cols * BN, false),
+    const long main = (long)(g.M / 256) * (g.N / BN - tail.cols), rest = (long)(g.M / 256) * tail.cols * tail.slices;
+    const int steps = blocks * 2, rest_steps = (blocks + tail.slices - 1) / tail.slices * 2;
+    take(2 * t.start + rounds_us(t, main, steps, epilogue) + rounds_us(t, rest, rest_steps, 0.0) +
+             planes_us((double)tail.slices * g.M * tail.cols * BN, false) +
+             kBusy * (busy_us(t, main, steps) + busy_us(t, rest, rest_steps)),
          kTileTail, tail.slices, tail);
   }
   return best;
