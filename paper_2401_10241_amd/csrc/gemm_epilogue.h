@@ -41,41 +41,6 @@ __device__ __forceinline__ void epilogue_one(const EpiParams& e, int m, int n, f
   }
 }
 
-// One 32 x 32 MFMA accumulator tile: lane holds column n and the 16 rows m0 + 8*(v/4) + (v%4), v = 0..15
-// (m0 already includes the lane's 4*(lane>>5) offset).  All reads of the tile are issued before any
-// write, so the loads overlap instead of each waiting for the previous store.  (The fp32 accumulate of
-// the wgrad GEMM is not an epilogue in the MFMA path: its kernel starts the accumulators from C.)
-template <typename T, int MODE>
-__device__ __forceinline__ void epilogue_tile(const EpiParams& e, int m0, int n, const f32x16& acc) {
-  size_t idx[16];
-#pragma unroll
-  for (int v = 0; v < 16; ++v) idx[v] = (size_t)(m0 + (v >> 2) * 8 + (v & 3)) * e.N + n;
-  if (MODE == EPI_PARTIAL) {  // e.outf already points at this K slice's [M,N] plane
-#pragma unroll
-    for (int v = 0; v < 16; ++v) e.outf[idx[v]] = acc[v];
-  } else if (MODE == EPI_BIAS_RESID || MODE == EPI_DGELU) {
-    float a[16];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) a[v] = to_f32(((const T*)e.aux)[idx[v]]);
-    const float b = MODE == EPI_BIAS_RESID ? e.bias[n] : 0.f;
-#pragma unroll
-    for (int v = 0; v < 16; ++v)
-      ((T*)e.out0)[idx[v]] = from_f32<T>(MODE == EPI_BIAS_RESID ? acc[v] + b + a[v] : acc[v] * gelu_grad<T>(a[v]));
-  } else if (MODE == EPI_BIAS_GELU) {
-    const float b = e.bias[n];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const float f = acc[v] + b;
-      ((T*)e.out0)[idx[v]] = from_f32<T>(f);
-      ((T*)e.out1)[idx[v]] = from_f32<T>(gelu<T>(f));
-    }
-  } else {
-    const float b = MODE == EPI_BIAS ? e.bias[n] : 0.f;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) ((T*)e.out0)[idx[v]] = from_f32<T>(acc[v] + b);
-  }
-}
-
 // Two accumulators of v_mfma_f32_16x16x32_bf16 side by side (columns 0-15 and 16-31 of a 16 x 32 block; lane l holds
 // column l & 15 and rows 4 (l >> 4) .. + 3 of each) -> column l & 31 and rows 8 (l >> 5) .. + 7, so that a wave's memory
 // access covers 128 bytes of two rows and not 64 of four (32 of sixteen with the block transposed: a W pass over 256 tokens
@@ -122,6 +87,7 @@ template <typename T> __device__ __forceinline__ __attribute__((address_space(1)
 
 // The 16 MT x 16 NT block at (m0, n0) (both the same for the whole wave: the addresses are scalar but for one lane offset).
 // All reads of 16 rows are issued before any of their writes, so they overlap instead of each waiting for a store.
+// (The fp32 accumulate of a wgrad GEMM is not an epilogue here: its kernels start the accumulators from C.)
 template <int MODE, int MT, int NT>
 __device__ __forceinline__ void epilogue_wave(const EpiParams& e, int m0, int n0, int lane, const f32x4 (&acc)[MT][NT]) {
   const unsigned off = rows8_lane_off(e.N, lane);

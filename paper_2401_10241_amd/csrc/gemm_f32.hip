@@ -3,10 +3,11 @@
 //
 // A workgroup owns one output tile and its waves split K between them, 32 k at a time in turn; fragments come
 // straight from memory into registers, and the waves' partial tiles are added through LDS in wave order.  What bounds
-// the products that come here (hundreds of tokens, widths up to a few thousand) is latency, so a wave has the loads of two
-// to four of its blocks in flight before the first product: with one block ahead of the products 128 x 256 x 1024 took
-// 22.5 us (dgrad 12.3).  Small products take 16 x 16 tiles, four times the workgroups: 5.9 us.  The rules are at `kSmallTiles` and
-// `four_waves`.
+// the products that come here (hundreds of tokens, widths up to a few thousand) is latency, so a wave has the loads of four
+// (16 x 16 tiles) or two (32 x 32) of its blocks in flight before the first product: with one block ahead of the products 128 x
+// 256 x 1024 took 22.5 us (dgrad 12.3).  Small products take 16 x 16 tiles, four times the workgroups: 5.9 us.  The 64 x 64 tiles of the
+// largest, which other workgroups' loads keep busy, and the W of four waves, which have one block each, load one at a time.  The
+// rules are at `kSmallTiles` and `four_waves`.
 #include <algorithm>
 
 #include "gemm_epilogue.h"

@@ -103,9 +103,9 @@ __global__ __launch_bounds__(256) void grad_sumsq_mid_kernel(const double* __res
 // The whole sum of up to kSumsqOnceWgs workgroups in one launch: the one that is through last adds the partials, which are
 // written and read past the caches of the XCDs.  `done` counts the workgroups modulo their number in one atomic operation,
 // so it is 0 again after any number of launches of this size, also of launches that overlapped and whose counts were mixed.
-// A second launch that waits for
-// the first costs 4 us; the count costs about 30 ns a workgroup, so these are of 1024 threads.  us per call, two launches /
-// one with 256 threads / one with 1024: 2^20 gradients 9.7 / 8.6 / 5.3, 2^22 - / 25.5 / 9.3, 2^16 - / 4.2 / 4.4.
+// A second launch that waits for the first costs 4 us; the count costs about 30 ns a workgroup, so these are of 1024
+// threads.  us per launch back to back, two launches / one with 256 threads / one with 1024: 2^20 gradients 9.7 / 8.6 / 5.3,
+// 2^22 - / 25.5 / 9.3, 2^16 - / 4.2 / 4.4 (a call of 2^20 among others 7.0, before 9.8).
 constexpr size_t kSumsqOnceWgs = 256, kSumsqOnceWg4 = 1024 * kSumsqPerThread;
 __global__ __launch_bounds__(1024) void grad_sumsq_once_kernel(const float4* __restrict__ g, size_t n4,
                                                                double* __restrict__ partial_sq,

@@ -256,9 +256,9 @@ struct OptHyper {
   float lr, beta1, beta2, eps, weight_decay, clip;
 };
 
-// Sum of squares and non-finite flag of n gradients (n % 4 == 0) in three levels, every sum in a fixed
-// order: per workgroup of 4096 elements, per kSumsqFan of those, then one workgroup.  partial_sq and
-// partial_nf need grad_sumsq_partials(n) entries each.
+// Sum of squares and non-finite flag of n gradients (n % 4 == 0), every sum in a fixed order: up to 2^22 of them in one launch
+// whose last workgroup adds what each makes of 16384, above in three (per workgroup of 4096, per kSumsqFan of
+// those, then one workgroup).  partial_sq and partial_nf need grad_sumsq_partials(n) entries each.
 constexpr int kSumsqFan = 1024;
 size_t grad_sumsq_partials(size_t n);
 hipError_t launch_grad_sumsq(const float* g, size_t n, double* partial_sq, int* partial_nf,
