@@ -17,6 +17,10 @@ SHAPES = [
     ("bf16", 600, 8, 77, 1),        # head size 75, two 64-row tiles
     ("bf16", 128, 4, 130, 2),       # head size 32, two rows past two tiles
     ("bf16", 256, 2, 200, 1),       # head size 128
+    ("bf16", 600, 8, 333, 1),       # from 256 tokens on two groups of waves take the tiles in turn: head size 75, forward
+    ("bf16", 128, 4, 300, 1),       # head size 32, both ways
+    ("bf16", 192, 4, 260, 1),       # 48
+    ("bf16", 256, 2, 300, 1),       # 128, forward
 ]
 # whole tiles: the kernels without edges
 WHOLE = [
@@ -91,7 +95,7 @@ def test_a_token_that_is_not_finite_stays_causal(shape, bad):
     y0 = dev.get_tensor(zb.T_OUTPUT_Y, 0, 0).copy()
     dx0 = dev.get_tensor(zb.T_OUTPUT_DX, 0, 0).copy()
     dev.close()
-    for t in (0, 20, seq - 1):          # a token of the first sample
+    for t in (0, 20, seq - 1) + ((70, 140) if seq > 256 else ()):   # a token of the first sample; in tiles of both groups
         # in the forward only tokens t .. seq-1 of its sample may see it
         Xb = X.copy()
         Xb[t, 3] = bad

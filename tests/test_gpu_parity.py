@@ -667,6 +667,10 @@ def test_gelu_and_its_derivative_keep_24_bits(cfg):
     (256, 4, 512, 256, 20),      # 160 short ones: the backward with one group of 64 rows
     (120, 3, 248, 300, 16),      # head size 40, 144 blocks with edges: the backward with one group of 128 rows
     (80, 2, 160, 257, 2),        # five tiles, both ways with two groups of 64 rows
+    (600, 8, 1208, 333, 1),      # head size 75, six tiles: the forward with two groups of 128
+    (128, 4, 264, 300, 1),       # head size 32, both ways with two groups of 64
+    (320, 5, 640, 128, 20),      # head size 64, 100 whole blocks of one row block each: the backward with one group
+    (1200, 16, 408, 257, 6),     # head size 75, 288 blocks: one group
     (200, 2, 400, 260, 1),       # head size 100: the forward with two groups of 128
     (240, 2, 480, 321, 1),       # head size 120, six tiles
 ], ids=lambda c: "h%d_a%d_f%d_s%d_b%d" % c)
@@ -689,7 +693,8 @@ def test_attention_with_many_heads(cfg):
 
 @pytest.mark.parametrize("cfg", [
     (72, 3, 136, 33, 1, 2),      # widths and tokens cut every tile
-    (512, 4, 2048, 300, 2, 1),   # enough tiles for the 64 x 64 form, 600 tokens ragged
+    (512, 4, 2048, 300, 2, 1),   # 600 tokens ragged, FC1 on 1216 tiles of 32 x 32
+    (256, 4, 3464, 300, 2, 1),   # the same with FC1 on tiles of 64 x 64 (2071 of 32 x 32 would be too many)
     (40, 5, 8, 5, 1, 1),         # contractions shorter than one wave's block of 32
     (160, 8, 320, 161, 1, 1),    # head size 20, six blocks of 32 rows (a wave takes two), the last one row long
     (384, 4, 768, 97, 2, 1),     # head size 96
@@ -722,7 +727,7 @@ def test_fp32_grouped_w_has_the_bits_of_one_by_one_w():
 
 @pytest.mark.parametrize("hidden,heads,ffn,seq,layers,groups", [
     (256, 4, 1024, 160, 2, (9, 1)),  # nine and more microbatches: one layer per W launch instead of both
-    (256, 4, 1024, 128, 2, (9, 1)),  # the same at 128 tokens: 64 x 64 tiles
+    (256, 4, 1024, 128, 2, (9, 1)),  # the same at 128 tokens: four waves a tile
     (160, 5, 640, 160, 4, (5, 5)),   # five microbatches: three layers and one instead of all four
     (1024, 8, 4096, 17, 2, (9, 1)),  # gradients on the vector ALUs, bias sums in a launch of their own
 ], ids=["h256_s160_L2", "h256_s128_L2", "h160_s160_L4", "h1024_s17_L2"])

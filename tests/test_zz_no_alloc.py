@@ -1,8 +1,8 @@
 """zb_grad_norm_static (the entry point for callers that cannot allocate) against the gradient-norm step
 of zb_optimizer_step_validated, through the C ABI: two calls in a row, the second on a smaller input.
 
-Both run the same three fixed-order fp64 reduction levels, so for the same gradient vector the sum of
-squares must agree bit for bit and the non-finite flag exactly; the flat gradient of a stage also has a
+Both run the same fixed-order fp64 sums (one launch up to 2^22 values, three above), so for the same gradient vector
+the sum of squares must agree bit for bit and the non-finite flag exactly; the flat gradient of a stage also has a
 plain definition (sum of squares of its entries), checked in fp64 to 1e-12 relative."""
 import numpy as np
 import pytest
