@@ -614,14 +614,14 @@ hipError_t run_tail_split(const GemmArgs& g, long lda, long ldb, hipStream_t s, 
 // no less than the weights take to come from memory (us per 10^6 of them).  K slices add a launch that adds the planes (3.8 us,
 // or 2.6 if it takes a LayerNorm over that runs anyway) and 1.7 us per 10^6 floats of planes, written and read.
 //
-// Fitted to 22 000 timings, back to back: every tile with up to four slices for the products of stages of hidden 96 to 6144, 128
-// to 6144 tokens (2447 products, 757 of them with a LayerNorm behind).  The figures tell the time of a launch within 9 % on
-// average, and which is the shortest: what they choose takes 0.4 % longer than the shortest on average.  But a launch that
-// is a little shorter on much more of the chip costs the launches beside it (777 x 4808 x 1200 alone 22.3 us on 64 x 64
-// tiles, 27.3 on 128 x 128 ones; three stages at once, an iteration of hidden 1200 2370 and 2254 us), so half of what a launch takes of the
-// chip is added: 0.8 % longer than the shortest on average, 6.7 % in one of 20 products, 23 % at most, and 4 % less of the chip.  A rule that
-// took 256-column tiles wherever they fill half the chip and asked for the cost of the others alone took 2.3 % longer, 13 %
-// in one of 20.
+// Fitted to 22 000 timings, back to back: every tile with up to four slices for the products of stages of hidden 96 to 6144,
+// 128 to 6144 tokens (2447 products, 757 of them with a LayerNorm behind).  The figures tell the time of a launch within 9 %
+// on average, and which is the shortest: what they choose takes 0.4 % longer than the shortest on average.  But a launch
+// that is a little shorter on much more of the chip costs the launches beside it (777 x 4808 x 1200 alone 22.3 us on 64 x 64
+// tiles, 27.3 on 128 x 128 ones; three stages at once, an iteration of hidden 1200 2370 and 2254 us), so half of what a
+// launch takes of the chip is added: 0.8 % longer than the shortest on average, 6.7 % in one of 20 products, 23 % at most,
+// and 4 % less of the chip.  A rule that took 256-column tiles wherever they fill half the chip and asked for the cost of the
+// others alone took 2.3 % longer, 13 % in one of 20.
 constexpr double kBusy = 0.5;
 struct Tile {
   int rows, cols, k, at_once;
